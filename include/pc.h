@@ -164,7 +164,7 @@ pc_status pc_copy_group(const pc_circuit *c, int32_t layer, int32_t dir, int32_t
 
 /* Workspace (device, caller-owned) for batches of up to B samples.  It holds three node buffers
  * of n_rows x stride floats, row = node offset, samples contiguous (l in R^{N x B} of Sec. 4.3):
- *   l  log-probability residuals, F  node flows, N  log(F) - l of sum rows (the log_nf of Alg. 3 / 4),
+ *   l  log-probability residuals, F  node flows, N  log(F) - l of sum rows (the log_nf of Alg. 3 / 4; scratch otherwise),
  * one block buffer R of (n_blocks+1) x stride floats, row = node offset / K, and small per-batch
  * scratch.  The log-probability of node row n in sample b is  R[n / K][b] + l[n][b]  (R holds
  * integers; keeping the bulk of a large log-probability there leaves l accurate to ~1e-6).

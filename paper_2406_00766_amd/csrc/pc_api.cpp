@@ -82,6 +82,10 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     add(&c->d_group_nch, c->group_nch);
     add(&c->d_init_ids, c->init_ids);
     add(&c->d_pf_pb, c->pf_pb); add(&c->d_pf_ptr, c->pf_ptr); add(&c->d_pf_sum, c->pf_sum); add(&c->d_pf_child, c->pf_child);
+    for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { add(&f->d_ent, f->ent); add(&f->d_rec, f->rec); add(&f->d_list, f->list); }
+    for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) {
+        add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
+    }
     const size_t zrow_off = reserve((size_t)c->n_em_groups * c->K + 1);
     const size_t ztab_off = reserve((size_t)c->n_tables * c->K + 1);
     PC_HIP(hipMalloc(&c->d_arena, bytes));
@@ -133,7 +137,7 @@ static LaunchPlan *make_plan(const pc_circuit *c)
 
 struct Ws {
     int64_t Bs;
-    size_t l_off, f_off, n_off, r_off, mx_off, xt_off, total;
+    size_t l_off, f_off, n_off, r_off, mx_off, xt_off, tk_off, total;
     size_t th_off, tl_off, tth_off, ttl_off, ph_off, pl_off;   // bf16 operand planes (only where a layer takes the bf16 kernels)
     bool bf16;
     int64_t l_rows;                                   // rows of l: all of them, or the persistent ones and the product window
@@ -165,7 +169,8 @@ static Ws ws_layout(const pc_circuit *c, int32_t B)
     w.r_off = lnode + fnode + nnode;
     w.mx_off = w.r_off + per_block;
     w.xt_off = w.mx_off + per_block;
-    w.total = w.xt_off + align_up((size_t)c->n_vars * w.Bs * 4, 256);
+    w.tk_off = w.xt_off + align_up((size_t)c->n_vars * w.Bs * 4, 256);     // ticket words of the dataflow launches
+    w.total = w.tk_off + 256;
     // layers with long dense rows run on the bf16 matrix cores and need theta and the node values split into planes
     w.bf16 = false;
     for (const LayerTab &L : c->layers)
@@ -179,6 +184,30 @@ static Ws ws_layout(const pc_circuit *c, int32_t B)
         w.total = w.pl_off + pplane;
     }
     return w;
+}
+
+// First layer of the part that runs as dataflow launches (from there to the root); layers.size(): none.
+static size_t flow_start(const pc_circuit *c, const Ws &w)
+{
+    const size_t L = c->layers.size();
+    if (c->flow_fwd.count_from.empty() || !use_flow()) return L;
+    size_t li0 = L;
+    for (size_t li = L; li-- > 1 && flow_narrow(c, li, w.Bs);) {
+        const LayerTab &t = c->layers[li];
+        if (w.bf16 && t.kind == KIND_SUM && t.fwd.size() == 1 && sum_layer_takes_bf16(c->K, 1, t.fwd[0].n_rows, t.fwd[0].width, w.Bs)) break;
+        if (c->flow_cut[li]) li0 = li;
+    }
+    return li0;
+}
+static FlowDev flow_dev(const FlowTab &f, size_t li0, bool suffix)
+{
+    const int32_t n = f.count_from[li0], first = suffix ? f.count_from[0] - n : 0;
+    return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0};
+}
+static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)
+{
+    const int32_t n = r.count_from[li0], first = suffix ? r.count_from[0] - n : 0;
+    return RowsDev{r.d_ids + first, r.d_start + first, r.d_list, r.d_lay, r.d_aux + first, n, r.max_nbr_from[li0], (int32_t)li0};
 }
 
 }  // namespace pc
@@ -323,15 +352,17 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     const int32_t K = c->K;
     c->fw_B = -1;
 
-    launch_prepare_x(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, s);
-    launch_fill(l, (int64_t)K * w.Bs, 0.0f, s);                                  // null block: probability 1
-    launch_fill(R, ((int64_t)c->n_blocks + 1) * w.Bs, 0.0f, s);                  // input and null blocks: R = 0
+    const size_t L = c->layers.size(), li0 = flow_start(c, w);
+    FlowDev flow{};
+    if (li0 < L) flow = flow_dev(c->flow_fwd, li0, true);
+    int32_t *ticket = (int32_t *)(base + w.tk_off);
+    launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), flow.ent, flow.n_ent, K, ticket, s);
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     if (w.bf16) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, false, base + w.th_off, base + w.tl_off, s);
-    for (size_t li = 0; li < c->layers.size(); ++li) {
+    for (size_t li = 0; li < li0; ++li) {
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_INPUT) {
-            launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, s);
+            launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, R, s);
         } else if (L.kind == KIND_PRODUCT) {
             launch_prod_fwd(l, c->product_scratch ? window_base(c, L, l, w.Bs) : l, R, plan.layers[li].fwd, K, w.Bs,
                             w.bf16 ? base + w.ph_off : nullptr, w.bf16 ? base + w.pl_off : nullptr, s);
@@ -344,7 +375,12 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
                            w.Bs, s);
         }
     }
-    launch_readout(l, R, (int64_t)(c->root_block + 1) * K, (int64_t)c->root_block + 1, w.Bs, B, ll, s);
+    if (li0 < L) {                                                       // the root is among these layers and writes ll
+        launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, s);
+        launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
+    } else {
+        launch_readout(l, R, (int64_t)(c->root_block + 1) * K, (int64_t)c->root_block + 1, w.Bs, B, ll, s);
+    }
     PC_HIP(hipGetLastError());
     return PC_OK;
 }
@@ -406,9 +442,19 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     // no clearing of F: every block's flow is stored by the first layer that feeds it, blocks nobody feeds are
     // initialised here
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
-    launch_init_flows(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, s);
+    const size_t li0 = flow_start(c, w);
+    FlowDev flow{};
+    if (li0 < c->layers.size()) flow = flow_dev(c->flow_bwd, li0, false);
+    int32_t *ticket = (int32_t *)(base + w.tk_off);
+    launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
+                          flow.n_ent, ticket, s);
+    if (li0 < c->layers.size()) {
+        launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, s);
+        launch_prod_bwd_rows(l, F, N, nfmax, rows_dev(c->prod_bwd_rows, li0, false), K, w.Bs, w.bf16 ? base + w.ph_off : nullptr,
+                             w.bf16 ? base + w.pl_off : nullptr, s);
+    }
     bool theta_t_split = false;
-    for (size_t li = c->layers.size(); li-- > 0;) {
+    for (size_t li = li0; li-- > 0;) {
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_SUM && w.bf16 && L.bwd.size() == 1 &&
             sum_layer_takes_bf16(K, 1, L.bwd[0].n_rows, L.bwd[0].width, w.Bs)) {

@@ -126,7 +126,144 @@ pc_status build_groups(std::vector<Row> &rows, int32_t max_groups, int32_t tol_p
     return PC_OK;
 }
 
+// Tables of the dataflow launches (pc_internal.h, pc_flow.hip), for the layers such a launch may cover at some batch size.
+void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &par_ptr, const std::vector<int32_t> &par_of,
+                  const std::vector<int64_t> &par_edge)
+{
+    const int32_t n = d->n_blocks, K = d->K, L = (int32_t)c->layers.size();
+    std::vector<int32_t> layer_of(n, 0);
+    for (int32_t li = 0; li < L; ++li)
+        for (int32_t id : c->layers[li].blk_ids) layer_of[id / K - 1] = li;
+    auto off = [&](int32_t u) { return (u + 1) * K; };
+
+    c->sum_edges.assign(L, 0);
+    c->max_items.assign(L, 0);
+    c->flow_cut.assign(L + 1, 0);
+    int32_t reach = 0;                                    // highest layer that reads a product block of the layers so far
+    for (int32_t li = 0; li < L; ++li) {
+        const LayerTab &T = c->layers[li];
+        c->flow_cut[li] = li > 0 && T.kind == KIND_PRODUCT && reach < li;
+        for (int32_t id : T.blk_ids) {
+            const int32_t u = id / K - 1;
+            if (T.kind == KIND_SUM) {
+                c->sum_edges[li] += d->child_ptr[u + 1] - d->child_ptr[u];
+                for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e)
+                    c->max_items[li] = std::max<int32_t>(c->max_items[li], (int32_t)(d->child_ptr[d->child[e] + 1] - d->child_ptr[d->child[e]]));
+            } else if (T.kind == KIND_PRODUCT) {
+                for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) reach = std::max(reach, layer_of[par_of[k]]);
+            }
+        }
+    }
+    int32_t from = L;                                     // the part at the smallest batch holds those at all others
+    for (int32_t li = L; li-- > 1 && flow_narrow(c, li, 32);) if (c->flow_cut[li]) from = li;
+    if (from == L) return;
+
+    for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { f->count_from.assign(L + 1, 0); f->max_nbr_from.assign(L + 1, 0); }
+    for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) { r->count_from.assign(L + 1, 0); r->max_nbr_from.assign(L + 1, 0); r->start.assign(1, 0); }
+    // list of every product block's children and of every sum block's product parents (or itself): (node offset, layer)
+    std::vector<int32_t> list_at(n, 0), list_n(n, 0);
+    for (int32_t u = 0; u < n; ++u) {
+        if (d->type[u] == KIND_INPUT || layer_of[u] < from) continue;
+        std::vector<int32_t> &to = d->type[u] == KIND_PRODUCT ? c->flow_fwd.list : c->flow_bwd.list;
+        list_at[u] = (int32_t)(to.size() / 2);
+        if (d->type[u] == KIND_PRODUCT) {
+            std::vector<int32_t> ch(d->child + d->child_ptr[u], d->child + d->child_ptr[u + 1]);
+            std::sort(ch.begin(), ch.end());
+            for (int32_t k : ch) to.insert(to.end(), {off(k), layer_of[k]});
+        } else {
+            for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k)       // an unused product parent has flow 0
+                if (par_ptr[par_of[k]] != par_ptr[par_of[k] + 1]) to.insert(to.end(), {off(par_of[k]), layer_of[par_of[k]]});
+            // the root or an unused sum block (its own flow rows are initialised); one whose parents are all unused: flow 0
+            if ((int32_t)(to.size() / 2) == list_at[u]) to.insert(to.end(), {par_ptr[u] == par_ptr[u + 1] ? off(u) : 0, -1});
+        }
+        list_n[u] = (int32_t)(to.size() / 2) - list_at[u];
+    }
+    auto add_rec = [&](FlowTab &f, int32_t par, int32_t nbr) {
+        const int32_t at = list_at[nbr], cnt = list_n[nbr];
+        f.rec.insert(f.rec.end(), {par, at, cnt, off(nbr), layer_of[nbr]});
+        for (int w = 0; w < 2; ++w)
+            for (int32_t k = 0; k < 5; ++k) f.rec.push_back(k < cnt ? f.list[2 * (at + k) + w] : -1);
+        f.rec.push_back(0);
+    };
+    for (int32_t li = from; li < L; ++li) {
+        const LayerTab &T = c->layers[li];
+        for (int32_t id : T.blk_ids) {
+            const int32_t u = id / K - 1;
+            std::vector<std::pair<int32_t, int64_t>> ch;
+            for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e) ch.emplace_back(d->child[e], e);
+            std::sort(ch.begin(), ch.end());
+            if (T.kind == KIND_SUM) {
+                FlowTab &f = c->flow_fwd;
+                f.ent.insert(f.ent.end(), {id, (int32_t)(f.rec.size() / 16), (int32_t)ch.size(), u == d->root_block ? 1 : 0});
+                for (auto &k : ch) add_rec(f, (d->param_blk[k.second] + 1) * K * K, k.first);
+                ++f.count_from[li];
+                f.max_nbr_from[li] = std::max(f.max_nbr_from[li], (int32_t)ch.size());
+            } else {
+                RowTab &r = c->prod_fwd_rows;
+                r.ids.push_back(id);
+                for (auto &k : ch) r.list.push_back(off(k.first));
+                r.start.push_back((int32_t)r.list.size());
+                r.aux.push_back((int32_t)ch.size() << AUX_COUNT_SHIFT);
+                ++r.count_from[li];
+                r.max_nbr_from[li] = std::max(r.max_nbr_from[li], (int32_t)ch.size());
+            }
+        }
+    }
+    for (int32_t li = L; li-- > from;) {
+        const LayerTab &T = c->layers[li];
+        if (T.kind != KIND_PRODUCT) continue;
+        for (int32_t id : T.blk_ids) {
+            const int32_t u = id / K - 1, n_par = par_ptr[u + 1] - par_ptr[u];
+            if (n_par == 0) continue;
+            FlowTab &f = c->flow_bwd;
+            f.ent.insert(f.ent.end(), {id, (int32_t)(f.rec.size() / 16), n_par, 0});
+            for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) add_rec(f, (d->param_blk[par_edge[k]] + 1) * K * K, par_of[k]);
+            ++f.count_from[li];
+            f.max_nbr_from[li] = std::max(f.max_nbr_from[li], n_par);
+        }
+    }
+    // backward rows: blocks with product parents of these layers, by descending layer of the highest one
+    std::vector<std::vector<int32_t>> by_top(L);
+    for (int32_t u = 0; u < n; ++u) {
+        if (d->type[u] == KIND_PRODUCT) continue;
+        int32_t top = 0;
+        for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) top = std::max(top, layer_of[par_of[k]]);
+        if (top >= from) by_top[top].push_back(u);
+    }
+    for (int32_t li = L; li-- > from;)
+        for (int32_t u : by_top[li]) {
+            RowTab &r = c->prod_bwd_rows;
+            std::vector<int32_t> pa(par_of.begin() + par_ptr[u], par_of.begin() + par_ptr[u + 1]);
+            std::stable_sort(pa.begin(), pa.end(), [&](int32_t a, int32_t b) { return layer_of[a] > layer_of[b]; });
+            r.ids.push_back(off(u));
+            for (int32_t p : pa) { r.list.push_back(off(p)); r.lay.push_back(layer_of[p]); }
+            r.start.push_back((int32_t)r.list.size());
+            r.aux.push_back((int32_t)pa.size() << AUX_COUNT_SHIFT | (d->type[u] == KIND_SUM ? 1 : 0));
+            ++r.count_from[li];
+            r.max_nbr_from[li] = std::max(r.max_nbr_from[li], (int32_t)pa.size());
+        }
+    auto accumulate = [&](std::vector<int32_t> &cnt, std::vector<int32_t> &most) {
+        for (int32_t li = L; li-- > 0;) { cnt[li] += cnt[li + 1]; most[li] = std::max(most[li], most[li + 1]); }
+    };
+    for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) accumulate(f->count_from, f->max_nbr_from);
+    for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) accumulate(r->count_from, r->max_nbr_from);
+}
+
 }  // namespace
+
+// A dataflow task repeats its neighbours' products and exponentials for every 16 or 32 rows, so a layer that fills the chip is
+// better off in the layer kernels; a narrow one costs them two launches and cold starts (5 + 5 us) where its tasks take
+// 2 - 3 us.  Measured on hidden Chow-Liu trees (M = 32, 128, 256; B = 100 .. 512), HMMs and RAT-SPNs: the line lies at 2048
+// tiles of 16 x 16 results (sum layer: forward, product layer: backward) and 16384 tile-chunks (16 x 16 results x 32 neighbour
+// nodes) per layer, and half or twice that makes 5 % of a pass.  Product blocks of many children (RAT-SPN leaves: 57 - 98)
+// are summed one child at a time by every task that reads them and belong in their own launch.
+bool flow_narrow(const pc_circuit *c, size_t li, int64_t Bs)
+{
+    const LayerTab &t = c->layers[li];
+    const int64_t ct = Bs / 16;
+    if ((int64_t)t.blk_ids.size() * (c->K / 16) * ct > 2048) return false;
+    return t.kind != KIND_SUM || (c->sum_edges[li] * (c->K / 16) * (c->K / 32) * ct <= 16384 && c->max_items[li] <= 12);
+}
 
 pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
 {
@@ -185,8 +322,13 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
     for (int64_t e = 0; e < n_edges; ++e) ++par_ptr[d->child[e] + 1];
     for (int32_t u = 0; u < n; ++u) par_ptr[u + 1] += par_ptr[u];
     std::vector<int32_t> par_of(n_edges), fill(par_ptr.begin(), par_ptr.end() - 1);
+    std::vector<int64_t> par_edge(n_edges);
     for (int32_t u = 0; u < n; ++u)
-        for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e) par_of[fill[d->child[e]]++] = u;
+        for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e) {
+            const int32_t at = fill[d->child[e]]++;
+            par_of[at] = u;
+            par_edge[at] = e;
+        }
     std::vector<int32_t> ready;
     for (int32_t u = 0; u < n; ++u) {
         pending[u] = (int32_t)(d->child_ptr[u + 1] - d->child_ptr[u]);
@@ -404,6 +546,7 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
         for (auto &sc : users[p]) { c->pf_sum.push_back(sc.first); c->pf_child.push_back(sc.second); }
         c->pf_ptr.push_back((int32_t)c->pf_sum.size());
     }
+    if (!c->product_scratch && (K == 32 || K == 64 || K == 128)) compile_flow(d, c, par_ptr, par_of, par_edge);
     return PC_OK;
 }
 

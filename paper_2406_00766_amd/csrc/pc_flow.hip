@@ -1,0 +1,551 @@
+// Dataflow sum layers: every sum layer from a given layer to the root in ONE launch per direction.
+//
+// A layer of a deep narrow circuit is a few microseconds of latency: a launch, a table row, the operands, the result.
+// Launched one by one the layers of a 784-variable tree cost 83 x (product + sum) launches of 5 us each per direction
+// while the chip idles.  Here a layer's tiles are TASKS of one launch.  A task is (sum or product block, tile of 16 RT of
+// its rows, tile of 16 NC columns); workgroups take tasks by a ticket counter, in layer order, and a task that needs
+// values of an earlier task reads them straight from the result buffer until they are there:
+//   * the rows a task publishes are filled with a sentinel (a NaN bit pattern no result has) before the launch; a consumer
+//     loads the values it needs with device-scope loads and repeats the load while any of them is the sentinel.  Data and
+//     signal are one word, so a hand-over costs one store and one load -- 0.8 us between workgroups against 1.7 us for an
+//     empty kernel boundary (measured) plus the consumer's cold start, which here is over before the values arrive: a
+//     waiting workgroup holds its weights in registers already.
+//   * no wait can last for ever: a task waits only for tasks with lower tickets, tickets are taken by running workgroups
+//     in increasing order and worked off in that order, so the lowest unfinished task never waits.  (No assumption about
+//     how many workgroups are resident.)  A bound on the spins ends the launch all the same should that ever be untrue.
+//
+// Forward (role of Alg. 1): a task computes 16 RT sum nodes.  Its neighbours' values are the PRODUCTS of their children's
+// log-probabilities, formed here from the children's rows (Sec. 3: a sum of log-probabilities), so a product layer is
+// not on the path from layer to layer at all; the product blocks' own rows are written by one ordinary launch after this
+// one (k_prod_fwd over all layers).  Backward (role of Alg. 4): a task computes 16 RT product nodes' flows; log_nf of its
+// parents (sum blocks) is formed here from their own parents' flows, and F, log_nf of the sum and input blocks are written
+// by one launch of k_prod_bwd afterwards.
+//
+// Arithmetic: v_mfma_f32_16x16x4_f32.  A (16 x 4): lane holds A[lane % 16][lane / 16]; B (4 x 16): lane holds
+// B[lane / 16][lane % 16]; D: register r holds D[4 * (lane / 16) + r][lane % 16].  Reduction in chunks of 32 neighbour
+// nodes, step (c2, e) pairs lane group g with node 16 c2 + 4 g + e, so that the forward weights are 16-byte loads.  The W
+// waves of a workgroup split the chunks and meet in LDS once.  A chunk's values are brought to an integer reference (the
+// rounded column maximum joins R), so every exponential sees an argument <= 0.5 and results need no running maximum.
+//
+// What bounds it: the chain through the layers.  Measured (time stamps of the tasks of one layer): values seen 0.5 - 0.7 us
+// after they were published, 0.4 - 0.5 us to exponentials and MFMAs (32 or 128 neighbour nodes; at 512, 1 us: the waves of a CU
+// share its matrix cores), 0.5 us to merge and publish: 1.6 us per layer at 32 nodes, 2 us at 128, 4.5 us at 512, against
+// 7 - 13 us for a layer's two launches.  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 34 us; forward,
+// 784-variable tree, M = 128, B = 100 908 -> 348 us; forward + backward, the same tree at B = 512 2.70 -> 1.68 ms; HMM T = 32, H = 512,
+// B = 77 865 -> 395 us.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "pc_device.h"
+#include "pc_kernels.h"
+
+namespace pc {
+
+#define PC_SENTINEL 0xFFFFFFFFu
+constexpr int FLOW_SPIN_LIMIT = 1 << 22;                               // some seconds of polling
+
+// Device-scope 4- and 16-byte accesses (sc1); every dword of a 16-byte access is a word of its own.  (A polling loop needs a
+// compiler barrier so that it loads again; a volatile access would be system-scope.)
+#define PC_BUF_RANGE 0x7fffffff
+#define PC_BUF_FLAGS 0x00020000
+#define PC_AUX_DEVICE 16
+__device__ inline floatx4 mail_load(const float *tile, int voff)
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)tile, 0, PC_BUF_RANGE, PC_BUF_FLAGS);
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, PC_AUX_DEVICE));
+}
+__device__ inline float flow_load(const float *p)
+{
+    return __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const uint32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// maximum over the four lane groups of a column (lanes j, j + 16, j + 32, j + 48)
+__device__ inline float max_over_groups(float v)
+{
+    // (as instructions: of the builtins' two results the compiler keeps one when the operands are equal)
+    float a = v, b = v;
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    a = b = fmaxf(a, b);
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return fmaxf(a, b);
+}
+__device__ inline bool is_sentinel(float v) { return __builtin_bit_cast(uint32_t, v) == PC_SENTINEL; }
+__device__ inline float no_sentinel(float v) { return v == v ? v : __builtin_bit_cast(float, 0x7FC00000u); }   // one NaN for all
+
+__device__ inline bool flow_give_up(int spin, int32_t *ticket)
+{
+    if (spin < FLOW_SPIN_LIMIT && ((spin & 1023) != 1023 || __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)) return false;
+    __hip_atomic_store(ticket + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// Sentinel (and zero) fills before a dataflow launch: workgroup i < n_blk fills the K rows of block ids[i] (rows of a block are
+// contiguous) and, forward, its row of R.  The last workgroup clears the ticket words.
+__device__ inline void flow_fill_block(float *X, float *R, int32_t id, int32_t K, int64_t Bs)
+{
+    const float s = __builtin_bit_cast(float, PC_SENTINEL);
+    floatx4 *dst = reinterpret_cast<floatx4 *>(X + (int64_t)id * Bs);
+    const floatx4 s4 = {s, s, s, s};
+    for (int64_t i = threadIdx.x; i < K * Bs / 4; i += blockDim.x) dst[i] = s4;
+    if (R) for (int64_t i = threadIdx.x; i < Bs; i += blockDim.x) R[(int64_t)(id / K) * Bs + i] = s;
+}
+
+// Start of a forward pass in one launch: x -> xT (see below), the null block's rows (l = 0, R = 0), the sentinels of the sum
+// blocks the dataflow launch will publish, its ticket words.
+// xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
+__global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B,
+                                                       int32_t D, int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT, int32_t n_xb,
+                                                       int32_t n_xtiles, float *__restrict__ l, float *__restrict__ R,
+                                                       float *__restrict__ mail, const int32_t *__restrict__ ent, int32_t n_ent,
+                                                       int32_t K, int32_t *ticket)
+{
+    __shared__ int32_t tile[32][33];
+    if ((int)blockIdx.x >= n_xtiles) {
+        const int q = (int)blockIdx.x - n_xtiles;
+        if (q < n_ent) { flow_fill_block(mail, R, ent[4 * q], K, Bs); return; }
+        for (int64_t i = threadIdx.x; i < K * Bs; i += 256) { l[i] = 0.0f; mail[i] = 0.0f; }
+        for (int64_t i = threadIdx.x; i < Bs; i += 256) R[i] = 0.0f;
+        if (threadIdx.x < 2) ticket[threadIdx.x] = 0;
+        return;
+    }
+    const int b0 = ((int)blockIdx.x % n_xb) * 32, v0 = ((int)blockIdx.x / n_xb) * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;           // 256 threads: ty in 0..7
+    for (int r = ty; r < 32; r += 8) {
+        const int b = b0 + r, v = v0 + tx;
+        int32_t val = -1;
+        if (b < B && v < D) {
+            const int64_t idx = (int64_t)b * D + v;
+            val = x[idx];
+            if (val < 0 || val >= n_cats) val = -2;
+            if (mask && mask[idx]) val = -1;
+        }
+        tile[r][tx] = val;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+        const int v = v0 + r, b = b0 + tx;
+        if (v < D && b < Bs) xT[(int64_t)v * Bs + b] = tile[tx][r];
+    }
+}
+
+// Start of a backward pass in one launch.  Workgroups < n_init * n_cb: blocks without parents, which no layer of the sweep
+// writes.  An entry >= 0 is a sum block: the root (flow 1 on node 0 of real samples with non-zero probability, Def. 2) or a
+// sum block nobody uses (flow 0); its log_nf rows and block maximum are set as well.  An entry < 0 is ~offset of another
+// block (the null block, a product or input block nobody uses): its flow rows are zeroed.  One workgroup per entry and 256
+// columns.  Workgroups behind them: the sentinels of the product blocks the dataflow launch will publish, its tickets.
+__global__ __launch_bounds__(256) void k_begin_backward(const float *__restrict__ l, float *__restrict__ F, float *__restrict__ N,
+                                                        float *__restrict__ nfmax, const int32_t *__restrict__ blk_ids, int32_t n_init,
+                                                        int32_t n_cb, int32_t root_id, int32_t K, int64_t Bs, int32_t B,
+                                                        const int32_t *__restrict__ ent, int32_t n_ent, int32_t *ticket)
+{
+    if ((int)blockIdx.x >= n_init * n_cb) {
+        const int q = (int)blockIdx.x - n_init * n_cb;
+        if (q < n_ent) flow_fill_block(N, nullptr, ent[4 * q], K, Bs);
+        else if (threadIdx.x < 2) ticket[threadIdx.x] = 0;
+        return;
+    }
+    const int32_t entry = blk_ids[blockIdx.x / n_cb];
+    const int64_t b = (int64_t)(blockIdx.x % n_cb) * 256 + threadIdx.x;
+    if (b >= Bs) return;
+    if (entry < 0) {
+        const int32_t id = ~entry;
+        for (int k = 0; k < K; ++k) F[(int64_t)(id + k) * Bs + b] = 0.0f;
+        return;
+    }
+    const int32_t id = entry;
+    float top = PC_NEG_INF, f0 = 0.0f;
+    if (id == root_id) {
+        const float lv = l[(int64_t)id * Bs + b];
+        const bool live = b < B && lv > PC_NEG_INF;
+        f0 = live ? 1.0f : 0.0f;
+        top = live ? -lv : PC_NEG_INF;
+    }
+    for (int k = 0; k < K; ++k) {
+        F[(int64_t)(id + k) * Bs + b] = k == 0 ? f0 : 0.0f;
+        N[(int64_t)(id + k) * Bs + b] = k == 0 ? top : PC_NEG_INF;
+    }
+    nfmax[(int64_t)(id / K) * Bs + b] = top;
+}
+
+// Tables (built by compile_flow):
+//   ent  4 words per task block, in task order: node offset, first neighbour record, neighbour records, 1 for the root
+//   rec  16 words per neighbour: parameter offset; start of its list; list items; neighbour's node offset; its layer; the first
+//        five items and then their layers.  A list holds items (node offset, layer); an item of layer li0 or above is waited for.
+//        Forward: the neighbour is a product block, the list its children; a neighbour below layer li0 has been evaluated
+//        already and stands for itself.  Backward: the neighbour is a sum block, the list its product parents, or itself
+//        (layer -1) where it has none.
+// `mail` (the rows of log_nf that are not in use at the time: sum rows forward, product rows backward) carries the published
+// values in MFMA operand order: per block, 16 rows and 16 columns one 1 KiB tile, lane (j, g) holding rows 4 g .. 4 g + 3 of
+// column j -- one 16-byte load per lane where the row-major buffer would take four loads of 4 x 64 bytes, and no line shared
+// by two column tiles.
+template <int W, int RT, int NC, int NCH, bool BWD>
+__global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__restrict__ theta, float *__restrict__ l, float *R,
+                                                                 float *__restrict__ F, float *mail,
+                                                                 const int32_t *__restrict__ ent, const int32_t *__restrict__ rec,
+                                                                 const int32_t *__restrict__ list, int32_t n_tasks, int32_t n_ct,
+                                                                 int32_t K, int64_t Bs, int32_t li0, int32_t *ticket,
+                                                                 float *__restrict__ ll, int32_t B)
+{
+    constexpr int NT = RT * NC;                                         // 16 x 16 tiles of the task
+    constexpr int TPW = (NT + W - 1) / W;                               // tiles whose results a wave writes
+    __shared__ floatx4 part[2][W][NT][64];                              // partial sums of the waves, double-buffered over tasks
+    __shared__ float pref[2][W][NC][16];                                // and their references
+    __shared__ int32_t s_ticket[2];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
+    const int ks = 31 - __builtin_clz(K);                               // K is 32, 64 or 128
+    const int TM = 16 * RT, subs = K / TM, cpb = K >> 5;
+
+    if (threadIdx.x == 0) s_ticket[0] = atomicAdd(ticket, 1);
+    __syncthreads();
+    int t = __builtin_amdgcn_readfirstlane(s_ticket[0]);
+    for (int buf = 1; t < n_tasks; buf ^= 1) {
+        int nxt = 0;
+        if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);               // arrives while this task is worked on
+        const int ct = t % n_ct, q = t / n_ct, sub = q % subs, e_i = q / subs;
+        const int32_t row0 = ent[4 * e_i], rec0 = ent[4 * e_i + 1], n_nbr = ent[4 * e_i + 2], root = ent[4 * e_i + 3];
+        const int C = n_nbr * cpb;                                      // chunks of 32 neighbour nodes
+        const int64_t col0 = (int64_t)ct * (16 * NC) + j16;             // column of tile nc: col0 + 16 nc
+
+        float lown[TPW][4], Rrow[NC];                                   // backward: the rows' own log-probabilities, R of their block
+        if (BWD) {
+#pragma unroll
+            for (int k = 0; k < TPW; ++k) {
+                const int u = wave + W * k < NT ? wave + W * k : 0, nc = u % NC, rt = u / NC;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lown[k][r] = l[(int64_t)(row0 + sub * TM + rt * 16 + 4 * g + r) * Bs + col0 + 16 * nc];
+            }
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) Rrow[nc] = R[(int64_t)(row0 >> ks) * Bs + col0 + 16 * nc];
+        }
+
+        floatx4 acc[RT][NC];
+        float ref[NC];                                                  // reference of acc; -inf: nothing live yet
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+            ref[nc] = PC_NEG_INF;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt][nc] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+
+        for (int cb = wave; cb < C; cb += W * NCH) {                    // this wave's chunks cb, cb + W, ... NCH at a time
+            floatx4 th[NCH][2][RT], v[NCH][NC][2];
+            float base[NCH][NC];
+            int32_t koff[NCH], own[NCH], cnt[NCH];
+            const int32_t *rp[NCH];
+            int max_cnt = 0;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int cc = cb + W * i < C ? cb + W * i : cb;        // past the end: the first chunk again, with value -inf
+                const int32_t *r = rec + 16 * (int64_t)(rec0 + cc / cpb);
+                rp[i] = r;
+                koff[i] = (cc % cpb) * 32;
+                cnt[i] = r[2]; own[i] = r[3];
+                if (!BWD && r[4] < li0) cnt[i] = -1;                    // evaluated before this launch
+                max_cnt = max(max_cnt, cnt[i] < 0 ? 1 : cnt[i]);
+                const float *tb = theta + r[0] + (BWD ? koff[i] * K + sub * TM : sub * TM * K + koff[i]);
+#pragma unroll
+                for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) {
+                        if (BWD) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) th[i][c2][rt][e] = tb[(16 * c2 + 4 * g + e) * K + rt * 16 + j16];
+                        } else {
+                            th[i][c2][rt] = *reinterpret_cast<const floatx4 *>(tb + (rt * 16 + j16) * K + 16 * c2 + 4 * g);
+                        }
+                    }
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) {
+                    base[i][nc] = 0.0f;
+#pragma unroll
+                    for (int c2 = 0; c2 < 2; ++c2) v[i][nc][c2] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            // Values: the sum of the list items' rows (forward: log-probabilities; backward: flows).  One item of every chunk's
+            // list at a time; past the end of a list the null block (value 0): no branch surrounds a load, which would make
+            // the compiler wait for the loads before it.
+            floatx4 own_l[BWD ? NCH : 1][NC][2];
+            if (BWD) {                                                  // the sum blocks' own log-probabilities and references
+#pragma unroll
+                for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            own_l[i][nc][k >> 2][k & 3] = l[(int64_t)(own[i] + koff[i] + 16 * (k >> 2) + 4 * g + (k & 3)) * Bs + col0 + 16 * nc];
+                        base[i][nc] = Rrow[nc] - R[(int64_t)(own[i] >> ks) * Bs + col0 + 16 * nc];
+                    }
+            }
+            // long lists: a running fp32 sum of many log-probabilities loses more than the flows' tolerance allows, so every
+            // four items its integer part moves into the reference
+            auto settle = [&]() {
+#pragma unroll
+                for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) {
+                        float cm = v[i][nc][0][0];
+#pragma unroll
+                        for (int k = 1; k < 8; ++k) cm = fmaxf(cm, v[i][nc][k >> 2][k & 3]);
+                        cm = max_over_groups(cm);
+                        cm = cm > PC_NEG_INF ? rintf(cm) : 0.0f;
+                        base[i][nc] += cm;
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) v[i][nc][k >> 2][k & 3] -= cm;
+                    }
+            };
+            // item n of chunk i if it is (wait) / is not (!wait) to be waited for, else the null block; any: there is one
+            auto item = [&](int i, int n, bool wait, int &any) -> int32_t {
+                if (cnt[i] < 0) { if (n == 0 && !wait) { any = 1; return own[i]; } return 0; }
+                if (n >= cnt[i]) return 0;
+                int32_t it, lay;
+                if (n < 5) { it = rp[i][5 + n]; lay = rp[i][10 + n]; }
+                else { it = list[2 * (rp[i][1] + n)]; lay = list[2 * (rp[i][1] + n) + 1]; }
+                if ((lay >= li0) != wait) return 0;
+                any = 1;
+                return it;
+            };
+            int since = 0;
+            for (int n = 0; n < max_cnt; ++n) {                         // items of earlier launches
+                int32_t its[NCH];
+                int any = 0;
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) its[i] = item(i, n, false, any);
+                if (!any) continue;
+                floatx4 x[NCH][NC][2];
+                float xr[NCH][NC];
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) {
+                    const int32_t it = its[i];
+                    const float *src = (BWD ? F : l) + (int64_t)(it + koff[i] + 4 * g) * Bs + col0;
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) x[i][nc][k >> 2][k & 3] = src[(int64_t)(16 * (k >> 2) + (k & 3)) * Bs + 16 * nc];
+                        if (!BWD) xr[i][nc] = R[(int64_t)(it >> ks) * Bs + col0 + 16 * nc];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                        for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[i][nc][c2][e] += x[i][nc][c2][e];
+                        if (!BWD) base[i][nc] += xr[i][nc];
+                    }
+                if (!BWD && (++since & 3) == 0) settle();
+            }
+            for (int n = 0; n < max_cnt; ++n) {                         // items of this launch: poll until they are there
+                int32_t its[NCH];
+                int any = 0;
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) its[i] = item(i, n, true, any);
+                if (!any) continue;
+                const float *src[NCH], *sr[NCH];
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) {
+                    const int32_t it = its[i];
+                    src[i] = mail + (int64_t)(it + koff[i]) * Bs + (int64_t)ct * (256 * NC);
+                    sr[i] = R + (int64_t)(it >> ks) * Bs + col0;
+                }
+                floatx4 x[NCH][NC][2];
+                float xr[NCH][NC];
+                for (int spin = 0;; ++spin) {
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                        for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                            for (int c2 = 0; c2 < 2; ++c2) x[i][nc][c2] = mail_load(src[i] + (int64_t)(16 * c2) * Bs + 256 * nc, 16 * lane);
+                            if (!BWD) xr[i][nc] = flow_load(sr[i] + 16 * nc);
+                        }
+                    int missing = 0;
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                        for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) missing |= is_sentinel(x[i][nc][k >> 2][k & 3]);
+                            if (!BWD) missing |= is_sentinel(xr[i][nc]);
+                        }
+                    if (!__any(missing) || flow_give_up(spin, ticket)) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+#pragma unroll
+                for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                        for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[i][nc][c2][e] += x[i][nc][c2][e];
+                        if (!BWD) base[i][nc] += xr[i][nc];
+                    }
+                if (!BWD && (++since & 3) == 0) settle();
+            }
+            // log_nf of the parents; integer reference of each chunk; the largest live one
+            float nref[NC];
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) nref[nc] = ref[nc];
+#pragma unroll
+            for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        float &x = reinterpret_cast<float *>(&v[i][nc][0])[k];
+                        if (BWD) {
+                            const float lo = own_l[i][nc][k >> 2][k & 3];
+                            x = (x > 0.0f && lo > PC_NEG_INF) ? __logf(x) - lo : PC_NEG_INF;
+                        }
+                        if (cb + W * i >= C) x = PC_NEG_INF;
+                    }
+                    float cm = v[i][nc][0][0];
+#pragma unroll
+                    for (int k = 1; k < 8; ++k) cm = fmaxf(cm, v[i][nc][k >> 2][k & 3]);
+                    cm = max_over_groups(cm);
+                    const bool live = cm > PC_NEG_INF;
+                    cm = live ? rintf(cm) : 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[i][nc][k >> 2][k & 3] -= cm;
+                    base[i][nc] = live ? base[i][nc] + cm : PC_NEG_INF;
+                    nref[nc] = fmaxf(nref[nc], base[i][nc]);
+                }
+            if (cb != wave) {                                           // not the first batch: rescale
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) {
+                    const float sc = nref[nc] > PC_NEG_INF ? pc_half_scale(ref[nc] - nref[nc]) : 1.0f;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[rt][nc][r] = acc[rt][nc][r] * sc * sc;
+                }
+            }
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) ref[nc] = nref[nc];
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                float sh2[NC];                                          // exp(v + base - ref + PC_UP) = exp2(v * log2e + sh2)
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc)
+                    sh2[nc] = base[i][nc] > PC_NEG_INF ? (base[i][nc] - ref[nc] + PC_UP) * PC_LOG2E : 0.0f;   // dead: v = -inf
+#pragma unroll
+                for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int nc = 0; nc < NC; ++nc) {
+                            const float p = __builtin_amdgcn_exp2f(fmaf(v[i][nc][c2][e], PC_LOG2E, sh2[nc]));
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt)
+                                acc[rt][nc] = __builtin_amdgcn_mfma_f32_16x16x4f32(th[i][c2][rt][e], p, acc[rt][nc], 0, 0, 0);
+                        }
+            }
+        }
+
+        // the waves' partial sums meet in LDS; tile u = (rt, nc) goes to wave u % W
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) part[buf][wave][rt * NC + nc][lane] = acc[rt][nc];
+        if (g == 0) {
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) pref[buf][wave][nc][j16] = ref[nc];
+        }
+        if (threadIdx.x == 0) s_ticket[buf] = nxt;
+        __syncthreads();
+        t = __builtin_amdgcn_readfirstlane(s_ticket[buf]);
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+            const int u = wave + W * k;
+            if (u >= NT) break;                                         // wave-uniform
+            const int nc = u % NC, rt = u / NC;
+            float rw[W], top = PC_NEG_INF;
+#pragma unroll
+            for (int w = 0; w < W; ++w) { rw[w] = pref[buf][w][nc][j16]; top = fmaxf(top, rw[w]); }
+            floatx4 tot = {0.f, 0.f, 0.f, 0.f}, val;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const float sc = rw[w] > PC_NEG_INF ? pc_half_scale(rw[w] - top) : 0.0f;
+                const floatx4 pw = part[buf][w][u][lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tot[r] += pw[r] * sc * sc;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (BWD) {
+                    // exp(ln(sum) + (ref - PC_UP) + l_row); sum = 0 or l_row = -inf gives exp2(-inf) = 0
+                    const float add = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(tot[r]) + (lown[k][r] + (top - PC_UP)) * PC_LOG2E);
+                    val[r] = top > PC_NEG_INF ? no_sentinel(add) : 0.0f;
+                } else {
+                    // ln(sum) - PC_UP relative to the largest reference, the logarithm taken of sum / 2^24: a base-2 logarithm
+                    // near 0 is far more accurate in absolute terms than one near 29, and these errors add up over the layers
+                    val[r] = no_sentinel(fmaf(__builtin_amdgcn_logf(tot[r] * 0x1p-24f), 0.6931471805599453f, 16.635532333f - PC_UP));
+                }
+            }
+            const int rrow = sub * TM + rt * 16;
+            const int64_t col = col0 + 16 * nc;
+            const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(mail + (int64_t)(row0 + rrow) * Bs + (int64_t)ct * (256 * NC) + 256 * nc), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, val), rm, 16 * lane, 0, PC_AUX_DEVICE);
+            if (!BWD && rrow == 0 && g == 0) {
+                const float rs = top > PC_NEG_INF ? top : 0.0f;         // all children dead: any finite reference
+                __hip_atomic_store(R + (int64_t)(row0 >> ks) * Bs + col, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (root && col < B) ll[col] = rs + val[0];
+            }
+            float *out = (BWD ? F : l) + (int64_t)(row0 + rrow + 4 * g) * Bs + col;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) out[(int64_t)r * Bs] = val[r];
+        }
+    }
+}
+
+// ---- launchers ----
+void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
+                          float *l, float *R, float *mail, const int32_t *ent, int32_t n_ent, int32_t K, int32_t *ticket, hipStream_t s)
+{
+    Timed timed(KC_MISC, s);
+    const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
+    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + n_ent + 1)), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
+                       n_xt, l, R, mail, ent, n_ent, K, ticket);
+}
+
+void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,
+                           int32_t K, int64_t Bs, int32_t B, const int32_t *ent, int32_t n_ent, int32_t *ticket, hipStream_t s)
+{
+    Timed timed(KC_MISC, s);
+    const int n_cb = (int)((Bs + 255) / 256);
+    hipLaunchKernelGGL(k_begin_backward, dim3((unsigned)(n_blk * n_cb + n_ent + 1)), dim3(256), 0, s, l, F, N, nfmax, blk_ids, n_blk,
+                       n_cb, root_id, K, Bs, B, ent, n_ent, ticket);
+}
+
+void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
+                 int32_t *ticket, float *ll, hipStream_t s)
+{
+    if (f.n_ent == 0) return;
+    Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
+    // Row tiles of 32 halve the number of tasks that read a neighbour; eight waves where four would have more than one chunk
+    // each (measured with 4, 8, 16 waves, 16 - 64 rows, 16 and 32 columns, 1 - 4 chunks at once: 32 columns lost everywhere, 64 rows
+    // won 1 - 2 % on 128- and 256-state trees and lost elsewhere).
+    const int chunks = f.max_nbr * (K / 32);
+#define PC_FLOW(WW, RR, NN, HH)                                                                                          \
+    do {                                                                                                                     \
+        const int n_ct = (int)(Bs / (16 * NN));                                                                              \
+        const int64_t tasks = (int64_t)f.n_ent * (K / (16 * RR)) * n_ct;                                                     \
+        const int grid = (int)std::min<int64_t>(tasks, 512);                                                                \
+        if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, NN, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+                                    f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                  \
+        else hipLaunchKernelGGL((k_flow<WW, RR, NN, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+                                f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                      \
+    } while (0)
+    if (chunks == 1) PC_FLOW(4, 1, 1, 1);
+    else if (chunks <= 4) PC_FLOW(4, 2, 1, 1);
+    else if (chunks <= 8) PC_FLOW(8, 2, 1, 1);
+    else PC_FLOW(8, 2, 1, 2);
+#undef PC_FLOW
+}
+
+}  // namespace pc

@@ -48,6 +48,23 @@ struct LayerTab {
     int32_t *d_pf_pb = nullptr, *d_pf_ptr = nullptr, *d_pf_sum = nullptr, *d_pf_child = nullptr;
 };
 
+// Tables of the dataflow launches (pc_flow.hip), for K = 32, 64, 128 and circuits that keep their product values.  Entries
+// are in task order -- forward: sum blocks by ascending layer, backward: product blocks by descending layer -- so the layers
+// from any given one to the root are a suffix (forward) or a prefix (backward).
+struct FlowTab {
+    std::vector<int32_t> ent, rec, list;              // words as described in pc_flow.hip
+    std::vector<int32_t> count_from, max_nbr_from;    // per layer index: entries in that layer and above; most neighbours of one
+    int32_t *d_ent = nullptr, *d_rec = nullptr, *d_list = nullptr;
+};
+// The product layers that belong to them, as rows with neighbour lists (CSR): forward, product blocks by ascending layer with
+// their children; backward, sum and input blocks by descending layer of their highest product parent, with their product
+// parents from the highest layer down (lay: the parents' layers).
+struct RowTab {
+    std::vector<int32_t> ids, start, list, lay, aux;  // aux: neighbours << AUX_COUNT_SHIFT | 1 for a sum block
+    std::vector<int32_t> count_from, max_nbr_from;    // per layer index: rows in that layer and above; most neighbours of one
+    int32_t *d_ids = nullptr, *d_start = nullptr, *d_list = nullptr, *d_lay = nullptr, *d_aux = nullptr;
+};
+
 }  // namespace pc
 
 struct pc_circuit {
@@ -70,6 +87,14 @@ struct pc_circuit {
     // node offsets; other blocks and the null block as ~offset
     std::vector<int32_t> init_ids;
     int32_t *d_init_ids = nullptr;
+
+    // dataflow launches (empty where they do not apply)
+    pc::FlowTab flow_fwd, flow_bwd;
+    std::vector<int64_t> sum_edges;                   // per layer (sum layers): block pairs,
+    std::vector<int32_t> max_items;                   // most children of a product block that it reads
+    std::vector<uint8_t> flow_cut;                    // per layer: a dataflow part may begin here (a product layer, and no product
+                                                      // block below it is read by a sum block above it)
+    pc::RowTab prod_fwd_rows, prod_bwd_rows;
 
     // product-scratch mode: product log-probabilities live in a window of max_window_blocks blocks behind the
     // n_persistent_blocks input and sum blocks
@@ -103,6 +128,8 @@ pc_status fail(pc_status st, const std::string &msg);
 // Host part of compilation: validation, layering, grouping, table construction, EM maps.
 // tables_on_host = false leaves the sum / product layer tables to build_tables_device.
 pc_status compile_host(const pc_dag *dag, pc_circuit *c, bool tables_on_host);
+// Whether a layer is narrow enough for the dataflow launches at row stride Bs (narrower at a smaller one).
+bool flow_narrow(const pc_circuit *c, size_t layer, int64_t Bs);
 // Device part of compilation: transposes the block graph, sorts neighbour lists and fills every forward and
 // backward table with HIP kernels; allocates the handle's device arena and uploads the remaining metadata.
 pc_status build_tables_device(const pc_dag *dag, pc_circuit *c, void *stream);

@@ -24,10 +24,24 @@ struct GroupSet {
     const int32_t *ids[PC_MAX_SET], *nbr[PC_MAX_SET], *par[PC_MAX_SET], *aux[PC_MAX_SET];
 };
 
+// The same for rows given as neighbour lists (CSR) instead of padded groups: ids[0], nbr[0] = list, par[0] = start, aux[0];
+// backward: nbr[1] = the neighbours' layers, width[1] = first layer whose neighbours count.
+constexpr int PC_ROWS_ONE = 0, PC_ROWS_MULTI = 1, PC_ROWS_CSR = 2;
+
 struct ParamFlowDev {        // parameter blocks with the (sum block, child block) pairs that use them
     int32_t n_pb;
     const int32_t *pb, *ptr, *sum, *child;
     int64_t n_pairs;         // entries of sum / child
+};
+
+struct FlowDev {             // a dataflow launch (pc_flow.hip): entries from layer li0 to the root
+    const int32_t *ent, *rec, *list;
+    int32_t n_ent, max_nbr, li0;
+};
+
+struct RowsDev {             // product-layer rows of a dataflow launch as neighbour lists
+    const int32_t *ids, *start, *list, *lay, *aux;
+    int32_t n_rows, max_nbr, li0;
 };
 
 struct EmDev {
@@ -54,16 +68,18 @@ struct Profiler {
     ~Profiler();
 };
 void set_profiler(Profiler *p);                        // nullptr switches timing off
+struct Timed {                                          // brackets one kernel launch
+    hipStream_t s;
+    hipEvent_t b = nullptr;
+    Timed(int cls, hipStream_t stream);
+    ~Timed();
+};
 
 void launch_fill(float *p, int64_t n, float v, hipStream_t s);
-void launch_prepare_x(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats,
-                      int32_t *xT, hipStream_t s);
 void launch_readout(const float *l, const float *R, int64_t root_row, int64_t root_blk, int64_t Bs, int32_t B, float *ll,
                     hipStream_t s);
-void launch_init_flows(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk,
-                       int32_t root_id, int32_t K, int64_t Bs, int32_t B, hipStream_t s);
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
-                      float *l, hipStream_t s);
+                      float *l, float *R, hipStream_t s);
 void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
                       float *table_flow, hipStream_t s);
 // The four layer launchers take all table groups of the layer, packed into sets by make_group_sets: the groups of a
@@ -76,6 +92,10 @@ void launch_prod_fwd(const float *l, float *lout, float *R, const std::vector<Gr
 // Fpar: base the parents' flows are read from (= F, except in the product-scratch mode)
 void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, float *nfmax, const std::vector<GroupSet> &sets, int32_t K,
                      int64_t Bs, void *Ph, void *Pl, hipStream_t s);
+// the product layers of a dataflow launch: all their rows in one launch
+void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, int64_t Bs, hipStream_t s);
+void launch_prod_bwd_rows(const float *l, float *F, float *N, float *nfmax, const RowsDev &rows, int32_t K, int64_t Bs, void *Ph,
+                          void *Pl, hipStream_t s);
 // lch: base the product children are read from; l: base of the sum rows written
 void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, const std::vector<GroupSet> &sets, int32_t K,
                     int64_t Bs, hipStream_t s);
@@ -91,9 +111,20 @@ void launch_split_p(const float *X, const float *ref, const int32_t *blk_ids, in
 void launch_sum_bf16(const void *Th, const void *Tl, const void *Ph, const void *Pl, float *l, float *R, const float *nfmax,
                      float *F, bool bwd, const GroupSet &gs, int32_t K, int64_t Bs, hipStream_t s);
 bool param_flow_by_block(int32_t K);
+bool use_flow();
 void launch_param_flow(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *G,
                        const ParamFlowDev &pf, int32_t K, int64_t Bs, hipStream_t s);
 void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow, const EmDev &em, int32_t K,
                int32_t n_param_blocks, int32_t n_tables, int32_t n_cats, float step, float pc, hipStream_t s);
+
+// pc_flow.hip: the first launch of a forward / backward pass (ent, n_ent: blocks the dataflow launch will publish) and the
+// dataflow launch itself
+void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
+                          float *l, float *R, float *mail, const int32_t *ent, int32_t n_ent, int32_t K, int32_t *ticket,
+                          hipStream_t s);
+void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,
+                           int32_t K, int64_t Bs, int32_t B, const int32_t *ent, int32_t n_ent, int32_t *ticket, hipStream_t s);
+void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
+                 int32_t *ticket, float *ll, hipStream_t s);
 
 }  // namespace pc

@@ -24,25 +24,11 @@
 #include <cstdint>
 #include <cstring>
 
+#include "pc_device.h"
 #include "pc_kernels.h"
 
 namespace pc {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-#define PC_NEG_INF (-__builtin_inff())
-// Sum-layer terms are theta * exp(value - running maximum + PC_UP).  The maximum is taken over the values alone (as in
-// Alg. 1 / Alg. 4), so without the upward shift a term with a large weight whose value lies 87 nats below that of a
-// child with a weight near FLT_MIN would be flushed to zero although it dominates the sum.  With it every term or
-// factor that underflows is at least e^-20 smaller than the largest term kept, and nothing can overflow.  The shift
-// is kept small because the result is  maximum - PC_UP + log(sum): the larger the two cancelling parts, the larger
-// the absolute rounding error of a log-probability near zero.
-#define PC_UP 20.0f
-// Rescaling an accumulator when the running maximum grows by -delta: the factor exp(delta) itself may leave the
-// fp32 range where accumulator * factor does not (the accumulator can be as large as e^28 times the term count),
-// so the factor is applied as two multiplications by exp(delta / 2); below delta = -174 the result is nil anyway.
-__device__ inline float pc_half_scale(float delta) { return __expf(0.5f * fmaxf(delta, -174.0f)); }
 // The running maximum is only a reference: it is raised (and the accumulator rescaled) when a chunk exceeds it by
 // more than PC_LAZY nats, not at every new maximum -- with 64 columns per wave some column has a new maximum in
 // almost every chunk, and the rescale costs a multiplication per accumulator register.  Terms reach e^(PC_UP + PC_LAZY).
@@ -55,31 +41,6 @@ __global__ void k_fill(float *p, int64_t n, float v)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
-// xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
-__global__ void k_prepare_x(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B, int32_t D,
-                            int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT)
-{
-    __shared__ int32_t tile[32][33];
-    const int b0 = blockIdx.x * 32, v0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;           // 256 threads: ty in 0..7
-    for (int r = ty; r < 32; r += 8) {
-        const int b = b0 + r, v = v0 + tx;
-        int32_t val = -1;
-        if (b < B && v < D) {
-            const int64_t idx = (int64_t)b * D + v;
-            val = x[idx];
-            if (val < 0 || val >= n_cats) val = -2;
-            if (mask && mask[idx]) val = -1;
-        }
-        tile[r][tx] = val;
-    }
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int v = v0 + r, b = b0 + tx;
-        if (v < D && b < Bs) xT[(int64_t)v * Bs + b] = tile[tx][r];
-    }
 }
 
 __global__ void k_readout(const float *__restrict__ l, const float *__restrict__ R, int64_t root_row, int64_t root_blk,
@@ -95,11 +56,12 @@ __global__ void k_readout(const float *__restrict__ l, const float *__restrict__
 __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                    const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
                                                    const int32_t *__restrict__ tab, int32_t K, int32_t n_cats,
-                                                   int64_t Bs, float *__restrict__ l)
+                                                   int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
     const int u = blockIdx.x;
     const int64_t b = (int64_t)blockIdx.y * 256 + threadIdx.x;
     if (b >= Bs) return;
+    R[(int64_t)(ids[u] / K) * Bs + b] = 0.0f;                           // an input block's reference
     const int32_t xv = xT[(int64_t)var[u] * Bs + b];
     float *out = l + (int64_t)ids[u] * Bs + b;
     if (xv < 0) {
@@ -127,7 +89,7 @@ __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tab
 __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                         const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
                                                         const int32_t *__restrict__ tab, int32_t K, int32_t n_cats,
-                                                        int64_t Bs, float *__restrict__ l)
+                                                        int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
     extern __shared__ float smem[];
     float *tile = smem;                                                 // [K][65]
@@ -154,6 +116,7 @@ __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict_
     }
     __syncthreads();
     const int32_t id = ids[u];
+    if (threadIdx.x < 64 && b0 + threadIdx.x < Bs) R[(int64_t)(id / K) * Bs + b0 + threadIdx.x] = 0.0f;   // an input block's reference
     for (int idx = threadIdx.x; idx < K * 16; idx += 256) {
         const int row = idx >> 4, c4 = (idx & 15) * 4;
         if (b0 + c4 < Bs) {
@@ -361,10 +324,11 @@ __global__ __launch_bounds__(256) void k_input_bwd_sorted(const float *__restric
 // index is found with a few scalar compares and the group's fields are read from the argument at that index (one
 // more dependent scalar load, which launches with several groups -- thousands of workgroups -- hide).
 struct GroupRow { int32_t r, width; const int32_t *ids, *nbr, *par, *aux; };
-template <bool MULTI>
+template <int ROWS>
 __device__ inline GroupRow locate_row(const GroupSet &gs, int row)
 {
-    if (!MULTI) return GroupRow{row, gs.width[0], gs.ids[0], gs.nbr[0], gs.par[0], gs.aux[0]};   // a set of one group
+    if (ROWS == PC_ROWS_CSR) return GroupRow{row, 0, gs.ids[0], gs.nbr[0] + gs.par[0][row], nullptr, gs.aux[0]};
+    if (ROWS == PC_ROWS_ONE) return GroupRow{row, gs.width[0], gs.ids[0], gs.nbr[0], gs.par[0], gs.aux[0]};   // a set of one group
     int g = 0;                                                          // groups are in row order: count the starts passed
 #pragma unroll
     for (int i = 1; i < PC_MAX_SET; ++i) g += (i < gs.n && row >= gs.first[i]) ? 1 : 0;
@@ -448,13 +412,13 @@ __device__ inline void block_col_max(float (&mx)[4], float (*red)[64], int wave,
 template <typename ACC> struct Acc4 { ACC x, y, z, w; };
 // `l` is the base the children are read from, `lout` the base the block's own rows are written to: the same buffer,
 // except in the product-scratch mode (Sec. 5), where product rows live in a window that every product layer reuses.
-template <int RPT, int U, bool MULTI, int CL, typename ACC, bool PLANES>
+template <int RPT, int U, int ROWS, int CL, typename ACC, bool PLANES>
 __global__ __launch_bounds__(256) void k_prod_fwd(const float *__restrict__ l, float *__restrict__ lout, float *__restrict__ R,
                                                   const GroupSet gs, int32_t K, int64_t Bs, uint4 *__restrict__ Ph,
                                                   uint4 *__restrict__ Pl)
 {
     __shared__ float red[4][64];
-    const GroupRow gr = locate_row<MULTI>(gs, blockIdx.x);
+    const GroupRow gr = locate_row<ROWS>(gs, blockIdx.x);
     const int r = gr.r;
     constexpr int RG = 256 / CL;                                        // row groups: a thread owns rows rg, rg + RG, ...
     const int rg = threadIdx.x / CL, cl = threadIdx.x % CL, wave = threadIdx.x >> 6;
@@ -557,13 +521,13 @@ __global__ __launch_bounds__(256) void k_prod_fwd(const float *__restrict__ l, f
 // flow is final, so log_nf = log F - l (Alg. 3 / 4) and its column maximum per block are produced here.
 // `Fpar` is the base the parents' (product blocks') flows are read from, `F` the base of the rows' own flows: the same
 // buffer, except in the product-scratch mode, where product rows live in a window.
-template <int RPT, int U, bool MULTI, int CL, bool PLANES>
+template <int RPT, int U, int ROWS, int CL, bool PLANES>
 __global__ __launch_bounds__(256) void k_prod_bwd(const float *__restrict__ l, float *__restrict__ F, const float *__restrict__ Fpar,
                                                   float *__restrict__ N, float *__restrict__ nfmax, const GroupSet gs, int32_t K,
                                                   int64_t Bs, uint4 *__restrict__ Ph, uint4 *__restrict__ Pl)
 {
     __shared__ float red[4][64];
-    const GroupRow gr = locate_row<MULTI>(gs, blockIdx.x);
+    const GroupRow gr = locate_row<ROWS>(gs, blockIdx.x);
     const int r = gr.r;
     constexpr int RG = 256 / CL;                                        // row groups: a thread owns rows rg, rg + RG, ...
     const int rg = threadIdx.x / CL, cl = threadIdx.x % CL, wave = threadIdx.x >> 6;
@@ -572,8 +536,16 @@ __global__ __launch_bounds__(256) void k_prod_bwd(const float *__restrict__ l, f
     const int32_t *row_nbr = gr.nbr + (int64_t)r * gr.width;
     const int32_t id = gr.ids[r];
     const int32_t fl = gr.aux[r];                                       // uniform over the workgroup
-    const bool final_flow = (fl & 1) != 0, first = (fl & 2) != 0;
-    const int32_t cnt = fl >> 8;
+    bool final_flow = (fl & 1) != 0;
+    const bool first = ROWS == PC_ROWS_CSR || (fl & 2) != 0;
+    int32_t cnt = fl >> 8;
+    if (ROWS == PC_ROWS_CSR) {                                          // parents from the highest layer down: those from layer
+        const int32_t *lay = gs.nbr[1] + gs.par[0][r];                  // width[1] on belong to this launch
+        int32_t in_launch = cnt;
+        while (lay[in_launch - 1] < gs.width[1]) --in_launch;           // the first one always does
+        final_flow = final_flow && in_launch == cnt;
+        cnt = in_launch;
+    }
     float4 f[RPT], lv[RPT];
     if (in) {
 #pragma unroll
@@ -665,37 +637,6 @@ __global__ __launch_bounds__(256) void k_prod_bwd(const float *__restrict__ l, f
                              (int64_t)id + 16 * ks, ct, n_ct, Ph, Pl, lane);
         }
     }
-}
-
-// Blocks without parents, which no layer of the backward sweep writes.  An entry >= 0 is a sum block: the root
-// (flow 1 on node 0 of real samples with non-zero probability, Def. 2) or a sum block nobody uses (flow 0); its
-// log_nf rows and block maximum are set as well.  An entry < 0 is ~offset of another block (the null block, a
-// product or input block nobody uses): its flow rows are zeroed.  One workgroup per entry and 256 columns.
-__global__ __launch_bounds__(256) void k_init_flows(const float *__restrict__ l, float *__restrict__ F, float *__restrict__ N,
-                                                    float *__restrict__ nfmax, const int32_t *__restrict__ blk_ids,
-                                                    int32_t root_id, int32_t K, int64_t Bs, int32_t B)
-{
-    const int32_t entry = blk_ids[blockIdx.x];
-    const int64_t b = (int64_t)blockIdx.y * 256 + threadIdx.x;
-    if (b >= Bs) return;
-    if (entry < 0) {
-        const int32_t id = ~entry;
-        for (int k = 0; k < K; ++k) F[(int64_t)(id + k) * Bs + b] = 0.0f;
-        return;
-    }
-    const int32_t id = entry;
-    float top = PC_NEG_INF, f0 = 0.0f;
-    if (id == root_id) {
-        const float lv = l[(int64_t)id * Bs + b];
-        const bool live = b < B && lv > PC_NEG_INF;
-        f0 = live ? 1.0f : 0.0f;
-        top = live ? -lv : PC_NEG_INF;
-    }
-    for (int k = 0; k < K; ++k) {
-        F[(int64_t)(id + k) * Bs + b] = k == 0 ? f0 : 0.0f;
-        N[(int64_t)(id + k) * Bs + b] = k == 0 ? top : PC_NEG_INF;
-    }
-    nfmax[(int64_t)(id / K) * Bs + b] = top;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1084,7 +1025,6 @@ __global__ __launch_bounds__(256) void k_param_flow_small(const float *__restric
 // per-block log-space update of the accumulator in Alg. 1 / Alg. 4, with one log per output instead of one
 // per block).  Partial sums of the SPLIT waves are merged through LDS at the end.  No lane-dependent
 // branch surrounds an MFMA.
-#define PC_LOG2E 1.4426950408889634f
 // buffer descriptor of the main-loop loads: raw (stride 0), 2 GiB window from the chunk's base, 32-bit data format
 #define PC_BUF_RANGE 0x7fffffff
 #define PC_BUF_FLAGS 0x00020000
@@ -1111,7 +1051,7 @@ __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ t
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ct = wave / SPLIT, sp = wave % SPLIT;
-    const GroupRow gr = locate_row<MULTI>(gs, blockIdx.x / SUB);
+    const GroupRow gr = locate_row<MULTI ? PC_ROWS_MULTI : PC_ROWS_ONE>(gs, blockIdx.x / SUB);
     const int r = gr.r, sub = blockIdx.x % SUB;
     const int64_t col0 = ((int64_t)blockIdx.y * NCT + ct) * 32;
     const bool active = col0 < Bs;                                      // wave-uniform
@@ -1457,7 +1397,7 @@ __global__ __launch_bounds__(256, CT == 1 ? 2 : 1) void k_sum_bf16(const uint4 *
     __shared__ float lds[2 * CT * 3 * 1024 + 4 * CT * 64];              // partial tiles of the merge and the waves' references
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
-    const GroupRow gr = locate_row<false>(gs, blockIdx.x / SUB);
+    const GroupRow gr = locate_row<PC_ROWS_ONE>(gs, blockIdx.x / SUB);
     const int r = gr.r, sub = blockIdx.x % SUB;
     const int n_ct = (int)(Bs / 32);
     const int ct0 = blockIdx.y * CT;
@@ -2242,21 +2182,15 @@ Profiler::~Profiler()
     for (hipEvent_t e : pool) (void)hipEventDestroy(e);
 }
 
-namespace {
-struct Timed {                                                          // brackets one kernel launch
-    hipStream_t s;
-    hipEvent_t b = nullptr;
-    Timed(int cls, hipStream_t stream) : s(stream)
-    {
-        if (!g_prof) return;
-        hipEvent_t a = g_prof->get();
-        b = g_prof->get();
-        (void)hipEventRecord(a, s);
-        g_prof->recs.push_back({cls, a, b});
-    }
-    ~Timed() { if (b) (void)hipEventRecord(b, s); }
-};
-}  // namespace
+Timed::Timed(int cls, hipStream_t stream) : s(stream)
+{
+    if (!g_prof) return;
+    hipEvent_t a = g_prof->get();
+    b = g_prof->get();
+    (void)hipEventRecord(a, s);
+    g_prof->recs.push_back({cls, a, b});
+}
+Timed::~Timed() { if (b) (void)hipEventRecord(b, s); }
 
 static inline int grid_for(int64_t items, int per_block = 256, int cap = 1 << 16)
 {
@@ -2286,14 +2220,6 @@ void launch_fill(float *p, int64_t n, float v, hipStream_t s)
     hipLaunchKernelGGL(k_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, p, n, v);
 }
 
-void launch_prepare_x(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats,
-                      int32_t *xT, hipStream_t s)
-{
-    Timed timed(KC_MISC, s);
-    dim3 grid((unsigned)((Bs + 31) / 32), (unsigned)((D + 31) / 32));
-    hipLaunchKernelGGL(k_prepare_x, grid, dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT);
-}
-
 void launch_readout(const float *l, const float *R, int64_t root_row, int64_t root_blk, int64_t Bs, int32_t B, float *ll,
                     hipStream_t s)
 {
@@ -2301,27 +2227,18 @@ void launch_readout(const float *l, const float *R, int64_t root_row, int64_t ro
     hipLaunchKernelGGL(k_readout, dim3((B + 255) / 256), dim3(256), 0, s, l, R, root_row, root_blk, Bs, B, ll);
 }
 
-void launch_init_flows(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk,
-                       int32_t root_id, int32_t K, int64_t Bs, int32_t B, hipStream_t s)
-{
-    if (n_blk == 0) return;
-    Timed timed(KC_MISC, s);
-    dim3 grid((unsigned)n_blk, (unsigned)((Bs + 255) / 256));
-    hipLaunchKernelGGL(k_init_flows, grid, dim3(256), 0, s, l, F, N, nfmax, blk_ids, root_id, K, Bs, B);
-}
-
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
-                      float *l, hipStream_t s)
+                      float *l, float *R, hipStream_t s)
 {
     Timed timed(KC_INPUT_FWD, s);
     if (g.n_rows == 0) return;
     if ((K & 3) == 0 && K <= 64) {                                    // larger blocks: the tile costs occupancy, rows are long enough
         dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 63) / 64));
         const size_t lds = (size_t)K * 65 * 4 + 64 * 4;
-        hipLaunchKernelGGL(k_input_fwd_tile, grid, dim3(256), lds, s, tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l);
+        hipLaunchKernelGGL(k_input_fwd_tile, grid, dim3(256), lds, s, tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l, R);
     } else {
         dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 255) / 256));
-        hipLaunchKernelGGL(k_input_fwd, grid, dim3(256), 0, s, tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l);
+        hipLaunchKernelGGL(k_input_fwd, grid, dim3(256), 0, s, tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l, R);
     }
 }
 
@@ -2382,8 +2299,8 @@ void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int3
     } while (0)
 #define PC_DISPATCH_PROD(KERNEL, ...)                                                                      \
     do {                                                                                                   \
-        if (gs.n > 1) PC_DISPATCH_PROD_M(KERNEL, true, __VA_ARGS__);                                       \
-        else PC_DISPATCH_PROD_M(KERNEL, false, __VA_ARGS__);                                               \
+        if (gs.n > 1) PC_DISPATCH_PROD_M(KERNEL, PC_ROWS_MULTI, __VA_ARGS__);                              \
+        else PC_DISPATCH_PROD_M(KERNEL, PC_ROWS_ONE, __VA_ARGS__);                                         \
     } while (0)
 #define PC_PROD_FWD_F32(RPT, U, MULTI, CL) k_prod_fwd<RPT, U, MULTI, CL, float, false>
 #define PC_PROD_FWD_F64(RPT, U, MULTI, CL) k_prod_fwd<RPT, U, MULTI, CL, double, false>
@@ -2436,6 +2353,42 @@ void launch_prod_fwd(const float *l, float *lout, float *R, const std::vector<Gr
         } else if (set_width(gs) > 8) PC_DISPATCH_PROD(PC_PROD_FWD_F64, grid, dim3(256), 0, s, l, lout, R, gs, K, Bs, ph, pl);
         else PC_DISPATCH_PROD(PC_PROD_FWD_F32, grid, dim3(256), 0, s, l, lout, R, gs, K, Bs, ph, pl);
     }
+}
+
+// rows of several layers as one launch of neighbour lists (CSR); K is 32, 64 or 128
+static GroupSet csr_set(const RowsDev &rows)
+{
+    GroupSet gs;
+    std::memset(&gs, 0, sizeof(gs));
+    gs.n = 1;
+    gs.first[1] = rows.n_rows;
+    gs.width[0] = rows.max_nbr; gs.width[1] = rows.li0;
+    gs.ids[0] = rows.ids; gs.nbr[0] = rows.list; gs.nbr[1] = rows.lay; gs.par[0] = rows.start; gs.aux[0] = rows.aux;
+    return gs;
+}
+
+void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, int64_t Bs, hipStream_t s)
+{
+    if (rows.n_rows == 0) return;
+    Timed timed(KC_PROD_FWD, s);
+    const GroupSet gs = csr_set(rows);
+    const bool narrow = prod_narrow(gs, Bs);
+    dim3 grid((unsigned)rows.n_rows, (unsigned)(narrow ? (Bs + 31) / 32 : (Bs + 63) / 64));
+    if (rows.max_nbr > 8) PC_DISPATCH_PROD_M(PC_PROD_FWD_F64, PC_ROWS_CSR, grid, dim3(256), 0, s, l, l, R, gs, K, Bs, nullptr, nullptr);
+    else PC_DISPATCH_PROD_M(PC_PROD_FWD_F32, PC_ROWS_CSR, grid, dim3(256), 0, s, l, l, R, gs, K, Bs, nullptr, nullptr);
+}
+
+void launch_prod_bwd_rows(const float *l, float *F, float *N, float *nfmax, const RowsDev &rows, int32_t K, int64_t Bs, void *Ph,
+                          void *Pl, hipStream_t s)
+{
+    if (rows.n_rows == 0) return;
+    Timed timed(KC_PROD_BWD, s);
+    const GroupSet gs = csr_set(rows);
+    const bool narrow = prod_narrow(gs, Bs);
+    dim3 grid((unsigned)rows.n_rows, (unsigned)(narrow ? (Bs + 31) / 32 : (Bs + 63) / 64));
+    uint4 *ph = (uint4 *)Ph, *pl = (uint4 *)Pl;
+    if (ph) PC_DISPATCH_PROD_M(PC_PROD_BWD_P, PC_ROWS_CSR, grid, dim3(256), 0, s, l, F, F, N, nfmax, gs, K, Bs, ph, pl);
+    else PC_DISPATCH_PROD_M(PC_PROD_BWD, PC_ROWS_CSR, grid, dim3(256), 0, s, l, F, F, N, nfmax, gs, K, Bs, nullptr, nullptr);
 }
 
 void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, float *nfmax, const std::vector<GroupSet> &sets, int32_t K,
@@ -2568,6 +2521,7 @@ static int bf16_enabled()                                              // PC_BF1
     return on;
 }
 
+bool use_flow() { return !g_force_generic; }
 bool param_flow_by_block(int32_t K) { return use_mfma(K) || use_small(K); }
 
 void launch_param_flow(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *G,
