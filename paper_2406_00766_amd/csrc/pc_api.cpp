@@ -1,6 +1,7 @@
 // C-ABI entry points of libpc: compile + upload, inspection, forward, backward, EM step.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -78,15 +79,14 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
             add(&layer.d_pf_sum, layer.pf_sum); add(&layer.d_pf_child, layer.pf_child);
         }
     }
-    add(&c->d_pb_group, c->pb_group); add(&c->d_pb_rows, c->pb_rows); add(&c->d_pb_cols, c->pb_cols);
-    add(&c->d_group_nch, c->group_nch);
+    add(&c->d_pb_rows, c->pb_rows); add(&c->d_pb_cols, c->pb_cols); add(&c->d_group_nch, c->group_nch);
+    add(&c->d_em_ptr, c->em_ptr); add(&c->d_em_list, c->em_list);
     add(&c->d_init_ids, c->init_ids);
     add(&c->d_pf_pb, c->pf_pb); add(&c->d_pf_ptr, c->pf_ptr); add(&c->d_pf_sum, c->pf_sum); add(&c->d_pf_child, c->pf_child);
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { add(&f->d_ent, f->ent); add(&f->d_rec, f->rec); add(&f->d_list, f->list); }
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) {
         add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
     }
-    const size_t zrow_off = reserve((size_t)c->n_em_groups * c->K + 1);
     const size_t ztab_off = reserve((size_t)c->n_tables * c->K + 1);
     PC_HIP(hipMalloc(&c->d_arena, bytes));
     c->arena_bytes = bytes;
@@ -95,7 +95,6 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
         *f.dst = base + f.off;
         if (f.n) PC_HIP(hipMemcpyAsync(base + f.off, f.src, f.n, hipMemcpyHostToDevice, stream));
     }
-    c->d_zrow = (float *)(base + zrow_off);
     c->d_ztab = (float *)(base + ztab_off);
     PC_HIP(hipStreamSynchronize(stream));
     c->on_device = true;
@@ -514,10 +513,10 @@ pc_status pc_em_step(pc_circuit *c, float *theta, float *tables, float *theta_fl
     if (misaligned(theta) || misaligned(tables) || misaligned(theta_flow) || misaligned(table_flow))
         return fail(PC_ERR_ARG, "theta, tables and their flow arrays must be 16-byte aligned");
     ProfScope prof(c);
-    EmDev em{c->n_em_groups, c->d_pb_group, c->d_pb_rows, c->d_pb_cols, c->d_group_nch, c->d_zrow, c->d_ztab};
-    launch_em(theta, tables, theta_flow, table_flow, em, c->K, c->n_param_blocks, c->n_tables, c->n_cats, step,
-              pseudocount, (hipStream_t)stream);
-    launch_fill(theta_flow, (int64_t)c->K * c->K, 0.0f, (hipStream_t)stream);     // the padding block of the flows
+    const int32_t avg = c->em_ptr[c->n_em_groups] / std::max(c->n_em_groups, 1);
+    EmDev em{c->n_em_groups, (int32_t)c->em_ptr.size() - 1, avg, c->d_em_ptr, c->d_em_list, c->d_pb_rows, c->d_pb_cols, c->d_group_nch,
+             c->d_ztab};
+    launch_em(theta, tables, theta_flow, table_flow, em, c->K, c->n_tables, c->n_cats, step, pseudocount, (hipStream_t)stream);
     PC_HIP(hipGetLastError());
     c->fw_B = -1;
     return PC_OK;

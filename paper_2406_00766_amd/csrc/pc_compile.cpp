@@ -530,6 +530,16 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
         }
     }
     c->n_em_groups = (int32_t)group_list.size();
+    // parameter blocks of every group, then one group without rows per block that no sum block uses and for the padding block:
+    // the EM kernel only clears their flows
+    c->em_ptr.assign(1, 0);
+    c->em_list.clear();
+    for (const std::vector<int32_t> &list : group_list) {
+        for (int32_t p : list) c->em_list.push_back(p + 1);
+        c->em_ptr.push_back((int32_t)c->em_list.size());
+    }
+    for (int32_t p = 0; p <= P; ++p)
+        if (c->pb_group[p] < 0) { c->em_list.push_back(p); c->em_ptr.push_back((int32_t)c->em_list.size()); }
 
     // Parameter-centric flow tables (App. A.3): every (sum block, child block) pair that uses a parameter
     // block, so that the flows of tied edges are reduced together; pairs in ascending sum-block order.

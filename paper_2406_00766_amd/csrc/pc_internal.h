@@ -75,8 +75,9 @@ struct pc_circuit {
     // EM normalisation: parameter block -> (row group, real rows, real cols); row group -> child count
     int32_t n_em_groups = 0;
     std::vector<int32_t> pb_group, pb_rows, pb_cols, group_nch;
-    int32_t *d_pb_group = nullptr, *d_pb_rows = nullptr, *d_pb_cols = nullptr, *d_group_nch = nullptr;
-    float *d_zrow = nullptr;                          // [n_em_groups * K] row sums of flows
+    std::vector<int32_t> em_ptr, em_list;             // row group -> its parameter blocks (CSR); groups without rows at the end
+    int32_t *d_em_ptr = nullptr, *d_em_list = nullptr;
+    int32_t *d_pb_rows = nullptr, *d_pb_cols = nullptr, *d_group_nch = nullptr;
     float *d_ztab = nullptr;                          // [n_tables * K] column sums of table flows
 
     // parameter-centric flow tables: parameter block offset -> CSR list of (sum block, child block) node offsets

@@ -44,10 +44,10 @@ struct RowsDev {             // product-layer rows of a dataflow launch as neigh
     int32_t n_rows, max_nbr, li0;
 };
 
-struct EmDev {
-    int32_t n_groups;
-    const int32_t *pb_group, *pb_rows, *pb_cols, *group_nch;
-    float *zrow, *ztab;
+struct EmDev {               // row groups with their parameter blocks; those from n_groups on have no rows
+    int32_t n_groups, n_all, avg_list;
+    const int32_t *ptr, *list, *pb_rows, *pb_cols, *group_nch;
+    float *ztab;
 };
 
 void set_force_generic(bool on);
@@ -115,7 +115,7 @@ bool use_flow();
 void launch_param_flow(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *G,
                        const ParamFlowDev &pf, int32_t K, int64_t Bs, hipStream_t s);
 void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow, const EmDev &em, int32_t K,
-               int32_t n_param_blocks, int32_t n_tables, int32_t n_cats, float step, float pc, hipStream_t s);
+               int32_t n_tables, int32_t n_cats, float step, float pc, hipStream_t s);
 
 // pc_flow.hip: the first launch of a forward / backward pass (ent, n_ent: blocks the dataflow launch will publish) and the
 // dataflow launch itself

@@ -1,0 +1,37 @@
+"""EM step at the sizes where its kernels change: rows held in registers or read twice, tables held by workgroups of 256, 512
+and 1024 threads or shared out, against the oracle's update."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import pc_oracle as orc
+from paper_2406_00766_amd import binding as pcb
+from paper_2406_00766_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("make", [
+    lambda: W.rat_spn(32, 2, 4, 256, 32, 20, 81, n_cats=6),        # the root's row: 256 blocks, more than registers hold
+    lambda: W.hmm(3, 2048, 20, 32, 20, 82),                        # rows of 64 blocks, tied
+    lambda: W.hclt(64, 64, 64, 20, 83, n_cats=401),                # tables of 401 x 64: 512 threads
+    lambda: W.hclt(64, 64, 64, 20, 84, n_cats=1000),               # 1024 threads
+    lambda: W.hclt(64, 64, 64, 20, 85, n_cats=1030),               # shared out
+    lambda: W.hmm(4, 16, 2000, 8, 40, 86),                         # few tables of 2000 x 8: shared out
+])
+def test_em_kernel_shapes(make):
+    w = make()
+    print(f"case em {w.name}", flush=True)
+    c = pcb.Circuit(w)
+    rng = np.random.default_rng(8)
+    c.theta_flow.copy_(torch.from_numpy((rng.random(w.theta.size) * (w.theta.ravel() > 0)).astype(np.float32)))
+    c.table_flow.copy_(torch.from_numpy(rng.random(w.tables.size).astype(np.float32)))
+    tf, gf = (t.double().cpu().numpy() for t in (c.theta_flow, c.table_flow))
+    ref_th, ref_tb = orc.em_step(w, w.theta, w.tables, tf.reshape(w.theta.shape), gf.reshape(w.tables.shape), step=0.4, pseudocount=0.05)
+    c.em_step(0.4, 0.05)
+    torch.cuda.synchronize()
+    assert np.allclose(c.theta.cpu().numpy().reshape(w.theta.shape), ref_th, rtol=1e-4, atol=1e-9)
+    assert np.allclose(c.tables.cpu().numpy().reshape(w.tables.shape), ref_tb, rtol=1e-4, atol=1e-9)
+    assert float(c.theta_flow.abs().max()) == 0.0 and float(c.table_flow.abs().max()) == 0.0
+    c.close()
