@@ -28,11 +28,11 @@
 // rounded column maximum joins R), so every exponential sees an argument <= 0.5 and results need no running maximum.
 //
 // What bounds it: the chain through the layers.  Measured (time stamps of the tasks of one layer): values seen 0.5 - 0.7 us
-// after they were published, 0.4 - 0.5 us to exponentials and MFMAs (32 or 128 neighbour nodes; at 512, 1 us: the waves of a CU
-// share its matrix cores), 0.5 us to merge and publish: 1.6 us per layer at 32 nodes, 2 us at 128, 4.5 us at 512, against
-// 7 - 13 us for a layer's two launches.  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 34 us; forward,
-// 784-variable tree, M = 128, B = 100 908 -> 348 us; forward + backward, the same tree at B = 512 2.70 -> 1.68 ms; HMM T = 32, H = 512,
-// B = 77 865 -> 395 us.
+// after they were published, 0.4 - 0.5 us to exponentials and MFMAs (up to 128 neighbour nodes; at 512, 1 us: the waves of a CU
+// share its matrix cores), 0.2 - 0.5 us to merge and publish: 1.3 us per layer at 32 nodes, 2 us at 128, 4.5 us at 512, against
+// 7 - 13 us for a layer's two launches.  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 29 us; forward,
+// 784-variable tree, M = 128, B = 100 908 -> 350 us; forward + backward, the same tree at B = 512 2.70 -> 1.69 ms; HMM T = 32, H = 512,
+// B = 77 865 -> 390 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void k_begin_backward(const float *__restrict_
 // values in MFMA operand order: per block, 16 rows and 16 columns one 1 KiB tile, lane (j, g) holding rows 4 g .. 4 g + 3 of
 // column j -- one 16-byte load per lane where the row-major buffer would take four loads of 4 x 64 bytes, and no line shared
 // by two column tiles.
-template <int W, int RT, int NC, int NCH, bool BWD>
+template <int W, int RT, int NCH, bool BWD>
 __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__restrict__ theta, float *__restrict__ l, float *R,
                                                                  float *__restrict__ F, float *mail,
                                                                  const int32_t *__restrict__ ent, const int32_t *__restrict__ rec,
@@ -186,156 +186,147 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                                                                  int32_t K, int64_t Bs, int32_t li0, int32_t *ticket,
                                                                  float *__restrict__ ll, int32_t B)
 {
-    constexpr int NT = RT * NC;                                         // 16 x 16 tiles of the task
-    constexpr int TPW = (NT + W - 1) / W;                               // tiles whose results a wave writes
-    __shared__ floatx4 part[2][W][NT][64];                              // partial sums of the waves, double-buffered over tasks
-    __shared__ float pref[2][W][NC][16];                                // and their references
+    constexpr int TPW = (RT + W - 1) / W;                               // 16 x 16 result tiles that a wave writes
+    __shared__ floatx4 part[2][W][RT][W > 1 ? 64 : 1];                              // partial sums of the waves, double-buffered over tasks
+    __shared__ float pref[2][W][16];                                    // and their references
     __shared__ int32_t s_ticket[2];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
     const int ks = 31 - __builtin_clz(K);                               // K is 32, 64 or 128
     const int TM = 16 * RT, subs = K / TM, cpb = K >> 5;
 
-    if (threadIdx.x == 0) s_ticket[0] = atomicAdd(ticket, 1);
-    __syncthreads();
-    int t = __builtin_amdgcn_readfirstlane(s_ticket[0]);
-    for (int buf = 1; t < n_tasks; buf ^= 1) {
-        int nxt = 0;
-        if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);               // arrives while this task is worked on
-        const int ct = t % n_ct, q = t / n_ct, sub = q % subs, e_i = q / subs;
-        const int32_t row0 = ent[4 * e_i], rec0 = ent[4 * e_i + 1], n_nbr = ent[4 * e_i + 2], root = ent[4 * e_i + 3];
-        const int C = n_nbr * cpb;                                      // chunks of 32 neighbour nodes
-        const int64_t col0 = (int64_t)ct * (16 * NC) + j16;             // column of tile nc: col0 + 16 nc
+    struct Task { int32_t ct, sub, row0, rec0, root, C; };              // C: chunks of 32 neighbour nodes
+    auto decode = [&](int t) -> Task {
+        if (t >= n_tasks) return Task{0, 0, 0, 0, 0, 0};
+        const int q = t / n_ct, e = 4 * (q / subs);
+        return Task{t % n_ct, q % subs, ent[e], ent[e + 1], ent[e + 3], ent[e + 2] * cpb};
+    };
 
-        float lown[TPW][4], Rrow[NC];                                   // backward: the rows' own log-probabilities, R of their block
+    // operands of this wave's chunks cb, cb + W, ... (NCH of them; past the end the first one again, given the value -inf)
+    floatx4 th[NCH][2][RT], v[NCH][2], own_l[BWD ? NCH : 1][2];
+    float base[NCH];
+    int32_t koff[NCH], own[NCH], cnt[NCH], skip[NCH];
+    const int32_t *rp[NCH];
+    // item n of chunk i if it is (wait) / is not (!wait) one to wait for, else the null block (value 0); any: there is one
+    auto item = [&](int i, int n, bool wait, int &any) -> int32_t {
+        if (cnt[i] < 0) { if (n == 0 && !wait) { any = 1; return own[i]; } return 0; }
+        if (n >= cnt[i]) return 0;
+        int32_t it, lay;
+        if (n < 5) { it = rp[i][5 + n]; lay = rp[i][10 + n]; }
+        else { it = list[2 * (rp[i][1] + n)]; lay = list[2 * (rp[i][1] + n) + 1]; }
+        if ((lay >= li0) != wait) return 0;
+        any = 1;
+        return it;
+    };
+    auto row_values = [&](const float *X, int32_t id, int i, int64_t col, floatx4 (&x)[2]) {
+        const float *src = X + (int64_t)(id + koff[i] + 4 * g) * Bs + col;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k >> 2][k & 3] = src[(int64_t)(16 * (k >> 2) + (k & 3)) * Bs];
+    };
+    auto request = [&](const Task &T, int cb) {
+        const int64_t col = (int64_t)T.ct * 16 + j16;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int cc = cb + W * i < T.C ? cb + W * i : cb;
+            const int32_t *r = rec + 16 * (int64_t)(T.rec0 + cc / cpb);
+            rp[i] = r;
+            koff[i] = (cc % cpb) * 32;
+            cnt[i] = r[2]; own[i] = r[3];
+            if (!BWD && r[4] < li0) cnt[i] = -1;                        // evaluated before this launch
+            const float *tb = theta + r[0] + (BWD ? koff[i] * K + T.sub * TM : T.sub * TM * K + koff[i]);
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    if (BWD) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) th[i][c2][rt][e] = tb[(16 * c2 + 4 * g + e) * K + rt * 16 + j16];
+                    } else {
+                        th[i][c2][rt] = *reinterpret_cast<const floatx4 *>(tb + (rt * 16 + j16) * K + 16 * c2 + 4 * g);
+                    }
+                }
+            // the first item if it is there already (else zeros from the null block); backward: the sum block's own rows
+            skip[i] = 0;
+            const int32_t it = item(i, 0, false, skip[i]);
+            row_values(BWD ? F : l, it, i, col, v[i]);
+            if (BWD) row_values(l, own[i], i, col, own_l[i]);
+            base[i] = R[(int64_t)((BWD ? own[i] : it) >> ks) * Bs + col];
+        }
+    };
+
+    int nxt = 0;
+    if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);
+    if (W > 1) {
+        if (threadIdx.x == 0) s_ticket[1] = nxt;
+        __syncthreads();
+    }
+    int t = __builtin_amdgcn_readfirstlane(W > 1 ? s_ticket[1] : nxt);
+    for (int buf = 0; t < n_tasks; buf ^= 1) {
+        if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);               // arrives while this task is worked on
+        const Task T = decode(t);
+        if (wave < T.C) request(T, wave);
+        const int64_t col = (int64_t)T.ct * 16 + j16;
+
+        float lown[TPW][4], Rrow = 0.0f;                                // backward: the rows' own log-probabilities, R of their block
         if (BWD) {
 #pragma unroll
             for (int k = 0; k < TPW; ++k) {
-                const int u = wave + W * k < NT ? wave + W * k : 0, nc = u % NC, rt = u / NC;
+                const int rt = wave + W * k < RT ? wave + W * k : 0;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) lown[k][r] = l[(int64_t)(row0 + sub * TM + rt * 16 + 4 * g + r) * Bs + col0 + 16 * nc];
+                for (int r = 0; r < 4; ++r) lown[k][r] = l[(int64_t)(T.row0 + T.sub * TM + rt * 16 + 4 * g + r) * Bs + col];
             }
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) Rrow[nc] = R[(int64_t)(row0 >> ks) * Bs + col0 + 16 * nc];
+            Rrow = R[(int64_t)(T.row0 >> ks) * Bs + col];
         }
 
-        floatx4 acc[RT][NC];
-        float ref[NC];                                                  // reference of acc; -inf: nothing live yet
+        floatx4 acc[RT];
+        float ref = PC_NEG_INF;                                         // reference of acc; -inf: nothing live yet
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) {
-            ref[nc] = PC_NEG_INF;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt][nc] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-        for (int cb = wave; cb < C; cb += W * NCH) {                    // this wave's chunks cb, cb + W, ... NCH at a time
-            floatx4 th[NCH][2][RT], v[NCH][NC][2];
-            float base[NCH][NC];
-            int32_t koff[NCH], own[NCH], cnt[NCH];
-            const int32_t *rp[NCH];
-            int max_cnt = 0;
+        for (int cb = wave; cb < T.C;) {
+            // Values: the sum of the list items' rows (forward: log-probabilities; backward: flows).  One item of every chunk's
+            // list at a time, the null block past its end: a branch around a load makes the compiler wait for all before it.
+            int max_cnt = 0, since = 0;
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
-                const int cc = cb + W * i < C ? cb + W * i : cb;        // past the end: the first chunk again, with value -inf
-                const int32_t *r = rec + 16 * (int64_t)(rec0 + cc / cpb);
-                rp[i] = r;
-                koff[i] = (cc % cpb) * 32;
-                cnt[i] = r[2]; own[i] = r[3];
-                if (!BWD && r[4] < li0) cnt[i] = -1;                    // evaluated before this launch
-                max_cnt = max(max_cnt, cnt[i] < 0 ? 1 : cnt[i]);
-                const float *tb = theta + r[0] + (BWD ? koff[i] * K + sub * TM : sub * TM * K + koff[i]);
-#pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        if (BWD) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) th[i][c2][rt][e] = tb[(16 * c2 + 4 * g + e) * K + rt * 16 + j16];
-                        } else {
-                            th[i][c2][rt] = *reinterpret_cast<const floatx4 *>(tb + (rt * 16 + j16) * K + 16 * c2 + 4 * g);
-                        }
-                    }
-#pragma unroll
-                for (int nc = 0; nc < NC; ++nc) {
-                    base[i][nc] = 0.0f;
-#pragma unroll
-                    for (int c2 = 0; c2 < 2; ++c2) v[i][nc][c2] = floatx4{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-            // Values: the sum of the list items' rows (forward: log-probabilities; backward: flows).  One item of every chunk's
-            // list at a time; past the end of a list the null block (value 0): no branch surrounds a load, which would make
-            // the compiler wait for the loads before it.
-            floatx4 own_l[BWD ? NCH : 1][NC][2];
-            if (BWD) {                                                  // the sum blocks' own log-probabilities and references
-#pragma unroll
-                for (int i = 0; i < NCH; ++i)
-#pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k)
-                            own_l[i][nc][k >> 2][k & 3] = l[(int64_t)(own[i] + koff[i] + 16 * (k >> 2) + 4 * g + (k & 3)) * Bs + col0 + 16 * nc];
-                        base[i][nc] = Rrow[nc] - R[(int64_t)(own[i] >> ks) * Bs + col0 + 16 * nc];
-                    }
+                max_cnt = max(max_cnt, cnt[i]);
+                if (BWD) base[i] = Rrow - base[i];
             }
             // long lists: a running fp32 sum of many log-probabilities loses more than the flows' tolerance allows, so every
             // four items its integer part moves into the reference
             auto settle = [&]() {
 #pragma unroll
-                for (int i = 0; i < NCH; ++i)
+                for (int i = 0; i < NCH; ++i) {
+                    float cm = v[i][0][0];
 #pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) {
-                        float cm = v[i][nc][0][0];
+                    for (int k = 1; k < 8; ++k) cm = fmaxf(cm, v[i][k >> 2][k & 3]);
+                    cm = max_over_groups(cm);
+                    cm = cm > PC_NEG_INF ? rintf(cm) : 0.0f;
+                    base[i] += cm;
 #pragma unroll
-                        for (int k = 1; k < 8; ++k) cm = fmaxf(cm, v[i][nc][k >> 2][k & 3]);
-                        cm = max_over_groups(cm);
-                        cm = cm > PC_NEG_INF ? rintf(cm) : 0.0f;
-                        base[i][nc] += cm;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) v[i][nc][k >> 2][k & 3] -= cm;
-                    }
+                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] -= cm;
+                }
             };
-            // item n of chunk i if it is (wait) / is not (!wait) to be waited for, else the null block; any: there is one
-            auto item = [&](int i, int n, bool wait, int &any) -> int32_t {
-                if (cnt[i] < 0) { if (n == 0 && !wait) { any = 1; return own[i]; } return 0; }
-                if (n >= cnt[i]) return 0;
-                int32_t it, lay;
-                if (n < 5) { it = rp[i][5 + n]; lay = rp[i][10 + n]; }
-                else { it = list[2 * (rp[i][1] + n)]; lay = list[2 * (rp[i][1] + n) + 1]; }
-                if ((lay >= li0) != wait) return 0;
-                any = 1;
-                return it;
-            };
-            int since = 0;
-            for (int n = 0; n < max_cnt; ++n) {                         // items of earlier launches
+            for (int n = 1; n < max_cnt; ++n) {                         // items of earlier launches (the first: requested before)
                 int32_t its[NCH];
                 int any = 0;
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) its[i] = item(i, n, false, any);
                 if (!any) continue;
-                floatx4 x[NCH][NC][2];
-                float xr[NCH][NC];
+                floatx4 x[NCH][2];
+                float xr[NCH];
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) {
-                    const int32_t it = its[i];
-                    const float *src = (BWD ? F : l) + (int64_t)(it + koff[i] + 4 * g) * Bs + col0;
-#pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) x[i][nc][k >> 2][k & 3] = src[(int64_t)(16 * (k >> 2) + (k & 3)) * Bs + 16 * nc];
-                        if (!BWD) xr[i][nc] = R[(int64_t)(it >> ks) * Bs + col0 + 16 * nc];
-                    }
+                    row_values(BWD ? F : l, its[i], i, col, x[i]);
+                    if (!BWD) xr[i] = R[(int64_t)(its[i] >> ks) * Bs + col];
                 }
 #pragma unroll
-                for (int i = 0; i < NCH; ++i)
+                for (int i = 0; i < NCH; ++i) {
 #pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                        for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) v[i][nc][c2][e] += x[i][nc][c2][e];
-                        if (!BWD) base[i][nc] += xr[i][nc];
-                    }
-                if (!BWD && (++since & 3) == 0) settle();
+                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
+                    if (!BWD) base[i] += xr[i];
+                }
+                if (!BWD && (++since & 3) == 3) settle();
             }
             for (int n = 0; n < max_cnt; ++n) {                         // items of this launch: poll until they are there
                 int32_t its[NCH];
@@ -343,136 +334,111 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) its[i] = item(i, n, true, any);
                 if (!any) continue;
-                const float *src[NCH], *sr[NCH];
-#pragma unroll
-                for (int i = 0; i < NCH; ++i) {
-                    const int32_t it = its[i];
-                    src[i] = mail + (int64_t)(it + koff[i]) * Bs + (int64_t)ct * (256 * NC);
-                    sr[i] = R + (int64_t)(it >> ks) * Bs + col0;
-                }
-                floatx4 x[NCH][NC][2];
-                float xr[NCH][NC];
+                floatx4 x[NCH][2];
+                float xr[NCH];
                 for (int spin = 0;; ++spin) {
                     asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int i = 0; i < NCH; ++i)
-#pragma unroll
-                        for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                            for (int c2 = 0; c2 < 2; ++c2) x[i][nc][c2] = mail_load(src[i] + (int64_t)(16 * c2) * Bs + 256 * nc, 16 * lane);
-                            if (!BWD) xr[i][nc] = flow_load(sr[i] + 16 * nc);
-                        }
                     int missing = 0;
 #pragma unroll
-                    for (int i = 0; i < NCH; ++i)
+                    for (int i = 0; i < NCH; ++i) {
+                        const float *src = mail + (int64_t)(its[i] + koff[i]) * Bs + (int64_t)T.ct * 256;
+                        x[i][0] = mail_load(src, 16 * lane);
+                        x[i][1] = mail_load(src + 16 * Bs, 16 * lane);
+                        if (!BWD) xr[i] = flow_load(R + (int64_t)(its[i] >> ks) * Bs + col);
+                    }
 #pragma unroll
-                        for (int nc = 0; nc < NC; ++nc) {
+                    for (int i = 0; i < NCH; ++i) {
 #pragma unroll
-                            for (int k = 0; k < 8; ++k) missing |= is_sentinel(x[i][nc][k >> 2][k & 3]);
-                            if (!BWD) missing |= is_sentinel(xr[i][nc]);
-                        }
+                        for (int k = 0; k < 8; ++k) missing |= is_sentinel(x[i][k >> 2][k & 3]);
+                        if (!BWD) missing |= is_sentinel(xr[i]);
+                    }
                     if (!__any(missing) || flow_give_up(spin, ticket)) break;
                     __builtin_amdgcn_s_sleep(1);
                 }
 #pragma unroll
-                for (int i = 0; i < NCH; ++i)
+                for (int i = 0; i < NCH; ++i) {
 #pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                        for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) v[i][nc][c2][e] += x[i][nc][c2][e];
-                        if (!BWD) base[i][nc] += xr[i][nc];
-                    }
-                if (!BWD && (++since & 3) == 0) settle();
+                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
+                    if (!BWD) base[i] += xr[i];
+                }
+                if (!BWD && (++since & 3) == 3) settle();
             }
             // log_nf of the parents; integer reference of each chunk; the largest live one
-            float nref[NC];
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) nref[nc] = ref[nc];
-#pragma unroll
-            for (int i = 0; i < NCH; ++i)
-#pragma unroll
-                for (int nc = 0; nc < NC; ++nc) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        float &x = reinterpret_cast<float *>(&v[i][nc][0])[k];
-                        if (BWD) {
-                            const float lo = own_l[i][nc][k >> 2][k & 3];
-                            x = (x > 0.0f && lo > PC_NEG_INF) ? __logf(x) - lo : PC_NEG_INF;
-                        }
-                        if (cb + W * i >= C) x = PC_NEG_INF;
-                    }
-                    float cm = v[i][nc][0][0];
-#pragma unroll
-                    for (int k = 1; k < 8; ++k) cm = fmaxf(cm, v[i][nc][k >> 2][k & 3]);
-                    cm = max_over_groups(cm);
-                    const bool live = cm > PC_NEG_INF;
-                    cm = live ? rintf(cm) : 0.0f;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) v[i][nc][k >> 2][k & 3] -= cm;
-                    base[i][nc] = live ? base[i][nc] + cm : PC_NEG_INF;
-                    nref[nc] = fmaxf(nref[nc], base[i][nc]);
-                }
-            if (cb != wave) {                                           // not the first batch: rescale
-#pragma unroll
-                for (int nc = 0; nc < NC; ++nc) {
-                    const float sc = nref[nc] > PC_NEG_INF ? pc_half_scale(ref[nc] - nref[nc]) : 1.0f;
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[rt][nc][r] = acc[rt][nc][r] * sc * sc;
-                }
-            }
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) ref[nc] = nref[nc];
+            float nref = ref;
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
-                float sh2[NC];                                          // exp(v + base - ref + PC_UP) = exp2(v * log2e + sh2)
+                float cm = PC_NEG_INF;
 #pragma unroll
-                for (int nc = 0; nc < NC; ++nc)
-                    sh2[nc] = base[i][nc] > PC_NEG_INF ? (base[i][nc] - ref[nc] + PC_UP) * PC_LOG2E : 0.0f;   // dead: v = -inf
+                for (int k = 0; k < 8; ++k) {
+                    float x = v[i][k >> 2][k & 3];
+                    if (BWD) {
+                        const float lo = own_l[i][k >> 2][k & 3];
+                        x = (x > 0.0f && lo > PC_NEG_INF) ? __logf(x) - lo : PC_NEG_INF;
+                    }
+                    if (cb + W * i >= T.C) x = PC_NEG_INF;
+                    v[i][k >> 2][k & 3] = x;
+                    cm = fmaxf(cm, x);
+                }
+                cm = max_over_groups(cm);
+                const bool live = cm > PC_NEG_INF;
+                cm = live ? rintf(cm) : 0.0f;
 #pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int nc = 0; nc < NC; ++nc) {
-                            const float p = __builtin_amdgcn_exp2f(fmaf(v[i][nc][c2][e], PC_LOG2E, sh2[nc]));
-#pragma unroll
-                            for (int rt = 0; rt < RT; ++rt)
-                                acc[rt][nc] = __builtin_amdgcn_mfma_f32_16x16x4f32(th[i][c2][rt][e], p, acc[rt][nc], 0, 0, 0);
-                        }
+                for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] -= cm;
+                base[i] = live ? base[i] + cm : PC_NEG_INF;
+                nref = fmaxf(nref, base[i]);
             }
+            if (cb != wave) {                                           // not the first batch: rescale
+                const float sc = nref > PC_NEG_INF ? pc_half_scale(ref - nref) : 1.0f;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[rt][r] = acc[rt][r] * sc * sc;
+            }
+            ref = nref;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                // exp(v + base - ref + PC_UP) = exp2(v * log2e + sh2); dead: v = -inf
+                const float sh2 = base[i] > PC_NEG_INF ? (base[i] - ref + PC_UP) * PC_LOG2E : 0.0f;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(v[i][k >> 2][k & 3], PC_LOG2E, sh2));
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(th[i][k >> 2][rt][k & 3], p, acc[rt], 0, 0, 0);
+                }
+            }
+            cb += W * NCH;
+            if (cb < T.C) request(T, cb);
         }
-
-        // the waves' partial sums meet in LDS; tile u = (rt, nc) goes to wave u % W
+        // the waves' partial sums meet in LDS; tile rt goes to wave rt % W
+        if (W > 1) {
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) part[buf][wave][rt * NC + nc][lane] = acc[rt][nc];
-        if (g == 0) {
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) pref[buf][wave][nc][j16] = ref[nc];
+            for (int rt = 0; rt < RT; ++rt) part[buf][wave][rt][lane] = acc[rt];
+            if (g == 0) pref[buf][wave][j16] = ref;
+            if (threadIdx.x == 0) s_ticket[buf] = nxt;
+            __syncthreads();
         }
-        if (threadIdx.x == 0) s_ticket[buf] = nxt;
-        __syncthreads();
-        t = __builtin_amdgcn_readfirstlane(s_ticket[buf]);
+        t = __builtin_amdgcn_readfirstlane(W > 1 ? s_ticket[buf] : nxt);
 #pragma unroll
         for (int k = 0; k < TPW; ++k) {
-            const int u = wave + W * k;
-            if (u >= NT) break;                                         // wave-uniform
-            const int nc = u % NC, rt = u / NC;
-            float rw[W], top = PC_NEG_INF;
-#pragma unroll
-            for (int w = 0; w < W; ++w) { rw[w] = pref[buf][w][nc][j16]; top = fmaxf(top, rw[w]); }
+            const int rt = wave + W * k;
+            if (rt >= RT) break;                                        // wave-uniform
+            float top = PC_NEG_INF;
             floatx4 tot = {0.f, 0.f, 0.f, 0.f}, val;
+            if (W == 1) {
+                top = ref;
+                tot = acc[k];
+            } else {
+                float rw[W];
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float sc = rw[w] > PC_NEG_INF ? pc_half_scale(rw[w] - top) : 0.0f;
-                const floatx4 pw = part[buf][w][u][lane];
+                for (int w = 0; w < W; ++w) { rw[w] = pref[buf][w][j16]; top = fmaxf(top, rw[w]); }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) tot[r] += pw[r] * sc * sc;
+                for (int w = 0; w < W; ++w) {
+                    const float sc = rw[w] > PC_NEG_INF ? pc_half_scale(rw[w] - top) : 0.0f;
+                    const floatx4 pw = part[buf][w][rt][lane];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tot[r] += pw[r] * sc * sc;
+                }
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -486,17 +452,16 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     val[r] = no_sentinel(fmaf(__builtin_amdgcn_logf(tot[r] * 0x1p-24f), 0.6931471805599453f, 16.635532333f - PC_UP));
                 }
             }
-            const int rrow = sub * TM + rt * 16;
-            const int64_t col = col0 + 16 * nc;
+            const int rrow = T.sub * TM + rt * 16;
             const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(mail + (int64_t)(row0 + rrow) * Bs + (int64_t)ct * (256 * NC) + 256 * nc), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
+                (void *)(mail + (int64_t)(T.row0 + rrow) * Bs + (int64_t)T.ct * 256), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, val), rm, 16 * lane, 0, PC_AUX_DEVICE);
             if (!BWD && rrow == 0 && g == 0) {
                 const float rs = top > PC_NEG_INF ? top : 0.0f;         // all children dead: any finite reference
-                __hip_atomic_store(R + (int64_t)(row0 >> ks) * Bs + col, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (root && col < B) ll[col] = rs + val[0];
+                __hip_atomic_store(R + (int64_t)(T.row0 >> ks) * Bs + col, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (T.root && col < B) ll[col] = rs + val[0];
             }
-            float *out = (BWD ? F : l) + (int64_t)(row0 + rrow + 4 * g) * Bs + col;
+            float *out = (BWD ? F : l) + (int64_t)(T.row0 + rrow + 4 * g) * Bs + col;
 #pragma unroll
             for (int r = 0; r < 4; ++r) out[(int64_t)r * Bs] = val[r];
         }
@@ -527,24 +492,28 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
 {
     if (f.n_ent == 0) return;
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
-    // Row tiles of 32 halve the number of tasks that read a neighbour; eight waves where four would have more than one chunk
-    // each (measured with 4, 8, 16 waves, 16 - 64 rows, 16 and 32 columns, 1 - 4 chunks at once: 32 columns lost everywhere, 64 rows
-    // won 1 - 2 % on 128- and 256-state trees and lost elsewhere).
+    // As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
+    // 16 x 32 states); row tiles of 32 halve the number of tasks that read a neighbour and win from 64 tasks per layer on, tiles
+    // of 16 leave a shorter chain before.  Measured with 1 - 16 waves, 16 - 64 rows, 16 and 32 columns, 1 - 4 chunks at once: 32
+    // columns lost everywhere, 64 rows won 1 - 2 % on 128- and 256-state trees and lost elsewhere.
     const int chunks = f.max_nbr * (K / 32);
-#define PC_FLOW(WW, RR, NN, HH)                                                                                          \
+#define PC_FLOW(WW, RR, HH)                                                                                                  \
     do {                                                                                                                     \
-        const int n_ct = (int)(Bs / (16 * NN));                                                                              \
+        const int n_ct = (int)(Bs / 16);                                                                                     \
         const int64_t tasks = (int64_t)f.n_ent * (K / (16 * RR)) * n_ct;                                                     \
-        const int grid = (int)std::min<int64_t>(tasks, 512);                                                                \
-        if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, NN, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+        const int grid = (int)std::min<int64_t>(tasks, 512);                                                                 \
+        if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                     f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                  \
-        else hipLaunchKernelGGL((k_flow<WW, RR, NN, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+        else hipLaunchKernelGGL((k_flow<WW, RR, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                 f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                      \
     } while (0)
-    if (chunks == 1) PC_FLOW(4, 1, 1, 1);
-    else if (chunks <= 4) PC_FLOW(4, 2, 1, 1);
-    else if (chunks <= 8) PC_FLOW(8, 2, 1, 1);
-    else PC_FLOW(8, 2, 1, 2);
+    if (chunks == 1) {
+        if ((int64_t)f.n_ent * (K / 16) * (Bs / 16) >= 64 * (int64_t)f.n_levels) PC_FLOW(1, 2, 1);
+        else PC_FLOW(1, 1, 1);
+    } else if (chunks == 2) PC_FLOW(2, 2, 1);
+    else if (chunks <= 4) PC_FLOW(4, 2, 1);
+    else if (chunks <= 8) PC_FLOW(8, 2, 1);
+    else PC_FLOW(8, 2, 2);
 #undef PC_FLOW
 }
 
