@@ -741,7 +741,7 @@ __global__ __launch_bounds__(256) void k_sum_bwd_param_generic(const float *__re
 }
 
 // ------------------------------------------------------------------------------------------
-// small-block sum-layer kernels (K in {1, 2, 4, 8, 16}): block-based parallelisation (Sec. 4.1) on the vector
+// small-block sum-layer kernels (K in {1, 2, 4, 8}): block-based parallelisation (Sec. 4.1) on the vector
 // ALU.  A thread owns one sample column of one node block: it reads each of the K neighbour values once,
 // exponentiates it once and uses it for all K outputs of the block -- the K-fold cut in reloads and in
 // exponentials that Sec. 4.1 describes.  The K x K weights have workgroup-uniform addresses and ride in scalar
@@ -830,7 +830,6 @@ __global__ __launch_bounds__(256) void k_sum_fwd_small(const float *__restrict__
             for (int i = 0; i < K; ++i) {
 #pragma unroll
                 for (int jj = 0; jj < K; ++jj) acc[i] = fmaf(th[i * K + jj], pv[jj], acc[i]);
-                if (K == 16 && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // keeps the 256 weights from all being live in scalar registers
             }
         }
     }
@@ -987,6 +986,206 @@ __global__ __launch_bounds__(256) void k_param_flow_small(const float *__restric
                 const float th = theta[at];
                 if (th > 0.0f) G[at] += pc_flow_out(th, acc[e]);
             }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// K = 16 on the matrix cores: one block is one v_mfma_f32_16x16x4_f32 tile
+// ------------------------------------------------------------------------------------------
+// A (16 x 4): lane holds A[lane % 16][lane / 16], B (4 x 16): B[lane / 16][lane % 16], D: register r holds
+// D[4 * (lane / 16) + r][lane % 16].  Forward and backward to the children: a wave owns one node block x 32 columns; per
+// neighbour block step e pairs lane group g with node 4 g + e, so the forward weights are one 16-byte load per lane (the
+// block's 1 KiB, coalesced) and nothing goes through LDS.  U neighbours are requested together.  SPLIT = 4: the waves of a
+// workgroup share one tile and deal the neighbours among them (launches too small to fill the chip).  References as in the
+// other kernels: forward the largest integer reference of a live neighbour, backward the running maximum of the parents'.
+// What bounds it: exponentials (a quarter of the vector rate) and MFMAs in turn, eight of each per neighbour.  Measured on
+// 28 sets of 1024 x 1024, 30 % of the 16 x 16 blocks kept, B = 333 (6.2 GFLOP): forward 526 -> 179 us, backward 432 -> 165 us
+// against the vector kernel (64 columns per wave: 205 and 216 us, the operands of four neighbours then take 170 - 210 registers).
+template <bool BWD, int SPLIT>
+__global__ __launch_bounds__(256) void k_sum_16(const float *__restrict__ theta, const float *__restrict__ X, float *__restrict__ l,
+                                                float *__restrict__ R, const float *__restrict__ nfmax, float *__restrict__ F,
+                                                const int32_t *__restrict__ ids, const int32_t *__restrict__ nbr,
+                                                const int32_t *__restrict__ par, const int32_t *__restrict__ aux, int32_t width, int64_t Bs)
+{
+    constexpr int K = 16, U = 4, NC = 2;
+    __shared__ floatx4 part[SPLIT > 1 ? 4 : 1][NC][SPLIT > 1 ? 64 : 1];
+    __shared__ float pref[SPLIT > 1 ? 4 : 1][NC][16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
+    const int r = blockIdx.x;
+    const int64_t cg = SPLIT > 1 ? blockIdx.y : (int64_t)blockIdx.y * 4 + wave;   // group of NC column tiles
+    if (SPLIT == 1 && cg * NC * 16 >= Bs) return;
+    int64_t col[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) col[c] = (cg * NC + c) * 16 + j16;     // Bs is a multiple of 32
+    const int32_t *row_nbr = nbr + (int64_t)r * width, *row_par = par + (int64_t)r * width;
+    const int32_t id = ids[r], fl = aux[r], cnt = fl >> 8;
+    float Rown[NC];
+    floatx4 lown[BWD ? NC : 1];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        Rown[c] = BWD ? R[(int64_t)(id / K) * Bs + col[c]] : 0.0f;
+        if (BWD)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) lown[c][e] = l[(int64_t)(id + 4 * g + e) * Bs + col[c]];
+    }
+    floatx4 acc[NC];
+    float m[NC];                                                        // reference of acc, -inf: nothing live yet
+#pragma unroll
+    for (int c = 0; c < NC; ++c) { acc[c] = floatx4{0.f, 0.f, 0.f, 0.f}; m[c] = PC_NEG_INF; }
+
+    const int first_j = SPLIT > 1 ? wave : 0;
+    for (int j0 = first_j; j0 < cnt; j0 += U * SPLIT) {
+        floatx4 th[U], v[U][NC];
+        float rb[U][NC], bm[BWD ? U : 1][NC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * SPLIT < cnt ? j0 + u * SPLIT : j0;   // past the end: the first again, unused
+            const int32_t ns = row_nbr[j], ps = row_par[j];
+            if (BWD) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) th[u][e] = theta[(int64_t)ps + (4 * g + e) * K + j16];
+            } else {
+                th[u] = *reinterpret_cast<const floatx4 *>(theta + (int64_t)ps + j16 * K + 4 * g);
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][c][e] = X[(int64_t)(ns + 4 * g + e) * Bs + col[c]];
+                rb[u][c] = R[(int64_t)(ns / K) * Bs + col[c]];
+                if (BWD) bm[u][c] = nfmax[(int64_t)(ns / K) * Bs + col[c]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (j0 + u * SPLIT >= cnt) break;                           // wave-uniform
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const float d = BWD ? Rown[c] - rb[u][c] : rb[u][c];
+                const float top = BWD ? bm[u][c] + d : d;
+                if (__any(top > (BWD ? m[c] + PC_LAZY : m[c]))) {       // a larger reference (forward: unless the block is dead)
+                    float live = v[u][c][0];
+                    if (!BWD) {
+                        live = fmaxf(fmaxf(live, v[u][c][1]), fmaxf(v[u][c][2], v[u][c][3]));
+                        live = fmaxf(live, __shfl_xor(live, 16)); live = fmaxf(live, __shfl_xor(live, 32));
+                    }
+                    const bool raise = (BWD ? top > m[c] + PC_LAZY : top > m[c] && live > PC_NEG_INF);
+                    const float mn = raise ? top : m[c];
+                    const float sc = mn > PC_NEG_INF ? pc_half_scale(m[c] - mn) : 1.0f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[c][e] = acc[c][e] * sc * sc;
+                    m[c] = mn;
+                }
+                const float sh2 = m[c] > PC_NEG_INF ? (d - m[c] + PC_UP) * PC_LOG2E : 0.0f;   // dead so far: v = -inf
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(v[u][c][e], PC_LOG2E, sh2));
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(th[u][e], p, acc[c], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (SPLIT > 1) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            part[wave][c][lane] = acc[c];
+            if (g == 0) pref[wave][c][j16] = m[c];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (SPLIT > 1) {
+            if (wave != c % 4) continue;                                // wave-uniform
+            float mt = PC_NEG_INF;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) mt = fmaxf(mt, pref[w][c][j16]);
+            floatx4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float mw = pref[w][c][j16], sc = mw > PC_NEG_INF ? pc_half_scale(mw - mt) : 0.0f;
+                const floatx4 pw = part[w][c][lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tot[e] += pw[e] * sc * sc;
+            }
+            acc[c] = tot;
+            m[c] = mt;
+        }
+        if (!BWD && g == 0) R[(int64_t)(id / K) * Bs + col[c]] = m[c] > PC_NEG_INF ? m[c] : 0.0f;   // all dead: any finite reference
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t at = (int64_t)(id + 4 * g + e) * Bs + col[c];
+            if (BWD) {
+                const float add = m[c] > PC_NEG_INF ? __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(acc[c][e]) + (lown[c][e] + (m[c] - PC_UP)) * PC_LOG2E)
+                                                    : 0.0f;
+                if (fl & 2) F[at] = add;                                // first layer that feeds the block stores
+                else if (add > 0.0f) F[at] += add;
+            } else {
+                // ln(sum) - PC_UP, the logarithm taken of sum / 2^24 (as in k_sum_mfma)
+                l[at] = fmaf(__builtin_amdgcn_logf(acc[c][e] * 0x1p-24f), 0.6931471805599453f, 16.635532333f - PC_UP);
+            }
+        }
+    }
+}
+
+// Parameter flows, K = 16: by parameter block as in k_param_flow_mfma, the batch on the reduction index: a wave takes one
+// 16 x 16 block (n_split > 1: a share of its pairs, added atomically) and 16 samples per four MFMAs, lane (row, g) holding
+// samples 4 g .. 4 g + 3 of its row -- 16-byte loads, no staging.  Per 64 samples the shifts of the two factors are computed once,
+// lane = sample, and handed round through LDS (2 KiB per workgroup; LDS operations of one wave complete in order): 262 -> 216 us
+// against every lane computing the shifts of its own samples, 382 us on the vector ALU (34 312 blocks, B = 333).
+__global__ __launch_bounds__(256) void k_param_flow_16(const float *__restrict__ theta, const float *__restrict__ l,
+                                                       const float *__restrict__ R, const float *__restrict__ N,
+                                                       const float *__restrict__ nfmax, float *__restrict__ G,
+                                                       const int32_t *__restrict__ pf_pb, const int32_t *__restrict__ pf_ptr,
+                                                       const int32_t *__restrict__ pf_sum, const int32_t *__restrict__ pf_child,
+                                                       int32_t n_pb, int32_t n_split, int64_t Bs)
+{
+    constexpr int K = 16, CH = 4;
+    __shared__ float q[4][2][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
+    const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+    const int pidx = (int)(w / n_split), spl = (int)(w % n_split);
+    if (pidx >= n_pb) return;                                           // wave-uniform; no workgroup barrier below
+    const int32_t pb = pf_pb[pidx];
+    const int i0 = pf_ptr[pidx], i1 = pf_ptr[pidx + 1];
+    floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int inst = i0 + spl; inst < i1; inst += n_split) {
+        const int32_t ms = pf_sum[inst], ns = pf_child[inst];
+        const float *np = N + (int64_t)(ms + j16) * Bs + 4 * g, *lp = l + (int64_t)(ns + j16) * Bs + 4 * g;
+        for (int64_t b = 0; b < Bs; b += 64) {                          // Bs is a multiple of 32: the last round may be a half one
+            const bool whole = b + 64 <= Bs;
+            floatx4 nf[CH], lc[CH];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int64_t at = b + (c < 2 || whole ? 16 * c : 0);
+                nf[c] = *reinterpret_cast<const floatx4 *>(np + at);
+                lc[c] = *reinterpret_cast<const floatx4 *>(lp + at);
+            }
+            const int64_t bl = b + (whole ? lane : lane & 31);
+            const float mx = nfmax[(int64_t)(ms / K) * Bs + bl];
+            const float gg = mx + (R[(int64_t)(ns / K) * Bs + bl] - R[(int64_t)(ms / K) * Bs + bl]), sb = pc_split_shift(gg);
+            const bool live = mx > PC_NEG_INF && (whole || lane < 32);  // dead sample: both factors 0
+            q[wave][0][lane] = live ? (sb - mx) * PC_LOG2E : PC_NEG_INF;
+            q[wave][1][lane] = live ? (gg - sb - PC_SPLIT_SCALE) * PC_LOG2E : PC_NEG_INF;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const floatx4 qa = *reinterpret_cast<const floatx4 *>(&q[wave][0][16 * c + 4 * g]);
+                const floatx4 qb = *reinterpret_cast<const floatx4 *>(&q[wave][1][16 * c + 4 * g]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float a = __builtin_amdgcn_exp2f(fmaf(nf[c][e], PC_LOG2E, qa[e]));
+                    const float p = __builtin_amdgcn_exp2f(fminf(fmaf(lc[c][e], PC_LOG2E, qb[e]), PC_SPLIT_CAP * PC_LOG2E));
+                    acc[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, p, acc[c & 1], 0, 0, 0);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int64_t at = (int64_t)pb + (4 * g + e) * K + j16;
+        const float th = theta[at], inc = pc_flow_out(th, acc[0][e] + acc[1][e]);
+        if (th > 0.0f) {                                                // theta = 0: no flow (and never 0 * inf)
+            if (n_split > 1) atomicAdd(G + at, inc); else G[at] += inc;
         }
     }
 }
@@ -2219,14 +2418,14 @@ static inline int grid_for(int64_t items, int per_block = 256, int cap = 1 << 16
 static bool g_force_generic = false;
 void set_force_generic(bool on) { g_force_generic = on; }
 static inline bool use_mfma(int32_t K) { return !g_force_generic && (K == 32 || K == 64 || K == 128); }
-static inline bool use_small(int32_t K) { return !g_force_generic && (K == 1 || K == 2 || K == 4 || K == 8 || K == 16); }
+static inline bool use_small(int32_t K) { return !g_force_generic && (K == 1 || K == 2 || K == 4 || K == 8); }
+static inline bool use_16(int32_t K) { return !g_force_generic && K == 16; }
 #define PC_DISPATCH_SMALL(KERNEL, ...)                                                                     \
     do {                                                                                                   \
         if (K == 1) hipLaunchKernelGGL((KERNEL<1>), __VA_ARGS__);                                          \
         else if (K == 2) hipLaunchKernelGGL((KERNEL<2>), __VA_ARGS__);                                     \
         else if (K == 4) hipLaunchKernelGGL((KERNEL<4>), __VA_ARGS__);                                     \
-        else if (K == 8) hipLaunchKernelGGL((KERNEL<8>), __VA_ARGS__);                                     \
-        else hipLaunchKernelGGL((KERNEL<16>), __VA_ARGS__);                                                \
+        else hipLaunchKernelGGL((KERNEL<8>), __VA_ARGS__);                                                 \
     } while (0)
 
 void launch_fill(float *p, int64_t n, float v, hipStream_t s)
@@ -2452,6 +2651,20 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
     while (split < 4 && tiles * split < want && (int64_t)width * (K / 32) >= 2 * split) split <<= 1;
 }
 
+// K = 16, one group: forward (F null; X = l of the children) or backward to the children (X = log_nf).  The neighbours of a row
+// are dealt to four waves where the tiles alone leave less than a wave per SIMD.
+static void launch_sum_16(const float *theta, const float *X, float *l, float *R, const float *nfmax, float *F, const GroupDev &g, int64_t Bs,
+                          hipStream_t s)
+{
+    const int64_t cgs = Bs / 32;
+    const bool split = (int64_t)g.n_rows * cgs < 1024 && g.width >= 8;
+    const dim3 grid((unsigned)g.n_rows, (unsigned)(split ? cgs : (cgs + 3) / 4));
+#define PC_SUM_16(BB, SS) hipLaunchKernelGGL((k_sum_16<BB, SS>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, g.ids, g.nbr, g.par, g.aux, g.width, Bs)
+    if (F) { if (split) PC_SUM_16(true, 4); else PC_SUM_16(true, 1); }
+    else { if (split) PC_SUM_16(false, 4); else PC_SUM_16(false, 1); }
+#undef PC_SUM_16
+}
+
 void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, const std::vector<GroupSet> &sets, int32_t K,
                     int64_t Bs, hipStream_t s)
 {
@@ -2475,7 +2688,9 @@ void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, co
     for (const GroupSet &gs : sets) for (int k = 0; k < gs.n; ++k) {
         const GroupDev g{gs.first[k + 1] - gs.first[k], gs.width[k], gs.ids[k], gs.nbr[k], gs.par[k], false, gs.aux[k]};
         Timed timed(KC_SUM_FWD, s);
-        if (use_small(K)) {
+        if (use_16(K)) {
+            launch_sum_16(theta, lch, l, R, nullptr, nullptr, g, Bs, s);
+        } else if (use_small(K)) {
             dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 255) / 256));
             PC_DISPATCH_SMALL(k_sum_fwd_small, grid, dim3(256), 0, s, theta, lch, l, R, g.ids, g.nbr, g.par, g.aux, g.width, Bs);
         } else {
@@ -2509,7 +2724,9 @@ void launch_sum_bwd_child(const float *theta, const float *l, const float *R, co
     for (const GroupSet &gs : sets) for (int k = 0; k < gs.n; ++k) {
         const GroupDev g{gs.first[k + 1] - gs.first[k], gs.width[k], gs.ids[k], gs.nbr[k], gs.par[k], false, gs.aux[k]};
         Timed timed(KC_SUM_BWD_CHILD, s);
-        if (use_small(K)) {
+        if (use_16(K)) {
+            launch_sum_16(theta, N, const_cast<float *>(l), const_cast<float *>(R), nfmax, F, g, Bs, s);
+        } else if (use_small(K)) {
             dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 255) / 256));
             PC_DISPATCH_SMALL(k_sum_bwd_small, grid, dim3(256), 0, s, theta, l, R, N, nfmax, F, g.ids, g.nbr, g.par, g.aux,
                               g.width, Bs);
@@ -2538,7 +2755,7 @@ static int bf16_enabled()                                              // PC_BF1
 }
 
 bool use_flow() { return !g_force_generic; }
-bool param_flow_by_block(int32_t K) { return use_mfma(K) || use_small(K); }
+bool param_flow_by_block(int32_t K) { return use_mfma(K) || use_16(K) || use_small(K); }
 
 void launch_param_flow(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *G,
                        const ParamFlowDev &pf, int32_t K, int64_t Bs, hipStream_t s)
@@ -2553,9 +2770,13 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
         if (K == 1) PC_PF_SMALL(1, 1);
         else if (K == 2) PC_PF_SMALL(2, 2);
         else if (K == 4) PC_PF_SMALL(4, 4);
-        else if (K == 8) PC_PF_SMALL(8, 8);
-        else PC_PF_SMALL(16, 8);
+        else PC_PF_SMALL(8, 8);
 #undef PC_PF_SMALL
+    } else if (use_16(K)) {
+        // few blocks with many tied pairs each: split the pairs over waves until the launch has some 1024 of them
+        const int n_split = (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 1024 / pf.n_pb));
+        hipLaunchKernelGGL(k_param_flow_16, dim3((unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4)), dim3(256), 0, s, theta, l, R, N, nfmax, G,
+                           pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
     } else if (K == 32) {
         // few blocks with many tied pairs each: split the pairs over waves until the launch has some 256 of them
         const int64_t avg_pairs = pf.n_pairs / pf.n_pb;
