@@ -463,7 +463,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
             if (!theta_t_split) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, true, base + w.tth_off, base + w.ttl_off, s);
             theta_t_split = true;
             // the planes of exp(log_nf - max) were written by the product layers that finished these blocks' flows; a
-            // block without parents (initialised by k_init_flows) has none, so such a layer splits here
+            // block without parents (initialised by k_begin_backward) has none, so such a layer splits here
             if (plan.layers[li].orphan_sum) launch_split_p(N, nfmax, L.d_blk_ids, (int32_t)L.blk_ids.size(), K, w.Bs, base + w.ph_off, base + w.pl_off, s);
             launch_sum_bf16(base + w.tth_off, base + w.ttl_off, base + w.ph_off, base + w.pl_off, l, const_cast<float *>(R), nfmax, F,
                             true, plan.layers[li].bwd[0], K, w.Bs, s);

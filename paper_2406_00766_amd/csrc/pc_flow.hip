@@ -496,12 +496,17 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
     // 16 x 32 states); row tiles of 32 halve the number of tasks that read a neighbour and win from 64 tasks per layer on, tiles
     // of 16 leave a shorter chain before.  Measured with 1 - 16 waves, 16 - 64 rows, 16 and 32 columns, 1 - 4 chunks at once: 32
     // columns lost everywhere, 64 rows won 1 - 2 % on 128- and 256-state trees and lost elsewhere.
+    // Workgroups: enough to hold a layer's tasks and the next ones' operands; those beyond that only poll.  256 / 320 / 512 measured:
+    // eight waves (one workgroup per CU is 256) HMM T = 60, H = 1024, B = 20 1110 / 1133 / 1189 us, T = 32, H = 512, B = 77 385 / 404 /
+    // 394; one and two waves, trees of 800 variables, M = 32 259 / 256 / 260 (with 2048: 297) and 500 variables 266 / 267 / 273, HMM
+    // T = 50, H = 64, B = 400 277 / 281 / 290, 784 variables, M = 64 722 / 721 / 729; four waves, M = 128, B = 512 1714 / 1719 / 1704.
+    // Below 256 all of them lose (784 variables, M = 64 at 192: 749).
     const int chunks = f.max_nbr * (K / 32);
 #define PC_FLOW(WW, RR, HH)                                                                                                  \
     do {                                                                                                                     \
         const int n_ct = (int)(Bs / 16);                                                                                     \
         const int64_t tasks = (int64_t)f.n_ent * (K / (16 * RR)) * n_ct;                                                     \
-        const int grid = (int)std::min<int64_t>(tasks, 512);                                                                 \
+        const int grid = (int)std::min<int64_t>(tasks, WW == 8 ? 256 : WW == 4 ? 512 : 320);                                 \
         if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                     f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                  \
         else hipLaunchKernelGGL((k_flow<WW, RR, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
