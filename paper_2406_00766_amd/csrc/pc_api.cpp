@@ -185,16 +185,19 @@ static Ws ws_layout(const pc_circuit *c, int32_t B)
     return w;
 }
 
-// First layer of the part that runs as dataflow launches (from there to the root); layers.size(): none.
+// First layer of the part that runs as dataflow launches (from there to the root); layers.size(): none.  Of the cuts that the
+// narrow layers reach, the one that saves most.
 static size_t flow_start(const pc_circuit *c, const Ws &w)
 {
     const size_t L = c->layers.size();
     if (c->flow_fwd.count_from.empty() || !use_flow()) return L;
     size_t li0 = L;
+    int64_t saved = 0, most = 0;
     for (size_t li = L; li-- > 1 && flow_narrow(c, li, w.Bs);) {
         const LayerTab &t = c->layers[li];
         if (w.bf16 && t.kind == KIND_SUM && t.fwd.size() == 1 && sum_layer_takes_bf16(c->K, 1, t.fwd[0].n_rows, t.fwd[0].width, w.Bs)) break;
-        if (c->flow_cut[li]) li0 = li;
+        saved += c->flow_saved[li];
+        if (c->flow_cut[li] && saved > most) { most = saved; li0 = li; }
     }
     return li0;
 }

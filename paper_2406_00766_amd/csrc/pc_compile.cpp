@@ -138,21 +138,36 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
 
     c->sum_edges.assign(L, 0);
     c->max_items.assign(L, 0);
+    c->flow_saved.assign(L, 0);
     c->flow_cut.assign(L + 1, 0);
     int32_t reach = 0;                                    // highest layer that reads a product block of the layers so far
     for (int32_t li = 0; li < L; ++li) {
         const LayerTab &T = c->layers[li];
         c->flow_cut[li] = li > 0 && T.kind == KIND_PRODUCT && reach < li;
+        int64_t row = 0;                                  // block pairs of the longest row
+        int32_t waits = 0;                                // most sum blocks among the children of a product that is read
         for (int32_t id : T.blk_ids) {
             const int32_t u = id / K - 1;
             if (T.kind == KIND_SUM) {
                 c->sum_edges[li] += d->child_ptr[u + 1] - d->child_ptr[u];
-                for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e)
-                    c->max_items[li] = std::max<int32_t>(c->max_items[li], (int32_t)(d->child_ptr[d->child[e] + 1] - d->child_ptr[d->child[e]]));
+                row = std::max<int64_t>(row, d->child_ptr[u + 1] - d->child_ptr[u]);
+                for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e) {
+                    const int64_t k0 = d->child_ptr[d->child[e]], k1 = d->child_ptr[d->child[e] + 1];
+                    c->max_items[li] = std::max(c->max_items[li], (int32_t)(k1 - k0));
+                    if (k1 - k0 <= 12)                    // (a layer that reads longer ones is out: flow_narrow)
+                        waits = std::max(waits, (int32_t)std::count_if(d->child + k0, d->child + k1, [&](int32_t k) { return d->type[k] == KIND_SUM; }));
+                }
             } else if (T.kind == KIND_PRODUCT) {
                 for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) reach = std::max(reach, layer_of[par_of[k]]);
             }
         }
+        // A task takes the sum blocks among its products' children one after the other, each in 1.2 us and 0.12 us more per
+        // chunk of 32 neighbour nodes in the row; on this scale (units of 0.12 us) a layer's own two launches cost 90.  Measured on a
+        // sum layer and a root that reads products of 5 / 6 / 7 / 8 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4
+        // chunks 30.6 -> 18.3, 29.1 -> 20.2, 29.2 -> 21.3, 29.2 -> 23.7, 28.9 -> 30.3 us; of 16 chunks 33.4 -> 30.9, 34.0 -> 33.8,
+        // 35.3 -> 36.0, 34.4 -> 39.5, 36.0 -> 53.2 us; of 32 chunks 40.7 -> 48.6 us and more.
+        if (T.kind == KIND_SUM)
+            c->flow_saved[li] = (int32_t)std::max<int64_t>(-1000000, 90 - std::max(waits, 1) * (10 + row * (K / 32)));
     }
     int32_t from = L;                                     // the part at the smallest batch holds those at all others
     for (int32_t li = L; li-- > 1 && flow_narrow(c, li, 32);) if (c->flow_cut[li]) from = li;

@@ -92,7 +92,8 @@ struct pc_circuit {
     // dataflow launches (empty where they do not apply)
     pc::FlowTab flow_fwd, flow_bwd;
     std::vector<int64_t> sum_edges;                   // per layer (sum layers): block pairs,
-    std::vector<int32_t> max_items;                   // most children of a product block that it reads
+    std::vector<int32_t> max_items;                   // most children of a product block that it reads,
+    std::vector<int32_t> flow_saved;                  // what a dataflow launch saves on it (pc_compile.cpp)
     std::vector<uint8_t> flow_cut;                    // per layer: a dataflow part may begin here (a product layer, and no product
                                                       // block below it is read by a sum block above it)
     pc::RowTab prod_fwd_rows, prod_bwd_rows;
