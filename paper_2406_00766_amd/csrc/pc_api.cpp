@@ -379,10 +379,13 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
                            w.Bs, s);
         }
     }
-    if (li0 < L) {                                                       // the root is among these layers and writes ll
+    if (li0 < L) {
         launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, s);
         launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
-    } else {
+    }
+    // a root among the layers of the dataflow launch has written ll; blocks it does not reach may lie deeper, and then the
+    // part that runs as dataflow can begin above the root
+    if ((size_t)c->root_layer < li0) {
         launch_readout(l, R, (int64_t)(c->root_block + 1) * K, (int64_t)c->root_block + 1, w.Bs, B, ll, s);
     }
     PC_HIP(hipGetLastError());

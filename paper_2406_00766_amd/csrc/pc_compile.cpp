@@ -422,7 +422,10 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
         LayerTab layer;
         layer.kind = key == 0 ? KIND_INPUT : d->type[blocks[0]];
         layer.depth = key == 0 ? 0 : depth[blocks[0]];
-        for (int32_t u : blocks) layer.blk_ids.push_back((u + 1) * K);
+        for (int32_t u : blocks) {
+            layer.blk_ids.push_back((u + 1) * K);
+            if (u == d->root_block) c->root_layer = (int32_t)c->layers.size();
+        }
         if (layer.kind == KIND_INPUT) {
             GroupTab g;
             g.n_rows = (int32_t)blocks.size();

@@ -71,6 +71,7 @@ struct pc_circuit {
     int32_t K = 0, n_blocks = 0, root_block = 0, n_param_blocks = 0;
     int32_t n_vars = 0, n_cats = 0, n_tables = 0;
     std::vector<pc::LayerTab> layers;
+    int32_t root_layer = 0;                           // not always the last one: blocks the root does not reach may lie deeper
 
     // EM normalisation: parameter block -> (row group, real rows, real cols); row group -> child count
     int32_t n_em_groups = 0;

@@ -41,3 +41,61 @@ def test_dataflow_layers_match_oracle(make):
     n_sum = sum(pcb.pc_get_layer(c.handle, i).kind == 2 for i in range(c.sizes.n_layers))
     assert prof["sum_fwd"][0] < n_sum and prof["sum_bwd_child"][0] < n_sum
     c.close()
+
+
+class Dag(W._Builder):
+    """Block DAGs written out by hand: every edge of a sum block has a parameter block of its own."""
+    n_params = 0
+
+    def input(self):
+        n = sum(t == W.INPUT for t in self.type)
+        return self.add(W.INPUT, var=n, table=n)
+
+    def product(self, children):
+        p = self.add(W.PRODUCT)
+        for c in children:
+            self.link(p, c)
+        return p
+
+    def sum(self, children, n_real=None):
+        s = self.add(W.SUM, n_real=n_real)
+        for c in children:
+            self.link(s, c, self.n_params)
+            self.n_params += 1
+        return s
+
+    def workload(self, root, B, seed, n_cats=5, table_alpha=1.0):
+        rng = np.random.Generator(np.random.PCG64(seed))
+        K, n = self.K, sum(t == W.INPUT for t in self.type)
+        theta = np.zeros((self.n_params + 1, K, K), dtype=np.float32)
+        for s in range(len(self.type)):
+            if self.type[s] == W.SUM:
+                ids, rows = self.params[s], self.n_real[s]
+                w = W._f32_floor(W._dirichlet_rows(rng, 1.0, (rows, len(ids) * K)))
+                for j, p in enumerate(ids):
+                    theta[p + 1, :rows] = w[:, j * K:(j + 1) * K]
+        tables = np.stack([W._f32_floor(W._dirichlet_rows(rng, table_alpha, (K, n_cats))).T for _ in range(n)])
+        return W._make(f"dag_{seed}", self, root, self.n_params, n, n_cats, n, theta, tables, rng.integers(0, n_cats, size=(B, n)), {})
+
+
+@pytest.mark.parametrize("K,B", [(32, 20), (64, 1)])
+def test_root_below_the_dataflow_layers(K, B):
+    """A root over a product of thirteen inputs (its layer is not one for a dataflow launch) beside a deeper chain that nothing
+    reads (its layers are): ll still comes from the root, and the chain's flows are 0."""
+    d = Dag(K)
+    inputs = [d.input() for _ in range(14)]
+    root = d.sum([d.product(inputs[:13])], n_real=1)
+    s = inputs[13]
+    for _ in range(4):
+        s = d.sum([d.product([s])])
+    w = d.workload(root, B, 79)
+    print(f"case shallow root K={K} B={B}", flush=True)
+    check_all(w)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    c.ll.fill_(float("nan"))
+    pcb.pc_profile_enable(c.handle, True)
+    ll = c.forward()
+    assert not torch.isnan(ll).any()
+    assert pcb.pc_profile_read(c.handle)["sum_fwd"][0] < 4                 # four sum layers, the upper three in one launch
+    c.close()
