@@ -10,7 +10,10 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Forward, backward
  *     and the EM step only enqueue kernels (no memset or copy nodes, no allocation); they never
  *     synchronise the device, so a caller may capture them into a HIP graph and replay it.  A kernel
- *     fault surfaces as PC_ERR_HIP from the next call that checks the runtime's error state.
+ *     fault surfaces as PC_ERR_HIP from the next call that checks the runtime's error state.  Narrow layers share one launch
+ *     whose workgroups wait for one another's results; should such a wait reach its limit of polls (pc_set_wait_limit),
+ *     the launch ends, log-likelihoods and node flows that depend on the missing values are NaN, and every call on the
+ *     handle that starts after that (forward, backward, EM step, profile read) returns PC_ERR_HIP.
  *   - Every call returns a pc_status; pc_last_error() gives a thread-local message for the last
  *     non-OK status.  No exceptions cross this boundary.
  *   - Node blocks hold K node slots.  The compiled node offset of user block u is (u+1)*K; rows
@@ -239,6 +242,11 @@ typedef struct {
 pc_status pc_profile_enable(pc_circuit *c, int32_t on);
 pc_status pc_profile_read(pc_circuit *c, pc_profile *out);
 const char *pc_kernel_class_name(int32_t cls);
+
+/* Polls after which a wait inside a dataflow launch is given up (2^22 after pc_compile: some seconds).  The limit is the
+ * handle's and applies from the next call on; 0 gives up on the first value that is not there yet, which is how the error
+ * path is tested. */
+pc_status pc_set_wait_limit(pc_circuit *c, int32_t polls);
 
 /* Achievable peaks of the device the calling thread has current, for quoting beside the published ones (measurement
  * protocol).  Both time `reps` launches of a plain kernel with HIP events on `stream` and wait for them.

@@ -65,7 +65,7 @@ EXPORTS = ["pc_compile", "pc_compile_host", "pc_destroy", "pc_last_error", "pc_g
            "pc_get_group", "pc_copy_group", "pc_workspace_layout", "pc_workspace_bytes", "pc_forward",
            "pc_forward_static", "pc_backward", "pc_em_step", "pc_profile_enable", "pc_profile_read", "pc_kernel_class_name",
            "pc_measure_copy", "pc_measure_mfma_f32", "pc_collapse", "pc_collapsed_dag", "pc_collapsed_theta",
-           "pc_collapsed_block_map", "pc_collapsed_destroy", "pc_order_for_scratch"]
+           "pc_collapsed_block_map", "pc_collapsed_destroy", "pc_order_for_scratch", "pc_set_wait_limit"]
 
 _lib = None
 
@@ -99,6 +99,7 @@ def lib():
                                  C.c_float, C.c_float, C.c_void_p]
         L.pc_profile_enable.argtypes = [C.c_void_p, C.c_int32]
         L.pc_profile_read.argtypes = [C.c_void_p, C.POINTER(pc_profile)]
+        L.pc_set_wait_limit.argtypes = [C.c_void_p, C.c_int32]
         L.pc_kernel_class_name.argtypes = [C.c_int32]
         L.pc_kernel_class_name.restype = C.c_char_p
         L.pc_measure_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_int32, C.c_void_p, C.POINTER(C.c_double)]
@@ -302,6 +303,10 @@ def pc_profile_read(handle: int, with_bf16: bool = False) -> dict:
         return {lib().pc_kernel_class_name(i).decode(): (int(p.launches[i]), float(p.ms[i]), int(p.bf16_launches[i]))
                 for i in range(p.n_classes)}
     return {lib().pc_kernel_class_name(i).decode(): (int(p.launches[i]), float(p.ms[i])) for i in range(p.n_classes)}
+
+
+def pc_set_wait_limit(handle: int, polls: int):
+    _check(lib().pc_set_wait_limit(handle, int(polls)))
 
 
 def pc_measure_copy(src, dst, nbytes: int, reps: int = 5, stream=None) -> float:

@@ -88,6 +88,11 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
         add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
     }
     const size_t ztab_off = reserve((size_t)c->n_tables * c->K + 1);
+    if (!c->flow_fwd.ent.empty()) {
+        PC_HIP(hipHostMalloc((void **)&c->fault, sizeof(int32_t), hipHostMallocMapped));
+        *c->fault = 0;
+        PC_HIP(hipHostGetDevicePointer((void **)&c->d_fault, c->fault, 0));
+    }
     PC_HIP(hipMalloc(&c->d_arena, bytes));
     c->arena_bytes = bytes;
     char *base = (char *)c->d_arena;
@@ -98,6 +103,15 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     c->d_ztab = (float *)(base + ztab_off);
     PC_HIP(hipStreamSynchronize(stream));
     c->on_device = true;
+    return PC_OK;
+}
+
+// Error of an earlier dataflow launch on this handle.  The word is read without waiting for the device, so a call sees the
+// launches that have ended by then.
+static pc_status check_fault(const pc_circuit *c)
+{
+    if (c->fault && __atomic_load_n(c->fault, __ATOMIC_RELAXED) != 0)
+        return fail(PC_ERR_HIP, "a wait inside an earlier dataflow launch on this circuit was given up; results since then hold NaN or are incomplete");
     return PC_OK;
 }
 
@@ -253,6 +267,7 @@ void pc_destroy(pc_circuit *c)
 {
     if (!c) return;
     if (c->d_arena) (void)hipFree(c->d_arena);
+    if (c->fault) (void)hipHostFree(c->fault);
     delete (Profiler *)c->profiler;
     delete (LaunchPlan *)c->plan;
     delete c;
@@ -349,6 +364,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         return fail(PC_ERR_ARG, "theta, tables and workspace must be 16-byte aligned");
     const Ws w = ws_layout(c, B);
     if (workspace_bytes < w.total) return fail(PC_ERR_WORKSPACE, "workspace smaller than pc_workspace_bytes");
+    if (check_fault(c) != PC_OK) return PC_ERR_HIP;
     ProfScope prof(profiled ? c : nullptr);
     char *base = (char *)workspace;
     float *l = (float *)(base + w.l_off), *R = (float *)(base + w.r_off);
@@ -380,7 +396,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         }
     }
     if (li0 < L) {
-        launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, s);
+        launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, c->wait_limit, c->d_fault, s);
         launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
     }
     // a root among the layers of the dataflow launch has written ll; blocks it does not reach may lie deeper, and then the
@@ -434,6 +450,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
         return fail(PC_ERR_ARG, "theta_flow and table_flow must be 16-byte aligned");
     const Ws w = ws_layout(c, B);
     if (workspace_bytes < w.total) return fail(PC_ERR_WORKSPACE, "workspace smaller than pc_workspace_bytes");
+    if (check_fault(c) != PC_OK) return PC_ERR_HIP;
     hipStream_t s = (hipStream_t)stream;
     ProfScope prof(c);
     char *base = (char *)workspace;
@@ -456,7 +473,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
                           flow.n_ent, ticket, s);
     if (li0 < c->layers.size()) {
-        launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, s);
+        launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, c->wait_limit, c->d_fault, s);
         launch_prod_bwd_rows(l, F, N, nfmax, rows_dev(c->prod_bwd_rows, li0, false), K, w.Bs, w.bf16 ? base + w.ph_off : nullptr,
                              w.bf16 ? base + w.pl_off : nullptr, s);
     }
@@ -520,6 +537,7 @@ pc_status pc_em_step(pc_circuit *c, float *theta, float *tables, float *theta_fl
     if (!(step >= 0.0f && step <= 1.0f) || !(pseudocount >= 0.0f)) return fail(PC_ERR_ARG, "step in [0,1], pseudocount >= 0");
     if (misaligned(theta) || misaligned(tables) || misaligned(theta_flow) || misaligned(table_flow))
         return fail(PC_ERR_ARG, "theta, tables and their flow arrays must be 16-byte aligned");
+    if (check_fault(c) != PC_OK) return PC_ERR_HIP;
     ProfScope prof(c);
     const int32_t avg = c->em_ptr[c->n_em_groups] / std::max(c->n_em_groups, 1);
     EmDev em{c->n_em_groups, (int32_t)c->em_ptr.size() - 1, avg, c->d_em_ptr, c->d_em_list, c->d_pb_rows, c->d_pb_cols, c->d_group_nch,
@@ -550,6 +568,14 @@ pc_status pc_profile_read(pc_circuit *c, pc_profile *out)
         out->bf16_launches[k] = (c->profiler && k < KC_COUNT) ? ((Profiler *)c->profiler)->bf16_launches[k] : 0;
     }
     PC_HIP(hipGetLastError());
+    return check_fault(c);
+}
+
+pc_status pc_set_wait_limit(pc_circuit *c, int32_t polls)
+{
+    if (!c) return fail(PC_ERR_ARG, "NULL argument");
+    if (polls < 0) return fail(PC_ERR_ARG, "polls must not be negative");
+    c->wait_limit = polls;
     return PC_OK;
 }
 

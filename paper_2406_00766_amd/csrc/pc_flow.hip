@@ -12,7 +12,8 @@
 //     waiting workgroup holds its weights in registers already.
 //   * no wait can last for ever: a task waits only for tasks with lower tickets, tickets are taken by running workgroups
 //     in increasing order and worked off in that order, so the lowest unfinished task never waits.  (No assumption about
-//     how many workgroups are resident.)  A bound on the spins ends the launch all the same should that ever be untrue.
+//     how many workgroups are resident.)  A bound on the polls ends the launch all the same should that ever be untrue: the
+//     task that gave up publishes NaN, its readers pass NaN on, and the host is told through a word in its memory.
 //
 // Forward (role of Alg. 1): a task computes 16 RT sum nodes.  Its neighbours' values are the PRODUCTS of their children's
 // log-probabilities, formed here from the children's rows (Sec. 3: a sum of log-probabilities), so a product layer is
@@ -43,7 +44,6 @@
 namespace pc {
 
 #define PC_SENTINEL 0xFFFFFFFFu
-constexpr int FLOW_SPIN_LIMIT = 1 << 22;                               // some seconds of polling
 
 // Device-scope 4- and 16-byte accesses (sc1); every dword of a 16-byte access is a word of its own.  (A polling loop needs a
 // compiler barrier so that it loads again; a volatile access would be system-scope.)
@@ -72,10 +72,11 @@ __device__ inline float max_over_groups(float v)
 __device__ inline bool is_sentinel(float v) { return __builtin_bit_cast(uint32_t, v) == PC_SENTINEL; }
 __device__ inline float no_sentinel(float v) { return v == v ? v : __builtin_bit_cast(float, 0x7FC00000u); }   // one NaN for all
 
-__device__ inline bool flow_give_up(int spin, int32_t *ticket)
+__device__ inline bool flow_give_up(int spin, int wait_limit, int32_t *ticket, int32_t *fault)
 {
-    if (spin < FLOW_SPIN_LIMIT && ((spin & 1023) != 1023 || __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)) return false;
+    if (spin < wait_limit && ((spin & 1023) != 1023 || __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)) return false;
     __hip_atomic_store(ticket + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return true;
 }
 
@@ -184,7 +185,8 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                                                                  const int32_t *__restrict__ ent, const int32_t *__restrict__ rec,
                                                                  const int32_t *__restrict__ list, int32_t n_tasks, int32_t n_ct,
                                                                  int32_t K, int64_t Bs, int32_t li0, int32_t *ticket,
-                                                                 float *__restrict__ ll, int32_t B)
+                                                                 float *__restrict__ ll, int32_t B, int32_t wait_limit,
+                                                                 int32_t *fault)
 {
     constexpr int TPW = (RT + W - 1) / W;                               // 16 x 16 result tiles that a wave writes
     __shared__ floatx4 part[2][W][RT][W > 1 ? 64 : 1];                              // partial sums of the waves, double-buffered over tasks
@@ -280,6 +282,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 
         floatx4 acc[RT];
         float ref = PC_NEG_INF;                                         // reference of acc; -inf: nothing live yet
+        bool lost = false;                                              // a wait of this wave was given up
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
@@ -352,7 +355,8 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                         for (int k = 0; k < 8; ++k) missing |= is_sentinel(x[i][k >> 2][k & 3]);
                         if (!BWD) missing |= is_sentinel(xr[i]);
                     }
-                    if (!__any(missing) || flow_give_up(spin, ticket)) break;
+                    if (!__any(missing)) break;
+                    if (flow_give_up(spin, wait_limit, ticket, fault)) { lost = true; break; }
                     __builtin_amdgcn_s_sleep(1);
                 }
 #pragma unroll
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     float x = v[i][k >> 2][k & 3];
                     if (BWD) {
                         const float lo = own_l[i][k >> 2][k & 3];
-                        x = (x > 0.0f && lo > PC_NEG_INF) ? __logf(x) - lo : PC_NEG_INF;
+                        x = lo > PC_NEG_INF ? __logf(x) - lo : PC_NEG_INF;   // flow 0: -inf; NaN (a wait given up) stays NaN
                     }
                     if (cb + W * i >= T.C) x = PC_NEG_INF;
                     v[i][k >> 2][k & 3] = x;
@@ -410,6 +414,12 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
             cb += W * NCH;
             if (cb < T.C) request(T, cb);
         }
+        if (lost) {                                                     // NaN in all its results (a factor 0 below keeps it)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[rt][r] = __builtin_nanf("");
+        }
         // the waves' partial sums meet in LDS; tile rt goes to wave rt % W
         if (W > 1) {
 #pragma unroll
@@ -445,7 +455,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                 if (BWD) {
                     // exp(ln(sum) + (ref - PC_UP) + l_row); sum = 0 or l_row = -inf gives exp2(-inf) = 0
                     const float add = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(tot[r]) + (lown[k][r] + (top - PC_UP)) * PC_LOG2E);
-                    val[r] = top > PC_NEG_INF ? no_sentinel(add) : 0.0f;
+                    val[r] = top > PC_NEG_INF || tot[r] != tot[r] ? no_sentinel(add) : 0.0f;
                 } else {
                     // ln(sum) - PC_UP relative to the largest reference, the logarithm taken of sum / 2^24: a base-2 logarithm
                     // near 0 is far more accurate in absolute terms than one near 29, and these errors add up over the layers
@@ -488,7 +498,7 @@ void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, con
 }
 
 void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
-                 int32_t *ticket, float *ll, hipStream_t s)
+                 int32_t *ticket, float *ll, int32_t wait_limit, int32_t *fault, hipStream_t s)
 {
     if (f.n_ent == 0) return;
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
@@ -508,9 +518,9 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
         const int64_t tasks = (int64_t)f.n_ent * (K / (16 * RR)) * n_ct;                                                     \
         const int grid = (int)std::min<int64_t>(tasks, WW == 8 ? 256 : WW == 4 ? 512 : 320);                                 \
         if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
-                                    f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                  \
+                                    f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);               \
         else hipLaunchKernelGGL((k_flow<WW, RR, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
-                                f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B);                                      \
+                                f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);                   \
     } while (0)
     if (chunks == 1) {
         if ((int64_t)f.n_ent * (K / 16) * (Bs / 16) >= 64 * (int64_t)f.n_levels) PC_FLOW(1, 2, 1);

@@ -98,6 +98,8 @@ struct pc_circuit {
     std::vector<uint8_t> flow_cut;                    // per layer: a dataflow part may begin here (a product layer, and no product
                                                       // block below it is read by a sum block above it)
     pc::RowTab prod_fwd_rows, prod_bwd_rows;
+    int32_t wait_limit = 1 << 22;                     // polls of a wait before it is given up: some seconds
+    int32_t *fault = nullptr, *d_fault = nullptr;     // a word of pinned host memory, set by a launch that gave up; its device address
 
     // product-scratch mode: product log-probabilities live in a window of max_window_blocks blocks behind the
     // n_persistent_blocks input and sum blocks

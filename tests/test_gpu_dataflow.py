@@ -99,3 +99,45 @@ def test_root_below_the_dataflow_layers(K, B):
     assert not torch.isnan(ll).any()
     assert pcb.pc_profile_read(c.handle)["sum_fwd"][0] < 4                 # four sum layers, the upper three in one launch
     c.close()
+
+
+@pytest.mark.parametrize("K,H,B", [(32, 32, 1), (64, 512, 40)])     # one wave per task, eight waves that meet in LDS
+def test_wait_that_is_given_up_is_visible(K, H, B):
+    """A wait given up (limit 0: at the first value that is not there yet) leaves NaN, never a finite wrong result, and the
+    handle's next call returns the error; forward and backward, each on a handle of its own."""
+    w = W.hmm(24, H, 20, K, B, 80)
+    print(f"case wait limit K={K} H={H} B={B}", flush=True)
+
+    def refused(call):
+        with pytest.raises(pcb.PcError) as e:
+            call()
+        assert e.value.status_name == "PC_ERR_HIP"
+
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    ref = c.forward().clone()
+    pcb.pc_set_wait_limit(c.handle, 0)
+    c.forward()
+    torch.cuda.synchronize()
+    same = c.ll == ref
+    assert torch.isnan(c.ll[~same]).all() and not same.all()
+    refused(c.forward)
+    refused(lambda: c.em_step(0.1, 0.0))
+    c.close()
+
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    c.forward(); c.backward()
+    torch.cuda.synchronize()
+    F_ref, table_ref = c.node_buffers()[1].clone(), c.table_flow.clone()
+    c.table_flow.zero_()
+    pcb.pc_set_wait_limit(c.handle, 0)
+    c.backward()
+    torch.cuda.synchronize()
+    F = c.node_buffers()[1]
+    other = F[:, :B] != F_ref[:, :B]
+    assert other.any() and torch.isnan(F[:, :B][other]).all()
+    assert torch.isnan(c.table_flow[~torch.isclose(c.table_flow, table_ref, rtol=1e-4, atol=0)]).all() and torch.isnan(c.table_flow).any()
+    refused(lambda: c.em_step(0.1, 0.0))
+    refused(c.backward)
+    c.close()
