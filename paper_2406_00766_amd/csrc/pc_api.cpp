@@ -215,12 +215,13 @@ static size_t flow_start(const pc_circuit *c, const Ws &w)
     }
     return li0;
 }
-static FlowDev flow_dev(const FlowTab &f, size_t li0, bool suffix)
+static FlowDev flow_dev(const pc_circuit *c, const FlowTab &f, size_t li0, bool suffix)
 {
     int32_t n_levels = 0;                                 // layers with entries
     for (size_t li = li0; li + 1 < f.count_from.size(); ++li) n_levels += f.count_from[li] > f.count_from[li + 1];
     const int32_t n = f.count_from[li0], first = suffix ? f.count_from[0] - n : 0;
-    return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, n_levels};
+    return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, n_levels,
+                   *std::max_element(c->max_items.begin() + li0, c->max_items.end())};
 }
 static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)
 {
@@ -374,7 +375,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
 
     const size_t L = c->layers.size(), li0 = flow_start(c, w);
     FlowDev flow{};
-    if (li0 < L) flow = flow_dev(c->flow_fwd, li0, true);
+    if (li0 < L) flow = flow_dev(c, c->flow_fwd, li0, true);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), flow.ent, flow.n_ent, K, ticket, s);
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
@@ -468,7 +469,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     const size_t li0 = flow_start(c, w);
     FlowDev flow{};
-    if (li0 < c->layers.size()) flow = flow_dev(c->flow_bwd, li0, false);
+    if (li0 < c->layers.size()) flow = flow_dev(c, c->flow_bwd, li0, false);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
                           flow.n_ent, ticket, s);

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void k_begin_backward(const float *__restrict_
 // values in MFMA operand order: per block, 16 rows and 16 columns one 1 KiB tile, lane (j, g) holding rows 4 g .. 4 g + 3 of
 // column j -- one 16-byte load per lane where the row-major buffer would take four loads of 4 x 64 bytes, and no line shared
 // by two column tiles.
-template <int W, int RT, int NCH, bool BWD>
+template <int W, int RT, int NCH, bool BWD, bool EXACT>
 __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__restrict__ theta, float *__restrict__ l, float *R,
                                                                  float *__restrict__ F, float *mail,
                                                                  const int32_t *__restrict__ ent, const int32_t *__restrict__ rec,
@@ -295,8 +295,17 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                 max_cnt = max(max_cnt, cnt[i]);
                 if (BWD) base[i] = Rrow - base[i];
             }
-            // long lists: a running fp32 sum of many log-probabilities loses more than the flows' tolerance allows, so every
-            // four items its integer part moves into the reference
+            // A running fp32 sum of several log-probabilities loses more than the flows' tolerance allows, so every four items its
+            // integer part moves into the reference (exactly: no value lies above the column's maximum).  EXACT (launches with
+            // products of more than eight children, which the product kernels sum in double): the rounding error of every
+            // addition is kept beside the sum (Knuth's two-sum) and added once the integer part is out.  Products of 12 children
+            // of -80 nats: largest error of the sum layer above 6.7e-5 -> 1.0e-6.  An instantiation of its own, as carrying it in
+            // every launch cost 1 - 5 % of a pass (HMM 16 x 32, one sample 29.1 -> 30.5 us).
+            floatx4 low[EXACT ? NCH : 1][2];
+            if (EXACT) {
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) low[i][0] = low[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
             auto settle = [&]() {
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) {
@@ -309,6 +318,24 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 #pragma unroll
                     for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] -= cm;
                 }
+            };
+            auto add_item = [&](const floatx4 (&x)[NCH][2], const float (&xr)[NCH]) {
+                if (EXACT) {
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) {
+                            const float a = v[i][k >> 2][k & 3], y = x[i][k >> 2][k & 3], s = a + y, t = s - a;
+                            low[EXACT ? i : 0][k >> 2][k & 3] += (a - (s - t)) + (y - t);   // NaN where s = -inf: not used then
+                        }
+                }
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
+                    if (!BWD) base[i] += xr[i];
+                }
+                if (!BWD && !EXACT && (++since & 3) == 3) settle();
             };
             for (int n = 1; n < max_cnt; ++n) {                         // items of earlier launches (the first: requested before)
                 int32_t its[NCH];
@@ -323,13 +350,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     row_values(BWD ? F : l, its[i], i, col, x[i]);
                     if (!BWD) xr[i] = R[(int64_t)(its[i] >> ks) * Bs + col];
                 }
-#pragma unroll
-                for (int i = 0; i < NCH; ++i) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
-                    if (!BWD) base[i] += xr[i];
-                }
-                if (!BWD && (++since & 3) == 3) settle();
+                add_item(x, xr);
             }
             for (int n = 0; n < max_cnt; ++n) {                         // items of this launch: poll until they are there
                 int32_t its[NCH];
@@ -359,13 +380,17 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     if (flow_give_up(spin, wait_limit, ticket, fault)) { lost = true; break; }
                     __builtin_amdgcn_s_sleep(1);
                 }
+                add_item(x, xr);
+            }
+            if (EXACT) {
+                settle();
 #pragma unroll
-                for (int i = 0; i < NCH; ++i) {
+                for (int i = 0; i < NCH; ++i)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
-                    if (!BWD) base[i] += xr[i];
-                }
-                if (!BWD && (++since & 3) == 3) settle();
+                    for (int k = 0; k < 8; ++k) {
+                        const float a = v[i][k >> 2][k & 3];
+                        v[i][k >> 2][k & 3] = a > PC_NEG_INF ? a + low[EXACT ? i : 0][k >> 2][k & 3] : a;
+                    }
             }
             // log_nf of the parents; integer reference of each chunk; the largest live one
             float nref = ref;
@@ -517,9 +542,11 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
         const int n_ct = (int)(Bs / 16);                                                                                     \
         const int64_t tasks = (int64_t)f.n_ent * (K / (16 * RR)) * n_ct;                                                     \
         const int grid = (int)std::min<int64_t>(tasks, WW == 8 ? 256 : WW == 4 ? 512 : 320);                                 \
-        if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+        if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                     f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);               \
-        else hipLaunchKernelGGL((k_flow<WW, RR, HH, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
+        else if (f.max_items > 8) hipLaunchKernelGGL((k_flow<WW, RR, HH, false, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, \
+                                mail, f.ent, f.rec, f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);     \
+        else hipLaunchKernelGGL((k_flow<WW, RR, HH, false, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                 f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);                   \
     } while (0)
     if (chunks == 1) {

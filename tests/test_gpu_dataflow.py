@@ -141,3 +141,43 @@ def test_wait_that_is_given_up_is_visible(K, H, B):
     refused(lambda: c.em_step(0.1, 0.0))
     refused(c.backward)
     c.close()
+
+
+@pytest.mark.parametrize("K,n_in,n_sum", [(32, 9, 0), (32, 12, 0), (128, 12, 0), (64, 7, 5)])
+def test_products_of_many_children_keep_their_precision(K, n_in, n_sum):
+    """Products of nine to twelve children with log-probabilities of some -80 nats, the next sum layer's values against the same
+    sums in 64 bits from the children's rows as stored.  With the products exact to their last bit, what is left is: the
+    exponential's argument (below 32, half an ulp 9.5e-7, times ln 2 0.7e-6), its v rounded once (below 8 nats: 2.4e-7), one ulp
+    of the exponential (1.2e-7) and of the logarithm (an argument below 16: 9.5e-7 ln 2 = 0.7e-6), the products' sum (a few
+    6e-8) and the result's own rounding (below 8: 2.4e-7) -- 2.2e-6, bound 4e-6.  Products summed in fp32 miss it: -80 x 3 alone
+    is rounded to 1.5e-5."""
+    d = Dag(K)
+    kids = [d.input() for _ in range(n_in)] + [d.sum([d.product([d.input()])]) for _ in range(n_sum)]
+    mid = d.sum([d.product(kids)])
+    root = d.sum([d.product([mid])], n_real=1)
+    B = 40
+    w = d.workload(root, B, 81)
+    rng = np.random.default_rng(5)
+    t = np.exp(-80 + rng.uniform(-1, 1, size=w.tables.shape))
+    t[:, -1] = 1.0 - t[:, :-1].sum(axis=1)
+    w.tables = t.astype(np.float32)
+    th = (0.97 * np.eye(K) + 0.03 / K).astype(np.float32)               # node i is nearly child i
+    for s in range(len(d.type)):
+        if d.type[s] == W.SUM and s != root:
+            w.theta[d.params[s][0] + 1] = th
+    w = w.with_batch(rng.integers(0, w.n_cats - 1, size=w.x.shape))
+    print(f"case precise products K={K} {n_in}+{n_sum}", flush=True)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    pcb.pc_profile_enable(c.handle, True)
+    c.forward()
+    assert pcb.pc_profile_read(c.handle)["sum_fwd"][0] == 1              # one dataflow launch
+    l, _, R = (t[:, :B].double().cpu().numpy() for t in c.node_buffers())
+    rows = lambda u: R[u + 1] + l[(u + 1) * K:(u + 2) * K]
+    p = sum(rows(u) for u in kids)
+    top = p.max(axis=0)
+    ref = top + np.log(th.astype(np.float64) @ np.exp(p - top))
+    err = np.abs(rows(mid) - ref).max()
+    print(f"  largest error {err:.2e}")
+    assert err < 4e-6
+    c.close()
