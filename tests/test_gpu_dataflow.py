@@ -113,6 +113,7 @@ def test_wait_that_is_given_up_is_visible(K, H, B):
             call()
         assert e.value.status_name == "PC_ERR_HIP"
 
+    other_handle = pcb.Circuit(w)
     c = pcb.Circuit(w)
     c.set_batch(w.x)
     ref = c.forward().clone()
@@ -140,6 +141,20 @@ def test_wait_that_is_given_up_is_visible(K, H, B):
     assert torch.isnan(c.table_flow[~torch.isclose(c.table_flow, table_ref, rtol=1e-4, atol=0)]).all() and torch.isnan(c.table_flow).any()
     refused(lambda: c.em_step(0.1, 0.0))
     refused(c.backward)
+    other_handle.set_batch(w.x)                                # the error is the handle's own
+    assert torch.equal(other_handle.forward(), ref)
+    other_handle.close(); c.close()
+
+
+def test_more_handles_than_fault_words():
+    w = W.hmm(3, 32, 5, 32, 1, 82)
+    handles = [pcb.pc_compile(w) for _ in range(1027)]
+    c = pcb.Circuit(w)                                          # one whose word is its own
+    c.set_batch(w.x)
+    ref = c.forward().clone()
+    for h in handles:
+        pcb.pc_destroy(h)
+    assert torch.equal(c.forward(), ref)
     c.close()
 
 
