@@ -219,8 +219,8 @@ static Ws ws_layout(const pc_circuit *c, int32_t B)
     w.r_off = lnode + fnode + nnode;
     w.mx_off = w.r_off + per_block;
     w.xt_off = w.mx_off + per_block;
-    w.tk_off = w.xt_off + align_up((size_t)c->n_vars * w.Bs * 4, 256);     // ticket words of the dataflow launches
-    w.total = w.tk_off + 256;
+    w.tk_off = w.mx_off;                              // ticket words of the dataflow launches: the null block has no log_nf maximum
+    w.total = w.xt_off + align_up((size_t)c->n_vars * w.Bs * 4, 256);
     // layers with long dense rows run on the bf16 matrix cores and need theta and the node values split into planes
     w.bf16 = false;
     for (const LayerTab &L : c->layers)

@@ -145,3 +145,17 @@ def test_batch_size_limits():
             assert e.value.status_name == status
     finally:
         pcb.pc_destroy(h)
+
+
+@pytest.mark.parametrize("make", [lambda: W.hmm(4, 32, 5, 32, 1, 7), lambda: W.hclt(9, 64, 64, 1, 9, n_cats=6),
+                                  lambda: W.hmm(5, 8, 9, 2, 1, 13)])
+@pytest.mark.parametrize("B", [1, 33, 512])
+def test_workspace_holds_the_node_and_block_buffers_and_nothing_else(make, B):
+    """l, F, N; R and the block maxima; the batch, transposed -- each rounded up to 256 bytes.  (A byte more would refuse
+    circuits that just fit PC_STATIC_SCRATCH_BYTES, and workspaces sized before.)"""
+    w = make()
+    h = pcb.pc_compile(w, host_only=True)
+    Bs = (B + 31) // 32 * 32
+    up = lambda n: (n + 255) // 256 * 256
+    assert pcb.pc_workspace_bytes(h, B) == 3 * up((w.n_blocks + 1) * w.K * Bs * 4) + 2 * up((w.n_blocks + 1) * Bs * 4) + up(w.n_vars * Bs * 4)
+    pcb.pc_destroy(h)
