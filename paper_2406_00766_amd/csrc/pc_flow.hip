@@ -81,7 +81,8 @@ __device__ inline bool flow_give_up(int spin, int wait_limit, int32_t *ticket, i
 }
 
 // Sentinel (and zero) fills before a dataflow launch: workgroup i < n_blk fills the K rows of block ids[i] (rows of a block are
-// contiguous) and, forward, its row of R.  The last workgroup clears the ticket words.
+// contiguous) and, forward, its row of R.
+#define PC_NULL_SHARE 4096
 __device__ inline void flow_fill_block(float *X, float *R, int32_t id, int32_t K, int64_t Bs)
 {
     const float s = __builtin_bit_cast(float, PC_SENTINEL);
@@ -91,8 +92,9 @@ __device__ inline void flow_fill_block(float *X, float *R, int32_t id, int32_t K
     if (R) for (int64_t i = threadIdx.x; i < Bs; i += blockDim.x) R[(int64_t)(id / K) * Bs + i] = s;
 }
 
-// Start of a forward pass in one launch: x -> xT (see below), the null block's rows (l = 0, R = 0), the sentinels of the sum
-// blocks the dataflow launch will publish, its ticket words.
+// Start of a forward pass in one launch: x -> xT (see below), the sentinels of the sum blocks the dataflow launch will publish,
+// the null block's rows (l = 0, R = 0; mail = 0 where there is a dataflow launch) and the ticket words.  The null block has K Bs
+// values, dealt out in shares of PC_NULL_SHARE (forward pass of a 3 x 32 HMM, B = 131072: one workgroup alone 561 us, so 88 us).
 // xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
 __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B,
                                                        int32_t D, int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT, int32_t n_xb,
@@ -104,9 +106,18 @@ __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict
     if ((int)blockIdx.x >= n_xtiles) {
         const int q = (int)blockIdx.x - n_xtiles;
         if (q < n_ent) { flow_fill_block(mail, R, ent[4 * q], K, Bs); return; }
-        for (int64_t i = threadIdx.x; i < K * Bs; i += 256) { l[i] = 0.0f; mail[i] = 0.0f; }
-        for (int64_t i = threadIdx.x; i < Bs; i += 256) R[i] = 0.0f;
-        if (threadIdx.x < 2) ticket[threadIdx.x] = 0;
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        const int64_t i0 = (int64_t)(q - n_ent) * PC_NULL_SHARE;        // K Bs and the share are multiples of 32
+#pragma unroll
+        for (int k = 0; k < PC_NULL_SHARE; k += 1024) {
+            const int64_t i = i0 + k + 4 * threadIdx.x;
+            if (i < K * Bs) {
+                *reinterpret_cast<floatx4 *>(l + i) = zero;
+                if (n_ent > 0) *reinterpret_cast<floatx4 *>(mail + i) = zero;
+            }
+            if (i < Bs) *reinterpret_cast<floatx4 *>(R + i) = zero;
+        }
+        if (q == n_ent && threadIdx.x < 2) ticket[threadIdx.x] = 0;
         return;
     }
     const int b0 = ((int)blockIdx.x % n_xb) * 32, v0 = ((int)blockIdx.x / n_xb) * 32;
@@ -508,8 +519,8 @@ void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int3
                           float *l, float *R, float *mail, const int32_t *ent, int32_t n_ent, int32_t K, int32_t *ticket, hipStream_t s)
 {
     Timed timed(KC_MISC, s);
-    const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
-    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + n_ent + 1)), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
+    const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32), n_null = (int)((K * Bs + PC_NULL_SHARE - 1) / PC_NULL_SHARE);
+    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + n_ent + n_null)), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
                        n_xt, l, R, mail, ent, n_ent, K, ticket);
 }
 
