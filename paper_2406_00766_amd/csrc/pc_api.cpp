@@ -119,6 +119,7 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     }
     add(&c->d_pb_rows, c->pb_rows); add(&c->d_pb_cols, c->pb_cols); add(&c->d_group_nch, c->group_nch);
     add(&c->d_em_ptr, c->em_ptr); add(&c->d_em_list, c->em_list);
+    add(&c->d_em_seg_ptr, c->em_seg_ptr); add(&c->d_em_seg, c->em_seg);
     add(&c->d_init_ids, c->init_ids);
     add(&c->d_pf_pb, c->pf_pb); add(&c->d_pf_ptr, c->pf_ptr); add(&c->d_pf_sum, c->pf_sum); add(&c->d_pf_child, c->pf_child);
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { add(&f->d_ent, f->ent); add(&f->d_rec, f->rec); add(&f->d_list, f->list); }
@@ -126,6 +127,7 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
         add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
     }
     const size_t ztab_off = reserve((size_t)c->n_tables * c->K + 1);
+    const size_t part_off = reserve((c->em_seg_ptr.size() - 1) * c->K + 1);
     if (!c->flow_fwd.ent.empty()) {
         const pc_status st = take_fault_word(c);
         if (st != PC_OK) return st;
@@ -138,6 +140,7 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
         if (f.n) PC_HIP(hipMemcpyAsync(base + f.off, f.src, f.n, hipMemcpyHostToDevice, stream));
     }
     c->d_ztab = (float *)(base + ztab_off);
+    c->d_em_part = (float *)(base + part_off);
     PC_HIP(hipStreamSynchronize(stream));
     c->on_device = true;
     return PC_OK;
@@ -578,8 +581,8 @@ pc_status pc_em_step(pc_circuit *c, float *theta, float *tables, float *theta_fl
     if (check_fault(c) != PC_OK) return PC_ERR_HIP;
     ProfScope prof(c);
     const int32_t avg = c->em_ptr[c->n_em_groups] / std::max(c->n_em_groups, 1);
-    EmDev em{c->n_em_groups, (int32_t)c->em_ptr.size() - 1, avg, c->d_em_ptr, c->d_em_list, c->d_pb_rows, c->d_pb_cols, c->d_group_nch,
-             c->d_ztab};
+    EmDev em{c->n_em_groups, (int32_t)c->em_ptr.size() - 1, avg, (int32_t)c->em_seg_ptr.size() - 1, c->d_em_ptr, c->d_em_list, c->d_pb_rows,
+             c->d_pb_cols, c->d_group_nch, c->d_em_seg_ptr, c->d_em_seg, c->d_em_part, c->d_ztab};
     launch_em(theta, tables, theta_flow, table_flow, em, c->K, c->n_tables, c->n_cats, step, pseudocount, (hipStream_t)stream);
     PC_HIP(hipGetLastError());
     c->fw_B = -1;

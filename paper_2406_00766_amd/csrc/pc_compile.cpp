@@ -547,17 +547,41 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
                     return fail(PC_ERR_TIE, "tied parameter blocks with different numbers of real nodes");
         }
     }
-    c->n_em_groups = (int32_t)group_list.size();
-    // parameter blocks of every group, then one group without rows per block that no sum block uses and for the padding block:
-    // the EM kernel only clears their flows
+    // Parameter blocks of every group of short rows, then one group without rows per block that no sum block uses and for the
+    // padding block: the EM kernel only clears their flows.  Rows of more than 2048 accesses (k_em_theta) go in segments of 256
+    // accesses, at most 1024 of them, so that they are as many waves' work: one wave takes 26 us for a row of 2048, 104 us for 8000
+    // and 1.5 ms for 80 000; in segments 16 and 40 us.  Shorter rows would only pay the two launches (a RAT-SPN's EM step, whose
+    // root has 2048 accesses beside 0.7 ms of other rows' work: 769 -> 778 us).
+    const int32_t row_acc = (K & 3) == 0 ? K / 4 : K;
+    auto is_long = [&](const std::vector<int32_t> &list) { return (int64_t)list.size() * row_acc > 2048; };
     c->em_ptr.assign(1, 0);
     c->em_list.clear();
-    for (const std::vector<int32_t> &list : group_list) {
-        for (int32_t p : list) c->em_list.push_back(p + 1);
+    std::vector<int32_t> nch_of = std::move(c->group_nch);
+    c->group_nch.clear();
+    for (size_t g = 0; g < group_list.size(); ++g) {
+        if (is_long(group_list[g])) continue;
+        for (int32_t p : group_list[g]) c->em_list.push_back(p + 1);
         c->em_ptr.push_back((int32_t)c->em_list.size());
+        c->group_nch.push_back(nch_of[g]);
     }
+    c->n_em_groups = (int32_t)c->group_nch.size();
     for (int32_t p = 0; p <= P; ++p)
         if (c->pb_group[p] < 0) { c->em_list.push_back(p); c->em_ptr.push_back((int32_t)c->em_list.size()); }
+    c->em_seg_ptr.assign(1, (int32_t)c->em_list.size());
+    c->em_seg.clear();
+    for (size_t g = 0; g < group_list.size(); ++g) {
+        const std::vector<int32_t> &list = group_list[g];
+        if (!is_long(list)) continue;
+        const size_t len = std::max<size_t>(256 / row_acc, (list.size() + 1023) / 1024);
+        const int32_t first = (int32_t)c->em_seg_ptr.size() - 1, n_seg = (int32_t)((list.size() + len - 1) / len);
+        for (size_t k = 0; k < list.size(); ++k) {
+            c->em_list.push_back(list[k] + 1);
+            if (k % len == len - 1 || k + 1 == list.size()) {
+                c->em_seg_ptr.push_back((int32_t)c->em_list.size());
+                c->em_seg.insert(c->em_seg.end(), {first, n_seg, nch_of[g]});
+            }
+        }
+    }
 
     // Parameter-centric flow tables (App. A.3): every (sum block, child block) pair that uses a parameter
     // block, so that the flows of tied edges are reduced together; pairs in ascending sum-block order.

@@ -73,12 +73,17 @@ struct pc_circuit {
     std::vector<pc::LayerTab> layers;
     int32_t root_layer = 0;                           // not always the last one: blocks the root does not reach may lie deeper
 
-    // EM normalisation: parameter block -> (row group, real rows, real cols); row group -> child count
+    // EM normalisation: parameter block -> (row group, real rows, real cols); row group (of short rows) -> child count
     int32_t n_em_groups = 0;
     std::vector<int32_t> pb_group, pb_rows, pb_cols, group_nch;
     std::vector<int32_t> em_ptr, em_list;             // row group -> its parameter blocks (CSR); groups without rows at the end
     int32_t *d_em_ptr = nullptr, *d_em_list = nullptr;
     int32_t *d_pb_rows = nullptr, *d_pb_cols = nullptr, *d_group_nch = nullptr;
+    // groups of long rows, not among those above, in segments: their blocks (CSR into em_list) and three words each -- first
+    // segment and number of segments of the group, child count of the group
+    std::vector<int32_t> em_seg_ptr, em_seg;
+    int32_t *d_em_seg_ptr = nullptr, *d_em_seg = nullptr;
+    float *d_em_part = nullptr;                       // [segments * K] row sums of flows
     float *d_ztab = nullptr;                          // [n_tables * K] column sums of table flows
 
     // parameter-centric flow tables: parameter block offset -> CSR list of (sum block, child block) node offsets

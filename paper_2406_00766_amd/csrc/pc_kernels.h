@@ -45,10 +45,10 @@ struct RowsDev {             // product-layer rows of a dataflow launch as neigh
     int32_t n_rows, max_nbr, li0;
 };
 
-struct EmDev {               // row groups with their parameter blocks; those from n_groups on have no rows
-    int32_t n_groups, n_all, avg_list;
-    const int32_t *ptr, *list, *pb_rows, *pb_cols, *group_nch;
-    float *ztab;
+struct EmDev {               // row groups with their parameter blocks; those from n_groups on have no rows; segments of long rows
+    int32_t n_groups, n_all, avg_list, n_seg;
+    const int32_t *ptr, *list, *pb_rows, *pb_cols, *group_nch, *seg_ptr, *seg;
+    float *part, *ztab;
 };
 
 void set_force_generic(bool on);

@@ -2157,18 +2157,21 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma_wg(const float *__re
 // in memory.  V consecutive columns per access; a row of more than 64 V NR columns is read a second time.  Bound by HBM: theta
 // and flows read and written once.  Measured on the 49 140 blocks of 64 x 64 of a 3072-variable tree (3.2 GB moved): 0.55 ms,
 // 5.8 TB/s, where the sums took 0.16 and the update 0.56 ms.
-template <int V, int NR>
+// SEG: much longer rows are cut into segments, and a wave takes one row of a segment: their sums come from k_em_row_sums (part),
+// every segment adds up those of its group.  Measured on one row of 10 000 blocks of 32 columns: 1519 us by one wave, so 40 us.
+template <int V, int NR, bool SEG>
 __global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, float *__restrict__ G, const int32_t *__restrict__ ptr,
                                                   const int32_t *__restrict__ list, const int32_t *__restrict__ pb_rows,
                                                   const int32_t *__restrict__ pb_cols, const int32_t *__restrict__ group_nch,
-                                                  int32_t n_groups, int32_t K, float step, float pc)
+                                                  int32_t n_groups, const int32_t *__restrict__ seg, const float *__restrict__ part,
+                                                  int32_t K, float step, float pc)
 {
     typedef float vec __attribute__((ext_vector_type(V)));
     const int g = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
     const int32_t *blk = list + ptr[g];
     const int n = ptr[g + 1] - ptr[g], kv = K / V, tot = n * kv;
     const int rows = g < n_groups ? pb_rows[blk[0]] : 0;
-    const float share = g < n_groups ? pc / (float)group_nch[g] : 0.0f;
+    const float share = g < n_groups ? pc / (float)(SEG ? seg[3 * g + 2] : group_nch[g]) : 0.0f;
     const vec zero = {};
     for (int i = blockIdx.y * n_waves + wave; i < K; i += gridDim.y * n_waves) {
         if (i >= rows) {                                                // wave-uniform: placeholders, unused blocks
@@ -2198,9 +2201,13 @@ __global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, flo
                 if (q < tot) { place(q, at[r], cols[r]); f[r] = *reinterpret_cast<const vec *>(G + at[r]); }
             }
 #pragma unroll
-            for (int r = 0; r < NR; ++r) if (lane + 64 * r < tot) add(f[r], cols[r]);
-        } else {
+            for (int r = 0; r < NR; ++r) if (!SEG && lane + 64 * r < tot) add(f[r], cols[r]);
+        } else if (!SEG) {
             for (int q = lane; q < tot; q += 64) { place(q, at[0], cols[0]); add(*reinterpret_cast<const vec *>(G + at[0]), cols[0]); }
+        }
+        if (SEG) {
+            const int first = seg[3 * g], n_seg = seg[3 * g + 1];
+            for (int t = lane; t < n_seg; t += 64) s += part[(int64_t)(first + t) * K + i];
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
@@ -2220,6 +2227,30 @@ __global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, flo
         } else {
             for (int q = lane; q < tot; q += 64) { place(q, at[0], cols[0]); update(*reinterpret_cast<const vec *>(G + at[0]), at[0], cols[0]); }
         }
+    }
+}
+
+// Row sums of the segments of long rows: a wave per row of a segment.
+template <int V>
+__global__ __launch_bounds__(256) void k_em_row_sums(const float *__restrict__ G, const int32_t *__restrict__ ptr,
+                                                     const int32_t *__restrict__ list, const int32_t *__restrict__ pb_rows,
+                                                     const int32_t *__restrict__ pb_cols, int32_t K, float *__restrict__ part)
+{
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const int g = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
+    const int32_t *blk = list + ptr[g];
+    const int kv = K / V, tot = (ptr[g + 1] - ptr[g]) * kv, rows = pb_rows[blk[0]];
+    for (int i = blockIdx.y * n_waves + wave; i < rows; i += gridDim.y * n_waves) {
+        float s = 0.0f;
+        for (int q = lane; q < tot; q += 64) {
+            const int b = blk[q / kv], j = (q % kv) * V, c = pb_cols[b] - j;
+            const vec x = *reinterpret_cast<const vec *>(G + (int64_t)b * K * K + (int64_t)i * K + j);
+#pragma unroll
+            for (int e = 0; e < V; ++e) s += e < c ? x[e] : 0.0f;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) part[(int64_t)g * K + i] = s;
     }
 }
 
@@ -2871,8 +2902,8 @@ void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow
         const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(4, (int64_t)em.n_all * K / 8192));
         const dim3 grid((unsigned)em.n_all, (unsigned)((K + rpw * waves - 1) / (rpw * waves))), blk((unsigned)(64 * waves));
 #define PC_EM_THETA(V, NR)                                                                                                \
-    hipLaunchKernelGGL((k_em_theta<V, NR>), grid, blk, 0, s, theta, theta_flow, em.ptr, em.list, em.pb_rows, em.pb_cols,  \
-                       em.group_nch, em.n_groups, K, step, pc)
+    hipLaunchKernelGGL((k_em_theta<V, NR, false>), grid, blk, 0, s, theta, theta_flow, em.ptr, em.list, em.pb_rows, em.pb_cols, \
+                       em.group_nch, em.n_groups, nullptr, nullptr, K, step, pc)
         if (v4) {
             if (tot <= 64) PC_EM_THETA(4, 1);
             else if (tot <= 256) PC_EM_THETA(4, 4);
@@ -2882,6 +2913,18 @@ void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow
             else PC_EM_THETA(1, 16);
         }
 #undef PC_EM_THETA
+        if (em.n_seg > 0) {
+            const dim3 sgrid((unsigned)em.n_seg, (unsigned)((K + waves - 1) / waves));
+#define PC_EM_SEG(V)                                                                                                      \
+    do {                                                                                                                  \
+        hipLaunchKernelGGL((k_em_row_sums<V>), sgrid, blk, 0, s, theta_flow, em.seg_ptr, em.list, em.pb_rows, em.pb_cols, K, em.part); \
+        hipLaunchKernelGGL((k_em_theta<V, 4, true>), sgrid, blk, 0, s, theta, theta_flow, em.seg_ptr, em.list, em.pb_rows, em.pb_cols, \
+                           nullptr, em.n_seg, em.seg, em.part, K, step, pc);                                              \
+    } while (0)
+            if (v4) PC_EM_SEG(4);
+            else PC_EM_SEG(1);
+#undef PC_EM_SEG
+        }
     }
     // one workgroup per table where it can hold the flows and there are enough tables, or too little data to share out
     const int64_t per_table = (int64_t)n_cats * K;

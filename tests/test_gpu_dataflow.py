@@ -74,7 +74,7 @@ class Dag(W._Builder):
                 w = W._f32_floor(W._dirichlet_rows(rng, 1.0, (rows, len(ids) * K)))
                 for j, p in enumerate(ids):
                     theta[p + 1, :rows] = w[:, j * K:(j + 1) * K]
-        tables = np.stack([W._f32_floor(W._dirichlet_rows(rng, table_alpha, (K, n_cats))).T for _ in range(n)])
+        tables = np.ascontiguousarray(np.stack([W._f32_floor(W._dirichlet_rows(rng, table_alpha, (K, n_cats))).T for _ in range(n)]))
         return W._make(f"dag_{seed}", self, root, self.n_params, n, n_cats, n, theta, tables, rng.integers(0, n_cats, size=(B, n)), {})
 
 
