@@ -80,21 +80,28 @@ __device__ inline bool flow_give_up(int spin, int wait_limit, int32_t *ticket, i
     return true;
 }
 
-// Sentinel (and zero) fills before a dataflow launch: workgroup i < n_blk fills the K rows of block ids[i] (rows of a block are
-// contiguous) and, forward, its row of R.
-#define PC_NULL_SHARE 4096
-__device__ inline void flow_fill_block(float *X, float *R, int32_t id, int32_t K, int64_t Bs)
+// Fills before a dataflow launch: a block's K rows (contiguous, K Bs values) are dealt to workgroups in shares of PC_FILL_SHARE
+// values, and with them its row of R or nothing.  fill_shares: of one block.
+#define PC_FILL_SHARE 4096
+static __host__ __device__ inline int fill_shares(int32_t K, int64_t Bs) { return (int)((K * Bs + PC_FILL_SHARE - 1) / PC_FILL_SHARE); }
+__device__ inline void fill_share(float *X, float *Y, float *R, int32_t id, int share, int32_t K, int64_t Bs, float value)
 {
-    const float s = __builtin_bit_cast(float, PC_SENTINEL);
-    floatx4 *dst = reinterpret_cast<floatx4 *>(X + (int64_t)id * Bs);
-    const floatx4 s4 = {s, s, s, s};
-    for (int64_t i = threadIdx.x; i < K * Bs / 4; i += blockDim.x) dst[i] = s4;
-    if (R) for (int64_t i = threadIdx.x; i < Bs; i += blockDim.x) R[(int64_t)(id / K) * Bs + i] = s;
+    const floatx4 v = {value, value, value, value};
+#pragma unroll
+    for (int k = 0; k < PC_FILL_SHARE; k += 1024) {
+        const int64_t i = (int64_t)share * PC_FILL_SHARE + k + 4 * threadIdx.x;   // K Bs, Bs and the share are multiples of 32
+        if (i < K * Bs) {
+            *reinterpret_cast<floatx4 *>(X + (int64_t)id * Bs + i) = v;
+            if (Y) *reinterpret_cast<floatx4 *>(Y + (int64_t)id * Bs + i) = v;
+        }
+        if (R && i < Bs) *reinterpret_cast<floatx4 *>(R + (int64_t)(id / K) * Bs + i) = v;
+    }
 }
 
 // Start of a forward pass in one launch: x -> xT (see below), the sentinels of the sum blocks the dataflow launch will publish,
-// the null block's rows (l = 0, R = 0; mail = 0 where there is a dataflow launch) and the ticket words.  The null block has K Bs
-// values, dealt out in shares of PC_NULL_SHARE (forward pass of a 3 x 32 HMM, B = 131072: one workgroup alone 561 us, so 88 us).
+// the null block's rows (l = 0, R = 0; mail = 0 where there is a dataflow launch) and the ticket words.  One workgroup per block
+// takes longer than the rest of the launch at a large batch: the null block alone, forward pass of a 3 x 32 HMM at B = 131072, 561 us
+// instead of 88; the published ones, this launch for a 16 x 128 HMM in blocks of 128 at B = 4096, 23 us instead of 16.
 // xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
 __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B,
                                                        int32_t D, int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT, int32_t n_xb,
@@ -105,19 +112,10 @@ __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict
     __shared__ int32_t tile[32][33];
     if ((int)blockIdx.x >= n_xtiles) {
         const int q = (int)blockIdx.x - n_xtiles;
-        if (q < n_ent) { flow_fill_block(mail, R, ent[4 * q], K, Bs); return; }
-        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-        const int64_t i0 = (int64_t)(q - n_ent) * PC_NULL_SHARE;        // K Bs and the share are multiples of 32
-#pragma unroll
-        for (int k = 0; k < PC_NULL_SHARE; k += 1024) {
-            const int64_t i = i0 + k + 4 * threadIdx.x;
-            if (i < K * Bs) {
-                *reinterpret_cast<floatx4 *>(l + i) = zero;
-                if (n_ent > 0) *reinterpret_cast<floatx4 *>(mail + i) = zero;
-            }
-            if (i < Bs) *reinterpret_cast<floatx4 *>(R + i) = zero;
-        }
-        if (q == n_ent && threadIdx.x < 2) ticket[threadIdx.x] = 0;
+        const int n_sh = fill_shares(K, Bs), b = q / n_sh, share = q % n_sh;
+        if (b < n_ent) fill_share(mail, nullptr, R, ent[4 * b], share, K, Bs, __builtin_bit_cast(float, PC_SENTINEL));
+        else fill_share(l, n_ent > 0 ? mail : nullptr, R, 0, share, K, Bs, 0.0f);
+        if (q == 0 && threadIdx.x < 2) ticket[threadIdx.x] = 0;
         return;
     }
     const int b0 = ((int)blockIdx.x % n_xb) * 32, v0 = ((int)blockIdx.x / n_xb) * 32;
@@ -152,7 +150,8 @@ __global__ __launch_bounds__(256) void k_begin_backward(const float *__restrict_
 {
     if ((int)blockIdx.x >= n_init * n_cb) {
         const int q = (int)blockIdx.x - n_init * n_cb;
-        if (q < n_ent) flow_fill_block(N, nullptr, ent[4 * q], K, Bs);
+        const int n_sh = fill_shares(K, Bs);
+        if (q < n_ent * n_sh) fill_share(N, nullptr, nullptr, ent[4 * (q / n_sh)], q % n_sh, K, Bs, __builtin_bit_cast(float, PC_SENTINEL));
         else if (threadIdx.x < 2) ticket[threadIdx.x] = 0;
         return;
     }
@@ -519,8 +518,8 @@ void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int3
                           float *l, float *R, float *mail, const int32_t *ent, int32_t n_ent, int32_t K, int32_t *ticket, hipStream_t s)
 {
     Timed timed(KC_MISC, s);
-    const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32), n_null = (int)((K * Bs + PC_NULL_SHARE - 1) / PC_NULL_SHARE);
-    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + n_ent + n_null)), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
+    const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
+    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs))), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
                        n_xt, l, R, mail, ent, n_ent, K, ticket);
 }
 
@@ -529,7 +528,7 @@ void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, con
 {
     Timed timed(KC_MISC, s);
     const int n_cb = (int)((Bs + 255) / 256);
-    hipLaunchKernelGGL(k_begin_backward, dim3((unsigned)(n_blk * n_cb + n_ent + 1)), dim3(256), 0, s, l, F, N, nfmax, blk_ids, n_blk,
+    hipLaunchKernelGGL(k_begin_backward, dim3((unsigned)(n_blk * n_cb + n_ent * fill_shares(K, Bs) + 1)), dim3(256), 0, s, l, F, N, nfmax, blk_ids, n_blk,
                        n_cb, root_id, K, Bs, B, ent, n_ent, ticket);
 }
 

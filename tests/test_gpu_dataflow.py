@@ -218,3 +218,22 @@ def test_null_block_is_filled_by_many_workgroups(K, B):
     print(f"  {us:.0f} us", flush=True)
     assert us < 20 + 1e6 * 4 * K * B / 0.55e12
     c.close()
+
+
+def test_published_blocks_are_filled_by_many_workgroups():
+    """Seventeen blocks of 1 MiB: the launch that writes them takes no longer than a launch that writes nothing (6.3 us between
+    two events, here 7) and its bytes at half the copy rate (5.5 TB/s); the shortest of ten."""
+    w = W.hmm(16, 128, 50, 128, 64, 84)
+    w = w.with_batch(np.tile(w.x, (32, 1)))
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    ref = c.forward().clone()
+    us = []
+    for _ in range(10):
+        pcb.pc_profile_enable(c.handle, True)
+        c.forward()
+        us.append(1e3 * pcb.pc_profile_read(c.handle)["misc"][1])
+    print(f"case fills {min(us):.1f} us", flush=True)
+    assert torch.equal(c.ll, ref) and torch.equal(ref, ref[:64].repeat(32))
+    assert min(us) < 7 + 1e6 * 4 * 17 * 128 * w.B / 2.75e12
+    c.close()
