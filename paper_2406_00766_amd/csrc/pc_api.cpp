@@ -239,19 +239,24 @@ static Ws ws_layout(const pc_circuit *c, int32_t B)
     return w;
 }
 
-// First layer of the part that runs as dataflow launches (from there to the root); layers.size(): none.  Of the cuts that the
-// narrow layers reach, the one that saves most.
-static size_t flow_start(const pc_circuit *c, const Ws &w)
+// First layer of the part that runs as dataflow launches in a direction (from there to the root); layers.size(): none.  Of the
+// cuts that the narrow layers reach, the one that saves most.
+static size_t flow_start(const pc_circuit *c, const Ws &w, bool bwd)
 {
     const size_t L = c->layers.size();
     if (c->flow_fwd.count_from.empty() || !use_flow()) return L;
     size_t li0 = L;
-    int64_t saved = 0, most = 0;
+    double saved = 0, most = 0, start_up = 0;
+    bool top = true;                                      // the highest layer of this direction's
     for (size_t li = L; li-- > 1 && flow_narrow(c, li, w.Bs);) {
         const LayerTab &t = c->layers[li];
         if (w.bf16 && t.kind == KIND_SUM && t.fwd.size() == 1 && sum_layer_takes_bf16(c->K, 1, t.fwd[0].n_rows, t.fwd[0].width, w.Bs)) break;
-        saved += c->flow_saved[li];
-        if (c->flow_cut[li] && saved > most) { most = saved; li0 = li; }
+        if (t.kind == (bwd ? KIND_PRODUCT : KIND_SUM)) {
+            saved += flow_gain(c, li, w.Bs);
+            if (top || !bwd) start_up = flow_start_up(c, li, w.Bs);      // forward the launch begins at the cut, backward at the top
+            top = false;
+        }
+        if (c->flow_cut[li] && saved - start_up > most) { most = saved - start_up; li0 = li; }
     }
     return li0;
 }
@@ -413,11 +418,12 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     const int32_t K = c->K;
     c->fw_B = -1;
 
-    const size_t L = c->layers.size(), li0 = flow_start(c, w);
+    const size_t L = c->layers.size(), li0 = flow_start(c, w, false);
     FlowDev flow{};
     if (li0 < L) flow = flow_dev(c, c->flow_fwd, li0, true);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
-    launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), flow.ent, flow.n_ent, K, ticket, s);
+    const bool null_mail = li0 < L || flow_start(c, w, true) < L;        // read by the dataflow launches of both directions
+    launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), null_mail, flow.ent, flow.n_ent, K, ticket, s);
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     if (w.bf16) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, false, base + w.th_off, base + w.tl_off, s);
     for (size_t li = 0; li < li0; ++li) {
@@ -507,7 +513,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     // no clearing of F: every block's flow is stored by the first layer that feeds it, blocks nobody feeds are
     // initialised here
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
-    const size_t li0 = flow_start(c, w);
+    const size_t li0 = flow_start(c, w, true);
     FlowDev flow{};
     if (li0 < c->layers.size()) flow = flow_dev(c, c->flow_bwd, li0, false);
     int32_t *ticket = (int32_t *)(base + w.tk_off);

@@ -138,14 +138,19 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
 
     c->sum_edges.assign(L, 0);
     c->max_items.assign(L, 0);
-    c->flow_saved.assign(L, 0);
+    c->flow_waits.assign(L, 0);
+    c->flow_chunks.assign(L, 0);
+    std::vector<int32_t> readers(n, 0);                   // product parents that are read themselves, of a sum block
+    for (int32_t u = 0; u < n; ++u)
+        if (d->type[u] == KIND_SUM) readers[u] = (int32_t)std::count_if(par_of.begin() + par_ptr[u], par_of.begin() + par_ptr[u + 1],
+                                                                       [&](int32_t p) { return par_ptr[p] != par_ptr[p + 1]; });
     c->flow_cut.assign(L + 1, 0);
     int32_t reach = 0;                                    // highest layer that reads a product block of the layers so far
     for (int32_t li = 0; li < L; ++li) {
         const LayerTab &T = c->layers[li];
         c->flow_cut[li] = li > 0 && T.kind == KIND_PRODUCT && reach < li;
         int64_t row = 0;                                  // block pairs of the longest row
-        int32_t waits = 0;                                // most sum blocks among the children of a product that is read
+        int32_t waits = 0;                                // most values that a task waits for at one neighbour
         for (int32_t id : T.blk_ids) {
             const int32_t u = id / K - 1;
             if (T.kind == KIND_SUM) {
@@ -158,16 +163,15 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
                         waits = std::max(waits, (int32_t)std::count_if(d->child + k0, d->child + k1, [&](int32_t k) { return d->type[k] == KIND_SUM; }));
                 }
             } else if (T.kind == KIND_PRODUCT) {
-                for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) reach = std::max(reach, layer_of[par_of[k]]);
+                for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k) {
+                    reach = std::max(reach, layer_of[par_of[k]]);
+                    waits = std::max(waits, readers[par_of[k]]);
+                }
+                row = std::max<int64_t>(row, par_ptr[u + 1] - par_ptr[u]);
             }
         }
-        // A task takes the sum blocks among its products' children one after the other, each in 1.2 us and 0.12 us more per
-        // chunk of 32 neighbour nodes in the row; on this scale (units of 0.12 us) a layer's own two launches cost 90.  Measured on a
-        // sum layer and a root that reads products of 5 / 6 / 7 / 8 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4
-        // chunks 30.6 -> 18.3, 29.1 -> 20.2, 29.2 -> 21.3, 29.2 -> 23.7, 28.9 -> 30.3 us; of 16 chunks 33.4 -> 30.9, 34.0 -> 33.8,
-        // 35.3 -> 36.0, 34.4 -> 39.5, 36.0 -> 53.2 us; of 32 chunks 40.7 -> 48.6 us and more.
-        if (T.kind == KIND_SUM)
-            c->flow_saved[li] = (int32_t)std::max<int64_t>(-1000000, 90 - std::max(waits, 1) * (10 + row * (K / 32)));
+        c->flow_waits[li] = waits;
+        c->flow_chunks[li] = (int32_t)std::min<int64_t>(row * (K / 32), 1 << 20);
     }
     int32_t from = L;                                     // the part at the smallest batch holds those at all others
     for (int32_t li = L; li-- > 1 && flow_narrow(c, li, 32);) if (c->flow_cut[li]) from = li;
@@ -278,6 +282,35 @@ bool flow_narrow(const pc_circuit *c, size_t li, int64_t Bs)
     const int64_t ct = Bs / 16;
     if ((int64_t)t.blk_ids.size() * (c->K / 16) * ct > 2048) return false;
     return t.kind != KIND_SUM || (c->sum_edges[li] * (c->K / 16) * (c->K / 32) * ct <= 16384 && c->max_items[li] <= 12);
+}
+
+// What a layer gains from the dataflow launch, in us: a sum layer in the forward, a product layer in the backward pass.
+// Forward, a task takes the sum blocks among its products' children one after the other, each in 1.2 us and 0.12 us more per
+// chunk of 32 neighbour nodes in the row; a layer's own two launches take 10.8 us.  Measured on a sum layer and a root that reads
+// products of 5 / 6 / 7 / 8 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4 chunks 30.6 -> 18.3, 29.1 -> 20.2, 29.2 ->
+// 21.3, 29.2 -> 23.7, 28.9 -> 30.3 us; of 16 chunks 33.4 -> 30.9, 34.0 -> 33.8, 35.3 -> 36.0, 34.4 -> 39.5, 36.0 -> 53.2 us; of 32
+// chunks 40.7 -> 48.6 us and more.
+// Backward, it takes the product parents of its sum blocks one after the other, each in 0.5 us and 0.06 us more per chunk, and
+// what the workgroups do in all grows with tiles and waits; the launches take 11.5 us.  Measured on seven layers whose sum
+// blocks feed 4 / 8 / 12 / 16 / 24 products, launches -> dataflow: one block of 32 nodes per layer, B = 30, 79 -> 44, 80 -> 58, 85 ->
+// 74, 86 -> 89, 91 -> 118 us, B = 300 111 -> 78, 112 -> 99, 118 -> 125, 123 -> 149, 133 -> 209 us; four blocks of 32, B = 30, 86 ->
+// 52, 87 -> 76, 96 -> 104, 102 -> 123 us (16 products); one block of 128, B = 300, 209 -> 178, 224 -> 231, 233 -> 272 us (12 products).
+static double flow_load(const pc_circuit *c, size_t li, int64_t Bs)
+{
+    return (double)((int64_t)c->layers[li].blk_ids.size() * (c->K / 16) * (Bs / 16)) * (1 + c->flow_waits[li] / 8.0);
+}
+double flow_gain(const pc_circuit *c, size_t li, int64_t Bs)
+{
+    const double waits = c->flow_waits[li], chunks = c->flow_chunks[li], load = flow_load(c, li, Bs);
+    if (c->layers[li].kind == KIND_SUM) return 10.8 - std::max(waits, 1.0) * (1.2 + 0.12 * chunks);
+    return 11.5 - std::max(2 + waits * (0.5 + 0.06 * chunks) + 0.003 * load, 0.007 * load);
+}
+// The first layer of the launch finds neither weights nor values requested ahead.  Backward pass of a RAT-SPN's root over 256 product blocks
+// of 32 nodes, B = 16 (1024 tiles) 90 us in launches, 100 as dataflow; of a 3 x 32 HMM, B = 4096 (512 tiles a layer), 565 and 577 us,
+// where the layers' gain alone would be 20 us.
+double flow_start_up(const pc_circuit *c, size_t li, int64_t Bs)
+{
+    return c->layers[li].kind == KIND_PRODUCT ? 0.04 * flow_load(c, li, Bs) : 0.0;
 }
 
 pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)

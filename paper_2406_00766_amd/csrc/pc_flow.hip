@@ -99,22 +99,22 @@ __device__ inline void fill_share(float *X, float *Y, float *R, int32_t id, int 
 }
 
 // Start of a forward pass in one launch: x -> xT (see below), the sentinels of the sum blocks the dataflow launch will publish,
-// the null block's rows (l = 0, R = 0; mail = 0 where there is a dataflow launch) and the ticket words.  One workgroup per block
+// the null block's rows (l = 0, R = 0; mail = 0 where a direction has a dataflow launch) and the ticket words.  One workgroup per block
 // takes longer than the rest of the launch at a large batch: the null block alone, forward pass of a 3 x 32 HMM at B = 131072, 561 us
 // instead of 88; the published ones, this launch for a 16 x 128 HMM in blocks of 128 at B = 4096, 23 us instead of 16.
 // xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
 __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B,
                                                        int32_t D, int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT, int32_t n_xb,
                                                        int32_t n_xtiles, float *__restrict__ l, float *__restrict__ R,
-                                                       float *__restrict__ mail, const int32_t *__restrict__ ent, int32_t n_ent,
-                                                       int32_t K, int32_t *ticket)
+                                                       float *__restrict__ mail, bool null_mail, const int32_t *__restrict__ ent,
+                                                       int32_t n_ent, int32_t K, int32_t *ticket)
 {
     __shared__ int32_t tile[32][33];
     if ((int)blockIdx.x >= n_xtiles) {
         const int q = (int)blockIdx.x - n_xtiles;
         const int n_sh = fill_shares(K, Bs), b = q / n_sh, share = q % n_sh;
         if (b < n_ent) fill_share(mail, nullptr, R, ent[4 * b], share, K, Bs, __builtin_bit_cast(float, PC_SENTINEL));
-        else fill_share(l, n_ent > 0 ? mail : nullptr, R, 0, share, K, Bs, 0.0f);
+        else fill_share(l, null_mail ? mail : nullptr, R, 0, share, K, Bs, 0.0f);
         if (q == 0 && threadIdx.x < 2) ticket[threadIdx.x] = 0;
         return;
     }
@@ -515,12 +515,13 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 
 // ---- launchers ----
 void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
-                          float *l, float *R, float *mail, const int32_t *ent, int32_t n_ent, int32_t K, int32_t *ticket, hipStream_t s)
+                          float *l, float *R, float *mail, bool null_mail, const int32_t *ent, int32_t n_ent, int32_t K,
+                          int32_t *ticket, hipStream_t s)
 {
     Timed timed(KC_MISC, s);
     const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
     hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs))), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
-                       n_xt, l, R, mail, ent, n_ent, K, ticket);
+                       n_xt, l, R, mail, null_mail, ent, n_ent, K, ticket);
 }
 
 void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,

@@ -99,7 +99,9 @@ struct pc_circuit {
     pc::FlowTab flow_fwd, flow_bwd;
     std::vector<int64_t> sum_edges;                   // per layer (sum layers): block pairs,
     std::vector<int32_t> max_items;                   // most children of a product block that it reads,
-    std::vector<int32_t> flow_saved;                  // what a dataflow launch saves on it (pc_compile.cpp)
+    // per layer, what its tasks read (sum layer: forward, product layer: backward): most values waited for at one neighbour, chunks of
+    // 32 neighbour nodes in the longest row
+    std::vector<int32_t> flow_waits, flow_chunks;
     std::vector<uint8_t> flow_cut;                    // per layer: a dataflow part may begin here (a product layer, and no product
                                                       // block below it is read by a sum block above it)
     pc::RowTab prod_fwd_rows, prod_bwd_rows;
@@ -140,6 +142,10 @@ pc_status fail(pc_status st, const std::string &msg);
 pc_status compile_host(const pc_dag *dag, pc_circuit *c, bool tables_on_host);
 // Whether a layer is narrow enough for the dataflow launches at row stride Bs (narrower at a smaller one).
 bool flow_narrow(const pc_circuit *c, size_t layer, int64_t Bs);
+// Microseconds that such a layer gains from them (negative: loses).
+double flow_gain(const pc_circuit *c, size_t layer, int64_t Bs);
+// Microseconds more that it takes as the first layer of the launch.
+double flow_start_up(const pc_circuit *c, size_t layer, int64_t Bs);
 // Device part of compilation: transposes the block graph, sorts neighbour lists and fills every forward and
 // backward table with HIP kernels; allocates the handle's device arena and uploads the remaining metadata.
 pc_status build_tables_device(const pc_dag *dag, pc_circuit *c, void *stream);

@@ -237,3 +237,35 @@ def test_published_blocks_are_filled_by_many_workgroups():
     assert torch.equal(c.ll, ref) and torch.equal(ref, ref[:64].repeat(32))
     assert min(us) < 7 + 1e6 * 4 * 17 * 128 * w.B / 2.75e12
     c.close()
+
+
+def layered(K, n_sum, n_prod, depth, B, seed):
+    """Levels of n_sum sum blocks, each of which feeds n_prod products (with an input of their own) that the whole next level reads."""
+    d = Dag(K)
+    level = [d.sum([d.product([d.input()])]) for _ in range(n_sum)]
+    for _ in range(depth):
+        products = [d.product([s, d.input()]) for s in level for _ in range(n_prod)]
+        level = [d.sum(products) for _ in range(n_sum)]
+    root = d.sum([d.product([s]) for s in level], n_real=1)
+    return d.workload(root, B, seed)
+
+
+@pytest.mark.parametrize("K,n_sum,n_prod,B,merged", [
+    (32, 1, 8, 30, True), (32, 1, 30, 30, False), (32, 1, 30, 300, False), (64, 4, 2, 30, True), (128, 1, 24, 60, False),
+])
+def test_sum_blocks_that_feed_many_products(K, n_sum, n_prod, B, merged):
+    """A dataflow task of the backward pass takes the product parents of its sum blocks one after the other: where a sum block has
+    many, these layers keep their own launches in that direction (six levels, and the read-out's product), whatever the forward
+    pass does; against the oracle."""
+    w = layered(K, n_sum, n_prod, 6, B, 85)
+    print(f"case many readers K={K} {n_sum} x {n_prod} B={B}", flush=True)
+    check_all(w)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    pcb.pc_profile_enable(c.handle, True)
+    c.forward()
+    c.backward()
+    prof = pcb.pc_profile_read(c.handle)
+    assert prof["sum_fwd"][0] == 1 if K == 32 else prof["sum_fwd"][0] >= 1
+    assert prof["sum_bwd_child"][0] < 3 if merged else prof["sum_bwd_child"][0] >= 6
+    c.close()
