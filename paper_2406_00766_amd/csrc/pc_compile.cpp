@@ -289,28 +289,31 @@ bool flow_narrow(const pc_circuit *c, size_t li, int64_t Bs)
 // chunk of 32 neighbour nodes in the row; a layer's own two launches take 10.8 us.  Measured on a sum layer and a root that reads
 // products of 5 / 6 / 7 / 8 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4 chunks 30.6 -> 18.3, 29.1 -> 20.2, 29.2 ->
 // 21.3, 29.2 -> 23.7, 28.9 -> 30.3 us; of 16 chunks 33.4 -> 30.9, 34.0 -> 33.8, 35.3 -> 36.0, 34.4 -> 39.5, 36.0 -> 53.2 us; of 32
-// chunks 40.7 -> 48.6 us and more.
+// chunks 40.7 -> 48.6 us and more.  Many tiles take 7 ns each, whatever their rows: HMMs of 16 layers of one block, B = 2048 / 4096 /
+// 8192 / 16384, launches -> dataflow: 32 nodes 127 -> 52, 132 -> 81, 144 -> 138, 157 -> 252 us (256 .. 2048 tiles a layer), 128 nodes
+// 173 -> 150, 207 -> 256 us (1024, 2048).
 // Backward, it takes the product parents of its sum blocks one after the other, each in 0.5 us and 0.06 us more per chunk, and
 // what the workgroups do in all grows with tiles and waits; the launches take 11.5 us.  Measured on seven layers whose sum
 // blocks feed 4 / 8 / 12 / 16 / 24 products, launches -> dataflow: one block of 32 nodes per layer, B = 30, 79 -> 44, 80 -> 58, 85 ->
 // 74, 86 -> 89, 91 -> 118 us, B = 300 111 -> 78, 112 -> 99, 118 -> 125, 123 -> 149, 133 -> 209 us; four blocks of 32, B = 30, 86 ->
 // 52, 87 -> 76, 96 -> 104, 102 -> 123 us (16 products); one block of 128, B = 300, 209 -> 178, 224 -> 231, 233 -> 272 us (12 products).
-static double flow_load(const pc_circuit *c, size_t li, int64_t Bs)
+static double flow_tiles(const pc_circuit *c, size_t li, int64_t Bs)
 {
-    return (double)((int64_t)c->layers[li].blk_ids.size() * (c->K / 16) * (Bs / 16)) * (1 + c->flow_waits[li] / 8.0);
+    return (double)((int64_t)c->layers[li].blk_ids.size() * (c->K / 16) * (Bs / 16));
 }
+static double flow_load(const pc_circuit *c, size_t li, int64_t Bs) { return flow_tiles(c, li, Bs) * (1 + c->flow_waits[li] / 8.0); }
 double flow_gain(const pc_circuit *c, size_t li, int64_t Bs)
 {
     const double waits = c->flow_waits[li], chunks = c->flow_chunks[li], load = flow_load(c, li, Bs);
-    if (c->layers[li].kind == KIND_SUM) return 10.8 - std::max(waits, 1.0) * (1.2 + 0.12 * chunks);
+    if (c->layers[li].kind == KIND_SUM) return 10.8 - std::max(std::max(waits, 1.0) * (1.2 + 0.12 * chunks), 0.007 * flow_tiles(c, li, Bs));
     return 11.5 - std::max(2 + waits * (0.5 + 0.06 * chunks) + 0.003 * load, 0.007 * load);
 }
 // The first layer of the launch finds neither weights nor values requested ahead.  Backward pass of a RAT-SPN's root over 256 product blocks
 // of 32 nodes, B = 16 (1024 tiles) 90 us in launches, 100 as dataflow; of a 3 x 32 HMM, B = 4096 (512 tiles a layer), 565 and 577 us,
-// where the layers' gain alone would be 20 us.
+// where the layers' gain alone would be 20 us.  Forward passes of 3 x 32 and 3 x 128 HMMs, 1024 tiles a layer: 36 -> 40 and 47 -> 52 us.
 double flow_start_up(const pc_circuit *c, size_t li, int64_t Bs)
 {
-    return c->layers[li].kind == KIND_PRODUCT ? 0.04 * flow_load(c, li, Bs) : 0.0;
+    return c->layers[li].kind == KIND_PRODUCT ? 0.04 * flow_load(c, li, Bs) : 0.012 * flow_tiles(c, li, Bs);
 }
 
 pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)

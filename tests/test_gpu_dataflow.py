@@ -269,3 +269,23 @@ def test_sum_blocks_that_feed_many_products(K, n_sum, n_prod, B, merged):
     assert prof["sum_fwd"][0] == 1 if K == 32 else prof["sum_fwd"][0] >= 1
     assert prof["sum_bwd_child"][0] < 3 if merged else prof["sum_bwd_child"][0] >= 6
     c.close()
+
+
+@pytest.mark.parametrize("T,K,B,merged", [(16, 32, 512, True), (16, 32, 16384, False), (3, 128, 4096, False), (16, 128, 4096, False),
+                                          (3, 64, 512, True)])
+def test_layers_of_many_column_tiles_keep_their_launches(T, K, B, merged):
+    """Narrow circuits at large batches: 2048 tiles a layer take longer as tasks than as launches.  Equal samples have equal
+    log-likelihoods wherever they stand in the batch, and those of the same batch in small parts."""
+    w = W.hmm(T, K, 50, K, 64, 86)
+    big = w.with_batch(np.tile(w.x, (B // 64, 1)))
+    print(f"case many tiles T={T} K={K} B={B}", flush=True)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    ref = c.forward().double().cpu()
+    c.set_batch(big.x)
+    pcb.pc_profile_enable(c.handle, True)
+    ll = c.forward().double().cpu()
+    assert pcb.pc_profile_read(c.handle)["sum_fwd"][0] == (1 if merged else T)
+    assert torch.equal(ll, ll[:64].repeat(B // 64))
+    assert ((ll[:64] - ref).abs() <= 1e-6 * ref.abs() + 4e-6).all()      # results are held to some 1e-6 (pc.h), R is exact
+    c.close()
