@@ -23,4 +23,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // so the factor is applied as two multiplications by exp(delta / 2); below delta = -174 the result is nil anyway.
 __device__ inline float pc_half_scale(float delta) { return __expf(0.5f * fmaxf(delta, -174.0f)); }
 
+// buffer descriptors: raw (stride 0), 2 GiB window from the base, 32-bit data format
+#define PC_BUF_RANGE 0x7fffffff
+#define PC_BUF_FLAGS 0x00020000
+
 }  // namespace pc

@@ -7,8 +7,8 @@
 // values of an earlier task reads them straight from the result buffer until they are there:
 //   * the rows a task publishes are filled with a sentinel (a NaN bit pattern no result has) before the launch; a consumer
 //     loads the values it needs with device-scope loads and repeats the load while any of them is the sentinel.  Data and
-//     signal are one word, so a hand-over costs one store and one load -- 0.8 us between workgroups against 1.7 us for an
-//     empty kernel boundary (measured) plus the consumer's cold start, which here is over before the values arrive: a
+//     signal are one word, so a hand-over costs one store and one load -- 0.5 - 0.7 us between workgroups (measured) where a kernel
+//     boundary costs that of the launch and the consumer's cold start, which here is over before the values arrive: a
 //     waiting workgroup holds its weights in registers already.
 //   * no wait can last for ever: a task waits only for tasks with lower tickets, tickets are taken by running workgroups
 //     in increasing order and worked off in that order, so the lowest unfinished task never waits.  (No assumption about
@@ -47,8 +47,6 @@ namespace pc {
 
 // Device-scope 4- and 16-byte accesses (sc1); every dword of a 16-byte access is a word of its own.  (A polling loop needs a
 // compiler barrier so that it loads again; a volatile access would be system-scope.)
-#define PC_BUF_RANGE 0x7fffffff
-#define PC_BUF_FLAGS 0x00020000
 #define PC_AUX_DEVICE 16
 __device__ inline floatx4 mail_load(const float *tile, int voff)
 {
@@ -217,7 +215,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
     // operands of this wave's chunks cb, cb + W, ... (NCH of them; past the end the first one again, given the value -inf)
     floatx4 th[NCH][2][RT], v[NCH][2], own_l[BWD ? NCH : 1][2];
     float base[NCH];
-    int32_t koff[NCH], own[NCH], cnt[NCH], skip[NCH];
+    int32_t koff[NCH], own[NCH], cnt[NCH];
     const int32_t *rp[NCH];
     // item n of chunk i if it is (wait) / is not (!wait) one to wait for, else the null block (value 0); any: there is one
     auto item = [&](int i, int n, bool wait, int &any) -> int32_t {
@@ -258,8 +256,8 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     }
                 }
             // the first item if it is there already (else zeros from the null block); backward: the sum block's own rows
-            skip[i] = 0;
-            const int32_t it = item(i, 0, false, skip[i]);
+            int any = 0;
+            const int32_t it = item(i, 0, false, any);
             row_values(BWD ? F : l, it, i, col, v[i]);
             if (BWD) row_values(l, own[i], i, col, own_l[i]);
             base[i] = R[(int64_t)((BWD ? own[i] : it) >> ks) * Bs + col];

@@ -1167,6 +1167,7 @@ __global__ __launch_bounds__(256) void k_param_flow_16(const float *__restrict__
             const bool live = mx > PC_NEG_INF && (whole || lane < 32);  // dead sample: both factors 0
             q[wave][0][lane] = live ? (sb - mx) * PC_LOG2E : PC_NEG_INF;
             q[wave][1][lane] = live ? (gg - sb - PC_SPLIT_SCALE) * PC_LOG2E : PC_NEG_INF;
+            __builtin_amdgcn_wave_barrier();                            // the lanes below read what others wrote
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
                 const floatx4 qa = *reinterpret_cast<const floatx4 *>(&q[wave][0][16 * c + 4 * g]);
@@ -1178,6 +1179,7 @@ __global__ __launch_bounds__(256) void k_param_flow_16(const float *__restrict__
                     acc[c & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, p, acc[c & 1], 0, 0, 0);
                 }
             }
+            __builtin_amdgcn_wave_barrier();                            // and write anew in the next round
         }
     }
 #pragma unroll
@@ -1224,9 +1226,6 @@ __global__ __launch_bounds__(256) void k_param_flow_16(const float *__restrict__
 // per-block log-space update of the accumulator in Alg. 1 / Alg. 4, with one log per output instead of one
 // per block).  Partial sums of the SPLIT waves are merged through LDS at the end.  No lane-dependent
 // branch surrounds an MFMA.
-// buffer descriptor of the main-loop loads: raw (stride 0), 2 GiB window from the chunk's base, 32-bit data format
-#define PC_BUF_RANGE 0x7fffffff
-#define PC_BUF_FLAGS 0x00020000
 template <int K, int RT, int SPLIT, bool BWD, bool MULTI, int MODE>
 __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ theta, float *__restrict__ l,
                                                      float *__restrict__ R, const float *__restrict__ N,
