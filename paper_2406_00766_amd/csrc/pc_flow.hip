@@ -30,8 +30,10 @@
 //
 // What bounds it: the chain through the layers.  Measured (time stamps of the tasks of one layer): values seen 0.5 - 0.7 us
 // after they were published, 0.4 - 0.5 us to exponentials and MFMAs (up to 128 neighbour nodes; at 512, 1 us: the waves of a CU
-// share its matrix cores), 0.2 - 0.5 us to merge and publish: 1.3 us per layer at 32 nodes, 2 us at 128, 4.5 us at 512, against
-// 7 - 13 us for a layer's two launches.  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 29 us; forward,
+// share its matrix cores), 0.2 - 0.5 us to merge and publish: 1.3 us at 32 nodes, 1.5 at 128, 2.2 at 512.  Launch time over layers:
+// 1.4 us at 32 nodes (HMM 16 x 32), 3.5 us on a 784-variable tree with M = 128, B = 512, 4.6 us at 512 (HMM 32 x 512), against
+// 7 - 13 us for a layer's two launches; what the stamps do not account for is not attributed (products that wait for several
+// children in turn; polls that read every operand of the wave again).  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 29 us; forward,
 // 784-variable tree, M = 128, B = 100 908 -> 350 us; forward + backward, the same tree at B = 512 2.70 -> 1.69 ms; HMM T = 32, H = 512,
 // B = 77 865 -> 390 us.
 #include <hip/hip_runtime.h>
@@ -290,7 +292,6 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 
         floatx4 acc[RT];
         float ref = PC_NEG_INF;                                         // reference of acc; -inf: nothing live yet
-        bool lost = false;                                              // a wait of this wave was given up
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
@@ -385,7 +386,13 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                         if (!BWD) missing |= is_sentinel(xr[i]);
                     }
                     if (!__any(missing)) break;
-                    if (flow_give_up(spin, wait_limit, ticket, fault)) { lost = true; break; }
+                    if (flow_give_up(spin, wait_limit, ticket, fault)) {    // NaN in all its results (a factor 0 below keeps it)
+#pragma unroll
+                        for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) x[i][k >> 2][k & 3] = __builtin_nanf("");
+                        break;
+                    }
                     __builtin_amdgcn_s_sleep(1);
                 }
                 add_item(x, xr);
@@ -446,12 +453,6 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
             }
             cb += W * NCH;
             if (cb < T.C) request(T, cb);
-        }
-        if (lost) {                                                     // NaN in all its results (a factor 0 below keeps it)
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[rt][r] = __builtin_nanf("");
         }
         // the waves' partial sums meet in LDS; tile rt goes to wave rt % W
         if (W > 1) {

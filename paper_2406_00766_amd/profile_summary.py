@@ -48,7 +48,7 @@ def write_stats(src, dst, command, note):
         for r in rows:
             if float(r["Percentage"]) < 0.01:
                 continue
-            name = r["Name"].split("(")[0].replace("void ", "")
+            name = r["Name"].replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
             f.write("%-90s %-14s %7s %12.3f %12.2f %7.2f\n" % (name, kernel_class(name), r["Calls"], float(r["TotalDurationNs"]) / 1e6,
                                                               float(r["AverageNs"]) / 1e3, float(r["Percentage"])))
 
@@ -59,7 +59,7 @@ def read_counter_csv(path):
     names = collections.defaultdict(set)
     seen = collections.defaultdict(set)
     for r in csv.DictReader(open(path)):
-        kname = r["Kernel_Name"].split("(")[0].replace("void ", "")
+        kname = r["Kernel_Name"].replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
         cls = kernel_class(kname)
         names[cls].add(kname.replace("pc::", ""))
         ctr = r["Counter_Name"]
