@@ -309,7 +309,8 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
             // products of more than eight children, which the product kernels sum in double): the rounding error of every
             // addition is kept beside the sum (Knuth's two-sum) and added once the integer part is out.  Products of 12 children
             // of -80 nats: largest error of the sum layer above 6.7e-5 -> 1.0e-6.  An instantiation of its own, as carrying it in
-            // every launch cost 1 - 5 % of a pass (HMM 16 x 32, one sample 29.1 -> 30.5 us).
+            // every launch cost 1 - 5 % of a pass (HMM 16 x 32, one sample 29.1 -> 30.5 us), and in it the tasks that have such a
+            // product (3072-variable tree, forward 2.71 -> 2.66 ms against all tasks).
             floatx4 low[EXACT ? NCH : 1][2];
             if (EXACT) {
 #pragma unroll
@@ -328,8 +329,9 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] -= cm;
                 }
             };
+            const bool exact = EXACT && max_cnt > 8;                    // wave-uniform: this task has such a product
             auto add_item = [&](const floatx4 (&x)[NCH][2], const float (&xr)[NCH]) {
-                if (EXACT) {
+                if (exact) {
 #pragma unroll
                     for (int i = 0; i < NCH; ++i)
 #pragma unroll
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                     for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] += x[i][k >> 2][k & 3];
                     if (!BWD) base[i] += xr[i];
                 }
-                if (!BWD && !EXACT && (++since & 3) == 3) settle();
+                if (!BWD && !exact && (++since & 3) == 3) settle();
             };
             for (int n = 1; n < max_cnt; ++n) {                         // items of earlier launches (the first: requested before)
                 int32_t its[NCH];
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                 }
                 add_item(x, xr);
             }
-            if (EXACT) {
+            if (exact) {
                 settle();
 #pragma unroll
                 for (int i = 0; i < NCH; ++i)
