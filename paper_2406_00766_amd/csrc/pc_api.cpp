@@ -262,10 +262,10 @@ static size_t flow_start(const pc_circuit *c, const Ws &w, bool bwd)
 }
 static FlowDev flow_dev(const pc_circuit *c, const FlowTab &f, size_t li0, bool suffix)
 {
-    int32_t n_levels = 0;                                 // layers with entries
-    for (size_t li = li0; li + 1 < f.count_from.size(); ++li) n_levels += f.count_from[li] > f.count_from[li + 1];
+    int32_t max_level = 0;
+    for (size_t li = li0; li + 1 < f.count_from.size(); ++li) max_level = std::max(max_level, f.count_from[li] - f.count_from[li + 1]);
     const int32_t n = f.count_from[li0], first = suffix ? f.count_from[0] - n : 0;
-    return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, n_levels,
+    return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, max_level,
                    *std::max_element(c->max_items.begin() + li0, c->max_items.end())};
 }
 static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)

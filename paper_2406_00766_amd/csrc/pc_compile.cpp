@@ -179,7 +179,8 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
 
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { f->count_from.assign(L + 1, 0); f->max_nbr_from.assign(L + 1, 0); }
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) { r->count_from.assign(L + 1, 0); r->max_nbr_from.assign(L + 1, 0); r->start.assign(1, 0); }
-    // list of every product block's children and of every sum block's product parents (or itself): (node offset, layer)
+    // list of every product block's children and of every sum block's product parents (or itself): (node offset, layer), in the order
+    // in which the sweep produces them
     std::vector<int32_t> list_at(n, 0), list_n(n, 0);
     for (int32_t u = 0; u < n; ++u) {
         if (d->type[u] == KIND_INPUT || layer_of[u] < from) continue;
@@ -187,11 +188,14 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
         list_at[u] = (int32_t)(to.size() / 2);
         if (d->type[u] == KIND_PRODUCT) {
             std::vector<int32_t> ch(d->child + d->child_ptr[u], d->child + d->child_ptr[u + 1]);
-            std::sort(ch.begin(), ch.end());
+            std::sort(ch.begin(), ch.end(), [&](int32_t a, int32_t b) { return layer_of[a] != layer_of[b] ? layer_of[a] < layer_of[b] : a < b; });
             for (int32_t k : ch) to.insert(to.end(), {off(k), layer_of[k]});
         } else {
+            std::vector<int32_t> pa;
             for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k)       // an unused product parent has flow 0
-                if (par_ptr[par_of[k]] != par_ptr[par_of[k] + 1]) to.insert(to.end(), {off(par_of[k]), layer_of[par_of[k]]});
+                if (par_ptr[par_of[k]] != par_ptr[par_of[k] + 1]) pa.push_back(par_of[k]);
+            std::stable_sort(pa.begin(), pa.end(), [&](int32_t a, int32_t b) { return layer_of[a] > layer_of[b]; });
+            for (int32_t k : pa) to.insert(to.end(), {off(k), layer_of[k]});
             // the root or an unused sum block (its own flow rows are initialised); one whose parents are all unused: flow 0
             if ((int32_t)(to.size() / 2) == list_at[u]) to.insert(to.end(), {par_ptr[u] == par_ptr[u + 1] ? off(u) : 0, -1});
         }

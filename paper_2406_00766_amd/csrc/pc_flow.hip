@@ -28,14 +28,15 @@
 // waves of a workgroup split the chunks and meet in LDS once.  A chunk's values are brought to an integer reference (the
 // rounded column maximum joins R), so every exponential sees an argument <= 0.5 and results need no running maximum.
 //
-// What bounds it: the chain through the layers.  Measured (time stamps of the tasks of one layer): values seen 0.5 - 0.7 us
-// after they were published, 0.4 - 0.5 us to exponentials and MFMAs (up to 128 neighbour nodes; at 512, 1 us: the waves of a CU
-// share its matrix cores), 0.2 - 0.5 us to merge and publish: 1.3 us at 32 nodes, 1.5 at 128, 2.2 at 512.  Launch time over layers:
-// 1.4 us at 32 nodes (HMM 16 x 32), 3.5 us on a 784-variable tree with M = 128, B = 512, 4.6 us at 512 (HMM 32 x 512), against
-// 7 - 13 us for a layer's two launches; what the stamps do not account for is not attributed (products that wait for several
-// children in turn; polls that read every operand of the wave again).  Before -> now, whole passes: forward, HMM T = 16, H = 32, one sample 137 -> 29 us; forward,
-// 784-variable tree, M = 128, B = 100 908 -> 350 us; forward + backward, the same tree at B = 512 2.70 -> 1.69 ms; HMM T = 32, H = 512,
-// B = 77 865 -> 390 us.
+// What bounds it: the chain through the layers.  Measured (time stamps of the tasks of one layer, forward, from the layer before
+// being published): values seen after 0.6 - 0.9 us (1.4 at 512 neighbour nodes; 0.57 us is the bare hand-over between two
+// workgroups, 0.45 on one XCD), 0.4 us at 32 nodes, 0.55 at 128, 1.3 at 512 to exponentials and MFMAs (there the eight waves of a CU
+// share its matrix cores for 0.85 us), 0.2 - 0.4 us to merge and publish: 1.2, 1.9 and 3.5 us a layer.  Three things had made that 1.4, 2.3
+// and 4.8 us: tickets drawn a task ahead, so that a workgroup could be left with a task of the very next layer and find its
+// weights unrequested; table words read through the vector memory pipe between two polls; lists in the order of the ids, so
+// that the value that arrives last was not the last to be asked for.  Before -> now: forward + backward of an HMM T = 32, H = 512, B = 77
+// 163 + 228 -> 126 + 201 us; T = 60, H = 1024, B = 20 523 + 606 -> 281 + 431; 784-variable tree, M = 128, B = 100 349 + 462 -> 316 +
+// 438; 500 variables, M = 64, B = 30 137 + 148 -> 114 + 128; HMM T = 50, H = 64, B = 400 114 + 210 -> 98 + 192.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,13 +48,26 @@ namespace pc {
 
 #define PC_SENTINEL 0xFFFFFFFFu
 
-// Device-scope 4- and 16-byte accesses (sc1); every dword of a 16-byte access is a word of its own.  (A polling loop needs a
+// Device-scope accesses (sc1); every dword of a wider access is a word of its own.  (A polling loop needs a
 // compiler barrier so that it loads again; a volatile access would be system-scope.)
 #define PC_AUX_DEVICE 16
 __device__ inline floatx4 mail_load(const float *tile, int voff)
 {
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)tile, 0, PC_BUF_RANGE, PC_BUF_FLAGS);
     return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, PC_AUX_DEVICE));
+}
+template <int N>
+__device__ inline void mail_store(float *tile, int voff, const float (&v)[N])
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)tile, 0, PC_BUF_RANGE, PC_BUF_FLAGS);
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    uint32_t w[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = __builtin_bit_cast(uint32_t, v[k]);
+    if constexpr (N == 4) __builtin_amdgcn_raw_buffer_store_b128(u4{w[0], w[1], w[2], w[3]}, r, voff, 0, PC_AUX_DEVICE);
+    else if constexpr (N == 2) __builtin_amdgcn_raw_buffer_store_b64(u2{w[0], w[1]}, r, voff, 0, PC_AUX_DEVICE);
+    else __builtin_amdgcn_raw_buffer_store_b32(w[0], r, voff, 0, PC_AUX_DEVICE);
 }
 __device__ inline float flow_load(const float *p)
 {
@@ -69,7 +83,6 @@ __device__ inline float max_over_groups(float v)
     asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
     return fmaxf(a, b);
 }
-__device__ inline bool is_sentinel(float v) { return __builtin_bit_cast(uint32_t, v) == PC_SENTINEL; }
 __device__ inline float no_sentinel(float v) { return v == v ? v : __builtin_bit_cast(float, 0x7FC00000u); }   // one NaN for all
 
 __device__ inline bool flow_give_up(int spin, int wait_limit, int32_t *ticket, int32_t *fault)
@@ -182,53 +195,64 @@ __global__ __launch_bounds__(256) void k_begin_backward(const float *__restrict_
 //   ent  4 words per task block, in task order: node offset, first neighbour record, neighbour records, 1 for the root
 //   rec  16 words per neighbour: parameter offset; start of its list; list items; neighbour's node offset; its layer; the first
 //        five items and then their layers.  A list holds items (node offset, layer); an item of layer li0 or above is waited for.
-//        Forward: the neighbour is a product block, the list its children; a neighbour below layer li0 has been evaluated
-//        already and stands for itself.  Backward: the neighbour is a sum block, the list its product parents, or itself
-//        (layer -1) where it has none.
+//        Items stand in the order in which they will be there, so those to wait for are the end of the list and the last is
+//        the one that arrives last.  Forward: the neighbour is a product block, the list its children; a neighbour below layer
+//        li0 has been evaluated already and stands for itself.  Backward: the neighbour is a sum block, the list its product
+//        parents, or itself (layer -1) where it has none.
+// They are read as constants, through the scalar cache: a vector load of a table word between two polls was a memory latency
+// of the chain.
 // `mail` (the rows of log_nf that are not in use at the time: sum rows forward, product rows backward) carries the published
 // values in MFMA operand order: per block, 16 rows and 16 columns one 1 KiB tile, lane (j, g) holding rows 4 g .. 4 g + 3 of
 // column j -- one 16-byte load per lane where the row-major buffer would take four loads of 4 x 64 bytes, and no line shared
 // by two column tiles.
+typedef const int32_t __attribute__((address_space(4))) *TabPtr;
+template <int N> struct FloatVec { typedef float type __attribute__((ext_vector_type(N))); };
+template <> struct FloatVec<1> { typedef float type; };
+
 template <int W, int RT, int NCH, bool BWD, bool EXACT>
 __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__restrict__ theta, float *__restrict__ l, float *R,
-                                                                 float *__restrict__ F, float *mail,
-                                                                 const int32_t *__restrict__ ent, const int32_t *__restrict__ rec,
-                                                                 const int32_t *__restrict__ list, int32_t n_tasks, int32_t n_ct,
-                                                                 int32_t K, int64_t Bs, int32_t li0, int32_t *ticket,
-                                                                 float *__restrict__ ll, int32_t B, int32_t wait_limit,
-                                                                 int32_t *fault)
+                                                                 float *__restrict__ F, float *mail, const int32_t *ent_words,
+                                                                 const int32_t *rec_words, const int32_t *list_words,
+                                                                 int32_t n_tasks, int32_t n_ct, int32_t K, int64_t Bs, int32_t li0,
+                                                                 int32_t *ticket, float *__restrict__ ll, int32_t B,
+                                                                 int32_t wait_limit, int32_t *fault)
 {
-    constexpr int TPW = (RT + W - 1) / W;                               // 16 x 16 result tiles that a wave writes
-    __shared__ floatx4 part[2][W][RT][W > 1 ? 64 : 1];                              // partial sums of the waves, double-buffered over tasks
+    // Results: the RT tiles of 256 words are dealt to the waves in equal shares, VL consecutive words a lane, so that merge and logarithms
+    // of a task take all its waves (dealt tile by tile two of four or eight worked: 0.1 us a layer).
+    constexpr int VL = W == 1 ? 4 : RT * 4 / W > 0 ? RT * 4 / W : 1;
+    constexpr int TPW = W == 1 ? RT : 1;                                // tiles of a wave's share
+    constexpr int RW = W == 1 ? 1 : RT * 4 / VL;                        // waves that have a share
+    __shared__ floatx4 part[2][W][RT][W > 1 ? 64 : 1];                  // partial sums of the waves, double-buffered over tasks
     __shared__ float pref[2][W][16];                                    // and their references
     __shared__ int32_t s_ticket[2];
+    const TabPtr ent = (TabPtr)(uintptr_t)ent_words, rec = (TabPtr)(uintptr_t)rec_words, list = (TabPtr)(uintptr_t)list_words;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
     const int ks = 31 - __builtin_clz(K);                               // K is 32, 64 or 128
     const int TM = 16 * RT, subs = K / TM, cpb = K >> 5;
+    // first word of this lane's share and the tile it lies in; word 4 u + r of a tile is row 4 (u / 16) + r of column u % 16
+    const int word0 = W == 1 ? 4 * lane : wave * VL * 64 % 256 + VL * lane;
+    const int rt0 = W == 1 ? 0 : wave * VL * 64 / 256 % RT;
+    const int rj = (word0 >> 2) & 15, rr = 4 * (word0 >> 6) + (word0 & 3);
 
     struct Task { int32_t ct, sub, row0, rec0, root, C; };              // C: chunks of 32 neighbour nodes
     auto decode = [&](int t) -> Task {
-        if (t >= n_tasks) return Task{0, 0, 0, 0, 0, 0};
         const int q = t / n_ct, e = 4 * (q / subs);
         return Task{t % n_ct, q % subs, ent[e], ent[e + 1], ent[e + 3], ent[e + 2] * cpb};
     };
+    // Tickets: the next task of this workgroup.  (Lane 0 of wave 0 draws; the other lanes' accesses lie outside the buffer's range and do
+    // nothing.  A branch around the atomic makes the compiler wait for its result at the branch's end.)
+    const __amdgpu_buffer_rsrc_t ticket_word = __builtin_amdgcn_make_buffer_rsrc((void *)ticket, 0, 4, PC_BUF_FLAGS);
+    auto draw = [&]() -> int { return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, ticket_word, threadIdx.x == 0 ? 0 : 4, 0, 0); };
 
     // operands of this wave's chunks cb, cb + W, ... (NCH of them; past the end the first one again, given the value -inf)
     floatx4 th[NCH][2][RT], v[NCH][2], own_l[BWD ? NCH : 1][2];
     float base[NCH];
-    int32_t koff[NCH], own[NCH], cnt[NCH];
-    const int32_t *rp[NCH];
-    // item n of chunk i if it is (wait) / is not (!wait) one to wait for, else the null block (value 0); any: there is one
-    auto item = [&](int i, int n, bool wait, int &any) -> int32_t {
-        if (cnt[i] < 0) { if (n == 0 && !wait) { any = 1; return own[i]; } return 0; }
-        if (n >= cnt[i]) return 0;
-        int32_t it, lay;
-        if (n < 5) { it = rp[i][5 + n]; lay = rp[i][10 + n]; }
-        else { it = list[2 * (rp[i][1] + n)]; lay = list[2 * (rp[i][1] + n) + 1]; }
-        if ((lay >= li0) != wait) return 0;
-        any = 1;
-        return it;
+    int32_t koff[NCH], own[NCH], cnt[NCH], pre[NCH];                    // list items; those at the beginning that are there already
+    TabPtr rp[NCH];
+    auto item = [&](int i, int n) -> int32_t {                          // item n of chunk i's list
+        if (!BWD && rp[i][4] < li0) return own[i];                      // evaluated before this launch
+        return n < 5 ? rp[i][5 + n] : list[2 * (rp[i][1] + n)];
     };
     auto row_values = [&](const float *X, int32_t id, int i, int64_t col, floatx4 (&x)[2]) {
         const float *src = X + (int64_t)(id + koff[i] + 4 * g) * Bs + col;
@@ -240,11 +264,10 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int cc = cb + W * i < T.C ? cb + W * i : cb;
-            const int32_t *r = rec + 16 * (int64_t)(T.rec0 + cc / cpb);
+            const TabPtr r = rec + 16 * (int64_t)(T.rec0 + cc / cpb);
             rp[i] = r;
             koff[i] = (cc % cpb) * 32;
             cnt[i] = r[2]; own[i] = r[3];
-            if (!BWD && r[4] < li0) cnt[i] = -1;                        // evaluated before this launch
             const float *tb = theta + r[0] + (BWD ? koff[i] * K + T.sub * TM : T.sub * TM * K + koff[i]);
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2)
@@ -257,36 +280,43 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                         th[i][c2][rt] = *reinterpret_cast<const floatx4 *>(tb + (rt * 16 + j16) * K + 16 * c2 + 4 * g);
                     }
                 }
+            if (BWD) {
+                pre[i] = r[10] < li0 ? cnt[i] : 0;                      // the block itself, or parents that are all waited for
+            } else if (r[4] < li0) {
+                cnt[i] = pre[i] = 1;
+            } else {
+                int p = 0;
+#pragma unroll
+                for (int k = 0; k < 5; ++k) p += k < cnt[i] && r[10 + k] < li0;
+                if (p == 5)
+                    while (p < cnt[i] && list[2 * (r[1] + p) + 1] < li0) ++p;
+                pre[i] = p;
+            }
             // the first item if it is there already (else zeros from the null block); backward: the sum block's own rows
-            int any = 0;
-            const int32_t it = item(i, 0, false, any);
+            const int32_t it = pre[i] > 0 ? item(i, 0) : 0;
             row_values(BWD ? F : l, it, i, col, v[i]);
             if (BWD) row_values(l, own[i], i, col, own_l[i]);
             base[i] = R[(int64_t)((BWD ? own[i] : it) >> ks) * Bs + col];
         }
     };
 
-    int nxt = 0;
-    if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);
+    int nxt = draw();
     if (W > 1) {
         if (threadIdx.x == 0) s_ticket[1] = nxt;
         __syncthreads();
     }
     int t = __builtin_amdgcn_readfirstlane(W > 1 ? s_ticket[1] : nxt);
     for (int buf = 0; t < n_tasks; buf ^= 1) {
-        if (threadIdx.x == 0) nxt = atomicAdd(ticket, 1);               // arrives while this task is worked on
         const Task T = decode(t);
         if (wave < T.C) request(T, wave);
-        const int64_t col = (int64_t)T.ct * 16 + j16;
+        const int64_t col = (int64_t)T.ct * 16 + j16, rcol = (int64_t)T.ct * 16 + rj;
 
-        float lown[TPW][4], Rrow = 0.0f;                                // backward: the rows' own log-probabilities, R of their block
+        float lown[TPW][VL], Rrow = 0.0f;                               // backward: the rows' own log-probabilities, R of their block
         if (BWD) {
 #pragma unroll
-            for (int k = 0; k < TPW; ++k) {
-                const int rt = wave + W * k < RT ? wave + W * k : 0;
+            for (int k = 0; k < TPW; ++k)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) lown[k][r] = l[(int64_t)(T.row0 + T.sub * TM + rt * 16 + 4 * g + r) * Bs + col];
-            }
+                for (int r = 0; r < VL; ++r) lown[k][r] = l[(int64_t)(T.row0 + T.sub * TM + (rt0 + k) * 16 + rr + r) * Bs + rcol];
             Rrow = R[(int64_t)(T.row0 >> ks) * Bs + col];
         }
 
@@ -297,10 +327,12 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 
         for (int cb = wave; cb < T.C;) {
             // Values: the sum of the list items' rows (forward: log-probabilities; backward: flows).  One item of every chunk's
-            // list at a time, the null block past its end: a branch around a load makes the compiler wait for all before it.
-            int max_cnt = 0, since = 0;
+            // list at a time, the null block where a list has none: a branch around a load makes the compiler wait for all before it.
+            int max_pre = 0, max_wait = 0, max_cnt = 0, since = 0;
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
+                max_pre = max(max_pre, pre[i]);
+                max_wait = max(max_wait, cnt[i] - pre[i]);
                 max_cnt = max(max_cnt, cnt[i]);
                 if (BWD) base[i] = Rrow - base[i];
             }
@@ -348,56 +380,62 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                 }
                 if (!BWD && !exact && (++since & 3) == 3) settle();
             };
-            for (int n = 1; n < max_cnt; ++n) {                         // items of earlier launches (the first: requested before)
-                int32_t its[NCH];
-                int any = 0;
-#pragma unroll
-                for (int i = 0; i < NCH; ++i) its[i] = item(i, n, false, any);
-                if (!any) continue;
+            for (int n = 1; n < max_pre; ++n) {                         // items of earlier launches (the first: requested before)
                 floatx4 x[NCH][2];
                 float xr[NCH];
 #pragma unroll
                 for (int i = 0; i < NCH; ++i) {
-                    row_values(BWD ? F : l, its[i], i, col, x[i]);
-                    if (!BWD) xr[i] = R[(int64_t)(its[i] >> ks) * Bs + col];
+                    const int32_t it = n < pre[i] ? item(i, n) : 0;
+                    row_values(BWD ? F : l, it, i, col, x[i]);
+                    if (!BWD) xr[i] = R[(int64_t)(it >> ks) * Bs + col];
                 }
                 add_item(x, xr);
             }
-            for (int n = 0; n < max_cnt; ++n) {                         // items of this launch: poll until they are there
-                int32_t its[NCH];
-                int any = 0;
+            // Items of this launch: poll until they are there.  The chunks' lists end together; the words of the next items are requested
+            // before the poll.
+            int32_t its[NCH];
+            auto items_from_end = [&](int w) {
 #pragma unroll
-                for (int i = 0; i < NCH; ++i) its[i] = item(i, n, true, any);
-                if (!any) continue;
+                for (int i = 0; i < NCH; ++i) its[i] = w >= 0 && cnt[i] - 1 - w >= pre[i] ? item(i, cnt[i] - 1 - w) : 0;
+            };
+            items_from_end(max_wait - 1);
+            for (int w = max_wait - 1; w >= 0; --w) {
                 floatx4 x[NCH][2];
                 float xr[NCH];
+                const float *src[NCH], *rsrc[NCH];
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) {
+                    src[i] = mail + (int64_t)(its[i] + koff[i]) * Bs + (int64_t)T.ct * 256;
+                    rsrc[i] = R + (int64_t)(its[i] >> ks) * Bs + col;
+                }
+                items_from_end(w - 1);
+                bool lost = false;
                 for (int spin = 0;; ++spin) {
                     asm volatile("" ::: "memory");
-                    int missing = 0;
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
-                        const float *src = mail + (int64_t)(its[i] + koff[i]) * Bs + (int64_t)T.ct * 256;
-                        x[i][0] = mail_load(src, 16 * lane);
-                        x[i][1] = mail_load(src + 16 * Bs, 16 * lane);
-                        if (!BWD) xr[i] = flow_load(R + (int64_t)(its[i] >> ks) * Bs + col);
+                        x[i][0] = mail_load(src[i], 16 * lane);
+                        x[i][1] = mail_load(src[i] + 16 * Bs, 16 * lane);
+                        if (!BWD) xr[i] = flow_load(rsrc[i]);
                     }
+                    uint32_t most = 0;                                  // the sentinel is the largest word
 #pragma unroll
                     for (int i = 0; i < NCH; ++i) {
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) missing |= is_sentinel(x[i][k >> 2][k & 3]);
-                        if (!BWD) missing |= is_sentinel(xr[i]);
+                        for (int k = 0; k < 8; ++k) most = max(most, __builtin_bit_cast(uint32_t, x[i][k >> 2][k & 3]));
+                        if (!BWD) most = max(most, __builtin_bit_cast(uint32_t, xr[i]));
                     }
-                    if (!__any(missing)) break;
-                    if (flow_give_up(spin, wait_limit, ticket, fault)) {    // NaN in all its results (a factor 0 below keeps it)
-#pragma unroll
-                        for (int i = 0; i < NCH; ++i)
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) x[i][k >> 2][k & 3] = __builtin_nanf("");
-                        break;
-                    }
+                    if (!__any(most == PC_SENTINEL)) break;
+                    if (flow_give_up(spin, wait_limit, ticket, fault)) { lost = true; break; }
                     __builtin_amdgcn_s_sleep(1);
                 }
                 add_item(x, xr);
+                if (lost) {                                             // NaN in all its results (a factor 0 below keeps it)
+#pragma unroll
+                    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) v[i][k >> 2][k & 3] = __builtin_nanf("");
+                }
             }
             if (exact) {
                 settle();
@@ -456,38 +494,47 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
             cb += W * NCH;
             if (cb < T.C) request(T, cb);
         }
-        // the waves' partial sums meet in LDS; tile rt goes to wave rt % W
-        if (W > 1) {
+        // The next ticket, drawn where nothing of this task waits for memory any more.  Drawn at the task's beginning, every
+        // workgroup held two tickets that could lie anything from one task to two grids apart, and some had the very next layer's
+        // behind a task they still worked on (HMM T = 32, H = 512, B = 77: the last weights of a layer arrived 1.7 us after its
+        // values, 4.8 us a layer; now 3.5); drawn between values and MFMAs it kept the MFMAs waiting (HMM 16 x 32, one sample 29 -> 34 us).
+        nxt = draw();
+        if (W > 1) {                                                    // the waves' partial sums meet in LDS
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) part[buf][wave][rt][lane] = acc[rt];
             if (g == 0) pref[buf][wave][j16] = ref;
-            if (threadIdx.x == 0) s_ticket[buf] = nxt;
             __syncthreads();
         }
-        t = __builtin_amdgcn_readfirstlane(W > 1 ? s_ticket[buf] : nxt);
 #pragma unroll
         for (int k = 0; k < TPW; ++k) {
-            const int rt = wave + W * k;
-            if (rt >= RT) break;                                        // wave-uniform
-            float top = PC_NEG_INF;
-            floatx4 tot = {0.f, 0.f, 0.f, 0.f}, val;
+            if (W > RW && wave >= RW) break;                            // wave-uniform
+            const int rt = rt0 + k;
+            float top = PC_NEG_INF, tot[VL], val[VL];
             if (W == 1) {
                 top = ref;
-                tot = acc[k];
-            } else {
-                float rw[W];
 #pragma unroll
-                for (int w = 0; w < W; ++w) { rw[w] = pref[buf][w][j16]; top = fmaxf(top, rw[w]); }
+                for (int r = 0; r < VL; ++r) tot[r] = acc[k][r];
+            } else {
+                typedef typename FloatVec<VL>::type Share;
+                float rw[W];
+                Share pw[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) rw[w] = pref[buf][w][rj];
+#pragma unroll
+                for (int w = 0; w < W; ++w) pw[w] = *reinterpret_cast<const Share *>(reinterpret_cast<const float *>(part[buf][w][rt]) + word0);
+#pragma unroll
+                for (int w = 0; w < W; ++w) top = fmaxf(top, rw[w]);
+#pragma unroll
+                for (int r = 0; r < VL; ++r) tot[r] = 0.0f;
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
                     const float sc = rw[w] > PC_NEG_INF ? pc_half_scale(rw[w] - top) : 0.0f;
-                    const floatx4 pw = part[buf][w][rt][lane];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) tot[r] += pw[r] * sc * sc;
+                    for (int r = 0; r < VL; ++r) tot[r] += reinterpret_cast<const float *>(&pw[w])[r] * sc * sc;
                 }
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < VL; ++r) {
                 if (BWD) {
                     // exp(ln(sum) + (ref - PC_UP) + l_row); sum = 0 or l_row = -inf gives exp2(-inf) = 0
                     const float add = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(tot[r]) + (lown[k][r] + (top - PC_UP)) * PC_LOG2E);
@@ -499,18 +546,21 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
                 }
             }
             const int rrow = T.sub * TM + rt * 16;
-            const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(mail + (int64_t)(T.row0 + rrow) * Bs + (int64_t)T.ct * 256), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, val), rm, 16 * lane, 0, PC_AUX_DEVICE);
-            if (!BWD && rrow == 0 && g == 0) {
+            mail_store<VL>(mail + (int64_t)(T.row0 + rrow) * Bs + (int64_t)T.ct * 256, 4 * word0, val);
+            if (!BWD && rrow == 0 && rr == 0) {
                 const float rs = top > PC_NEG_INF ? top : 0.0f;         // all children dead: any finite reference
-                __hip_atomic_store(R + (int64_t)(T.row0 >> ks) * Bs + col, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (T.root && col < B) ll[col] = rs + val[0];
+                __hip_atomic_store(R + (int64_t)(T.row0 >> ks) * Bs + rcol, rs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (T.root && rcol < B) ll[rcol] = rs + val[0];
             }
-            float *out = (BWD ? F : l) + (int64_t)(T.row0 + rrow + 4 * g) * Bs + col;
+            float *out = (BWD ? F : l) + (int64_t)(T.row0 + rrow + rr) * Bs + rcol;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) out[(int64_t)r * Bs] = val[r];
+            for (int r = 0; r < VL; ++r) out[(int64_t)r * Bs] = val[r];
         }
+        if (W > 1) {
+            if (threadIdx.x == 0) s_ticket[buf] = nxt;
+            __syncthreads();
+        }
+        t = __builtin_amdgcn_readfirstlane(W > 1 ? s_ticket[buf] : nxt);
     }
 }
 
@@ -540,14 +590,15 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
     if (f.n_ent == 0) return;
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
     // As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
-    // 16 x 32 states); row tiles of 32 halve the number of tasks that read a neighbour and win from 64 tasks per layer on, tiles
-    // of 16 leave a shorter chain before.  Measured with 1 - 16 waves, 16 - 64 rows, 16 and 32 columns, 1 - 4 chunks at once: 32
-    // columns lost everywhere, 64 rows won 1 - 2 % on 128- and 256-state trees and lost elsewhere.
-    // Workgroups: enough to hold a layer's tasks and the next ones' operands; those beyond that only poll.  256 / 320 / 512 measured:
-    // eight waves (one workgroup per CU is 256) HMM T = 60, H = 1024, B = 20 1110 / 1133 / 1189 us, T = 32, H = 512, B = 77 385 / 404 /
-    // 394; one and two waves, trees of 800 variables, M = 32 259 / 256 / 260 (with 2048: 297) and 500 variables 266 / 267 / 273, HMM
-    // T = 50, H = 64, B = 400 277 / 281 / 290, 784 variables, M = 64 722 / 721 / 729; four waves, M = 128, B = 512 1714 / 1719 / 1704.
-    // Below 256 all of them lose (784 variables, M = 64 at 192: 749).
+    // 16 x 32 states); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
+    // us two at a time, 324 four; fewer waves with two chunks each lost everywhere but on a 3072-variable tree's forward pass, 2587 ->
+    // 2502).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
+    // the widest layer has at most 128 tasks of them, 16 -> 32: HMM T = 60, H = 1024, B = 20 (128 tasks) 281 -> 324 us, T = 40, H = 256, B =
+    // 10 (32) 90 -> 100, T = 50, H = 64, B = 400 (104) 98 -> 101; T = 32, H = 512, B = 77 (192) 131 -> 126, trees (thousands in their lower
+    // layers) of 784 variables, M = 128, B = 512 788 -> 650, of 500, M = 64, B = 30 120 -> 114.  64 rows and 32 columns lost.
+    // Workgroups: enough to hold a layer's tasks and the next ones' operands; those beyond that only poll.  256 / 512 measured: eight waves
+    // (one workgroup per CU is 256) HMM T = 32, H = 512, B = 77 126 / 154 us, T = 40, H = 256, B = 10 90 / 98; one and two waves, trees of
+    // 800 variables, M = 32, B = 300 166 / 167, HMM T = 50, H = 64, B = 400 98 / 101; four waves, trees, no difference.
     const int chunks = f.max_nbr * (K / 32);
 #define PC_FLOW(WW, RR, HH)                                                                                                  \
     do {                                                                                                                     \
@@ -561,13 +612,14 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
         else hipLaunchKernelGGL((k_flow<WW, RR, HH, false, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                 f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);                   \
     } while (0)
-    if (chunks == 1) {
-        if ((int64_t)f.n_ent * (K / 16) * (Bs / 16) >= 64 * (int64_t)f.n_levels) PC_FLOW(1, 2, 1);
-        else PC_FLOW(1, 1, 1);
-    } else if (chunks == 2) PC_FLOW(2, 2, 1);
-    else if (chunks <= 4) PC_FLOW(4, 2, 1);
-    else if (chunks <= 8) PC_FLOW(8, 2, 1);
-    else PC_FLOW(8, 2, 2);
+#define PC_FLOW_ROWS(WW, HH) do { if (f.max_level * (int64_t)(K / 16) * (Bs / 16) <= 128) PC_FLOW(WW, 1, HH); else PC_FLOW(WW, 2, HH); } while (0)
+    if (chunks == 1) PC_FLOW_ROWS(1, 1);
+    else if (chunks == 2) PC_FLOW_ROWS(2, 1);
+    else if (chunks <= 4) PC_FLOW_ROWS(4, 1);
+    else if (chunks <= 8) PC_FLOW_ROWS(8, 1);
+    else if (chunks <= 16) PC_FLOW_ROWS(8, 2);
+    else PC_FLOW_ROWS(8, 4);
+#undef PC_FLOW_ROWS
 #undef PC_FLOW
 }
 

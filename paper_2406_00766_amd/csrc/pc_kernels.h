@@ -36,7 +36,7 @@ struct ParamFlowDev {        // parameter blocks with the (sum block, child bloc
 
 struct FlowDev {             // a dataflow launch (pc_flow.hip): entries from layer li0 to the root
     const int32_t *ent, *rec, *list;
-    int32_t n_ent, max_nbr, li0, n_levels;
+    int32_t n_ent, max_nbr, li0, max_level; // max_level: entries of the widest layer
     int32_t max_items;       // forward: most children of a product block that is read
 };
 

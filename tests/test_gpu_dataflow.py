@@ -43,6 +43,20 @@ def test_dataflow_layers_match_oracle(make):
     c.close()
 
 
+@pytest.mark.parametrize("K,H,B", [
+    (64, 64, 512), (64, 64, 513),                              # two chunks: 128 tasks of 16 rows in a layer, then 32 rows
+    (32, 128, 256), (32, 128, 257),                            # four chunks
+    (64, 256, 128), (64, 256, 129),                            # eight
+    (64, 512, 64), (64, 512, 65),                              # sixteen: two per wave
+    (128, 640, 16), (128, 640, 65),                            # twenty: up to four per wave
+])
+def test_tile_shapes_match_oracle(K, H, B):
+    """HMMs on both sides of the line between row tiles of 16 and 32, for every number of waves and chunks per wave."""
+    w = W.hmm(4, H, 30, K, B, 90, alpha_trans=0.2)
+    print(f"case tile shape K={K} H={H} B={B}", flush=True)
+    check_all(w)
+
+
 class Dag(W._Builder):
     """Block DAGs written out by hand: every edge of a sum block has a parameter block of its own."""
     n_params = 0
