@@ -1227,7 +1227,7 @@ __global__ __launch_bounds__(256) void k_param_flow_16(const float *__restrict__
 // per block).  Partial sums of the SPLIT waves are merged through LDS at the end.  No lane-dependent
 // branch surrounds an MFMA.
 template <int K, int RT, int SPLIT, bool BWD, bool MULTI, int MODE>
-__global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ theta, float *__restrict__ l,
+__global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) void k_sum_mfma(const float *__restrict__ theta, float *__restrict__ l,
                                                      float *__restrict__ R, const float *__restrict__ N,
                                                      const float *__restrict__ nfmax, float *__restrict__ F,
                                                      const GroupSet gs, int64_t Bs)
@@ -1237,14 +1237,16 @@ __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ t
     constexpr int SUB = K / TM;
     constexpr int NQ = KC / 2;                                          // MFMA steps per chunk
     constexpr int CPB = K / KC;                                         // chunks per neighbour block
-    constexpr int NCT = 4 / SPLIT;                                      // column tiles per workgroup
+    constexpr int WAVES = SPLIT > 4 ? SPLIT : 4;
+    constexpr int NCT = WAVES / SPLIT;                                  // column tiles per workgroup
+    constexpr int ES = RT * 16 / SPLIT;                                 // results per lane that a wave writes
     constexpr int NF4 = TM * KC / 4 / 64;                               // forward: 16-byte loads per lane per chunk
     constexpr int LDA = KC + 4;                                         // LDS row stride (floats): b128 reads conflict-free
     constexpr int TILE = BWD ? 0 : TM * LDA;                            // the backward kernel stages nothing
     constexpr int XCH = RT * 16 * 64 + 128;                             // one partial accumulator, its maxima and references
     constexpr int WSZ = TILE > XCH ? TILE : XCH;
-    static_assert(K % TM == 0 && (SPLIT == 1 || SPLIT == 2 || SPLIT == 4), "tile shape");
-    __shared__ float lds[4 * WSZ];
+    static_assert(K % TM == 0 && ES * SPLIT == RT * 16, "tile shape");
+    __shared__ float lds[WAVES * WSZ];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
@@ -1277,18 +1279,16 @@ __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ t
     // behind the whole reduction (short reductions are latency-bound)
     // (the tile's rows through one buffer descriptor at its first row: per-lane offset = rows 4 * half + (0..3) of a
     // group of 8 rows and the column, scalar offset per row -- no per-element address arithmetic)
-    floatx16 lown[BWD ? RT : 1];
+    // (a wave's results are the elements sp * ES, sp * ES + 1, ... of its tile's accumulators)
+    auto row_off = [&](int q) { return __builtin_amdgcn_readfirstlane((int)((int64_t)(q / 16 * 32 + 8 * (q % 16 / 4) + q % 4) * Bs * 4)); };
+    float lown[BWD ? ES : 1];
     const int ooff = (int)(((int64_t)(4 * half) * Bs + col) * 4);
     if (BWD) {
         const __amdgpu_buffer_rsrc_t rl =
             __builtin_amdgcn_make_buffer_rsrc((void *)(l + (int64_t)(id + sub * TM) * Bs), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int so = __builtin_amdgcn_readfirstlane((int)((int64_t)(rt * 32 + 8 * (e / 4) + (e % 4)) * Bs * 4));
-                lown[rt][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, ooff, so, 0));
-            }
+        for (int k = 0; k < ES; ++k)
+            lown[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, ooff, row_off(sp * ES + k), 0));
     }
 
     // Operands of one chunk: `ar` the MFMA A operands (theta), `v` the neighbour values with their block scalars;
@@ -1427,41 +1427,44 @@ __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ t
         if (c < n_chunks) run_chunk(oa);
     }
 
-    if (SPLIT > 1) {                                                    // merge the partial sums of the SPLIT waves of a tile
+    // Merge of the SPLIT waves' partial sums: each takes its share of the elements from all of them, and writes them.
+    float res[ES];
+    if (SPLIT == 1) {
+#pragma unroll
+        for (int q = 0; q < ES; ++q) res[q] = acc[q / 16][q % 16];
+    } else {
+#pragma unroll
+        for (int q = 0; q < RT * 16; ++q) buf[q * 64 + lane] = acc[q / 16][q % 16];   // (the wave's own staging tile until now)
+        buf[RT * 16 * 64 + lane] = m;
+        if (!BWD) buf[RT * 16 * 64 + 64 + lane] = Rrow;
         __syncthreads();
-        if (sp != 0) {
+        const float *part = lds + ct * SPLIT * WSZ;
+        float sc[SPLIT], Ro[BWD ? 1 : SPLIT];
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) buf[(rt * 16 + e) * 64 + lane] = acc[rt][e];
-            buf[RT * 16 * 64 + lane] = m;
-            if (!BWD) buf[RT * 16 * 64 + 64 + lane] = Rrow;
+        for (int s = 0; s < SPLIT; ++s) {
+            sc[s] = part[s * WSZ + RT * 16 * 64 + lane];
+            if (!BWD) Ro[BWD ? 0 : s] = part[s * WSZ + RT * 16 * 64 + 64 + lane];   // -inf: that wave had no chunk (its sum is 0)
         }
-        __syncthreads();
-        if (sp != 0) return;
-#pragma unroll 1                                                        // unrolled, the loads of all partners are hoisted: 45 registers
-        for (int s = 1; s < SPLIT; ++s) {
-            const float *ob = lds + (wave + s) * WSZ;
-            float mo = ob[RT * 16 * 64 + lane];
-            if (!BWD) {                                                 // bring both partial sums to the larger reference
-                const float Ro = ob[RT * 16 * 64 + 64 + lane];          // -inf: that wave had no chunk (its sum is 0)
-                const float Rn = fmaxf(Rrow, Ro);
-                m += Rrow - Rn;
-                mo = Ro > PC_NEG_INF ? mo + (Ro - Rn) : PC_NEG_INF;
-                Rrow = Rn;
-            }
-            const float m_new = fmaxf(m, mo);
-            const bool dead = !(m_new > PC_NEG_INF);
-            const float s0 = dead ? 1.0f : pc_half_scale(m - m_new), s1 = dead ? 0.0f : pc_half_scale(mo - m_new);
+        if (!BWD) {                                                     // all partial sums to the largest reference
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+            for (int s = 0; s < SPLIT; ++s) Rrow = fmaxf(Rrow, Ro[BWD ? 0 : s]);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[rt][e] = acc[rt][e] * s0 * s0 + ob[(rt * 16 + e) * 64 + lane] * s1 * s1;
-            m = m_new;
+            for (int s = 0; s < SPLIT; ++s) sc[s] = Ro[BWD ? 0 : s] > PC_NEG_INF ? sc[s] + (Ro[BWD ? 0 : s] - Rrow) : PC_NEG_INF;
+        }
+#pragma unroll
+        for (int s = 0; s < SPLIT; ++s) m = fmaxf(s == 0 ? sc[0] : m, sc[s]);
+        const bool dead = !(m > PC_NEG_INF);
+#pragma unroll
+        for (int k = 0; k < ES; ++k) res[k] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < SPLIT; ++s) {
+            const float h = dead ? 0.0f : pc_half_scale(sc[s] - m);
+#pragma unroll
+            for (int k = 0; k < ES; ++k) res[k] += part[s * WSZ + (sp * ES + k) * 64 + lane] * h * h;
         }
     }
     if (!active) return;
-    if (!BWD && sub == 0 && half == 0) R[(int64_t)(id / K) * Bs + col] = Rrow;
+    if (!BWD && sub == 0 && sp == 0 && half == 0) R[(int64_t)(id / K) * Bs + col] = Rrow;
     // Results out.  The rows are addressed through one buffer descriptor at the tile's first row with a scalar offset
     // per row.  Backward: log and exp are the hardware's base-2 instructions (the accumulator of a column with any
     // term is a normal number -- the largest term is at least FLT_MIN * e^PC_UP -- so no denormal care is needed).
@@ -1470,31 +1473,29 @@ __global__ __launch_bounds__(256, 2) void k_sum_mfma(const float *__restrict__ t
         __builtin_amdgcn_make_buffer_rsrc((void *)(out + (int64_t)(id + sub * TM) * Bs), 0, PC_BUF_RANGE, PC_BUF_FLAGS);
     const float mb = (m - PC_UP) * PC_LOG2E;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int so = __builtin_amdgcn_readfirstlane((int)((int64_t)(rt * 32 + 8 * (e / 4) + (e % 4)) * Bs * 4));
-            const float a = acc[rt][e];
-            if (BWD) {
-                const float lg = __builtin_amdgcn_logf(a);              // log2; a = 0 -> -inf
-                const float lc = lown[rt][e];
-                // exp(ln a + (m - PC_UP) + lc); a = 0 or lc = -inf gives exp2(-inf) = 0
-                const float add = __builtin_amdgcn_exp2f(lg + fmaf(lc, PC_LOG2E, mb));
-                if (first) {
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, add), ro, ooff, so, 0);
-                } else if (add > 0.0f) {
-                    const float old = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ro, ooff, so, 0));
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, old + add), ro, ooff, so, 0);
-                }
-            } else {
-                // ln a + (m - PC_UP), with the logarithm taken of a / 2^24: the accumulator of a live column is around
-                // e^PC_UP, and a base-2 logarithm near 0 is far more accurate in absolute terms than one near 29 --
-                // these errors add up from layer to layer (a log-likelihood near 0 has an absolute tolerance of 1e-5).
-                // a = 0: -inf.  (a >= FLT_MIN * e^PC_UP > 2^-98, so a / 2^24 is a normal number.)
-                const float v = fmaf(__builtin_amdgcn_logf(a * 0x1p-24f), 0.6931471805599453f, m + (16.635532333f - PC_UP));
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ro, ooff, so, 0);
+    for (int k = 0; k < ES; ++k) {
+        const int so = row_off(sp * ES + k);
+        const float a = res[k];
+        if (BWD) {
+            const float lg = __builtin_amdgcn_logf(a);                  // log2; a = 0 -> -inf
+            const float lc = lown[k];
+            // exp(ln a + (m - PC_UP) + lc); a = 0 or lc = -inf gives exp2(-inf) = 0
+            const float add = __builtin_amdgcn_exp2f(lg + fmaf(lc, PC_LOG2E, mb));
+            if (first) {
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, add), ro, ooff, so, 0);
+            } else if (add > 0.0f) {
+                const float old = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ro, ooff, so, 0));
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, old + add), ro, ooff, so, 0);
             }
+        } else {
+            // ln a + (m - PC_UP), with the logarithm taken of a / 2^24: the accumulator of a live column is around
+            // e^PC_UP, and a base-2 logarithm near 0 is far more accurate in absolute terms than one near 29 --
+            // these errors add up from layer to layer (a log-likelihood near 0 has an absolute tolerance of 1e-5).
+            // a = 0: -inf.  (a >= FLT_MIN * e^PC_UP > 2^-98, so a / 2^24 is a normal number.)
+            const float v = fmaf(__builtin_amdgcn_logf(a * 0x1p-24f), 0.6931471805599453f, m + (16.635532333f - PC_UP));
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ro, ooff, so, 0);
         }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2658,8 +2659,18 @@ void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, floa
         else hipLaunchKernelGGL((k_sum_mfma<KK, RR, SS, BWD, false, 0>), __VA_ARGS__);                     \
         break;                                                                                             \
     }
+// eight or sixteen waves to a tile: rows of 32 (pick_sum_shape), a register budget without a second operand set at sixteen
+#define PC_SUM_WIDE(KK, SS, BWD, ...)                                                                      \
+    if (K == KK && rt == 1 && split == SS) {                                                               \
+        if (gs.n > 1) hipLaunchKernelGGL((k_sum_mfma<KK, 1, SS, BWD, true, 0>), __VA_ARGS__);              \
+        else if (SS == 8 && prefetch) hipLaunchKernelGGL((k_sum_mfma<KK, 1, SS, BWD, false, SS == 8 ? 1 : 0>), __VA_ARGS__); \
+        else hipLaunchKernelGGL((k_sum_mfma<KK, 1, SS, BWD, false, 0>), __VA_ARGS__);                      \
+        break;                                                                                             \
+    }
 #define PC_DISPATCH_SUM(BWD, ...)                                                                         \
     do {                                                                                                  \
+        PC_SUM_WIDE(32, 8, BWD, __VA_ARGS__) PC_SUM_WIDE(64, 8, BWD, __VA_ARGS__) PC_SUM_WIDE(128, 8, BWD, __VA_ARGS__)            \
+        PC_SUM_WIDE(32, 16, BWD, __VA_ARGS__) PC_SUM_WIDE(64, 16, BWD, __VA_ARGS__) PC_SUM_WIDE(128, 16, BWD, __VA_ARGS__)         \
         PC_SUM_CASE(32, 1, 1, BWD, __VA_ARGS__) PC_SUM_CASE(32, 1, 2, BWD, __VA_ARGS__) PC_SUM_CASE(32, 1, 4, BWD, __VA_ARGS__)    \
         PC_SUM_CASE(64, 1, 1, BWD, __VA_ARGS__) PC_SUM_CASE(64, 1, 2, BWD, __VA_ARGS__) PC_SUM_CASE(64, 1, 4, BWD, __VA_ARGS__)    \
         PC_SUM_CASE(64, 2, 1, BWD, __VA_ARGS__) PC_SUM_CASE(64, 2, 2, BWD, __VA_ARGS__) PC_SUM_CASE(64, 2, 4, BWD, __VA_ARGS__)    \
@@ -2669,7 +2680,11 @@ void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, floa
 
 // Tile shape for the forward / backward-to-children kernel: the largest row tile (least exp work and
 // neighbour traffic per flop) that still leaves two waves per SIMD (2048 waves on 256 CUs), splitting
-// the reduction over up to four waves when rows x columns alone are too few.
+// the reduction over up to four waves when rows x columns alone are too few, and over eight or sixteen where each still has
+// two chunks: a wave has one or two chunks in flight, 1.2 us of latency each (a RAT-SPN's root over 256 blocks of 32 nodes, one tile:
+// 79 us with four waves).  Four -> up to sixteen: HMM H = 4096, B = 10, per layer forward 39 -> 28 us, backward 41 -> 27;
+// H = 3072 in blocks of 64, B = 40 31 -> 23, 32 -> 21; RAT-SPN of 784 variables, B = 16, forward pass 300 -> 251.  (Eight from one chunk a wave
+// on: PD of 5 x 5 cells, B = 100 106 -> 108 us.)
 static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs, int &rt, int &split)
 {
     const int64_t col_tiles = (Bs + 31) / 32;
@@ -2678,7 +2693,7 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
     while (rt > 1 && (int64_t)n_rows * (K / (32 * rt)) * col_tiles * 4 < want) rt >>= 1;
     const int64_t tiles = (int64_t)n_rows * (K / (32 * rt)) * col_tiles;
     split = 1;
-    while (split < 4 && tiles * split < want && (int64_t)width * (K / 32) >= 2 * split) split <<= 1;
+    while (split < (rt == 1 ? 16 : 4) && tiles * split < want && (int64_t)width * (K / 32) >= (split < 4 ? 2 : 4) * split) split <<= 1;
 }
 
 // K = 16, one group: forward (F null; X = l of the children) or backward to the children (X = log_nf).  The neighbours of a row
@@ -2703,13 +2718,14 @@ void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, co
             Timed timed(KC_SUM_FWD, s);
             int rt, split;
             pick_sum_shape(K, set_rows(gs), set_width(gs), Bs, rt, split);
-            const int64_t cols_per_wg = 32 * (4 / split);
+            const int waves = std::max(split, 4);
+            const int64_t cols_per_wg = 32 * (waves / split);
             dim3 grid((unsigned)(set_rows(gs) * (K / (32 * rt))), (unsigned)((Bs + cols_per_wg - 1) / cols_per_wg));
-            const bool prefetch = (int64_t)grid.x * grid.y * 4 <= 1024;    // at most one wave per SIMD
+            const bool prefetch = (int64_t)grid.x * grid.y * waves <= 1024;   // at most one wave per SIMD
             // long reductions at two waves per SIMD or fewer: see WAIT_ALL in the kernel
-            const bool wait_all = (int64_t)set_width(gs) * (K / 32) >= 16 * split && (int64_t)grid.x * grid.y * 4 <= 2048;
+            const bool wait_all = (int64_t)set_width(gs) * (K / 32) >= 16 * split && (int64_t)grid.x * grid.y * waves <= 2048;
             (void)wait_all;
-            PC_DISPATCH_SUM(false, grid, dim3(256), 0, s, theta, l, R, lch, (const float *)nullptr,
+            PC_DISPATCH_SUM(false, grid, dim3(64 * waves), 0, s, theta, l, R, lch, (const float *)nullptr,
                             (float *)nullptr, gs, Bs);
         }
         return;
@@ -2739,13 +2755,14 @@ void launch_sum_bwd_child(const float *theta, const float *l, const float *R, co
             Timed timed(KC_SUM_BWD_CHILD, s);
             int rt, split;
             pick_sum_shape(K, set_rows(gs), set_width(gs), Bs, rt, split);
-            const int64_t cols_per_wg = 32 * (4 / split);
+            const int waves = std::max(split, 4);
+            const int64_t cols_per_wg = 32 * (waves / split);
             dim3 grid((unsigned)(set_rows(gs) * (K / (32 * rt))), (unsigned)((Bs + cols_per_wg - 1) / cols_per_wg));
-            const bool prefetch = (int64_t)grid.x * grid.y * 4 <= 1024;    // at most one wave per SIMD
+            const bool prefetch = (int64_t)grid.x * grid.y * waves <= 1024;   // at most one wave per SIMD
             // long reductions at two waves per SIMD or fewer: see WAIT_ALL in the kernel
-            const bool wait_all = (int64_t)set_width(gs) * (K / 32) >= 16 * split && (int64_t)grid.x * grid.y * 4 <= 2048;
+            const bool wait_all = (int64_t)set_width(gs) * (K / 32) >= 16 * split && (int64_t)grid.x * grid.y * waves <= 2048;
             (void)wait_all;
-            PC_DISPATCH_SUM(true, grid, dim3(256), 0, s, theta, const_cast<float *>(l), const_cast<float *>(R), N, nfmax,
+            PC_DISPATCH_SUM(true, grid, dim3(64 * waves), 0, s, theta, const_cast<float *>(l), const_cast<float *>(R), N, nfmax,
                             F, gs, Bs);
         }
         return;
