@@ -116,11 +116,17 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
             add(&layer.d_pf_pb, layer.pf_pb); add(&layer.d_pf_ptr, layer.pf_ptr);
             add(&layer.d_pf_sum, layer.pf_sum); add(&layer.d_pf_child, layer.pf_child);
         }
+        if (!layer.cls_first.empty()) {
+            add(&layer.d_cls_ptr, layer.cls_ptr); add(&layer.d_cls_blk, layer.cls_blk); add(&layer.d_cls_first, layer.cls_first);
+            add(&layer.d_cls_par_ptr, layer.cls_par_ptr); add(&layer.d_cls_par, layer.cls_par);
+        }
+        if (!layer.tile.empty()) { add(&layer.d_tile, layer.tile); add(&layer.d_tile_order, layer.tile_order); }
     }
     add(&c->d_pb_rows, c->pb_rows); add(&c->d_pb_cols, c->pb_cols); add(&c->d_group_nch, c->group_nch);
     add(&c->d_em_ptr, c->em_ptr); add(&c->d_em_list, c->em_list);
     add(&c->d_em_seg_ptr, c->em_seg_ptr); add(&c->d_em_seg, c->em_seg);
     add(&c->d_init_ids, c->init_ids);
+    add(&c->d_flow_rep, c->flow_rep);
     add(&c->d_pf_pb, c->pf_pb); add(&c->d_pf_ptr, c->pf_ptr); add(&c->d_pf_sum, c->pf_sum); add(&c->d_pf_child, c->pf_child);
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { add(&f->d_ent, f->ent); add(&f->d_rec, f->rec); add(&f->d_list, f->list); }
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) {
@@ -267,6 +273,17 @@ static FlowDev flow_dev(const pc_circuit *c, const FlowTab &f, size_t li0, bool 
     const int32_t n = f.count_from[li0], first = suffix ? f.count_from[0] - n : 0;
     return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, max_level,
                    *std::max_element(c->max_items.begin() + li0, c->max_items.end())};
+}
+static int32_t max_width(const std::vector<GroupTab> &groups)
+{
+    int32_t w = 0;
+    for (const GroupTab &g : groups) w = std::max(w, g.width);
+    return w;
+}
+static ClassesDev classes_dev(const LayerTab &L)
+{
+    const int32_t n = (int32_t)L.cls_first.size();
+    return ClassesDev{n, (int32_t)L.cls_blk.size() / n, L.d_cls_ptr, L.d_cls_blk, L.d_cls_par_ptr, L.d_cls_par, L.d_cls_first};
 }
 static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)
 {
@@ -430,6 +447,8 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_INPUT) {
             launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, R, s);
+        } else if (L.kind == KIND_PRODUCT && !w.bf16 && !L.tile.empty() && prod_takes_tiles(K, (int32_t)L.blk_ids.size(), max_width(L.fwd), w.Bs)) {
+            launch_prod_fwd_tiles(l, R, L.d_tile, (int32_t)(L.tile.size() / PROD_TILE_WORDS), L.d_tile_order, L.d_cls_blk, K, w.Bs, s);
         } else if (L.kind == KIND_PRODUCT) {
             launch_prod_fwd(l, c->product_scratch ? window_base(c, L, l, w.Bs) : l, R, plan.layers[li].fwd, K, w.Bs,
                             w.bf16 ? base + w.ph_off : nullptr, w.bf16 ? base + w.pl_off : nullptr, s);
@@ -562,10 +581,14 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
             if (li + 1 == c->layers.size())
                 launch_fill(Fw + (int64_t)(L.scr_first_block + 1) * K * w.Bs, (int64_t)L.blk_ids.size() * K * w.Bs, 0.0f, s);
             launch_prod_bwd(l, F, Fw, N, nfmax, plan.layers[li].bwd, K, w.Bs, nullptr, nullptr, s);
+        } else if (L.kind == KIND_PRODUCT && !L.cls_first.empty()) {
+            launch_prod_bwd_classes(F, classes_dev(L), K, w.Bs, s);      // every child of the layer is an input block: no log_nf, no planes
         } else if (L.kind == KIND_PRODUCT) {
             launch_prod_bwd(l, F, F, N, nfmax, plan.layers[li].bwd, K, w.Bs, w.bf16 ? base + w.ph_off : nullptr, w.bf16 ? base + w.pl_off : nullptr, s);
         } else if (table_flow) {
-            launch_input_bwd(F, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, table_flow, s);
+            GroupDev g = dev(L.fwd[0]);
+            if (!c->flow_rep.empty()) g.ids = c->d_flow_rep;                    // blocks of equal flows: one set of rows stays in the caches
+            launch_input_bwd(F, xT, g, K, c->n_cats, w.Bs, table_flow, s);
         }
     }
     if (theta_flow && batched_params && !c->product_scratch) {

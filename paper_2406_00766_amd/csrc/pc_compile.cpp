@@ -11,6 +11,7 @@
 //     that holds its count; a row lists its neighbours by ascending node offset;
 //   * product layers get the same forward / backward table pair as sum layers.
 #include <algorithm>
+#include <array>
 #include <cstring>
 #include <limits>
 #include <map>
@@ -270,6 +271,145 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
     };
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) accumulate(f->count_from, f->max_nbr_from);
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) accumulate(r->count_from, r->max_nbr_from);
+}
+
+// Tiles of a product layer whose classes are there already (LayerTab::tile): the product blocks must be the pairs of classes of two
+// sets each, and the blocks of a pair's classes must alternate in the same order in every product of the sets.
+void compile_product_tiles(LayerTab &T, int32_t K, int32_t n)
+{
+    const int32_t n_cls = (int32_t)T.cls_first.size();
+    std::vector<std::array<int32_t, 2>> of_row(n, {-1, -1});                // product block -> its two classes
+    std::vector<std::vector<int32_t>> next(n_cls);
+    for (int32_t q = 0; q < n_cls; ++q)
+        for (int32_t k = T.cls_par_ptr[q]; k < T.cls_par_ptr[q + 1]; ++k) {
+            auto &two = of_row[T.cls_par[k] / K - 1];
+            if (two[1] >= 0) return;
+            two[two[0] < 0 ? 0 : 1] = q;
+        }
+    for (int32_t id : T.blk_ids) {
+        const auto &two = of_row[id / K - 1];
+        if (two[1] < 0) return;
+        next[two[0]].push_back(two[1]); next[two[1]].push_back(two[0]);
+    }
+    auto blocks = [&](int32_t q) { return T.cls_ptr[q + 1] - T.cls_ptr[q]; };
+    auto order_of = [&](int32_t qa, int32_t qb) {                            // a bit per block of the merged classes, 1: of the second
+        const int32_t na = blocks(qa), nb = blocks(qb);
+        std::vector<int32_t> bits((na + nb + 31) / 32, 0);
+        const int32_t *a = &T.cls_blk[T.cls_ptr[qa]], *b = &T.cls_blk[T.cls_ptr[qb]];
+        for (int32_t i = 0, j = 0; i + j < na + nb;) {
+            if (i < na && (j == nb || a[i] < b[j])) ++i;
+            else { bits[(i + j) >> 5] = (int32_t)((uint32_t)bits[(i + j) >> 5] | 1u << ((i + j) & 31)); ++j; }
+        }
+        return bits;
+    };
+    std::vector<int32_t> side(n_cls, -1), tile, order, row_at(n_cls, -1);
+    for (int32_t q0 = 0; q0 < n_cls; ++q0) {
+        if (side[q0] >= 0) continue;
+        std::vector<int32_t> set[2], todo(1, q0);                            // the component of q0, two-coloured
+        side[q0] = 0;
+        while (!todo.empty()) {
+            const int32_t q = todo.back();
+            todo.pop_back();
+            set[side[q]].push_back(q);
+            for (int32_t o : next[q]) {
+                if (side[o] == side[q]) return;
+                if (side[o] < 0) { side[o] = 1 - side[q]; todo.push_back(o); }
+            }
+        }
+        for (auto &v : set) std::sort(v.begin(), v.end());
+        if (set[1].empty()) return;
+        const std::vector<int32_t> bits = order_of(set[0][0], set[1][0]);
+        const int32_t n_pos = blocks(set[0][0]) + blocks(set[1][0]), at = (int32_t)order.size();
+        order.insert(order.end(), bits.begin(), bits.end());
+        const size_t first_tile = tile.size();
+        const int32_t ta = ((int32_t)set[0].size() + 3) / 4, tb = ((int32_t)set[1].size() + 3) / 4;
+        for (int32_t i = 0; i < ta; ++i)
+            for (int32_t j = 0; j < tb; ++j) {
+                std::vector<int32_t> w(PROD_TILE_WORDS, 0);
+                for (int32_t k = 0; k < 4; ++k) {                            // (past the end: the last class again, without a product)
+                    w[k] = T.cls_ptr[set[0][std::min<size_t>(4 * i + k, set[0].size() - 1)]];
+                    w[4 + k] = T.cls_ptr[set[1][std::min<size_t>(4 * j + k, set[1].size() - 1)]];
+                }
+                w[24] = at; w[25] = n_pos;
+                tile.insert(tile.end(), w.begin(), w.end());
+            }
+        for (auto &v : set) for (size_t k = 0; k < v.size(); ++k) row_at[v[k]] = (int32_t)k;
+        for (int32_t qa : set[0]) {
+            if (next[qa].size() != set[1].size()) return;
+            for (int32_t k = T.cls_par_ptr[qa]; k < T.cls_par_ptr[qa + 1]; ++k) {
+                const auto &two = of_row[T.cls_par[k] / K - 1];
+                const int32_t qb = two[0] == qa ? two[1] : two[0], i = row_at[qa], j = row_at[qb];
+                if (order_of(qa, qb) != bits || blocks(qa) + blocks(qb) != n_pos) return;
+                int32_t &at16 = tile[first_tile + PROD_TILE_WORDS * (size_t)(i / 4 * tb + j / 4) + 8 + 4 * (i % 4) + j % 4];
+                if (at16 != 0) return;                                       // two products of one pair
+                at16 = T.cls_par[k];
+            }
+        }
+    }
+    T.tile = std::move(tile);
+    T.tile_order = std::move(order);
+}
+
+// Classes of input blocks with equal product parents (LayerTab::cls_*), and the tiles of the products over them.
+void compile_classes(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &par_ptr, const std::vector<int32_t> &par_of)
+{
+    const int32_t n = d->n_blocks, K = d->K;
+    std::vector<int32_t> layer_of(n, 0), rep(n);
+    for (int32_t li = 0; li < (int32_t)c->layers.size(); ++li)
+        for (int32_t id : c->layers[li].blk_ids) layer_of[id / K - 1] = li;
+    for (int32_t u = 0; u < n; ++u) rep[u] = u;
+    std::vector<uint8_t> seen(n, 0);
+    for (int32_t li = 0; li < (int32_t)c->layers.size(); ++li) {
+        LayerTab &T = c->layers[li];
+        if (T.kind != KIND_PRODUCT) continue;
+        int64_t reads = 0;                                // block rows that the product kernels read
+        bool inputs_only = true;
+        std::vector<int32_t> members;
+        for (int32_t id : T.blk_ids) {
+            const int32_t u = id / K - 1;
+            reads += d->child_ptr[u + 1] - d->child_ptr[u];
+            for (int64_t e = d->child_ptr[u]; e < d->child_ptr[u + 1]; ++e) {
+                const int32_t ch = d->child[e];
+                inputs_only = inputs_only && d->type[ch] == KIND_INPUT;
+                if (!seen[ch]) { seen[ch] = 1; members.push_back(ch); }
+            }
+            if (!inputs_only) break;
+        }
+        for (int32_t u : members) seen[u] = 0;
+        if (!inputs_only || 2 * (int64_t)members.size() > reads) continue;
+        // blocks by their parents in this layer, then by BWD_FIRST; equal ones become neighbours (lists are ascending)
+        std::vector<std::pair<int32_t, int32_t>> par(n);  // block -> its parents' range in `at`
+        std::vector<int32_t> at;
+        for (int32_t u : members) {
+            par[u].first = (int32_t)at.size();
+            for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k)
+                if (layer_of[par_of[k]] == li) at.push_back((par_of[k] + 1) * K);
+            at.push_back(c->an_first_parent_depth[u] == T.depth ? -1 : -2);
+            par[u].second = (int32_t)at.size();
+        }
+        auto less = [&](int32_t a, int32_t b) {
+            return std::lexicographical_compare(at.begin() + par[a].first, at.begin() + par[a].second, at.begin() + par[b].first, at.begin() + par[b].second);
+        };
+        std::sort(members.begin(), members.end(), [&](int32_t a, int32_t b) { return less(a, b) || (a < b && !less(b, a)); });
+        T.cls_ptr.assign(1, 0); T.cls_par_ptr.assign(1, 0);
+        for (size_t k0 = 0, k1; k0 < members.size(); k0 = k1) {
+            const int32_t u0 = members[k0];
+            for (k1 = k0; k1 < members.size() && !less(u0, members[k1]); ++k1) {
+                T.cls_blk.push_back((members[k1] + 1) * K);
+                if (par_ptr[members[k1] + 1] - par_ptr[members[k1]] == par[u0].second - par[u0].first - 1) rep[members[k1]] = u0;
+            }
+            T.cls_ptr.push_back((int32_t)T.cls_blk.size());
+            T.cls_par.insert(T.cls_par.end(), at.begin() + par[u0].first, at.begin() + par[u0].second - 1);
+            T.cls_par_ptr.push_back((int32_t)T.cls_par.size());
+            T.cls_first.push_back(at[par[u0].second - 1] == -1 ? 1 : 0);
+        }
+        if (2 * T.cls_first.size() > members.size()) {    // too few blocks share their parents
+            T.cls_ptr.clear(); T.cls_par_ptr.clear(); T.cls_blk.clear(); T.cls_par.clear(); T.cls_first.clear();
+            continue;
+        }
+        compile_product_tiles(T, K, n);
+    }
+    for (int32_t id : c->layers[0].blk_ids) c->flow_rep.push_back((rep[id / K - 1] + 1) * K);
 }
 
 }  // namespace
@@ -639,6 +779,7 @@ pc_status compile_host(const pc_dag *d, pc_circuit *c, bool tables_on_host)
         c->pf_ptr.push_back((int32_t)c->pf_sum.size());
     }
     if (!c->product_scratch && (K == 32 || K == 64 || K == 128)) compile_flow(d, c, par_ptr, par_of, par_edge);
+    if (!c->product_scratch) compile_classes(d, c, par_ptr, par_of);
     return PC_OK;
 }
 

@@ -27,6 +27,10 @@ inline int32_t bwd_row_flags(int layer_kind, int child_kind, int32_t layer_depth
     return f;
 }
 
+// Words of a tile of products (LayerTab::tile): starts of the member lists of four classes of the first and four of the second
+// set; the node offsets of the 4 x 4 products, 0: none; start of the order's bits; children of a product.
+constexpr int PROD_TILE_WORDS = 32;
+
 // One group of a layer: rows padded to a common width (Sec. 4.3).
 struct GroupTab {
     int32_t n_rows = 0, width = 0;
@@ -46,6 +50,15 @@ struct LayerTab {
     int32_t scr_first_block = -1;                     // product layers: id of the first block of the layer
     std::vector<int32_t> pf_pb, pf_ptr, pf_sum, pf_child;
     int32_t *d_pf_pb = nullptr, *d_pf_ptr = nullptr, *d_pf_sum = nullptr, *d_pf_child = nullptr;
+    // Product layer over input blocks many of which have the same product parents here: its children by equal parents (and equal
+    // BWD_FIRST), so that the flow of a class is summed once and not once per block.  Empty where few do.
+    std::vector<int32_t> cls_ptr, cls_blk;            // class -> its input blocks (node offsets, ascending)
+    std::vector<int32_t> cls_par_ptr, cls_par, cls_first;   // class -> its product parents (node offsets, ascending); 1: the flow is stored
+    int32_t *d_cls_ptr = nullptr, *d_cls_blk = nullptr, *d_cls_par_ptr = nullptr, *d_cls_par = nullptr, *d_cls_first = nullptr;
+    // Such a layer whose product blocks are the pairs of two sets of classes each: tiles of up to 4 x 4 of them, PROD_TILE_WORDS words
+    // (k_prod_tile), and the order of the two classes' blocks in the products' rows, a bit per block.  Empty elsewhere.
+    std::vector<int32_t> tile, tile_order;
+    int32_t *d_tile = nullptr, *d_tile_order = nullptr;
 };
 
 // Tables of the dataflow launches (pc_flow.hip), for K = 32, 64, 128 and circuits that keep their product values.  Entries
@@ -94,6 +107,11 @@ struct pc_circuit {
     // node offsets; other blocks and the null block as ~offset
     std::vector<int32_t> init_ids;
     int32_t *d_init_ids = nullptr;
+
+    // per input block (in the order of the input layer): the block whose flow rows hold its flows as well -- the first of its class
+    // (LayerTab::cls_blk) where the class has all its parents, else itself
+    std::vector<int32_t> flow_rep;
+    int32_t *d_flow_rep = nullptr;
 
     // dataflow launches (empty where they do not apply)
     pc::FlowTab flow_fwd, flow_bwd;

@@ -45,6 +45,11 @@ struct RowsDev {             // product-layer rows of a dataflow launch as neigh
     int32_t n_rows, max_nbr, li0;
 };
 
+struct ClassesDev {          // input blocks in classes of equal product parents (LayerTab::cls_*)
+    int32_t n, avg;          // classes; blocks of one, on average
+    const int32_t *ptr, *blk, *par_ptr, *par, *first;
+};
+
 struct EmDev {               // row groups with their parameter blocks; those from n_groups on have no rows; segments of long rows
     int32_t n_groups, n_all, avg_list, n_seg;
     const int32_t *ptr, *list, *pb_rows, *pb_cols, *group_nch, *seg_ptr, *seg;
@@ -93,6 +98,11 @@ void launch_prod_fwd(const float *l, float *lout, float *R, const std::vector<Gr
 // Fpar: base the parents' flows are read from (= F, except in the product-scratch mode)
 void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, float *nfmax, const std::vector<GroupSet> &sets, int32_t K,
                      int64_t Bs, void *Ph, void *Pl, hipStream_t s);
+// Product layer over classes of input blocks: forward, tiles of products (LayerTab::tile); backward, a class's flow stored to its blocks
+bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs);   // width: most children of a product
+void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,
+                           int64_t Bs, hipStream_t s);
+void launch_prod_bwd_classes(float *F, const ClassesDev &c, int32_t K, int64_t Bs, hipStream_t s);
 // the product layers of a dataflow launch: all their rows in one launch
 void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, int64_t Bs, hipStream_t s);
 void launch_prod_bwd_rows(const float *l, float *F, float *N, float *nfmax, const RowsDev &rows, int32_t K, int64_t Bs, void *Ph,

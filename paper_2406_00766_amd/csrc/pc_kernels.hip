@@ -25,6 +25,7 @@
 #include <cstring>
 
 #include "pc_device.h"
+#include "pc_internal.h"
 #include "pc_kernels.h"
 
 namespace pc {
@@ -635,6 +636,154 @@ __global__ __launch_bounds__(256) void k_prod_bwd(const float *__restrict__ l, f
             const float top = ptile[128 * LDT + cw * 32 + (lane & 31)];
             split_value_rows(ptile + 16 * ks * LDT + cw * 32 + (lane & 31), LDT, top > PC_NEG_INF ? PC_UP - top : PC_NEG_INF,
                              (int64_t)id + 16 * ks, ct, n_ct, Ph, Pl, lane);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// product layers over input blocks in classes of equal parents (LayerTab::cls_*, ::tile)
+// ------------------------------------------------------------------------------------------
+// The leaf regions of a RAT-SPN: every product adds up the blocks of two classes (49 + 49), every class is added up by eight
+// products.  k_prod_fwd asks L2 for a block once per product (13 GB for 1.6 GB of rows at D = 784, B = 512, and L2 is what it
+// waits for).  Here a workgroup takes 4 x 4 products at once: at each place of the products' rows stand four blocks of the one or of
+// the other side's classes, each loaded once and added to the four products that have it.  The sums are those of k_prod_fwd to the
+// last bit -- four children in fp32, the fours in double, children ascending --; sums of a class taken once and added up by the
+// products would need two reads per product instead, but round differently, and three EM steps on the same batch turn
+// differences of 6e-5 in single weights into 3e-3.
+// D = 784, B = 512: 1.01 ms -> 0.43.  Thread (k, c): row k, two adjacent columns; C2 column pairs per workgroup, T x T products, in 128
+// registers for four waves per SIMD (0.57 ms with three).  The four tiles that share their classes run one
+// after another on one XCD (workgroup h runs on XCD h mod 8), for the blocks to be in its L2.
+template <int C2, int T>
+__global__ __launch_bounds__(512, 4) void k_prod_tile(float *__restrict__ l, float *__restrict__ R, const int32_t *tile_words, int32_t n_tiles,
+                                                   const int32_t *order_words, const int32_t *blk_words, int32_t K, int64_t Bs)
+{
+    typedef const int32_t __attribute__((address_space(4))) *TabPtr;       // (read as constants: scalar loads)
+    __shared__ float red[T * T][8][2 * C2];                                // [product][wave][column]
+    constexpr int U = 4;                                                // children of a round
+    constexpr int PARTS = 16 / (T * T);                                 // workgroups of a 4 x 4 tile
+    const int32_t n4 = (n_tiles * PARTS + 3) & ~3;
+    const int32_t h = (int32_t)blockIdx.x, q = h >> 3, m = ((q >> 2) * 8 + (h & 7)) * 4 + (q & 3);
+    const int32_t ti = m % n4 / PARTS, i0 = T * (m % n4 % PARTS / (4 / T)), j0 = T * (m % n4 % PARTS % (4 / T));
+    const int64_t b = (int64_t)(m / n4) * (2 * C2) + 2 * (threadIdx.x % C2);
+    if (ti >= n_tiles || (int64_t)(m / n4) * (2 * C2) >= Bs) return;    // the whole workgroup
+    const TabPtr tw = (TabPtr)(uintptr_t)tile_words + PROD_TILE_WORDS * (int64_t)ti, blk = (TabPtr)(uintptr_t)blk_words;
+    const TabPtr order = (TabPtr)(uintptr_t)order_words + tw[24];
+    const int k = threadIdx.x / C2, wave = threadIdx.x >> 6;
+    const int32_t n = tw[25];
+    double2 s[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) { s[i][j] = make_double2(0, 0); }
+    int32_t at_a = 0, at_b = 0, ids[U][T];
+    uint32_t sides = 0;
+    auto places = [&](int32_t p0) {                                     // the blocks at the places p0 .. p0 + U - 1 of the products' rows
+        sides = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool on = p0 + u < n;
+            const int sd = on ? (order[(p0 + u) >> 5] >> ((p0 + u) & 31)) & 1 : 0;
+#pragma unroll
+            for (int i = 0; i < T; ++i) ids[u][i] = on ? blk[sd ? tw[4 + j0 + i] + at_b : tw[i0 + i] + at_a] : 0;
+            at_b += on && sd; at_a += on && !sd;
+            sides |= (uint32_t)sd << u;
+        }
+    };
+    places(0);
+    for (int32_t p0 = 0; p0 < n; p0 += U) {
+        float2 y[U][T];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < T; ++i) y[u][i] = *reinterpret_cast<const float2 *>(l + (int64_t)(ids[u][i] + k) * Bs + b);
+        const uint32_t sides_now = sides;                               // (past the end: the null block's rows, 0)
+        places(p0 + U);
+        float2 part[T][T];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool sd = (sides_now >> u) & 1;                       // uniform
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) {
+                    const float2 x = sd ? y[u][j] : y[u][i];
+                    part[i][j].x = u == 0 ? x.x : part[i][j].x + x.x; part[i][j].y = u == 0 ? x.y : part[i][j].y + x.y;
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j) { s[i][j].x += (double)part[i][j].x; s[i][j].y += (double)part[i][j].y; }
+    }
+    // renormalise: the column maxima of a product's K rows
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+            float mx = (float)s[i][j].x, my = (float)s[i][j].y;
+#pragma unroll
+            for (int o = C2; o < 64; o <<= 1) { mx = fmaxf(mx, __shfl_xor(mx, o)); my = fmaxf(my, __shfl_xor(my, o)); }
+            if ((threadIdx.x & 63) < C2) { red[T * i + j][wave][2 * (threadIdx.x % C2)] = mx; red[T * i + j][wave][2 * (threadIdx.x % C2) + 1] = my; }
+        }
+    __syncthreads();
+    const int n_waves = (int)blockDim.x >> 6, c0 = 2 * (threadIdx.x % C2);
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+            const int32_t id = tw[8 + 4 * (i0 + i) + j0 + j];
+            if (id == 0) continue;
+            float mx = PC_NEG_INF, my = PC_NEG_INF;
+            for (int w = 0; w < n_waves; ++w) { mx = fmaxf(mx, red[T * i + j][w][c0]); my = fmaxf(my, red[T * i + j][w][c0 + 1]); }
+            mx = mx > PC_NEG_INF ? rintf(mx) : 0.0f;
+            my = my > PC_NEG_INF ? rintf(my) : 0.0f;
+            if (k == 0) *reinterpret_cast<float2 *>(R + (int64_t)(id / K) * Bs + b) = make_float2(mx, my);   // (R of input blocks is 0)
+            *reinterpret_cast<float2 *>(l + (int64_t)(id + k) * Bs + b) = make_float2((float)(s[i][j].x - (double)mx), (float)(s[i][j].y - (double)my));
+        }
+}
+
+// Backward, the flow that a class's blocks share is summed once and stored to each (0.49 -> 0.25 ms at D = 784, B = 512).  Workgroup = one
+// class x 4 CL columns as in k_prod_bwd; gridDim.z shares of the class's blocks, each of which sums the parents again (they are few).
+template <int RPT, int U, int CL>
+__global__ __launch_bounds__(256) void k_class_bwd(float *F, const ClassesDev c, int32_t K, int64_t Bs)
+{
+    constexpr int RG = 256 / CL;
+    const int rg = threadIdx.x / CL, cl = threadIdx.x % CL;
+    const int64_t b = (int64_t)blockIdx.y * (4 * CL) + cl * 4;
+    if (b >= Bs) return;
+    const int32_t p1 = c.par_ptr[blockIdx.x + 1];
+    float4 f[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) f[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int32_t p0 = c.par_ptr[blockIdx.x]; p0 < p1; p0 += U) {
+        float4 t[U][RPT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool on = p0 + u < p1;                               // uniform over the workgroup
+            const int32_t pa = on ? c.par[p0 + u] : 0;
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const int k = rg + RG * i;
+                t[u][i] = (on && k < K) ? *reinterpret_cast<const float4 *>(F + (int64_t)(pa + k) * Bs + b) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) { f[i].x += t[u][i].x; f[i].y += t[u][i].y; f[i].z += t[u][i].z; f[i].w += t[u][i].w; }
+    }
+    const bool first = c.first[blockIdx.x] != 0;
+    const int32_t j1 = c.ptr[blockIdx.x + 1];
+    for (int32_t j = c.ptr[blockIdx.x] + (int32_t)blockIdx.z; j < j1; j += (int32_t)gridDim.z) {
+        const int32_t id = c.blk[j];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int k = rg + RG * i;
+            if (k >= K) continue;
+            float4 *dst = reinterpret_cast<float4 *>(F + (int64_t)(id + k) * Bs + b);
+            float4 v = f[i];
+            if (!first) { const float4 old = *dst; v = make_float4(old.x + v.x, old.y + v.y, old.z + v.z, old.w + v.w); }
+            *dst = v;
         }
     }
 }
@@ -2611,6 +2760,50 @@ static GroupSet csr_set(const RowsDev &rows)
     gs.width[0] = rows.max_nbr; gs.width[1] = rows.li0;
     gs.ids[0] = rows.ids; gs.nbr[0] = rows.list; gs.nbr[1] = rows.lay; gs.par[0] = rows.start; gs.aux[0] = rows.aux;
     return gs;
+}
+
+#define PC_DISPATCH_CLASS(KERNEL, U, ...)                                                                  \
+    do {                                                                                                   \
+        if (narrow) {                                                                                      \
+            if (K <= 32) hipLaunchKernelGGL((KERNEL<1, U, 8>), __VA_ARGS__);                               \
+            else if (K <= 64) hipLaunchKernelGGL((KERNEL<2, U, 8>), __VA_ARGS__);                          \
+            else hipLaunchKernelGGL((KERNEL<4, U / 2, 8>), __VA_ARGS__);                                   \
+        } else if (K <= 16) hipLaunchKernelGGL((KERNEL<1, U, 16>), __VA_ARGS__);                           \
+        else if (K <= 32) hipLaunchKernelGGL((KERNEL<2, U, 16>), __VA_ARGS__);                             \
+        else if (K <= 64) hipLaunchKernelGGL((KERNEL<4, U / 2, 16>), __VA_ARGS__);                         \
+        else hipLaunchKernelGGL((KERNEL<8, U / 4, 16>), __VA_ARGS__);                                      \
+    } while (0)
+// Where k_prod_fwd sums rows of more than eight children in fours of fp32 and double beyond, in launches that fill the chip (a narrow one
+// takes eights at K = 32, and tiles would leave most CUs idle: RAT-SPN of 100 variables, B = 3, 38.5 -> 44 us).
+bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs)
+{
+    return (K == 32 || K == 64) && width > 8 && (int64_t)n_rows * ((Bs + 63) / 64) >= 1024;
+}
+
+// 2 x 2 products a workgroup where 4 x 4 would not give every CU two: RAT-SPN of 784 variables, forward pass at B = 16 251 us with k_prod_fwd,
+// 244 in 128 workgroups, 228 in 512.
+void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,
+                           int64_t Bs, hipStream_t s)
+{
+    Timed timed(KC_PROD_FWD, s);
+    const int64_t cols = K == 64 ? 16 : 32;
+    const bool small = (int64_t)n_tiles * (Bs / cols) < 512;
+    const int64_t wgs = (int64_t)((n_tiles * (small ? 4 : 1) + 3) & ~3) * (Bs / cols);
+    const dim3 grid((unsigned)((wgs + 31) / 32 * 32));
+#define PC_PROD_TILE(CC, TT) hipLaunchKernelGGL((k_prod_tile<CC, TT>), grid, dim3(512), 0, s, l, R, tile, n_tiles, order, cls_blk, K, Bs)
+    if (K == 64) { if (small) PC_PROD_TILE(8, 2); else PC_PROD_TILE(8, 4); }
+    else { if (small) PC_PROD_TILE(16, 2); else PC_PROD_TILE(16, 4); }
+#undef PC_PROD_TILE
+}
+
+void launch_prod_bwd_classes(float *F, const ClassesDev &c, int32_t K, int64_t Bs, hipStream_t s)
+{
+    Timed timed(KC_PROD_BWD, s);
+    const bool narrow = (int64_t)c.n * ((Bs + 63) / 64) < 1024;
+    const int64_t tiles = (int64_t)c.n * (narrow ? (Bs + 31) / 32 : (Bs + 63) / 64);
+    const int shares = (int)std::max<int64_t>(1, std::min<int64_t>(4096 / tiles, c.avg / 4));
+    dim3 grid((unsigned)c.n, (unsigned)(narrow ? (Bs + 31) / 32 : (Bs + 63) / 64), (unsigned)shares);
+    PC_DISPATCH_CLASS(k_class_bwd, 8, grid, dim3(256), 0, s, F, c, K, Bs);
 }
 
 void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, int64_t Bs, hipStream_t s)
