@@ -415,9 +415,10 @@ pc_status pc_workspace_bytes(const pc_circuit *c, int32_t B, size_t *bytes)
     return st;
 }
 
-// The forward pass proper: argument checks, then kernels only.  `profiled` installs the circuit's per-launch timer.
+// The forward pass proper: argument checks, then kernels only.  ll_only: nothing but ll is kept (pc_forward_static), so product rows that
+// only the backward pass would read are not written, and there is no per-launch timing (the timer creates events).
 static pc_status forward_on(pc_circuit *c, const float *theta, const float *tables, const int32_t *x, const uint8_t *mask,
-                            int32_t B, void *workspace, size_t workspace_bytes, float *ll, hipStream_t s, bool profiled)
+                            int32_t B, void *workspace, size_t workspace_bytes, float *ll, hipStream_t s, bool ll_only)
 {
     if (!c || !theta || !tables || !x || !workspace || !ll) return fail(PC_ERR_ARG, "NULL argument");
     if (!c->on_device) return fail(PC_ERR_STATE, "circuit was compiled without a device");
@@ -428,7 +429,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     const Ws w = ws_layout(c, B);
     if (workspace_bytes < w.total) return fail(PC_ERR_WORKSPACE, "workspace smaller than pc_workspace_bytes");
     if (check_fault(c) != PC_OK) return PC_ERR_HIP;
-    ProfScope prof(profiled ? c : nullptr);
+    ProfScope prof(ll_only ? nullptr : c);
     char *base = (char *)workspace;
     float *l = (float *)(base + w.l_off), *R = (float *)(base + w.r_off);
     int32_t *xT = (int32_t *)(base + w.xt_off);
@@ -463,7 +464,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     }
     if (li0 < L) {
         launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, c->wait_limit, c->d_fault, s);
-        launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
+        if (!ll_only) launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
     }
     // a root among the layers of the dataflow launch has written ll; blocks it does not reach may lie deeper, and then the
     // part that runs as dataflow can begin above the root
@@ -478,7 +479,7 @@ pc_status pc_forward(pc_circuit *c, const float *theta, const float *tables, con
                      const uint8_t *mask, int32_t B, void *workspace, size_t workspace_bytes,
                      float *ll, void *stream)
 {
-    pc_status st = forward_on(c, theta, tables, x, mask, B, workspace, workspace_bytes, ll, (hipStream_t)stream, true);
+    pc_status st = forward_on(c, theta, tables, x, mask, B, workspace, workspace_bytes, ll, (hipStream_t)stream, false);
     if (st != PC_OK) return st;
     c->fw_workspace = workspace; c->fw_theta = theta; c->fw_tables = tables; c->fw_x = x; c->fw_mask = mask;
     c->fw_B = B;
@@ -499,8 +500,7 @@ pc_status pc_forward_static(pc_circuit *c, const float *theta, const float *tabl
     void *ws = nullptr;
     pc_status st = static_scratch(&ws);
     if (st != PC_OK) return st;
-    // no per-launch timing here: the timer creates events
-    return forward_on(c, theta, tables, x, mask, B, ws, (size_t)PC_STATIC_SCRATCH_BYTES, ll, (hipStream_t)stream, false);
+    return forward_on(c, theta, tables, x, mask, B, ws, (size_t)PC_STATIC_SCRATCH_BYTES, ll, (hipStream_t)stream, true);
 }
 
 pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, const int32_t *x,
