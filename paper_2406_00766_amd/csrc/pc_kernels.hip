@@ -1151,24 +1151,24 @@ __global__ __launch_bounds__(256) void k_param_flow_small(const float *__restric
 // What bounds it: exponentials (a quarter of the vector rate) and MFMAs in turn, eight of each per neighbour.  Measured on
 // 28 sets of 1024 x 1024, 30 % of the 16 x 16 blocks kept, B = 333 (6.2 GFLOP): forward 526 -> 179 us, backward 432 -> 165 us
 // against the vector kernel (64 columns per wave: 205 and 216 us, the operands of four neighbours then take 170 - 210 registers).
-template <bool BWD, int SPLIT>
+template <bool BWD, int SPLIT, int ROWS>
 __global__ __launch_bounds__(256) void k_sum_16(const float *__restrict__ theta, const float *__restrict__ X, float *__restrict__ l,
                                                 float *__restrict__ R, const float *__restrict__ nfmax, float *__restrict__ F,
-                                                const int32_t *__restrict__ ids, const int32_t *__restrict__ nbr,
-                                                const int32_t *__restrict__ par, const int32_t *__restrict__ aux, int32_t width, int64_t Bs)
+                                                const GroupSet gs, int64_t Bs)
 {
     constexpr int K = 16, U = 4, NC = 2;
     __shared__ floatx4 part[SPLIT > 1 ? 4 : 1][NC][SPLIT > 1 ? 64 : 1];
     __shared__ float pref[SPLIT > 1 ? 4 : 1][NC][16];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
-    const int r = blockIdx.x;
+    const GroupRow gr = locate_row<ROWS>(gs, blockIdx.x);
+    const int r = gr.r;
     const int64_t cg = SPLIT > 1 ? blockIdx.y : (int64_t)blockIdx.y * 4 + wave;   // group of NC column tiles
     if (SPLIT == 1 && cg * NC * 16 >= Bs) return;
     int64_t col[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) col[c] = (cg * NC + c) * 16 + j16;     // Bs is a multiple of 32
-    const int32_t *row_nbr = nbr + (int64_t)r * width, *row_par = par + (int64_t)r * width;
-    const int32_t id = ids[r], fl = aux[r], cnt = fl >> 8;
+    const int32_t *row_nbr = gr.nbr + (int64_t)r * gr.width, *row_par = gr.par + (int64_t)r * gr.width;
+    const int32_t id = gr.ids[r], fl = gr.aux[r], cnt = fl >> 8;
     float Rown[NC];
     floatx4 lown[BWD ? NC : 1];
 #pragma unroll
@@ -2907,15 +2907,20 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
     while (split < (rt == 1 ? 16 : 4) && tiles * split < want && (int64_t)width * (K / 32) >= (split < 4 ? 2 : 4) * split) split <<= 1;
 }
 
-// K = 16, one group: forward (F null; X = l of the children) or backward to the children (X = log_nf).  The neighbours of a row
-// are dealt to four waves where the tiles alone leave less than a wave per SIMD.
-static void launch_sum_16(const float *theta, const float *X, float *l, float *R, const float *nfmax, float *F, const GroupDev &g, int64_t Bs,
+// K = 16: forward (F null; X = l of the children) or backward to the children (X = log_nf).  The neighbours of a row
+// are dealt to four waves where the tiles alone leave less than a wave per SIMD.  All groups of the layer in one launch: three launches
+// of 28 sets of 1024 x 1024, 30 % kept, B = 333 took 161 us forward and 158 backward, one 143 and 145.
+static void launch_sum_16(const float *theta, const float *X, float *l, float *R, const float *nfmax, float *F, const GroupSet &gs, int64_t Bs,
                           hipStream_t s)
 {
     const int64_t cgs = Bs / 32;
-    const bool split = (int64_t)g.n_rows * cgs < 1024 && g.width >= 8;
-    const dim3 grid((unsigned)g.n_rows, (unsigned)(split ? cgs : (cgs + 3) / 4));
-#define PC_SUM_16(BB, SS) hipLaunchKernelGGL((k_sum_16<BB, SS>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, g.ids, g.nbr, g.par, g.aux, g.width, Bs)
+    const bool split = (int64_t)set_rows(gs) * cgs < 1024 && set_width(gs) >= 8;
+    const dim3 grid((unsigned)set_rows(gs), (unsigned)(split ? cgs : (cgs + 3) / 4));
+#define PC_SUM_16(BB, SS)                                                                                                     \
+    do {                                                                                                                      \
+        if (gs.n > 1) hipLaunchKernelGGL((k_sum_16<BB, SS, PC_ROWS_MULTI>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, gs, Bs); \
+        else hipLaunchKernelGGL((k_sum_16<BB, SS, PC_ROWS_ONE>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, gs, Bs);    \
+    } while (0)
     if (F) { if (split) PC_SUM_16(true, 4); else PC_SUM_16(true, 1); }
     else { if (split) PC_SUM_16(false, 4); else PC_SUM_16(false, 1); }
 #undef PC_SUM_16
@@ -2941,13 +2946,18 @@ void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, co
         }
         return;
     }
+    if (use_16(K)) {
+        for (const GroupSet &gs : sets) {
+            Timed timed(KC_SUM_FWD, s);
+            launch_sum_16(theta, lch, l, R, nullptr, nullptr, gs, Bs, s);
+        }
+        return;
+    }
     // other block sizes: one launch per group
     for (const GroupSet &gs : sets) for (int k = 0; k < gs.n; ++k) {
         const GroupDev g{gs.first[k + 1] - gs.first[k], gs.width[k], gs.ids[k], gs.nbr[k], gs.par[k], false, gs.aux[k]};
         Timed timed(KC_SUM_FWD, s);
-        if (use_16(K)) {
-            launch_sum_16(theta, lch, l, R, nullptr, nullptr, g, Bs, s);
-        } else if (use_small(K)) {
+        if (use_small(K)) {
             dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 255) / 256));
             PC_DISPATCH_SMALL(k_sum_fwd_small, grid, dim3(256), 0, s, theta, lch, l, R, g.ids, g.nbr, g.par, g.aux, g.width, Bs);
         } else {
@@ -2978,13 +2988,18 @@ void launch_sum_bwd_child(const float *theta, const float *l, const float *R, co
         }
         return;
     }
+    if (use_16(K)) {
+        for (const GroupSet &gs : sets) {
+            Timed timed(KC_SUM_BWD_CHILD, s);
+            launch_sum_16(theta, N, const_cast<float *>(l), const_cast<float *>(R), nfmax, F, gs, Bs, s);
+        }
+        return;
+    }
     // other block sizes: one launch per group
     for (const GroupSet &gs : sets) for (int k = 0; k < gs.n; ++k) {
         const GroupDev g{gs.first[k + 1] - gs.first[k], gs.width[k], gs.ids[k], gs.nbr[k], gs.par[k], false, gs.aux[k]};
         Timed timed(KC_SUM_BWD_CHILD, s);
-        if (use_16(K)) {
-            launch_sum_16(theta, N, const_cast<float *>(l), const_cast<float *>(R), nfmax, F, g, Bs, s);
-        } else if (use_small(K)) {
+        if (use_small(K)) {
             dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 255) / 256));
             PC_DISPATCH_SMALL(k_sum_bwd_small, grid, dim3(256), 0, s, theta, l, R, N, nfmax, F, g.ids, g.nbr, g.par, g.aux,
                               g.width, Bs);
