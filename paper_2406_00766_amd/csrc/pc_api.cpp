@@ -128,6 +128,7 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     add(&c->d_init_ids, c->init_ids);
     add(&c->d_flow_rep, c->flow_rep);
     add(&c->d_pf_pb, c->pf_pb); add(&c->d_pf_ptr, c->pf_ptr); add(&c->d_pf_sum, c->pf_sum); add(&c->d_pf_child, c->pf_child);
+    for (ChainTab *t : {&c->chain_fwd, &c->chain_bwd}) add(&t->d_words, t->words);
     for (FlowTab *f : {&c->flow_fwd, &c->flow_bwd}) { add(&f->d_ent, f->ent); add(&f->d_rec, f->rec); add(&f->d_list, f->list); }
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) {
         add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
@@ -273,6 +274,14 @@ static FlowDev flow_dev(const pc_circuit *c, const FlowTab &f, size_t li0, bool 
     const int32_t n = f.count_from[li0], first = suffix ? f.count_from[0] - n : 0;
     return FlowDev{f.d_ent + 4 * (size_t)first, f.d_rec, f.d_list, n, f.max_nbr_from[li0], (int32_t)li0, max_level,
                    *std::max_element(c->max_items.begin() + li0, c->max_items.end())};
+}
+// The links from layer li0 up (words: forward a suffix, backward a prefix).  None where a limit of polls was set: that is for launches
+// that poll.
+static ChainDev chain_dev(const pc_circuit *c, const ChainTab &t, size_t li0, bool suffix)
+{
+    const int32_t n = t.from[li0];
+    if (n <= 0 || c->wait_limit != pc_circuit::kWaitLimit) return ChainDev{nullptr, 0};
+    return ChainDev{t.d_words + (suffix ? t.words.size() - (size_t)n * CHAIN_WORDS : 0), n};
 }
 static int32_t max_width(const std::vector<GroupTab> &groups)
 {
@@ -438,7 +447,9 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
 
     const size_t L = c->layers.size(), li0 = flow_start(c, w, false);
     FlowDev flow{};
-    if (li0 < L) flow = flow_dev(c, c->flow_fwd, li0, true);
+    ChainDev chain{};
+    if (li0 < L) chain = chain_dev(c, c->chain_fwd, li0, true);
+    if (li0 < L && chain.n_links == 0) flow = flow_dev(c, c->flow_fwd, li0, true);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     const bool null_mail = li0 < L || flow_start(c, w, true) < L;        // read by the dataflow launches of both directions
     launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), null_mail, flow.ent, flow.n_ent, K, ticket, s);
@@ -463,7 +474,8 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         }
     }
     if (li0 < L) {
-        launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, c->wait_limit, c->d_fault, s);
+        if (chain.n_links > 0) launch_chain(theta, l, R, nullptr, false, chain, w.Bs, B, ll, s);
+        else launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, c->wait_limit, c->d_fault, s);
         if (!ll_only) launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
     }
     // a root among the layers of the dataflow launch has written ll; blocks it does not reach may lie deeper, and then the
@@ -534,12 +546,15 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     const size_t li0 = flow_start(c, w, true);
     FlowDev flow{};
-    if (li0 < c->layers.size()) flow = flow_dev(c, c->flow_bwd, li0, false);
+    ChainDev chain{};
+    if (li0 < c->layers.size()) chain = chain_dev(c, c->chain_bwd, li0, false);
+    if (li0 < c->layers.size() && chain.n_links == 0) flow = flow_dev(c, c->flow_bwd, li0, false);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
                           flow.n_ent, ticket, s);
     if (li0 < c->layers.size()) {
-        launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, c->wait_limit, c->d_fault, s);
+        if (chain.n_links > 0) launch_chain(theta, l, const_cast<float *>(R), F, true, chain, w.Bs, B, nullptr, s);
+        else launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, c->wait_limit, c->d_fault, s);
         launch_prod_bwd_rows(l, F, N, nfmax, rows_dev(c->prod_bwd_rows, li0, false), K, w.Bs, w.bf16 ? base + w.ph_off : nullptr,
                              w.bf16 ? base + w.pl_off : nullptr, s);
     }

@@ -127,6 +127,55 @@ pc_status build_groups(std::vector<Row> &rows, int32_t max_groups, int32_t tol_p
     return PC_OK;
 }
 
+// Chains (ChainTab): one block a layer with one neighbour, which takes the values of the sum layer before (forward) or of the product
+// layer above (backward), or none of this launch.
+void compile_chain(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &par_ptr, const std::vector<int32_t> &par_of,
+                   const std::vector<int64_t> &par_edge, const std::vector<int32_t> &layer_of, int32_t from)
+{
+    const int32_t K = d->K, L = (int32_t)c->layers.size();
+    auto off = [&](int32_t u) { return (u + 1) * K; };
+    auto only = [&](int32_t li) { return li >= 0 && li < L && c->layers[li].blk_ids.size() == 1 ? c->layers[li].blk_ids[0] / K - 1 : -1; };
+    auto fwd_link = [&](int32_t li, std::vector<int32_t> &w) -> bool {
+        const int32_t u = only(li);
+        if (u < 0 || d->child_ptr[u + 1] - d->child_ptr[u] != 1) return false;
+        const int32_t p = d->child[d->child_ptr[u]];
+        if (layer_of[p] != li - 1) return false;
+        w = {off(u), off(p), 0, 0, (d->param_blk[d->child_ptr[u]] + 1) * K * K, u == d->root_block ? 1 : 0, 0, 0};
+        for (int64_t e = d->child_ptr[p]; e < d->child_ptr[p + 1]; ++e) {
+            const int32_t k = d->child[e];
+            int32_t &at = d->type[k] == KIND_INPUT ? w[3] : w[2];
+            if (at != 0 || (d->type[k] == KIND_SUM && k != only(li - 2))) return false;
+            at = off(k);
+        }
+        return true;
+    };
+    auto bwd_link = [&](int32_t li, std::vector<int32_t> &w) -> bool {
+        const int32_t u = only(li);
+        if (u < 0 || par_ptr[u + 1] - par_ptr[u] != 1) return false;
+        const int32_t s = par_of[par_ptr[u]], ns = par_ptr[s + 1] - par_ptr[s];
+        if (layer_of[s] != li + 1 || ns > 1) return false;
+        w = {off(u), off(s), 0, 0, (d->param_blk[par_edge[par_ptr[u]]] + 1) * K * K, 0, 0, 0};
+        // a flow that is there already (the root's, or 0 of an unused block) is read by the first link only
+        if (ns == 0) return s != d->root_block || c->chain_bwd.words.empty();
+        const int32_t p = par_of[par_ptr[s]];
+        w[2] = off(p);
+        return p == only(li + 2) && par_ptr[p] != par_ptr[p + 1];
+    };
+    for (ChainTab *t : {&c->chain_fwd, &c->chain_bwd}) t->from.assign(L + 1, 0);
+    std::vector<std::vector<int32_t>> fwd;
+    for (int32_t li = L; li-- > from;) {
+        const bool sums = c->layers[li].kind == KIND_SUM;
+        c->chain_fwd.from[li] = c->chain_fwd.from[li + 1]; c->chain_bwd.from[li] = c->chain_bwd.from[li + 1];
+        int32_t &n = (sums ? c->chain_fwd : c->chain_bwd).from[li];
+        std::vector<int32_t> w;
+        if (n < 0 || K != 32 || !(sums ? fwd_link(li, w) : bwd_link(li, w))) { n = -1; continue; }
+        ++n;
+        if (sums) fwd.push_back(w);
+        else c->chain_bwd.words.insert(c->chain_bwd.words.end(), w.begin(), w.end());
+    }
+    for (size_t k = fwd.size(); k-- > 0;) c->chain_fwd.words.insert(c->chain_fwd.words.end(), fwd[k].begin(), fwd[k].end());
+}
+
 // Tables of the dataflow launches (pc_internal.h, pc_flow.hip), for the layers such a launch may cover at some batch size.
 void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &par_ptr, const std::vector<int32_t> &par_of,
                   const std::vector<int64_t> &par_edge)
@@ -266,6 +315,7 @@ void compile_flow(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &pa
             ++r.count_from[li];
             r.max_nbr_from[li] = std::max(r.max_nbr_from[li], (int32_t)pa.size());
         }
+    compile_chain(d, c, par_ptr, par_of, par_edge, layer_of, from);
     auto accumulate = [&](std::vector<int32_t> &cnt, std::vector<int32_t> &most) {
         for (int32_t li = L; li-- > 0;) { cnt[li] += cnt[li + 1]; most[li] = std::max(most[li], most[li + 1]); }
     };

@@ -42,6 +42,7 @@
 #include <algorithm>
 
 #include "pc_device.h"
+#include "pc_internal.h"
 #include "pc_kernels.h"
 
 namespace pc {
@@ -564,6 +565,138 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
     }
 }
 
+
+// ------------------------------------------------------------------------------------------
+// Chains: the same layers where each is one block of 32 nodes that takes values of the layer before it only (ChainTab; an HMM of 32
+// states).  One wave walks the whole chain for 16 columns: in MFMA layout the results of one layer are the operands of the
+// next lane by lane, so they are handed on in registers.  Nothing is polled and nothing published.
+// Bound: the instructions of a layer, one wave's -- some 250, 0.6 us against 1.1 us for a task of k_flow with its hand-over.  For it to be
+// that and not the memory, nothing in a layer may wait: operands that do not depend on the chain are requested a layer ahead (two
+// and three made no difference), the words of a link come through the scalar cache a link before they are needed, and stores
+// that do not apply go to a descriptor of no bytes instead of round a branch (behind a branch the compiler does not know how many
+// stores are under way and waits for them all).  HMM 16 x 32: forward pass, one sample, 28.7 -> 21.9 us, backward
+// 41.1 -> 35.6; B = 128 30.8 -> 22.9, 55.9 -> 46.3.  The same for 64 nodes (four waves, results through LDS) took 1.4 us a layer forward and 3.5 backward, k_flow 1.6 and 3.1.
+struct ChainLink { int32_t id, nbr, src, in, par, root; };              // a link's words (ChainTab)
+
+template <bool BWD>
+__global__ __launch_bounds__(64) void k_chain(const float *__restrict__ theta, float *l, float *R, float *F, const int32_t *link_words,
+                                              int32_t n_links, int64_t Bs, float *__restrict__ ll, int32_t B)
+{
+    constexpr int K = 32;
+    const int lane = threadIdx.x, g = lane >> 4, j16 = lane & 15;
+    const int64_t col = (int64_t)blockIdx.x * 16 + j16;
+    const TabPtr table = (TabPtr)(uintptr_t)link_words;
+    const int row4 = (int)(Bs * 4), tile_off = (int)((4 * g * Bs + col) * 4), col_off = (int)(col * 4);   // bytes: a row; row 4 g of a tile
+    const int first_off = g == 0 ? col_off : -1;                        // beyond every descriptor: lanes without row 0 of a tile
+    auto buf = [](const void *p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, PC_BUF_FLAGS); };
+    auto load = [](__amdgpu_buffer_rsrc_t r, int voff, int soff) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0)); };
+    auto store = [](float v, __amdgpu_buffer_rsrc_t r, int voff, int soff) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, voff, soff, 0); };
+
+    auto words = [&](int k) -> ChainLink {
+        const TabPtr w = table + CHAIN_WORDS * (k < n_links ? k : n_links - 1);
+        return ChainLink{w[0], w[1], w[2], w[3], w[4], w[5]};
+    };
+    auto rows = [&](const float *X, int32_t row, floatx4 (&x)[2]) {     // 32 rows in operand order: lane (j, g), rows 16 c2 + 4 g + e of column j
+        const __amdgpu_buffer_rsrc_t r = buf(X + (int64_t)row * Bs, PC_BUF_RANGE);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k >> 2][k & 3] = load(r, tile_off, (16 * (k >> 2) + (k & 3)) * row4);
+    };
+    struct Operands {
+        floatx4 th[2][2], in[2], lown[2];
+        float base, Rrow;
+        int32_t id, src, root;
+    };
+    // what a link reads that the chain does not compute
+    auto request = [&](const ChainLink &w, Operands &o) {
+        o.id = w.id; o.src = w.src; o.root = w.root;
+        const __amdgpu_buffer_rsrc_t r = buf(theta + w.par, PC_BUF_RANGE);
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2) {
+                if (BWD) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o.th[c2][rt][e] = load(r, (4 * g * K + j16) * 4, ((16 * c2 + e) * K + 16 * rt) * 4);
+                } else {
+                    o.th[c2][rt] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, (j16 * K + 4 * g) * 4, 64 * K * rt + 64 * c2, 0));
+                }
+            }
+        const int32_t from = BWD ? w.nbr : w.in;                        // (no input block: the null block's rows, 0)
+        rows(l, from, o.in);
+        o.base = load(buf(R + (int64_t)(from / K) * Bs, PC_BUF_RANGE), col_off, 0);
+        if (BWD) {
+            rows(l, w.id, o.lown);
+            o.Rrow = load(buf(R + (int64_t)(w.id / K) * Bs, PC_BUF_RANGE), col_off, 0);
+        }
+    };
+
+    // the values that the first link takes have been there before this launch (backward: the root's own flow, or 0 of an unused block)
+    ChainLink w = words(0);
+    floatx4 x[2];
+    rows(BWD ? F : l, BWD ? w.nbr : w.src, x);
+    float Rx = BWD ? 0.0f : R[(int64_t)(w.src / K) * Bs + col];
+    auto link = [&](int k, const Operands &o, Operands &ahead) {
+        request(w, ahead);                                              // link k + 1
+        w = words(k + 2);
+        const bool taken = o.src != 0 || (BWD && k == 0);               // uniform
+        float base = BWD ? o.Rrow - o.base : o.base + (taken ? Rx : 0.0f), cm = PC_NEG_INF;
+        floatx4 v[2], acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}, val[2];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float y = taken ? x[e >> 2][e & 3] : 0.0f;
+            if (BWD) {
+                const float lo = o.in[e >> 2][e & 3];
+                y = lo > PC_NEG_INF ? __logf(y) - lo : PC_NEG_INF;       // flow 0: -inf
+            } else {
+                y += o.in[e >> 2][e & 3];
+            }
+            v[e >> 2][e & 3] = y;
+            cm = fmaxf(cm, y);
+        }
+        cm = max_over_groups(cm);
+        const bool live = cm > PC_NEG_INF;
+        cm = live ? rintf(cm) : 0.0f;
+        base = live ? base + cm : PC_NEG_INF;                           // the reference: there is but one chunk
+        // exp(v - cm + PC_UP); dead: v = -inf
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(v[e >> 2][e & 3] - cm, PC_LOG2E, live ? PC_UP * PC_LOG2E : 0.0f));
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.th[e >> 2][rt][e & 3], p, acc[rt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                               // as in k_flow
+                if (BWD) {
+                    const float add = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(acc[rt][r]) + (o.lown[rt][r] + (base - PC_UP)) * PC_LOG2E);
+                    val[rt][r] = live ? add : 0.0f;
+                } else {
+                    val[rt][r] = fmaf(__builtin_amdgcn_logf(acc[rt][r] * 0x1p-24f), 0.6931471805599453f, 16.635532333f - PC_UP);
+                }
+            }
+        const __amdgpu_buffer_rsrc_t out = buf((BWD ? F : l) + (int64_t)o.id * Bs, PC_BUF_RANGE);
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) store(val[rt][r], out, tile_off, (16 * rt + r) * row4);
+        if (!BWD) {
+            Rx = live ? base : 0.0f;                                    // all children dead: any finite reference
+            store(Rx, buf(R + (int64_t)(o.id / K) * Bs, PC_BUF_RANGE), first_off, 0);
+            store(Rx + val[0][0], buf(ll, o.root ? 4 * B : 0), first_off, 0);
+        }
+        x[0] = val[0]; x[1] = val[1];
+        asm volatile("" :: "s"(w.id), "s"(w.nbr), "s"(w.src), "s"(w.in), "s"(w.par), "s"(w.root));   // the words are here by now
+    };
+    Operands a, b;                                                      // in turn: a copy would be some forty moves a layer
+    request(w, a);
+    w = words(1);
+    for (int k = 0; k < n_links; k += 2) {
+        link(k, a, b);
+        if (k + 1 < n_links) link(k + 1, b, a);
+    }
+}
+
 // ---- launchers ----
 void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
                           float *l, float *R, float *mail, bool null_mail, const int32_t *ent, int32_t n_ent, int32_t K,
@@ -621,6 +754,14 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
     else PC_FLOW_ROWS(8, 4);
 #undef PC_FLOW_ROWS
 #undef PC_FLOW
+}
+
+void launch_chain(const float *theta, float *l, float *R, float *F, bool bwd, const ChainDev &c, int64_t Bs, int32_t B, float *ll, hipStream_t s)
+{
+    Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
+    const dim3 grid((unsigned)(Bs / 16));
+    if (bwd) hipLaunchKernelGGL(k_chain<true>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
+    else hipLaunchKernelGGL(k_chain<false>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
 }
 
 }  // namespace pc

@@ -69,6 +69,16 @@ struct FlowTab {
     std::vector<int32_t> count_from, max_nbr_from;    // per layer index: entries in that layer and above; most neighbours of one
     int32_t *d_ent = nullptr, *d_rec = nullptr, *d_list = nullptr;
 };
+// The same launches where the circuit is a chain of single blocks of 32 nodes (k_chain): CHAIN_WORDS words per sum layer (forward,
+// ascending) or product layer (backward, descending), and per layer index how many of them from there up, -1: a layer there is no link
+// of a chain.
+//   0 node offset of the layer's block  1 its neighbour's (a product block; backward: a sum block)  2 the block whose published values
+//   the neighbour takes, 0: none  3 forward: the input block multiplied to them, 0: none  4 parameter offset  5 1 for the root
+constexpr int CHAIN_WORDS = 8;
+struct ChainTab {
+    std::vector<int32_t> words, from;
+    int32_t *d_words = nullptr;
+};
 // The product layers that belong to them, as rows with neighbour lists (CSR): forward, product blocks by ascending layer with
 // their children; backward, sum and input blocks by descending layer of their highest product parent, with their product
 // parents from the highest layer down (lay: the parents' layers).
@@ -115,6 +125,7 @@ struct pc_circuit {
 
     // dataflow launches (empty where they do not apply)
     pc::FlowTab flow_fwd, flow_bwd;
+    pc::ChainTab chain_fwd, chain_bwd;
     std::vector<int64_t> sum_edges;                   // per layer (sum layers): block pairs,
     std::vector<int32_t> max_items;                   // most children of a product block that it reads,
     // per layer, what its tasks read (sum layer: forward, product layer: backward): most values waited for at one neighbour, chunks of
@@ -123,7 +134,8 @@ struct pc_circuit {
     std::vector<uint8_t> flow_cut;                    // per layer: a dataflow part may begin here (a product layer, and no product
                                                       // block below it is read by a sum block above it)
     pc::RowTab prod_fwd_rows, prod_bwd_rows;
-    int32_t wait_limit = 1 << 22;                     // polls of a wait before it is given up: some seconds
+    static constexpr int32_t kWaitLimit = 1 << 22;    // polls of a wait before it is given up: some seconds
+    int32_t wait_limit = kWaitLimit;
     int32_t *fault = nullptr, *d_fault = nullptr;     // a word of pinned host memory, set by a launch that gave up; its device address
 
     // product-scratch mode: product log-probabilities live in a window of max_window_blocks blocks behind the

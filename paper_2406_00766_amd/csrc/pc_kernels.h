@@ -40,6 +40,11 @@ struct FlowDev {             // a dataflow launch (pc_flow.hip): entries from la
     int32_t max_items;       // forward: most children of a product block that is read
 };
 
+struct ChainDev {            // a dataflow launch over a chain (k_chain): its links in the order they are worked off
+    const int32_t *words;
+    int32_t n_links;         // 0: not a chain
+};
+
 struct RowsDev {             // product-layer rows of a dataflow launch as neighbour lists
     const int32_t *ids, *start, *list, *lay, *aux;
     int32_t n_rows, max_nbr, li0;
@@ -135,6 +140,7 @@ void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int3
                           int32_t *ticket, hipStream_t s);
 void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,
                            int32_t K, int64_t Bs, int32_t B, const int32_t *ent, int32_t n_ent, int32_t *ticket, hipStream_t s);
+void launch_chain(const float *theta, float *l, float *R, float *F, bool bwd, const ChainDev &c, int64_t Bs, int32_t B, float *ll, hipStream_t s);
 void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
                  int32_t *ticket, float *ll, int32_t wait_limit, int32_t *fault, hipStream_t s);
 
