@@ -89,19 +89,15 @@ static void return_fault_word(pc_circuit *c)
     else (void)hipHostFree(c->fault);
 }
 
-// One arena for every table: sizes first, then pointers.  Host copies are uploaded where they exist; tables built
-// on the device only get their space.
+// One arena for every table: sizes first, then pointers.  Host copies stand first and go up in one piece (a copy each took a 16 x 32 HMM's
+// pc_compile some 0.4 ms); tables built on the device only get their space.
 pc_status upload(pc_circuit *c, hipStream_t stream)
 {
-    size_t bytes = 0;
-    auto reserve = [&](size_t n_i32) { size_t off = bytes; bytes = align_up(bytes + n_i32 * 4, 256); return off; };
-    struct Fix { void **dst; size_t off; const void *src; size_t n; };
+    struct Fix { int32_t **dst; const void *src; size_t bytes, n; };      // n: bytes of the host copy
     std::vector<Fix> fixes;
-    auto add = [&](int32_t **dst, const std::vector<int32_t> &v) {
-        fixes.push_back({(void **)dst, reserve(v.size()), v.data(), v.size() * 4});
-    };
+    auto add = [&](int32_t **dst, const std::vector<int32_t> &v) { fixes.push_back({dst, v.data(), v.size() * 4, v.size() * 4}); };
     auto add_sized = [&](int32_t **dst, const std::vector<int32_t> &v, size_t n) {   // n entries, copied only if present
-        fixes.push_back({(void **)dst, reserve(n), v.data(), v.size() == n ? n * 4 : 0});
+        fixes.push_back({dst, v.data(), n * 4, v.size() == n ? n * 4 : 0});
     };
     for (auto &layer : c->layers) {
         add(&layer.d_blk_ids, layer.blk_ids);
@@ -133,6 +129,17 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     for (RowTab *r : {&c->prod_fwd_rows, &c->prod_bwd_rows}) {
         add(&r->d_ids, r->ids); add(&r->d_start, r->start); add(&r->d_list, r->list); add(&r->d_lay, r->lay); add(&r->d_aux, r->aux);
     }
+    size_t bytes = 0;
+    std::vector<size_t> off(fixes.size());
+    auto place = [&](bool copied) {
+        for (size_t k = 0; k < fixes.size(); ++k)
+            if ((fixes[k].n > 0) == copied) { off[k] = bytes; bytes = align_up(bytes + fixes[k].bytes, 256); }
+    };
+    place(true);
+    std::vector<char> host(bytes);
+    for (size_t k = 0; k < fixes.size(); ++k) if (fixes[k].n) std::memcpy(host.data() + off[k], fixes[k].src, fixes[k].n);
+    place(false);
+    auto reserve = [&](size_t n_f32) { const size_t at = bytes; bytes = align_up(bytes + n_f32 * 4, 256); return at; };
     const size_t ztab_off = reserve((size_t)c->n_tables * c->K + 1);
     const size_t part_off = reserve((c->em_seg_ptr.size() - 1) * c->K + 1);
     if (!c->flow_fwd.ent.empty()) {
@@ -142,10 +149,8 @@ pc_status upload(pc_circuit *c, hipStream_t stream)
     PC_HIP(hipMalloc(&c->d_arena, bytes));
     c->arena_bytes = bytes;
     char *base = (char *)c->d_arena;
-    for (auto &f : fixes) {
-        *f.dst = base + f.off;
-        if (f.n) PC_HIP(hipMemcpyAsync(base + f.off, f.src, f.n, hipMemcpyHostToDevice, stream));
-    }
+    for (size_t k = 0; k < fixes.size(); ++k) *fixes[k].dst = (int32_t *)(base + off[k]);
+    if (!host.empty()) PC_HIP(hipMemcpyAsync(base, host.data(), host.size(), hipMemcpyHostToDevice, stream));
     c->d_ztab = (float *)(base + ztab_off);
     c->d_em_part = (float *)(base + part_off);
     PC_HIP(hipStreamSynchronize(stream));

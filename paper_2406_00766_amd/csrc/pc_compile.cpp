@@ -342,16 +342,6 @@ void compile_product_tiles(LayerTab &T, int32_t K, int32_t n)
         next[two[0]].push_back(two[1]); next[two[1]].push_back(two[0]);
     }
     auto blocks = [&](int32_t q) { return T.cls_ptr[q + 1] - T.cls_ptr[q]; };
-    auto order_of = [&](int32_t qa, int32_t qb) {                            // a bit per block of the merged classes, 1: of the second
-        const int32_t na = blocks(qa), nb = blocks(qb);
-        std::vector<int32_t> bits((na + nb + 31) / 32, 0);
-        const int32_t *a = &T.cls_blk[T.cls_ptr[qa]], *b = &T.cls_blk[T.cls_ptr[qb]];
-        for (int32_t i = 0, j = 0; i + j < na + nb;) {
-            if (i < na && (j == nb || a[i] < b[j])) ++i;
-            else { bits[(i + j) >> 5] = (int32_t)((uint32_t)bits[(i + j) >> 5] | 1u << ((i + j) & 31)); ++j; }
-        }
-        return bits;
-    };
     std::vector<int32_t> side(n_cls, -1), tile, order, row_at(n_cls, -1);
     for (int32_t q0 = 0; q0 < n_cls; ++q0) {
         if (side[q0] >= 0) continue;
@@ -368,9 +358,29 @@ void compile_product_tiles(LayerTab &T, int32_t K, int32_t n)
         }
         for (auto &v : set) std::sort(v.begin(), v.end());
         if (set[1].empty()) return;
-        const std::vector<int32_t> bits = order_of(set[0][0], set[1][0]);
-        const int32_t n_pos = blocks(set[0][0]) + blocks(set[1][0]), at = (int32_t)order.size();
-        order.insert(order.end(), bits.begin(), bits.end());
+        // the order in which the blocks of a pair's classes stand in a product's row: that of the first pair, a bit per block, 1 for the
+        // second set's.  It is every pair's where at each change of sides all blocks of the one place come before all of the next.
+        const int32_t na = blocks(set[0][0]), nb = blocks(set[1][0]), n_pos = na + nb, at = (int32_t)order.size();
+        std::vector<int32_t> lo[2], hi[2];
+        for (int h = 0; h < 2; ++h) {
+            lo[h].assign(h ? nb : na, std::numeric_limits<int32_t>::max()); hi[h].assign(h ? nb : na, 0);
+            for (int32_t q : set[h]) {
+                if (blocks(q) != (h ? nb : na)) return;
+                for (int32_t k = 0; k < blocks(q); ++k) {
+                    const int32_t id = T.cls_blk[T.cls_ptr[q] + k];
+                    lo[h][k] = std::min(lo[h][k], id); hi[h][k] = std::max(hi[h][k], id);
+                }
+            }
+        }
+        order.resize(order.size() + (n_pos + 31) / 32, 0);
+        for (int32_t i = 0, j = 0, last = -1; i + j < n_pos;) {
+            const int32_t h = i < na && (j == nb || T.cls_blk[T.cls_ptr[set[0][0]] + i] < T.cls_blk[T.cls_ptr[set[1][0]] + j]) ? 0 : 1;
+            if (last >= 0 && last != h && hi[last][last ? j - 1 : i - 1] >= lo[h][h ? j : i]) return;
+            int32_t &word = order[at + ((i + j) >> 5)];
+            word = (int32_t)((uint32_t)word | (uint32_t)h << ((i + j) & 31));
+            ++(h ? j : i);
+            last = h;
+        }
         const size_t first_tile = tile.size();
         const int32_t ta = ((int32_t)set[0].size() + 3) / 4, tb = ((int32_t)set[1].size() + 3) / 4;
         for (int32_t i = 0; i < ta; ++i)
@@ -389,7 +399,6 @@ void compile_product_tiles(LayerTab &T, int32_t K, int32_t n)
             for (int32_t k = T.cls_par_ptr[qa]; k < T.cls_par_ptr[qa + 1]; ++k) {
                 const auto &two = of_row[T.cls_par[k] / K - 1];
                 const int32_t qb = two[0] == qa ? two[1] : two[0], i = row_at[qa], j = row_at[qb];
-                if (order_of(qa, qb) != bits || blocks(qa) + blocks(qb) != n_pos) return;
                 int32_t &at16 = tile[first_tile + PROD_TILE_WORDS * (size_t)(i / 4 * tb + j / 4) + 8 + 4 * (i % 4) + j % 4];
                 if (at16 != 0) return;                                       // two products of one pair
                 at16 = T.cls_par[k];
@@ -428,7 +437,8 @@ void compile_classes(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> 
         for (int32_t u : members) seen[u] = 0;
         if (!inputs_only || 2 * (int64_t)members.size() > reads) continue;
         // blocks by their parents in this layer, then by BWD_FIRST; equal ones become neighbours (lists are ascending)
-        std::vector<std::pair<int32_t, int32_t>> par(n);  // block -> its parents' range in `at`
+        std::vector<std::pair<int32_t, int32_t>> par(n);  // block -> its parents' range in `at`; a hash of them decides most comparisons
+        std::vector<uint64_t> hash(n, 0);
         std::vector<int32_t> at;
         for (int32_t u : members) {
             par[u].first = (int32_t)at.size();
@@ -436,8 +446,10 @@ void compile_classes(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> 
                 if (layer_of[par_of[k]] == li) at.push_back((par_of[k] + 1) * K);
             at.push_back(c->an_first_parent_depth[u] == T.depth ? -1 : -2);
             par[u].second = (int32_t)at.size();
+            for (int32_t k = par[u].first; k < par[u].second; ++k) hash[u] = (hash[u] ^ (uint32_t)at[k]) * 0x9E3779B97F4A7C15ull;
         }
         auto less = [&](int32_t a, int32_t b) {
+            if (hash[a] != hash[b]) return hash[a] < hash[b];
             return std::lexicographical_compare(at.begin() + par[a].first, at.begin() + par[a].second, at.begin() + par[b].first, at.begin() + par[b].second);
         };
         std::sort(members.begin(), members.end(), [&](int32_t a, int32_t b) { return less(a, b) || (a < b && !less(b, a)); });
