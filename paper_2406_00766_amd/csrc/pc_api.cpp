@@ -457,13 +457,14 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     if (li0 < L && chain.n_links == 0) flow = flow_dev(c, c->flow_fwd, li0, true);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     const bool null_mail = li0 < L || flow_start(c, w, true) < L;        // read by the dataflow launches of both directions
-    launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), null_mail, flow.ent, flow.n_ent, K, ticket, s);
+    launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), null_mail, flow.ent, flow.n_ent, K, ticket,
+                         tables, dev(c->layers[0].fwd[0]), s);
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     if (w.bf16) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, false, base + w.th_off, base + w.tl_off, s);
     for (size_t li = 0; li < li0; ++li) {
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_INPUT) {
-            launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, R, s);
+            if (!input_in_begin(dev(L.fwd[0]), K, w.Bs)) launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, R, s);
         } else if (L.kind == KIND_PRODUCT && !w.bf16 && !L.tile.empty() && prod_takes_tiles(K, (int32_t)L.blk_ids.size(), max_width(L.fwd), w.Bs)) {
             launch_prod_fwd_tiles(l, R, L.d_tile, (int32_t)(L.tile.size() / PROD_TILE_WORDS), L.d_tile_order, L.d_cls_blk, K, w.Bs, s);
         } else if (L.kind == KIND_PRODUCT) {

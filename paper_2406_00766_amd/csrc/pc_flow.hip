@@ -116,33 +116,42 @@ __device__ inline void fill_share(float *X, float *Y, float *R, int32_t id, int 
 // the null block's rows (l = 0, R = 0; mail = 0 where a direction has a dataflow launch) and the ticket words.  One workgroup per block
 // takes longer than the rest of the launch at a large batch: the null block alone, forward pass of a 3 x 32 HMM at B = 131072, 561 us
 // instead of 88; the published ones, this launch for a 16 x 128 HMM in blocks of 128 at B = 4096, 23 us instead of 16.
-// xT[v][b] = category, -1 if marginalised (mask, or padding column b >= B), -2 if out of range.
+// xT[v][b] = pc_category.
+// KI = 32, 64: a small input layer of blocks of that size in the same launch, which saves its own (3.3 us of the 17.6 of a 16 x 32 HMM's
+// query); its workgroups read x itself, a line per sample where xT would be one for 16 (input_in_begin).
+template <int KI>
 __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict__ x, const uint8_t *__restrict__ mask, int32_t B,
                                                        int32_t D, int64_t Bs, int32_t n_cats, int32_t *__restrict__ xT, int32_t n_xb,
                                                        int32_t n_xtiles, float *__restrict__ l, float *__restrict__ R,
                                                        float *__restrict__ mail, bool null_mail, const int32_t *__restrict__ ent,
-                                                       int32_t n_ent, int32_t K, int32_t *ticket)
+                                                       int32_t n_ent, int32_t K, int32_t *ticket, const float *__restrict__ tables,
+                                                       const int32_t *__restrict__ in_ids, const int32_t *__restrict__ in_var,
+                                                       const int32_t *__restrict__ in_tab, int32_t n_in)
 {
+    if constexpr (KI != 0) {
+        const int n_ct = (int)((Bs + 63) / 64);
+        if ((int)blockIdx.x < n_in * n_ct) {
+            __shared__ float smem[KI * 65 + 64];
+            input_tile<KI, 64, true>(smem, (int)blockIdx.x / n_ct, (int64_t)((int)blockIdx.x % n_ct) * 64, tables, x, mask, B, D, in_ids, in_var, in_tab, KI,
+                                     n_cats, Bs, l, R);
+            return;
+        }
+    }
+    const int block = KI ? (int)blockIdx.x - n_in * (int)((Bs + 63) / 64) : (int)blockIdx.x;
     __shared__ int32_t tile[32][33];
-    if ((int)blockIdx.x >= n_xtiles) {
-        const int q = (int)blockIdx.x - n_xtiles;
+    if (block >= n_xtiles) {
+        const int q = block - n_xtiles;
         const int n_sh = fill_shares(K, Bs), b = q / n_sh, share = q % n_sh;
         if (b < n_ent) fill_share(mail, nullptr, R, ent[4 * b], share, K, Bs, __builtin_bit_cast(float, PC_SENTINEL));
         else fill_share(l, null_mail ? mail : nullptr, R, 0, share, K, Bs, 0.0f);
         if (q == 0 && threadIdx.x < 2) ticket[threadIdx.x] = 0;
         return;
     }
-    const int b0 = ((int)blockIdx.x % n_xb) * 32, v0 = ((int)blockIdx.x / n_xb) * 32;
+    const int b0 = (block % n_xb) * 32, v0 = (block / n_xb) * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;           // 256 threads: ty in 0..7
     for (int r = ty; r < 32; r += 8) {
         const int b = b0 + r, v = v0 + tx;
-        int32_t val = -1;
-        if (b < B && v < D) {
-            const int64_t idx = (int64_t)b * D + v;
-            val = x[idx];
-            if (val < 0 || val >= n_cats) val = -2;
-            if (mask && mask[idx]) val = -1;
-        }
+        const int32_t val = v < D ? pc_category(x, mask, b, v, B, D, n_cats) : -1;
         tile[r][tx] = val;
     }
     __syncthreads();
@@ -698,14 +707,24 @@ __global__ __launch_bounds__(64) void k_chain(const float *__restrict__ theta, f
 }
 
 // ---- launchers ----
+// A small input layer joins the begin of the pass.  Up to 4096 workgroups: beyond, a launch is nothing beside them, and they would read x a line
+// per sample.
+bool input_in_begin(const GroupDev &in, int32_t K, int64_t Bs) { return (K == 32 || K == 64) && in.n_rows * ((Bs + 63) / 64) <= 4096; }
+
 void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
                           float *l, float *R, float *mail, bool null_mail, const int32_t *ent, int32_t n_ent, int32_t K,
-                          int32_t *ticket, hipStream_t s)
+                          int32_t *ticket, const float *tables, const GroupDev &in, hipStream_t s)
 {
-    Timed timed(KC_MISC, s);
+    const bool with_input = input_in_begin(in, K, Bs);
+    Timed timed(with_input ? KC_INPUT_FWD : KC_MISC, s);
     const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
-    hipLaunchKernelGGL(k_begin_forward, dim3((unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs))), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb,
-                       n_xt, l, R, mail, null_mail, ent, n_ent, K, ticket);
+    const unsigned wgs = (unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs) + (with_input ? in.n_rows * ((Bs + 63) / 64) : 0));
+#define PC_BEGIN(KI) hipLaunchKernelGGL(k_begin_forward<KI>, dim3(wgs), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb, n_xt, l, R, mail, null_mail, \
+                                        ent, n_ent, K, ticket, tables, in.ids, in.nbr, in.par, in.n_rows)
+    if (with_input && K == 32) PC_BEGIN(32);
+    else if (with_input) PC_BEGIN(64);
+    else PC_BEGIN(0);
+#undef PC_BEGIN
 }
 
 void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,

@@ -135,9 +135,11 @@ void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow
 
 // pc_flow.hip: the first launch of a forward / backward pass (ent, n_ent: blocks the dataflow launch will publish) and the
 // dataflow launch itself (fault: set to 1 if a wait was given up after wait_limit polls)
+// (in: the input layer, evaluated here if input_in_begin)
+bool input_in_begin(const GroupDev &in, int32_t K, int64_t Bs);
 void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
                           float *l, float *R, float *mail, bool null_mail, const int32_t *ent, int32_t n_ent, int32_t K,
-                          int32_t *ticket, hipStream_t s);
+                          int32_t *ticket, const float *tables, const GroupDev &in, hipStream_t s);
 void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,
                            int32_t K, int64_t Bs, int32_t B, const int32_t *ent, int32_t n_ent, int32_t *ticket, hipStream_t s);
 void launch_chain(const float *theta, float *l, float *R, float *F, bool bwd, const ChainDev &c, int64_t Bs, int32_t B, float *ll, hipStream_t s);

@@ -84,62 +84,15 @@ __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tab
     }
 }
 
-// The same through an LDS tile, for K a multiple of 4: one workgroup per (block, 64 samples).  K / 4 lanes fetch one
-// sample's table row with 16-byte loads (every global read is a whole contiguous row), the logs go into a
-// [K x 64] tile, and the tile leaves as 16-byte stores along the batch -- no access is narrower than a row.
-// KC: the block size at compile time, 0 any multiple of 4; COLS columns per workgroup.  Bound: the chain of a workgroup -- block, categories,
-// table rows, stores --, of which a CU holds eight; a thread's table rows are requested together, and wide tiles carry more per chain.
-// One row after the other / together / 128 columns, K = 32: RAT-SPN of 784 variables, B = 512 577 / 553 / 496 us, PD of 1024
-// variables, B = 256 93 / 89 / 85; launches of a few thousand workgroups lose with wide tiles (RAT-SPN of 784, B = 16 52 -> 56), 256 columns do
-// (641), and so does K = 64 with 128 (784-variable tree, B = 512 68 -> 82): the tiles leave room for fewer workgroups.
+// The same through an LDS tile (input_tile)
 template <int KC, int COLS>
 __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                         const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
-                                                        const int32_t *__restrict__ tab, int32_t K_, int32_t n_cats,
+                                                        const int32_t *__restrict__ tab, int32_t K, int32_t n_cats,
                                                         int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
-    constexpr int LD = COLS + 1, N = KC ? COLS * KC / 1024 : 1, C4 = COLS / 4;
-    const int K = KC ? KC : K_;
     extern __shared__ float smem[];
-    float *tile = smem;                                                 // [K][LD]
-    int *cats = reinterpret_cast<int *>(tile + K * LD);
-    const int u = blockIdx.x;
-    const int64_t b0 = (int64_t)blockIdx.y * COLS;
-    if (threadIdx.x < COLS) cats[threadIdx.x] = (b0 + threadIdx.x < Bs) ? xT[(int64_t)var[u] * Bs + b0 + threadIdx.x] : -1;
-    __syncthreads();
-    const int lps = K / 4;                                              // lanes per sample
-    const float *tbase = tables + (int64_t)tab[u] * n_cats * K;
-    for (int idx0 = threadIdx.x; idx0 < COLS * lps; idx0 += 256 * N) {
-        float4 r[N];
-        int xv[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const int idx = idx0 + 256 * n, sidx = idx / lps, kl = idx - sidx * lps;
-            xv[n] = cats[sidx];
-            r[n] = xv[n] >= 0 ? *reinterpret_cast<const float4 *>(tbase + (int64_t)xv[n] * K + kl * 4) : make_float4(1.f, 1.f, 1.f, 1.f);
-        }
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const int idx = idx0 + 256 * n, sidx = idx / lps, kl = idx - sidx * lps;
-            float4 t = make_float4(__logf(r[n].x), __logf(r[n].y), __logf(r[n].z), __logf(r[n].w));
-            if (xv[n] < 0) {
-                const float v = xv[n] == -1 ? 0.0f : PC_NEG_INF;        // marginalised / tail : out-of-range category
-                t = make_float4(v, v, v, v);
-            }
-            float *dst = tile + (kl * 4) * LD + sidx;
-            dst[0] = t.x; dst[LD] = t.y; dst[2 * LD] = t.z; dst[3 * LD] = t.w;
-        }
-    }
-    __syncthreads();
-    const int32_t id = ids[u];
-    if (threadIdx.x < COLS && b0 + threadIdx.x < Bs) R[(int64_t)(id / K) * Bs + b0 + threadIdx.x] = 0.0f;   // an input block's reference
-    for (int idx = threadIdx.x; idx < K * C4; idx += 256) {
-        const int row = idx / C4, c4 = (idx % C4) * 4;
-        if (b0 + c4 < Bs) {
-            const float *src = tile + row * LD + c4;
-            *reinterpret_cast<float4 *>(l + (int64_t)(id + row) * Bs + b0 + c4) = make_float4(src[0], src[1], src[2], src[3]);
-        }
-    }
+    input_tile<KC, COLS, false>(smem, (int)blockIdx.x, (int64_t)blockIdx.y * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
 }
 
 // table_flow[t][x_b,v][k] += F[n,b] for observed variables.

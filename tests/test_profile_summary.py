@@ -18,3 +18,16 @@ from paper_2406_00766_amd.profile_summary import kernel_class
 ])
 def test_kernel_class(name, cls):
     assert kernel_class(name) == cls
+
+
+@pytest.mark.parametrize("name,cls", [
+    ("void pc::k_chain<false>(float const*, float*)", "sum_fwd"),
+    ("pc::k_chain<true>", "sum_bwd_child"),
+    ("pc::k_sum_16<true, 1, 1>", "sum_bwd_child"),
+    ("pc::k_prod_tile<16, 4>", "prod_fwd"),
+    ("pc::k_class_bwd<2, 8, 16>", "prod_bwd"),
+    ("pc::k_begin_forward<0>", "misc"),
+    ("pc::k_begin_forward<32>", "input_fwd"),
+])
+def test_kernel_class_of_chains_tiles_and_begins(name, cls):
+    assert kernel_class(name) == cls
