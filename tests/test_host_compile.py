@@ -2,6 +2,8 @@
 produces tables that equal the compile oracle's bit for bit (no GPU needed for these calls)."""
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -71,6 +73,34 @@ def test_host_compile_large_configs(idx):
         assert_tables_equal(h, w)
     finally:
         pcb.pc_destroy(h)
+
+
+RING = """
+import resource
+import numpy as np
+from paper_2406_00766_amd import binding as pcb
+from paper_2406_00766_amd import workloads as W
+N, K = 16000, 4
+b = W._Builder(K)
+pairs = {i: [b.add(W.INPUT, var=0, table=0) for _ in range(2)] for i in [*range(0, N, 2), *range(1, N, 2)]}
+root = b.add(W.SUM, n_real=1)
+for i in range(N):
+    p = b.add(W.PRODUCT)
+    for c in pairs[i] + pairs[(i + 1) % N]:
+        b.link(p, c)
+    b.link(root, p, i)
+w = W._make("ring", b, root, N, 1, 2, 1, np.zeros((1, K, K), np.float32), np.zeros((1, 2, K), np.float32), np.zeros((1, 1), np.int32), {})
+before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+pcb.pc_destroy(pcb.pc_compile(w, host_only=True))
+print(resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before)
+"""
+
+
+def test_memory_of_compilation_grows_with_the_circuit():
+    """16 000 pairs of input blocks, each in two products, neighbours in a ring: two sets of 8000 classes of equal parents, but only
+    16 000 of their 64 M pairs are products.  The compiler's tables for these blocks and edges take a few MB."""
+    out = subprocess.run([sys.executable, "-c", RING], cwd=ROOT, check=True, capture_output=True, text=True).stdout
+    assert int(out) < 64 * 1024                                # KiB
 
 
 def test_group_tolerance_and_max_groups_are_honoured():
