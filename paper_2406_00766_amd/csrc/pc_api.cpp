@@ -6,6 +6,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <stdexcept>
 #include <string>
 
 #include "pc_internal.h"
@@ -309,6 +310,15 @@ static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)
 
 using namespace pc;
 
+// The compiler's containers throw; the C entries must not.
+template <class Fn>
+static pc_status no_throw(Fn fn)
+{
+    try { return fn(); }
+    catch (const std::bad_alloc &) { return fail(PC_ERR_ARG, "out of host memory"); }
+    catch (const std::length_error &) { return fail(PC_ERR_ARG, "out of host memory"); }
+}
+
 extern "C" {
 
 const char *pc_last_error(void) { return last_error_cstr(); }
@@ -319,7 +329,7 @@ pc_status pc_compile_host(const pc_dag *dag, pc_circuit **out)
     if (!out) return fail(PC_ERR_ARG, "out is NULL");
     pc_circuit *c = new (std::nothrow) pc_circuit();
     if (!c) return fail(PC_ERR_ARG, "out of host memory");
-    pc_status st = compile_host(dag, c, /*tables_on_host=*/true);
+    const pc_status st = no_throw([&] { return compile_host(dag, c, /*tables_on_host=*/true); });
     if (st != PC_OK) { delete c; return st; }
     *out = c;
     return PC_OK;
@@ -330,9 +340,12 @@ pc_status pc_compile(const pc_dag *dag, void *stream, pc_circuit **out)
     if (!out) return fail(PC_ERR_ARG, "out is NULL");
     pc_circuit *c = new (std::nothrow) pc_circuit();
     if (!c) return fail(PC_ERR_ARG, "out of host memory");
-    pc_status st = compile_host(dag, c, /*tables_on_host=*/false);      // validation, layering, EM and flow maps
-    if (st == PC_OK) st = build_tables_device(dag, c, stream);          // groups (Alg. 2) + tables filled by HIP kernels
-    if (st == PC_OK && !(c->plan = make_plan(c))) st = fail(PC_ERR_ARG, "out of host memory");
+    const pc_status st = no_throw([&] {
+        pc_status s = compile_host(dag, c, /*tables_on_host=*/false);   // validation, layering, EM and flow maps
+        if (s == PC_OK) s = build_tables_device(dag, c, stream);        // groups (Alg. 2) + tables filled by HIP kernels
+        if (s == PC_OK && !(c->plan = make_plan(c))) s = fail(PC_ERR_ARG, "out of host memory");
+        return s;
+    });
     if (st != PC_OK) { pc_destroy(c); return st; }
     const char *env = std::getenv("PC_FORCE_GENERIC");
     set_force_generic(env && env[0] == '1');

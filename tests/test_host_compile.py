@@ -103,6 +103,36 @@ def test_memory_of_compilation_grows_with_the_circuit():
     assert int(out) < 64 * 1024                                # KiB
 
 
+STARVED = """
+import resource
+import numpy as np
+from paper_2406_00766_amd import binding as pcb
+from paper_2406_00766_amd import workloads as W
+N, K = 150000, 2
+b = W._Builder(K)
+s = b.add(W.INPUT, var=0, table=0)
+for i in range(N):
+    p, t = b.add(W.PRODUCT), b.add(W.SUM, n_real=1 if i == N - 1 else None)
+    b.link(p, s)
+    b.link(t, p, i)
+    s = t
+w = W._make("line", b, s, N, 1, 2, 1, np.zeros((1, K, K), np.float32), np.zeros((1, 2, K), np.float32), np.zeros((1, 1), np.int32), {})
+pcb.pc_destroy(pcb.pc_compile(W.hmm(2, 2, 3, 2, 1, 0), host_only=True))
+now = 1024 * int([line.split()[1] for line in open("/proc/self/status") if line.startswith("VmSize")][0])
+resource.setrlimit(resource.RLIMIT_AS, (now + (16 << 20), now + (16 << 20)))
+try:
+    pcb.pc_compile(w, host_only=True)
+except pcb.PcError as e:
+    print(e)
+"""
+
+
+def test_compilation_that_runs_out_of_memory_is_an_error():
+    """A chain of 300 000 blocks with 16 MiB of address space left: an error status, not the end of the process."""
+    r = subprocess.run([sys.executable, "-c", STARVED], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and "PC_ERR_ARG: out of host memory" in r.stdout, (r.returncode, r.stdout, r.stderr)
+
+
 def test_group_tolerance_and_max_groups_are_honoured():
     w = W.reduced(5)
     for G, tol in [(1, 0), (2, 100), (8, 0), (8, 1000)]:
