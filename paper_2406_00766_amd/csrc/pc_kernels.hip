@@ -304,6 +304,9 @@ __device__ inline GroupRow locate_row(const GroupSet &gs, int row)
     return GroupRow{row - gs.first[g], gs.width[g], gs.ids[g], gs.nbr[g], gs.par[g], gs.aux[g]};
 }
 
+template <int>
+__device__ inline GroupRow locate_row(const GroupDev &g, int row) { return GroupRow{row, g.width, g.ids, g.nbr, g.par, g.aux}; }
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -1119,16 +1122,19 @@ __global__ __launch_bounds__(256) void k_param_flow_small(const float *__restric
 // What bounds it: exponentials (a quarter of the vector rate) and MFMAs in turn, eight of each per neighbour.  Measured on
 // 28 sets of 1024 x 1024, 30 % of the 16 x 16 blocks kept, B = 333 (6.2 GFLOP): forward 526 -> 179 us, backward 432 -> 165 us
 // against the vector kernel (64 columns per wave: 205 and 216 us, the operands of four neighbours then take 170 - 210 registers).
-template <bool BWD, int SPLIT, int ROWS>
+// Rows: GroupSet, or GroupDev for a layer of one group.  The set is 332 bytes of kernel arguments in six cache lines, each read before
+// anything else can be: 5 sets of 256 x 256, B = 64, forward 5.5, backward 5.6 and 4.8 us a launch with the set, 5.3, 5.5 and 4.1 with
+// the group alone.
+template <bool BWD, int SPLIT, class Rows>
 __global__ __launch_bounds__(256) void k_sum_16(const float *__restrict__ theta, const float *__restrict__ X, float *__restrict__ l,
                                                 float *__restrict__ R, const float *__restrict__ nfmax, float *__restrict__ F,
-                                                const GroupSet gs, int64_t Bs)
+                                                const Rows rows, int64_t Bs)
 {
     constexpr int K = 16, U = 4, NC = 2;
     __shared__ floatx4 part[SPLIT > 1 ? 4 : 1][NC][SPLIT > 1 ? 64 : 1];
     __shared__ float pref[SPLIT > 1 ? 4 : 1][NC][16];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, j16 = lane & 15;
-    const GroupRow gr = locate_row<ROWS>(gs, blockIdx.x);
+    const GroupRow gr = locate_row<PC_ROWS_MULTI>(rows, blockIdx.x);
     const int r = gr.r;
     const int64_t cg = SPLIT > 1 ? blockIdx.y : (int64_t)blockIdx.y * 4 + wave;   // group of NC column tiles
     if (SPLIT == 1 && cg * NC * 16 >= Bs) return;
@@ -2889,10 +2895,11 @@ static void launch_sum_16(const float *theta, const float *X, float *l, float *R
     const int64_t cgs = Bs / 32;
     const bool split = (int64_t)set_rows(gs) * cgs < 1024 && set_width(gs) >= 8;
     const dim3 grid((unsigned)set_rows(gs), (unsigned)(split ? cgs : (cgs + 3) / 4));
+    const GroupDev one{gs.first[1], gs.width[0], gs.ids[0], gs.nbr[0], gs.par[0], false, gs.aux[0]};
 #define PC_SUM_16(BB, SS)                                                                                                     \
     do {                                                                                                                      \
-        if (gs.n > 1) hipLaunchKernelGGL((k_sum_16<BB, SS, PC_ROWS_MULTI>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, gs, Bs); \
-        else hipLaunchKernelGGL((k_sum_16<BB, SS, PC_ROWS_ONE>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, gs, Bs);    \
+        if (gs.n > 1) hipLaunchKernelGGL((k_sum_16<BB, SS, GroupSet>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, gs, Bs);     \
+        else hipLaunchKernelGGL((k_sum_16<BB, SS, GroupDev>), grid, dim3(256), 0, s, theta, X, l, R, nfmax, F, one, Bs);      \
     } while (0)
     if (F) { if (split) PC_SUM_16(true, 4); else PC_SUM_16(true, 1); }
     else { if (split) PC_SUM_16(false, 4); else PC_SUM_16(false, 1); }
