@@ -165,6 +165,12 @@ pc_status pc_get_group(const pc_circuit *c, int32_t layer, int32_t dir, int32_t 
 pc_status pc_copy_group(const pc_circuit *c, int32_t layer, int32_t dir, int32_t group,
                         int32_t *ids_host, int32_t *nbr_host, int32_t *par_host);
 
+/* The kernel that serves a layer in a pass over B samples, as kernel traces name it with the template arguments that a rule
+ * on sizes chooses ("k_chain<false>", "k_flow<1, 2, 1, true, false>"; of a layer in several launches, the first's), for inspection and tests.  dir 0:
+ * the blocks of the layer are evaluated; dir 1: their flows go to their children, those of input blocks to the tables.  The
+ * text is the calling thread's until its next such call. */
+pc_status pc_get_kernel(const pc_circuit *c, int32_t layer, int32_t dir, int32_t B, const char **name);
+
 /* Workspace (device, caller-owned) for batches of up to B samples.  It holds three node buffers
  * of n_rows x stride floats, row = node offset, samples contiguous (l in R^{N x B} of Sec. 4.3):
  *   l  log-probability residuals, F  node flows, N  log(F) - l of sum rows (the log_nf of Alg. 3 / 4; scratch otherwise),

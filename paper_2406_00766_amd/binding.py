@@ -62,7 +62,7 @@ class pc_profile(C.Structure):
 
 
 EXPORTS = ["pc_compile", "pc_compile_host", "pc_destroy", "pc_last_error", "pc_get_sizes", "pc_get_layer",
-           "pc_get_group", "pc_copy_group", "pc_workspace_layout", "pc_workspace_bytes", "pc_forward",
+           "pc_get_group", "pc_copy_group", "pc_get_kernel", "pc_workspace_layout", "pc_workspace_bytes", "pc_forward",
            "pc_forward_static", "pc_backward", "pc_em_step", "pc_profile_enable", "pc_profile_read", "pc_kernel_class_name",
            "pc_measure_copy", "pc_measure_mfma_f32", "pc_collapse", "pc_collapsed_dag", "pc_collapsed_theta",
            "pc_collapsed_block_map", "pc_collapsed_destroy", "pc_order_for_scratch", "pc_set_wait_limit"]
@@ -87,6 +87,7 @@ def lib():
         L.pc_get_layer.argtypes = [C.c_void_p, C.c_int32, C.POINTER(pc_layer_desc)]
         L.pc_get_group.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.POINTER(pc_group_desc)]
         L.pc_copy_group.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+        L.pc_get_kernel.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_char_p)]
         L.pc_workspace_layout.argtypes = [C.c_void_p, C.c_int32, C.POINTER(pc_ws_layout)]
         L.pc_workspace_bytes.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_size_t)]
         L.pc_forward.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
@@ -253,6 +254,13 @@ def pc_copy_group(handle: int, layer: int, direction: int, group: int):
     par = np.empty((g.n_rows, g.width), dtype=np.int32)
     _check(lib().pc_copy_group(handle, layer, direction, group, ids.ctypes.data, nbr.ctypes.data, par.ctypes.data))
     return ids, nbr, par
+
+
+def pc_get_kernel(handle: int, layer: int, direction: int, B: int) -> str:
+    """The kernel that serves a layer at batch size B (direction 0 forward, 1 backward)."""
+    name = C.c_char_p()
+    _check(lib().pc_get_kernel(handle, layer, direction, int(B), C.byref(name)))
+    return name.value.decode()
 
 
 def pc_workspace_layout(handle: int, B: int) -> pc_ws_layout:

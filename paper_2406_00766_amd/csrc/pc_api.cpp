@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -300,6 +301,14 @@ static ClassesDev classes_dev(const LayerTab &L)
     const int32_t n = (int32_t)L.cls_first.size();
     return ClassesDev{n, (int32_t)L.cls_blk.size() / n, L.d_cls_ptr, L.d_cls_blk, L.d_cls_par_ptr, L.d_cls_par, L.d_cls_first};
 }
+static bool takes_tiles(const pc_circuit *c, const LayerTab &L, const Ws &w)
+{
+    return !w.bf16 && !L.tile.empty() && prod_takes_tiles(c->K, (int32_t)L.blk_ids.size(), max_width(L.fwd), w.Bs);
+}
+static bool takes_bf16(const pc_circuit *c, const std::vector<GroupTab> &groups, const Ws &w)
+{
+    return w.bf16 && groups.size() == 1 && sum_layer_takes_bf16(c->K, 1, groups[0].n_rows, groups[0].width, w.Bs);
+}
 static RowsDev rows_dev(const RowTab &r, size_t li0, bool suffix)
 {
     const int32_t n = r.count_from[li0], first = suffix ? r.count_from[0] - n : 0;
@@ -420,6 +429,54 @@ pc_status pc_copy_group(const pc_circuit *c, int32_t layer, int32_t dir, int32_t
     return PC_OK;
 }
 
+pc_status pc_get_kernel(const pc_circuit *c, int32_t layer, int32_t dir, int32_t B, const char **name)
+{
+    static thread_local char text[64];
+    if (!c || !name) return fail(PC_ERR_ARG, "NULL argument");
+    if (layer < 0 || layer >= (int32_t)c->layers.size() || dir < 0 || dir > 1) return fail(PC_ERR_ARG, "layer / dir out of range");
+    if (B < 1 || B > PC_MAX_BATCH) return fail(PC_ERR_ARG, "B out of range");
+    return no_throw([&] {
+        const Ws w = ws_layout(c, B);
+        const LayerTab &L = c->layers[layer];
+        const int32_t K = c->K;
+        const bool bwd = dir == 1;
+        const size_t li0 = flow_start(c, w, bwd);
+        const auto print = [&](auto... args) { std::snprintf(text, sizeof(text), args...); };
+        const auto truth = [](bool b) { return b ? "true" : "false"; };
+        if (L.kind == KIND_INPUT) {
+            const GroupDev g = dev(L.fwd[0]);
+            const int cols = input_tile_cols(g, K, w.Bs);
+            if (bwd) print("%s", "k_input_bwd");
+            else if (input_in_begin(g, K, w.Bs)) print("k_begin_forward<%d>", (int)K);
+            else if (cols) print("k_input_fwd_tile<%d, %d>", K == 32 || K == 64 ? (int)K : 0, cols);
+            else print("%s", "k_input_fwd");
+        } else if (L.kind == KIND_PRODUCT) {
+            const bool rows = (size_t)layer >= li0;                     // the rows of a dataflow part
+            if (bwd) print("%s", !rows && !L.cls_first.empty() ? "k_class_bwd" : "k_prod_bwd");
+            else if (rows || !takes_tiles(c, L, w)) print("%s", "k_prod_fwd");
+            else {
+                const ProdTile t = prod_tile_shape((int32_t)(L.tile.size() / PROD_TILE_WORDS), K, w.Bs);
+                print("k_prod_tile<%d, %d>", t.pairs, t.side);
+            }
+        } else if ((size_t)layer >= li0) {
+            if (chain_dev(c, bwd ? c->chain_bwd : c->chain_fwd, li0, !bwd).n_links > 0) {
+                print("k_chain<%s>", truth(bwd));
+            } else {
+                const FlowShape f = flow_shape(flow_dev(c, bwd ? c->flow_bwd : c->flow_fwd, li0, !bwd), bwd, K, w.Bs);
+                print("k_flow<%d, %d, %d, %s, %s>", f.waves, f.tiles, f.chunks, truth(bwd), truth(f.exact));
+            }
+        } else if (takes_bf16(c, bwd ? L.bwd : L.fwd, w)) {
+            print("k_sum_bf16<%s>", truth(bwd));
+        } else {
+            std::vector<GroupDev> groups;
+            for (const GroupTab &g : bwd ? L.bwd : L.fwd) groups.push_back(dev(g));
+            sum_kernel_name(text, make_group_sets(groups)[0], bwd, K, w.Bs);
+        }
+        *name = text;
+        return PC_OK;
+    });
+}
+
 pc_status pc_workspace_layout(const pc_circuit *c, int32_t B, pc_ws_layout *out)
 {
     if (!c || !out) return fail(PC_ERR_ARG, "NULL argument");
@@ -478,12 +535,12 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_INPUT) {
             if (!input_in_begin(dev(L.fwd[0]), K, w.Bs)) launch_input_fwd(tables, xT, dev(L.fwd[0]), K, c->n_cats, w.Bs, l, R, s);
-        } else if (L.kind == KIND_PRODUCT && !w.bf16 && !L.tile.empty() && prod_takes_tiles(K, (int32_t)L.blk_ids.size(), max_width(L.fwd), w.Bs)) {
+        } else if (L.kind == KIND_PRODUCT && takes_tiles(c, L, w)) {
             launch_prod_fwd_tiles(l, R, L.d_tile, (int32_t)(L.tile.size() / PROD_TILE_WORDS), L.d_tile_order, L.d_cls_blk, K, w.Bs, s);
         } else if (L.kind == KIND_PRODUCT) {
             launch_prod_fwd(l, c->product_scratch ? window_base(c, L, l, w.Bs) : l, R, plan.layers[li].fwd, K, w.Bs,
                             w.bf16 ? base + w.ph_off : nullptr, w.bf16 ? base + w.pl_off : nullptr, s);
-        } else if (w.bf16 && L.fwd.size() == 1 && sum_layer_takes_bf16(K, 1, L.fwd[0].n_rows, L.fwd[0].width, w.Bs)) {
+        } else if (takes_bf16(c, L.fwd, w)) {
             launch_sum_bf16(base + w.th_off, base + w.tl_off, base + w.ph_off, base + w.pl_off, l, R, nullptr, nullptr, false,
                             plan.layers[li].fwd[0], K, w.Bs, s);
         } else {
@@ -580,8 +637,7 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     bool theta_t_split = false;
     for (size_t li = li0; li-- > 0;) {
         const LayerTab &L = c->layers[li];
-        if (L.kind == KIND_SUM && w.bf16 && L.bwd.size() == 1 &&
-            sum_layer_takes_bf16(K, 1, L.bwd[0].n_rows, L.bwd[0].width, w.Bs)) {
+        if (L.kind == KIND_SUM && takes_bf16(c, L.bwd, w)) {
             // long dense rows: bf16 matrix cores on planes of theta^T (once per pass) and of this layer's exp(log_nf - max)
             if (!theta_t_split) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, true, base + w.tth_off, base + w.ttl_off, s);
             theta_t_split = true;

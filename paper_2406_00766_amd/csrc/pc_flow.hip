@@ -736,22 +736,29 @@ void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, con
                        n_cb, root_id, K, Bs, B, ent, n_ent, ticket);
 }
 
+// As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
+// 16 x 32 states); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
+// us two at a time, 324 four; fewer waves with two chunks each lost everywhere but on a 3072-variable tree's forward pass, 2587 ->
+// 2502).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
+// the widest layer has at most 128 tasks of them, 16 -> 32: HMM T = 60, H = 1024, B = 20 (128 tasks) 281 -> 324 us, T = 40, H = 256, B =
+// 10 (32) 90 -> 100, T = 50, H = 64, B = 400 (104) 98 -> 101; T = 32, H = 512, B = 77 (192) 131 -> 126, trees (thousands in their lower
+// layers) of 784 variables, M = 128, B = 512 788 -> 650, of 500, M = 64, B = 30 120 -> 114.  64 rows and 32 columns lost.
+FlowShape flow_shape(const FlowDev &f, bool bwd, int32_t K, int64_t Bs)
+{
+    const int chunks = f.max_nbr * (K / 32);
+    return FlowShape{chunks <= 2 ? chunks : chunks <= 4 ? 4 : 8, f.max_level * (int64_t)(K / 16) * (Bs / 16) <= 128 ? 1 : 2,
+                     chunks <= 8 ? 1 : chunks <= 16 ? 2 : 4, !bwd && f.max_items > 8};
+}
+
 void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
                  int32_t *ticket, float *ll, int32_t wait_limit, int32_t *fault, hipStream_t s)
 {
     if (f.n_ent == 0) return;
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
-    // As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
-    // 16 x 32 states); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
-    // us two at a time, 324 four; fewer waves with two chunks each lost everywhere but on a 3072-variable tree's forward pass, 2587 ->
-    // 2502).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
-    // the widest layer has at most 128 tasks of them, 16 -> 32: HMM T = 60, H = 1024, B = 20 (128 tasks) 281 -> 324 us, T = 40, H = 256, B =
-    // 10 (32) 90 -> 100, T = 50, H = 64, B = 400 (104) 98 -> 101; T = 32, H = 512, B = 77 (192) 131 -> 126, trees (thousands in their lower
-    // layers) of 784 variables, M = 128, B = 512 788 -> 650, of 500, M = 64, B = 30 120 -> 114.  64 rows and 32 columns lost.
     // Workgroups: enough to hold a layer's tasks and the next ones' operands; those beyond that only poll.  256 / 512 measured: eight waves
     // (one workgroup per CU is 256) HMM T = 32, H = 512, B = 77 126 / 154 us, T = 40, H = 256, B = 10 90 / 98; one and two waves, trees of
     // 800 variables, M = 32, B = 300 166 / 167, HMM T = 50, H = 64, B = 400 98 / 101; four waves, trees, no difference.
-    const int chunks = f.max_nbr * (K / 32);
+    const FlowShape sh = flow_shape(f, bwd, K, Bs);
 #define PC_FLOW(WW, RR, HH)                                                                                                  \
     do {                                                                                                                     \
         const int n_ct = (int)(Bs / 16);                                                                                     \
@@ -759,17 +766,17 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
         const int grid = (int)std::min<int64_t>(tasks, WW == 8 ? 256 : WW == 4 ? 512 : 320);                                 \
         if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                     f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);               \
-        else if (f.max_items > 8) hipLaunchKernelGGL((k_flow<WW, RR, HH, false, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, \
+        else if (sh.exact) hipLaunchKernelGGL((k_flow<WW, RR, HH, false, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, \
                                 mail, f.ent, f.rec, f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);     \
         else hipLaunchKernelGGL((k_flow<WW, RR, HH, false, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                 f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);                   \
     } while (0)
-#define PC_FLOW_ROWS(WW, HH) do { if (f.max_level * (int64_t)(K / 16) * (Bs / 16) <= 128) PC_FLOW(WW, 1, HH); else PC_FLOW(WW, 2, HH); } while (0)
-    if (chunks == 1) PC_FLOW_ROWS(1, 1);
-    else if (chunks == 2) PC_FLOW_ROWS(2, 1);
-    else if (chunks <= 4) PC_FLOW_ROWS(4, 1);
-    else if (chunks <= 8) PC_FLOW_ROWS(8, 1);
-    else if (chunks <= 16) PC_FLOW_ROWS(8, 2);
+#define PC_FLOW_ROWS(WW, HH) do { if (sh.tiles == 1) PC_FLOW(WW, 1, HH); else PC_FLOW(WW, 2, HH); } while (0)
+    if (sh.waves == 1) PC_FLOW_ROWS(1, 1);
+    else if (sh.waves == 2) PC_FLOW_ROWS(2, 1);
+    else if (sh.waves == 4) PC_FLOW_ROWS(4, 1);
+    else if (sh.chunks == 1) PC_FLOW_ROWS(8, 1);
+    else if (sh.chunks == 2) PC_FLOW_ROWS(8, 2);
     else PC_FLOW_ROWS(8, 4);
 #undef PC_FLOW_ROWS
 #undef PC_FLOW

@@ -89,6 +89,7 @@ struct Timed {                                          // brackets one kernel l
 void launch_fill(float *p, int64_t n, float v, hipStream_t s);
 void launch_readout(const float *l, const float *R, int64_t root_row, int64_t root_blk, int64_t Bs, int32_t B, float *ll,
                     hipStream_t s);
+int input_tile_cols(const GroupDev &g, int32_t K, int64_t Bs);
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
                       float *l, float *R, hipStream_t s);
 void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
@@ -105,6 +106,8 @@ void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, floa
                      int64_t Bs, void *Ph, void *Pl, hipStream_t s);
 // Product layer over classes of input blocks: forward, tiles of products (LayerTab::tile); backward, a class's flow stored to its blocks
 bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs);   // width: most children of a product
+struct ProdTile { int pairs, side; };                                   // k_prod_tile's template arguments: column pairs, side x side products
+ProdTile prod_tile_shape(int32_t n_tiles, int32_t K, int64_t Bs);
 void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,
                            int64_t Bs, hipStream_t s);
 void launch_prod_bwd_classes(float *F, const ClassesDev &c, int32_t K, int64_t Bs, hipStream_t s);
@@ -113,6 +116,7 @@ void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, in
 void launch_prod_bwd_rows(const float *l, float *F, float *N, float *nfmax, const RowsDev &rows, int32_t K, int64_t Bs, void *Ph,
                           void *Pl, hipStream_t s);
 // lch: base the product children are read from; l: base of the sum rows written
+void sum_kernel_name(char (&name)[64], const GroupSet &gs, bool bwd, int32_t K, int64_t Bs);
 void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, const std::vector<GroupSet> &sets, int32_t K,
                     int64_t Bs, hipStream_t s);
 void launch_sum_bwd_child(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *F,
@@ -136,6 +140,8 @@ void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow
 // pc_flow.hip: the first launch of a forward / backward pass (ent, n_ent: blocks the dataflow launch will publish) and the
 // dataflow launch itself (fault: set to 1 if a wait was given up after wait_limit polls)
 // (in: the input layer, evaluated here if input_in_begin)
+struct FlowShape { int waves, tiles, chunks; bool exact; };             // k_flow's template arguments: waves, row tiles of 16, chunks per wave
+FlowShape flow_shape(const FlowDev &f, bool bwd, int32_t K, int64_t Bs);
 bool input_in_begin(const GroupDev &in, int32_t K, int64_t Bs);
 void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int32_t D, int64_t Bs, int32_t n_cats, int32_t *xT,
                           float *l, float *R, float *mail, bool null_mail, const int32_t *ent, int32_t n_ent, int32_t K,

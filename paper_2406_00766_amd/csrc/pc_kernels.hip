@@ -22,6 +22,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdint>
+#include <cstdio>
 #include <cstring>
 
 #include "pc_device.h"
@@ -2614,16 +2615,23 @@ void launch_readout(const float *l, const float *R, int64_t root_row, int64_t ro
     hipLaunchKernelGGL(k_readout, dim3((B + 255) / 256), dim3(256), 0, s, l, R, root_row, root_blk, Bs, B, ll);
 }
 
+// Columns of an input tile, 0: no tile (larger blocks: it costs occupancy, rows are long enough).
+int input_tile_cols(const GroupDev &g, int32_t K, int64_t Bs)
+{
+    if ((K & 3) != 0 || K > 64) return 0;
+    return K == 32 && g.n_rows * (Bs / 128) >= 2048 ? 128 : 64;
+}
+
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
                       float *l, float *R, hipStream_t s)
 {
     Timed timed(KC_INPUT_FWD, s);
     if (g.n_rows == 0) return;
-    if ((K & 3) == 0 && K <= 64) {                                    // larger blocks: the tile costs occupancy, rows are long enough
+    if (input_tile_cols(g, K, Bs) > 0) {
 #define PC_INPUT_TILE(KK, CC) \
         hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), dim3((unsigned)g.n_rows, (unsigned)((Bs + CC - 1) / CC)), dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, \
                            tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l, R)
-        if (K == 32 && g.n_rows * (Bs / 128) >= 2048) PC_INPUT_TILE(32, 128);
+        if (input_tile_cols(g, K, Bs) == 128) PC_INPUT_TILE(32, 128);
         else if (K == 32) PC_INPUT_TILE(32, 64);
         else if (K == 64) PC_INPUT_TILE(64, 64);
         else PC_INPUT_TILE(0, 64);
@@ -2779,13 +2787,18 @@ bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs)
 
 // 2 x 2 products a workgroup where 4 x 4 would not give every CU two: RAT-SPN of 784 variables, forward pass at B = 16 251 us with k_prod_fwd,
 // 244 in 128 workgroups, 228 in 512.
+ProdTile prod_tile_shape(int32_t n_tiles, int32_t K, int64_t Bs)
+{
+    const int pairs = K == 64 ? 8 : 16;
+    return ProdTile{pairs, (int64_t)n_tiles * (Bs / (2 * pairs)) < 512 ? 2 : 4};
+}
 void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,
                            int64_t Bs, hipStream_t s)
 {
     Timed timed(KC_PROD_FWD, s);
-    const int64_t cols = K == 64 ? 16 : 32;
-    const bool small = (int64_t)n_tiles * (Bs / cols) < 512;
-    const int64_t wgs = (int64_t)((n_tiles * (small ? 4 : 1) + 3) & ~3) * (Bs / cols);
+    const ProdTile t = prod_tile_shape(n_tiles, K, Bs);
+    const bool small = t.side == 2;
+    const int64_t wgs = (int64_t)((n_tiles * (small ? 4 : 1) + 3) & ~3) * (Bs / (2 * t.pairs));
     const dim3 grid((unsigned)((wgs + 31) / 32 * 32));
 #define PC_PROD_TILE(CC, TT) hipLaunchKernelGGL((k_prod_tile<CC, TT>), grid, dim3(512), 0, s, l, R, tile, n_tiles, order, cls_blk, K, Bs)
     if (K == 64) { if (small) PC_PROD_TILE(8, 2); else PC_PROD_TILE(8, 4); }
@@ -2884,6 +2897,22 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
     const int64_t tiles = (int64_t)n_rows * (K / (32 * rt)) * col_tiles;
     split = 1;
     while (split < (rt == 1 ? 16 : 4) && tiles * split < want && (int64_t)width * (K / 32) >= (split < 4 ? 2 : 4) * split) split <<= 1;
+}
+
+void sum_kernel_name(char (&name)[64], const GroupSet &gs, bool bwd, int32_t K, int64_t Bs)
+{
+    const char *dir = bwd ? "bwd" : "fwd";
+    if (use_mfma(K)) {
+        int rt, split;
+        pick_sum_shape(K, set_rows(gs), set_width(gs), Bs, rt, split);
+        std::snprintf(name, sizeof(name), "k_sum_mfma<%d, %d, %d, %s>", (int)K, rt, split, bwd ? "true" : "false");
+    } else if (use_16(K)) {
+        std::snprintf(name, sizeof(name), "k_sum_16<%s>", bwd ? "true" : "false");
+    } else if (use_small(K)) {
+        std::snprintf(name, sizeof(name), "k_sum_%s_small<%d>", dir, (int)K);
+    } else {
+        std::snprintf(name, sizeof(name), bwd ? "k_sum_bwd_child_generic" : "k_sum_fwd_generic");
+    }
 }
 
 // K = 16: forward (F null; X = l of the children) or backward to the children (X = log_nf).  The neighbours of a row

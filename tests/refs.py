@@ -68,3 +68,13 @@ def latent_tree_loglik_torch(parent, order, log_pi, log_W, log_tab, x):
             m = m + torch.logsumexp(log_W[c][None, :, :] + msg[c][:, None, :], dim=2)
         msg[v] = m
     return torch.logsumexp(log_pi[None, :] + msg[0], dim=1)
+
+
+def kernels(w, direction, B=None):
+    """The kernel that serves each layer of a workload's circuit, 0 forward, 1 backward."""
+    from paper_2406_00766_amd import binding as pcb
+    h = pcb.pc_compile(w, host_only=True)
+    try:
+        return [pcb.pc_get_kernel(h, li, direction, B or w.B) for li in range(pcb.pc_get_sizes(h).n_layers)]
+    finally:
+        pcb.pc_destroy(h)

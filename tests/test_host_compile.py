@@ -133,6 +133,21 @@ def test_compilation_that_runs_out_of_memory_is_an_error():
     assert r.returncode == 0 and "PC_ERR_ARG: out of host memory" in r.stdout, (r.returncode, r.stdout, r.stderr)
 
 
+def test_kernel_of_a_layer():
+    """pc_get_kernel needs no GPU: the rules on sizes, and its errors."""
+    h = pcb.pc_compile(W.hmm(4, 32, 5, 32, 1, 0, draw=False), host_only=True)
+    assert [pcb.pc_get_kernel(h, li, 0, 7) for li in range(3)] == ["k_begin_forward<32>", "k_prod_fwd", "k_chain<false>"]
+    assert [pcb.pc_get_kernel(h, li, 1, 7) for li in range(3)] == ["k_input_bwd", "k_prod_bwd", "k_chain<true>"]
+    assert pcb.pc_get_kernel(h, 2, 0, 16384) == "k_sum_mfma<32, 1, 1, false>"
+    pcb.pc_set_wait_limit(h, 5)                                # launches that wait only
+    assert pcb.pc_get_kernel(h, 2, 0, 7) == "k_flow<1, 1, 1, false, false>"
+    for bad in ((9, 0, 1), (-1, 0, 1), (0, 2, 1), (0, 0, 0), (0, 0, (1 << 21) + 1)):
+        with pytest.raises(pcb.PcError) as e:
+            pcb.pc_get_kernel(h, *bad)
+        assert e.value.status_name == "PC_ERR_ARG"
+    pcb.pc_destroy(h)
+
+
 def test_group_tolerance_and_max_groups_are_honoured():
     w = W.reduced(5)
     for G, tol in [(1, 0), (2, 100), (8, 0), (8, 1000)]:
