@@ -251,7 +251,8 @@ const char *pc_kernel_class_name(int32_t cls);
 
 /* Polls after which a wait inside a dataflow launch is given up (2^22 after pc_compile: some seconds).  The limit is the
  * handle's and applies from the next call on; 0 gives up on the first value that is not there yet, which is how the error
- * path is tested. */
+ * path is tested.  Any other limit than the first also sends chains of single blocks of 32 nodes, which are walked without waits
+ * (k_chain), through a launch that waits; log-likelihoods and flows agree within the same tolerances. */
 pc_status pc_set_wait_limit(pc_circuit *c, int32_t polls);
 
 /* Achievable peaks of the device the calling thread has current, for quoting beside the published ones (measurement
