@@ -8,6 +8,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2406_00766_amd import binding as pcb
 from paper_2406_00766_amd import workloads as W
+from tests.refs import kernels
 from tests.test_gpu_parity import check_all
 
 pytestmark = pytest.mark.gpu
@@ -43,17 +44,19 @@ def test_dataflow_layers_match_oracle(make):
     c.close()
 
 
-@pytest.mark.parametrize("K,H,B", [
-    (64, 64, 512), (64, 64, 513),                              # two chunks: 128 tasks of 16 rows in a layer, then 32 rows
-    (32, 128, 256), (32, 128, 257),                            # four chunks
-    (64, 256, 128), (64, 256, 129),                            # eight
-    (64, 512, 64), (64, 512, 65),                              # sixteen: two per wave
-    (128, 640, 16), (128, 640, 65),                            # twenty: up to four per wave
+@pytest.mark.parametrize("K,H,B,waves,tiles,chunks", [
+    (64, 64, 512, 2, 1, 1), (64, 64, 513, 2, 2, 1),            # two chunks: 128 tasks of 16 rows in a layer, then 32 rows
+    (32, 128, 256, 4, 1, 1), (32, 128, 257, 4, 2, 1),          # four chunks
+    (64, 256, 128, 8, 1, 1), (64, 256, 129, 8, 2, 1),          # eight
+    (64, 512, 64, 8, 1, 2), (64, 512, 65, 8, 2, 2),            # sixteen: two per wave
+    (128, 640, 16, 8, 1, 4), (128, 640, 65, 8, 2, 4),          # twenty: up to four per wave
 ])
-def test_tile_shapes_match_oracle(K, H, B):
-    """HMMs on both sides of the line between row tiles of 16 and 32, for every number of waves and chunks per wave."""
+def test_tile_shapes_match_oracle(K, H, B, waves, tiles, chunks):
+    """HMMs on both sides of the line between row tiles of 16 and 32, for every number of waves from two on and chunks per wave."""
     w = W.hmm(4, H, 30, K, B, 90, alpha_trans=0.2)
     print(f"case tile shape K={K} H={H} B={B}", flush=True)
+    assert kernels(w, 0)[4] == f"k_flow<{waves}, {tiles}, {chunks}, false, false>"
+    assert kernels(w, 1)[4] == f"k_flow<{waves}, {tiles}, {chunks}, true, false>"
     check_all(w)
 
 
@@ -90,6 +93,30 @@ class Dag(W._Builder):
                     theta[p + 1, :rows] = w[:, j * K:(j + 1) * K]
         tables = np.ascontiguousarray(np.stack([W._f32_floor(W._dirichlet_rows(rng, table_alpha, (K, n_cats))).T for _ in range(n)]))
         return W._make(f"dag_{seed}", self, root, self.n_params, n, n_cats, n, theta, tables, rng.integers(0, n_cats, size=(B, n)), {})
+
+
+def parallel_lines(B):
+    """Five lines of four sum blocks, each over one product of the block before and eight inputs, that meet in one product."""
+    d = Dag(32)
+    ends = [d.input() for _ in range(5)]
+    for _ in range(4):
+        ends = [d.sum([d.product([s] + [d.input() for _ in range(8)])]) for s in ends]
+    return d.workload(d.sum([d.product(ends)], n_real=1), B, 97)
+
+
+@pytest.mark.parametrize("make,B,tiles,exact", [
+    (lambda B: W.hclt(16, 32, 32, B, 96, n_cats=8), 100, 1, False), (lambda B: W.hclt(16, 32, 32, B, 96, n_cats=8), 300, 2, False),
+    (parallel_lines, 192, 1, True), (parallel_lines, 193, 2, True),      # 120 and 140 tasks of 16 rows
+])
+def test_rows_of_one_block_match_oracle(make, B, tiles, exact):
+    """One wave per task (rows of one neighbour block of 32 nodes, several blocks a layer): row tiles of 16 and 32, products of
+    few children and of nine."""
+    w = make(B)
+    print(f"case one wave {w.name} B={B}", flush=True)
+    for direction, e in ((0, exact), (1, False)):
+        want = f"k_flow<1, {tiles}, 1, {'true' if direction else 'false'}, {'true' if e else 'false'}>"
+        assert [k for k in kernels(w, direction) if k.startswith(("k_sum", "k_flow", "k_chain"))].count(want) > 2
+    check_all(w)
 
 
 @pytest.mark.parametrize("K,B", [(32, 20), (64, 1)])
