@@ -1,24 +1,30 @@
 """Input layer through LDS tiles: 64 and 128 columns a workgroup, last tiles partly outside the batch, block sizes with a kernel of their own
-and without; masked and out-of-range categories."""
+and without, in a launch of its own (on the transposed batch) and in the one that begins the pass (on the batch itself), on both sides of the
+line between them; masked and out-of-range categories.  The kernels are asserted."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 from paper_2406_00766_amd import workloads as W
+from tests.refs import kernels
 from tests.test_gpu_parity import check_all
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,S,K,B", [
-    (64, 256, 32, 150), (64, 256, 32, 256), (64, 256, 32, 290),     # 2048 input blocks: 128 columns, the last tile whole and cut
-    (64, 256, 32, 100), (20, 64, 32, 70),                           # 64 columns
-    (24, 128, 64, 97), (12, 60, 20, 65), (12, 12, 12, 130),
+@pytest.mark.parametrize("D,S,K,B,kernel", [
+    (64, 256, 32, 150, "k_input_fwd_tile<32, 128>"), (64, 256, 32, 256, "k_input_fwd_tile<32, 128>"),   # 2048 input blocks: the last tile
+    (64, 256, 32, 290, "k_input_fwd_tile<32, 128>"),                                                    # whole and cut
+    (65, 256, 32, 90, "k_input_fwd_tile<32, 64>"), (65, 256, 64, 200, "k_input_fwd_tile<64, 64>"),      # 4160 workgroups of 64 columns
+    (64, 256, 32, 100, "k_begin_forward<32>"), (64, 256, 64, 200, "k_begin_forward<64>"),               # 4096
+    (20, 64, 32, 70, "k_begin_forward<32>"), (24, 128, 64, 97, "k_begin_forward<64>"),
+    (12, 60, 20, 65, "k_input_fwd_tile<0, 64>"), (12, 12, 12, 130, "k_input_fwd_tile<0, 64>"),
 ])
-def test_input_tiles_match_oracle(D, S, K, B):
+def test_input_tiles_match_oracle(D, S, K, B, kernel):
     w = W.rat_spn(D, 2, 4, S, K, B, 96, n_cats=11)
     print(f"case input tiles D={D} S={S} K={K} B={B}", flush=True)
+    assert kernels(w, 0)[0] == kernel
     rng = np.random.default_rng(7)
     mask = (rng.random(w.x.shape) < 0.2).astype(np.uint8)
     x = w.x.copy()
