@@ -1,15 +1,22 @@
-"""Chains of up to 64 nodes a layer, walked by one workgroup per 16 samples: against the oracle for both widths and block sizes, one link
-and many, one sample to several workgroups, masked and impossible values, and circuits that are almost chains."""
+"""Chains of single blocks of 32 nodes, walked by one wave per 16 samples (k_chain): against the oracle with one link and many, one
+sample to several waves, masked and impossible values; HMMs of 64 states and circuits that are almost chains, which are not theirs.
+The kernels are asserted."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 from paper_2406_00766_amd import workloads as W
+from tests.refs import kernels
 from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all
 
 pytestmark = pytest.mark.gpu
+
+
+def chains(w):
+    """Whether the forward and the backward pass walk a chain."""
+    return tuple(any(k.startswith("k_chain") for k in kernels(w, direction)) for direction in (0, 1))
 
 
 @pytest.mark.parametrize("K,H,T,B", [
@@ -23,6 +30,7 @@ def test_chains_match_oracle(K, H, T, B):
     x = w.x.copy()
     if B > 4:
         x[3, 0] = w.n_cats + 2; mask[3, 0] = 0                 # a sample of probability 0
+    assert chains(w) == (K == H == 32, K == H == 32)
     check_all(w.with_batch(x), mask)
 
 
@@ -47,4 +55,6 @@ def test_almost_chains_match_oracle(kind, K, B):
         t = d.sum([d.product([s[0]])])
         for _ in range(4): t = d.sum([d.product([t])])
     print(f"case almost a chain {kind} K={K} B={B}", flush=True)
-    check_all(d.workload(root, B, 95))
+    w = d.workload(root, B, 95)
+    assert chains(w) == (K == 32 and kind == "untied", K == 32 and kind in ("untied", "two_inputs"))   # (two inputs: no matter to flows)
+    check_all(w)
