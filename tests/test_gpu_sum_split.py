@@ -4,24 +4,27 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from tests.refs import kernels
 from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K,widths,B", [
-    (32, [15] * 3, 20), (32, [16] * 16, 33), (32, [31] * 9, 1), (32, [33] * 33, 40),    # four, eight and sixteen waves
-    (64, [8] * 7, 50), (64, [17] * 17, 3), (128, [4] * 4, 60), (128, [9] * 9, 20),
-    (32, [3, 20, 37], 70), (64, [2, 18], 1), (128, [9, 1, 2], 33),                      # several groups in a launch
-    (32, [40] * 64, 200),                                                               # tiles enough: fewer waves again
+@pytest.mark.parametrize("K,widths,B,waves", [
+    (32, [15] * 3, 20, (4, 2)), (32, [16] * 16, 33, (8, 8)), (32, [31] * 9, 1, (8, 4)), (32, [33] * 33, 40, (16, 16)),
+    (64, [8] * 7, 50, (8, 4)), (64, [17] * 17, 3, (16, 16)), (128, [4] * 4, 60, (8, 8)), (128, [9] * 9, 20, (16, 16)),
+    (32, [3, 20, 37], 70, (16, 2)), (64, [2, 18], 1, (16, 4)), (128, [9, 1, 2], 33, (16, 4)),   # several groups in a launch
+    (32, [40] * 64, 200, (8, 8)),                                                               # tiles enough: fewer waves again
 ])
-def test_split_reductions_match_oracle(K, widths, B):
-    """Sum blocks over products of thirteen inputs (too many for a dataflow launch), one single-child product over each, a root."""
+def test_split_reductions_match_oracle(K, widths, B, waves):
+    """Waves that share a tile forward and backward.  Sum blocks over products of thirteen inputs (too many for a dataflow launch), one single-child product over each, a root."""
     d = Dag(K)
     inputs = [d.input() for _ in range(13)]
     products = [d.product(inputs) for _ in range(max(widths))]
     sums = [d.sum(products[:n]) for n in widths]
     w = d.workload(d.sum([d.product([s]) for s in sums], n_real=1), B, 91)
     print(f"case split K={K} widths={widths[:3]}x{len(widths)} B={B}", flush=True)
+    for direction, n in enumerate(waves):
+        assert kernels(w, direction)[2] == f"k_sum_mfma<{K}, 1, {n}, {'true' if direction else 'false'}>"
     check_all(w)
