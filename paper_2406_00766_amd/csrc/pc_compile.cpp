@@ -16,6 +16,7 @@
 #include <limits>
 #include <map>
 #include <numeric>
+#include <unordered_map>
 
 #include "pc_internal.h"
 
@@ -435,41 +436,53 @@ void compile_classes(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> 
             }
             if (!inputs_only) break;
         }
-        for (int32_t u : members) seen[u] = 0;
-        if (!inputs_only || 2 * (int64_t)members.size() > reads) continue;
-        // blocks by their parents in this layer, then by BWD_FIRST; equal ones become neighbours (lists are ascending)
-        std::vector<std::pair<int32_t, int32_t>> par(n);  // block -> its parents' range in `at`; a hash of them decides most comparisons
-        std::vector<uint64_t> hash(n, 0);
-        std::vector<int32_t> at;
-        for (int32_t u : members) {
-            par[u].first = (int32_t)at.size();
+        const bool shared = inputs_only && 2 * (int64_t)members.size() <= reads;
+        for (int32_t u : members) seen[u] = shared;
+        if (!shared) continue;
+        members.clear();                                  // again, ascending
+        for (int32_t u = 0; u < n; ++u) if (seen[u]) { seen[u] = 0; members.push_back(u); }
+        // Classes: blocks with equal parents in this layer and equal BWD_FIRST (lists are ascending), told apart by a hash that is unique to
+        // a class.  Only a class's first list is kept; sorting the blocks by hash and list took five times as long (25 K blocks of a
+        // RAT-SPN of 784 variables: 8.2 ms, now 1.7; pc_compile 9.1 -> 7.2 ms).
+        std::unordered_map<uint64_t, int32_t> found;
+        std::vector<std::pair<uint64_t, int32_t>> cls;    // hash, number in the order of first blocks
+        std::vector<int32_t> at, at_ptr(1, 0), size, first, of(members.size());
+        for (size_t i = 0; i < members.size(); ++i) {
+            const int32_t u = members[i], b = at_ptr.back();
+            uint64_t hash = 0;
+            int32_t q = -1;
             for (int32_t k = par_ptr[u]; k < par_ptr[u + 1]; ++k)
                 if (layer_of[par_of[k]] == li) at.push_back((par_of[k] + 1) * K);
             at.push_back(c->an_first_parent_depth[u] == T.depth ? -1 : -2);
-            par[u].second = (int32_t)at.size();
-            for (int32_t k = par[u].first; k < par[u].second; ++k) hash[u] = (hash[u] ^ (uint32_t)at[k]) * 0x9E3779B97F4A7C15ull;
-        }
-        auto less = [&](int32_t a, int32_t b) {
-            if (hash[a] != hash[b]) return hash[a] < hash[b];
-            return std::lexicographical_compare(at.begin() + par[a].first, at.begin() + par[a].second, at.begin() + par[b].first, at.begin() + par[b].second);
-        };
-        std::sort(members.begin(), members.end(), [&](int32_t a, int32_t b) { return less(a, b) || (a < b && !less(b, a)); });
-        T.cls_ptr.assign(1, 0); T.cls_par_ptr.assign(1, 0);
-        for (size_t k0 = 0, k1; k0 < members.size(); k0 = k1) {
-            const int32_t u0 = members[k0];
-            for (k1 = k0; k1 < members.size() && !less(u0, members[k1]); ++k1) {
-                T.cls_blk.push_back((members[k1] + 1) * K);
-                if (par_ptr[members[k1] + 1] - par_ptr[members[k1]] == par[u0].second - par[u0].first - 1) rep[members[k1]] = u0;
+            for (size_t k = b; k < at.size(); ++k) hash = (hash ^ (uint32_t)at[k]) * 0x9E3779B97F4A7C15ull;
+            for (;; ++hash) {
+                const auto it = found.try_emplace(hash, (int32_t)cls.size());
+                q = it.first->second;
+                if (it.second) {
+                    cls.push_back({hash, q}); size.push_back(0); first.push_back(u);
+                    at_ptr.push_back((int32_t)at.size());
+                    break;
+                }
+                if (std::equal(at.begin() + at_ptr[q], at.begin() + at_ptr[q + 1], at.begin() + b, at.end())) { at.resize(b); break; }
             }
-            T.cls_ptr.push_back((int32_t)T.cls_blk.size());
-            T.cls_par.insert(T.cls_par.end(), at.begin() + par[u0].first, at.begin() + par[u0].second - 1);
+            of[i] = q;
+            ++size[q];
+            if (par_ptr[u + 1] - par_ptr[u] == at_ptr[q + 1] - 1 - at_ptr[q]) rep[u] = first[q];
+        }
+        if (2 * cls.size() > members.size()) continue;    // too few blocks share their parents
+        std::sort(cls.begin(), cls.end());
+        T.cls_ptr.assign(1, 0); T.cls_par_ptr.assign(1, 0);
+        std::vector<int32_t> next(cls.size());
+        for (const auto &hq : cls) {
+            const int32_t q = hq.second, last = at_ptr[q + 1] - 1;
+            next[q] = T.cls_ptr.back();
+            T.cls_ptr.push_back(T.cls_ptr.back() + size[q]);
+            T.cls_par.insert(T.cls_par.end(), at.begin() + at_ptr[q], at.begin() + last);
             T.cls_par_ptr.push_back((int32_t)T.cls_par.size());
-            T.cls_first.push_back(at[par[u0].second - 1] == -1 ? 1 : 0);
+            T.cls_first.push_back(at[last] == -1 ? 1 : 0);
         }
-        if (2 * T.cls_first.size() > members.size()) {    // too few blocks share their parents
-            T.cls_ptr.clear(); T.cls_par_ptr.clear(); T.cls_blk.clear(); T.cls_par.clear(); T.cls_first.clear();
-            continue;
-        }
+        T.cls_blk.resize(members.size());
+        for (size_t i = 0; i < members.size(); ++i) T.cls_blk[next[of[i]]++] = (members[i] + 1) * K;
         compile_product_tiles(T, K, n);
     }
     for (int32_t id : c->layers[0].blk_ids) c->flow_rep.push_back((rep[id / K - 1] + 1) * K);
