@@ -739,15 +739,17 @@ void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, con
 // As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
 // 16 x 32 states); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
 // us two at a time, 324 four; fewer waves with two chunks each lost everywhere but on a 3072-variable tree's forward pass, 2587 ->
-// 2502).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
+// 2502), but no more than two where the products' rounding errors are kept: four take 256 registers and spill (PD of 4 x 4 cells, rows of
+// 24 chunks, K = 64, B = 32 62 us four at a time, 44 two; K = 32, B = 64 86, 58).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
 // the widest layer has at most 128 tasks of them, 16 -> 32: HMM T = 60, H = 1024, B = 20 (128 tasks) 281 -> 324 us, T = 40, H = 256, B =
 // 10 (32) 90 -> 100, T = 50, H = 64, B = 400 (104) 98 -> 101; T = 32, H = 512, B = 77 (192) 131 -> 126, trees (thousands in their lower
 // layers) of 784 variables, M = 128, B = 512 788 -> 650, of 500, M = 64, B = 30 120 -> 114.  64 rows and 32 columns lost.
 FlowShape flow_shape(const FlowDev &f, bool bwd, int32_t K, int64_t Bs)
 {
     const int chunks = f.max_nbr * (K / 32);
+    const bool exact = !bwd && f.max_items > 8;
     return FlowShape{chunks <= 2 ? chunks : chunks <= 4 ? 4 : 8, f.max_level * (int64_t)(K / 16) * (Bs / 16) <= 128 ? 1 : 2,
-                     chunks <= 8 ? 1 : chunks <= 16 ? 2 : 4, !bwd && f.max_items > 8};
+                     chunks <= 8 ? 1 : chunks <= 16 || exact ? 2 : 4, exact};
 }
 
 void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
@@ -766,7 +768,7 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
         const int grid = (int)std::min<int64_t>(tasks, WW == 8 ? 256 : WW == 4 ? 512 : 320);                                 \
         if (bwd) hipLaunchKernelGGL((k_flow<WW, RR, HH, true, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                     f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);               \
-        else if (sh.exact) hipLaunchKernelGGL((k_flow<WW, RR, HH, false, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, \
+        else if (sh.exact) hipLaunchKernelGGL((k_flow<WW, RR, HH == 4 ? 2 : HH, false, true>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, \
                                 mail, f.ent, f.rec, f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);     \
         else hipLaunchKernelGGL((k_flow<WW, RR, HH, false, false>), dim3(grid), dim3(64 * WW), 0, s, theta, l, R, F, mail, f.ent, f.rec, \
                                 f.list, (int)tasks, n_ct, K, Bs, f.li0, ticket, ll, B, wait_limit, fault);                   \

@@ -119,6 +119,17 @@ def test_rows_of_one_block_match_oracle(make, B, tiles, exact):
     check_all(w)
 
 
+@pytest.mark.parametrize("make,tiles", [
+    (lambda: W.pd(4, 3, 128, 64, 33, 98, keep=1.0, n_cats=8), 2), (lambda: W.rat_spn(24, 2, 4, 128, 64, 1, 99, n_cats=8), 1),
+])
+def test_long_rows_of_products_with_many_children_match_oracle(make, tiles):
+    """More than sixteen chunks a row over products of nine inputs and more: two chunks per wave at once (four spill registers)."""
+    w = make()
+    print(f"case long rows {w.name}", flush=True)
+    assert f"k_flow<8, {tiles}, 2, false, true>" in kernels(w, 0)
+    check_all(w)
+
+
 @pytest.mark.parametrize("K,B", [(32, 20), (64, 1)])
 def test_root_below_the_dataflow_layers(K, B):
     """A root over a product of thirteen inputs (its layer is not one for a dataflow launch) beside a deeper chain that nothing
