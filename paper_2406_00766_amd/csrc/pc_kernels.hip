@@ -624,7 +624,9 @@ __global__ __launch_bounds__(256) void k_prod_bwd(const float *__restrict__ l, f
 // differences of 6e-5 in single weights into 3e-3.
 // D = 784, B = 512: 1.01 ms -> 0.43.  Thread (k, c): row k, two adjacent columns; C2 column pairs per workgroup, T x T products, in 128
 // registers for four waves per SIMD (0.57 ms with three).  The four tiles that share their classes run one
-// after another on one XCD (workgroup h runs on XCD h mod 8), for the blocks to be in its L2.
+// after another on one XCD (workgroup h runs on XCD h mod 8), for the blocks to be in its L2.  So do the two column tiles of a
+// 128-byte line where a tile has 16 columns (K = 64): on two XCDs each line was fetched twice (300 variables, K = 64, B = 1000: k_prod_fwd 322 us,
+// tiles 350, now 295; B = 512 158, 142, 126).
 template <int C2, int T>
 __global__ __launch_bounds__(512, 4) void k_prod_tile(float *__restrict__ l, float *__restrict__ R, const int32_t *tile_words, int32_t n_tiles,
                                                    const int32_t *order_words, const int32_t *blk_words, int32_t K, int64_t Bs)
@@ -635,9 +637,10 @@ __global__ __launch_bounds__(512, 4) void k_prod_tile(float *__restrict__ l, flo
     constexpr int PARTS = 16 / (T * T);                                 // workgroups of a 4 x 4 tile
     const int32_t n4 = (n_tiles * PARTS + 3) & ~3;
     const int32_t h = (int32_t)blockIdx.x, q = h >> 3, m = ((q >> 2) * 8 + (h & 7)) * 4 + (q & 3);
-    const int32_t ti = m % n4 / PARTS, i0 = T * (m % n4 % PARTS / (4 / T)), j0 = T * (m % n4 % PARTS % (4 / T));
-    const int64_t b = (int64_t)(m / n4) * (2 * C2) + 2 * (threadIdx.x % C2);
-    if (ti >= n_tiles || (int64_t)(m / n4) * (2 * C2) >= Bs) return;    // the whole workgroup
+    constexpr int LINE = C2 < 16 ? 16 / C2 : 1;                         // column tiles of a line (Bs is a multiple of 32 columns)
+    const int32_t part = m / LINE % n4, ti = part / PARTS, i0 = T * (part % PARTS / (4 / T)), j0 = T * (part % PARTS % (4 / T));
+    const int64_t col0 = (int64_t)(m / LINE / n4 * LINE + m % LINE) * (2 * C2), b = col0 + 2 * (threadIdx.x % C2);
+    if (ti >= n_tiles || col0 >= Bs) return;                            // the whole workgroup
     const TabPtr tw = (TabPtr)(uintptr_t)tile_words + PROD_TILE_WORDS * (int64_t)ti, blk = (TabPtr)(uintptr_t)blk_words;
     const TabPtr order = (TabPtr)(uintptr_t)order_words + tw[24];
     const int k = threadIdx.x / C2, wave = threadIdx.x >> 6;
