@@ -303,7 +303,7 @@ static ClassesDev classes_dev(const LayerTab &L)
 }
 static bool takes_tiles(const pc_circuit *c, const LayerTab &L, const Ws &w)
 {
-    return !w.bf16 && !L.tile.empty() && prod_takes_tiles(c->K, (int32_t)L.blk_ids.size(), max_width(L.fwd), w.Bs);
+    return !w.bf16 && !L.tile.empty() && prod_takes_tiles(c->K, (int32_t)L.blk_ids.size(), (int32_t)(L.tile.size() / PROD_TILE_WORDS), max_width(L.fwd), w.Bs);
 }
 static bool takes_bf16(const pc_circuit *c, const std::vector<GroupTab> &groups, const Ws &w)
 {

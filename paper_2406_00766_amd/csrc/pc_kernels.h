@@ -105,7 +105,7 @@ void launch_prod_fwd(const float *l, float *lout, float *R, const std::vector<Gr
 void launch_prod_bwd(const float *l, float *F, const float *Fpar, float *N, float *nfmax, const std::vector<GroupSet> &sets, int32_t K,
                      int64_t Bs, void *Ph, void *Pl, hipStream_t s);
 // Product layer over classes of input blocks: forward, tiles of products (LayerTab::tile); backward, a class's flow stored to its blocks
-bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs);   // width: most children of a product
+bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t n_tiles, int32_t width, int64_t Bs);   // width: most children of a product
 struct ProdTile { int pairs, side; };                                   // k_prod_tile's template arguments: column pairs, side x side products
 ProdTile prod_tile_shape(int32_t n_tiles, int32_t K, int64_t Bs);
 void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,

@@ -2782,18 +2782,23 @@ static GroupSet csr_set(const RowsDev &rows)
         else hipLaunchKernelGGL((KERNEL<8, U / 4, 16>), __VA_ARGS__);                                      \
     } while (0)
 // Where k_prod_fwd sums rows of more than eight children in fours of fp32 and double beyond, in launches that fill the chip (a narrow one
-// takes eights at K = 32, and tiles would leave most CUs idle: RAT-SPN of 100 variables, B = 3, 38.5 -> 44 us).
-bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t width, int64_t Bs)
+// takes eights at K = 32, and tiles would leave most CUs idle: RAT-SPN of 100 variables, B = 3, 38.5 -> 44 us), and where the tiles hold 6 of
+// 16 products and more: sets of two classes (4 of 16) have nothing to share, RAT-SPNs of 784 and 300 variables, four replicas, depth 4, S / K =
+// 2, B = 480, k_prod_fwd -> 4 x 4: K = 32 146 -> 156, 70 -> 66 us, K = 64 283 -> 277, 115 -> 129; 2 x 2 at K = 32 225, 93.  Sets of
+// five (25 of 64): 784 variables, depth 3, B = 256 392 -> 236 (K = 32), 751 -> 490 (K = 64); of three (9 of 16): 163 -> 103, 288 -> 242.
+bool prod_takes_tiles(int32_t K, int32_t n_rows, int32_t n_tiles, int32_t width, int64_t Bs)
 {
-    return (K == 32 || K == 64) && width > 8 && (int64_t)n_rows * ((Bs + 63) / 64) >= 1024;
+    return (K == 32 || K == 64) && width > 8 && n_rows >= 6 * (int64_t)n_tiles && (int64_t)n_rows * ((Bs + 63) / 64) >= 1024;
 }
 
-// 2 x 2 products a workgroup where 4 x 4 would not give every CU two: RAT-SPN of 784 variables, forward pass at B = 16 251 us with k_prod_fwd,
-// 244 in 128 workgroups, 228 in 512.
+// 2 x 2 products a workgroup where 4 x 4 make less than 192 workgroups, which full tiles can at K = 32 only.  RAT-SPNs at K = 32, k_prod_fwd / 2 x 2 /
+// 4 x 4: 128 workgroups 297 / 241 / 257, 72 / 53 / 64, 71 / 59 / 70 us (784, 400, 300 variables), 248 .. 256 564 / 381 / 265, 116 / 75 / 70, 123 / 90 /
+// 75, 384 178 / 127 / 119.  At K = 64 4 x 4 are the faster ones from the smallest launches on (240 .. 256 workgroups 150 / 138 / 108, 202 / 164 / 142,
+// 752 / 633 / 496).
 ProdTile prod_tile_shape(int32_t n_tiles, int32_t K, int64_t Bs)
 {
-    const int pairs = K == 64 ? 8 : 16;
-    return ProdTile{pairs, (int64_t)n_tiles * (Bs / (2 * pairs)) < 512 ? 2 : 4};
+    if (K == 64) return ProdTile{8, 4};
+    return ProdTile{16, (int64_t)n_tiles * (Bs / 32) < 192 ? 2 : 4};
 }
 void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_tiles, const int32_t *order, const int32_t *cls_blk, int32_t K,
                            int64_t Bs, hipStream_t s)
@@ -2804,8 +2809,9 @@ void launch_prod_fwd_tiles(float *l, float *R, const int32_t *tile, int32_t n_ti
     const int64_t wgs = (int64_t)((n_tiles * (small ? 4 : 1) + 3) & ~3) * (Bs / (2 * t.pairs));
     const dim3 grid((unsigned)((wgs + 31) / 32 * 32));
 #define PC_PROD_TILE(CC, TT) hipLaunchKernelGGL((k_prod_tile<CC, TT>), grid, dim3(512), 0, s, l, R, tile, n_tiles, order, cls_blk, K, Bs)
-    if (K == 64) { if (small) PC_PROD_TILE(8, 2); else PC_PROD_TILE(8, 4); }
-    else { if (small) PC_PROD_TILE(16, 2); else PC_PROD_TILE(16, 4); }
+    if (K == 64) PC_PROD_TILE(8, 4);
+    else if (small) PC_PROD_TILE(16, 2);
+    else PC_PROD_TILE(16, 4);
 #undef PC_PROD_TILE
 }
 

@@ -36,10 +36,10 @@ def pairs(K, B, m, p, seed, above):
 
 @pytest.mark.parametrize("K,B,m,p,tile", [
     (32, 1000, 9, 8, "k_prod_tile<16, 2>"), (32, 1010, 5, 17, "k_prod_tile<16, 4>"), (32, 1350, 13, 7, "k_prod_tile<16, 2>"),
-    (64, 961, 7, 8, "k_prod_tile<8, 2>"), (64, 1000, 5, 9, "k_prod_tile<8, 4>"), (64, 417, 5, 17, "k_prod_tile<8, 4>"),
-    # sets of different sizes, blocks in turn: 6 x 3 classes, 5 x 2, 18 x 11, 17 x 14 (cut tiles on one side and on both)
-    (32, 3700, (6, 4), (6, 3), "k_prod_tile<16, 2>"), (64, 6600, (3, 9), (5, 2), "k_prod_tile<8, 4>"),
-    (32, 900, (7, 5), (18, 11), "k_prod_tile<16, 2>"), (64, 500, (4, 5), (17, 14), "k_prod_tile<8, 4>"),
+    (64, 961, 7, 8, "k_prod_tile<8, 4>"), (64, 1000, 5, 9, "k_prod_tile<8, 4>"), (64, 417, 5, 17, "k_prod_tile<8, 4>"),
+    # sets of different sizes, blocks in turn: 6 x 3 classes, 7 x 2, 18 x 11, 17 x 14 (cut tiles on one side and on both)
+    (32, 3700, (6, 4), (6, 3), "k_prod_tile<16, 4>"), (64, 4800, (3, 9), (7, 2), "k_prod_tile<8, 4>"),
+    (32, 350, (7, 5), (18, 11), "k_prod_tile<16, 2>"), (64, 500, (4, 5), (17, 14), "k_prod_tile<8, 4>"),
 ])
 def test_tiles_of_products_match_oracle(K, B, m, p, tile):
     w = pairs(K, B, m, p, 92, False)

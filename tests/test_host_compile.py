@@ -148,6 +148,18 @@ def test_kernel_of_a_layer():
     pcb.pc_destroy(h)
 
 
+@pytest.mark.parametrize("K,S,B,kernel", [
+    (32, 64, 480, "k_prod_fwd"), (64, 128, 480, "k_prod_fwd"),                     # two classes a set: four of a tile's sixteen products
+    (32, 96, 480, "k_prod_tile<16, 4>"), (64, 192, 480, "k_prod_tile<8, 4>"),
+    (32, 256, 32, "k_prod_tile<16, 2>"), (32, 256, 64, "k_prod_tile<16, 4>"), (64, 256, 128, "k_prod_tile<8, 4>"),
+])
+def test_kernel_of_leaf_products(K, S, B, kernel):
+    w = W.rat_spn(96, 4, 4, S, K, 1, 5, n_cats=3, draw=False)
+    h = pcb.pc_compile(w, host_only=True)
+    assert pcb.pc_get_kernel(h, 1, 0, B) == kernel
+    pcb.pc_destroy(h)
+
+
 def test_group_tolerance_and_max_groups_are_honoured():
     w = W.reduced(5)
     for G, tol in [(1, 0), (2, 100), (8, 0), (8, 1000)]:
