@@ -492,7 +492,7 @@ void compile_classes(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> 
 
 // A dataflow task repeats its neighbours' products and exponentials for every 16 or 32 rows, so a layer that fills the chip is
 // better off in the layer kernels; a narrow one costs them two launches and cold starts (5 + 5 us) where its tasks take
-// 2 - 3 us.  Measured on hidden Chow-Liu trees (M = 32, 128, 256; B = 100 .. 512), HMMs and RAT-SPNs: the line lies at 2048
+// 1.2 - 4 us.  Measured, with the kernels as they were when the lines were drawn, on hidden Chow-Liu trees (M = 32, 128, 256; B = 100 .. 512), HMMs and RAT-SPNs: the line lies at 2048
 // tiles of 16 x 16 results (sum layer: forward, product layer: backward) and 16384 tile-chunks (16 x 16 results x 32 neighbour
 // nodes) per layer, and half or twice that makes 5 % of a pass.  Product blocks of many children (RAT-SPN leaves: 57 - 98)
 // are summed one child at a time by every task that reads them and belong in their own launch.
@@ -504,19 +504,22 @@ bool flow_narrow(const pc_circuit *c, size_t li, int64_t Bs)
     return t.kind != KIND_SUM || (c->sum_edges[li] * (c->K / 16) * (c->K / 32) * ct <= 16384 && c->max_items[li] <= 12);
 }
 
-// What a layer gains from the dataflow launch, in us: a sum layer in the forward, a product layer in the backward pass.
+// What a layer gains from the dataflow launch, in us: a sum layer in the forward, a product layer in the backward pass.  The constants were
+// set with earlier kernels; both sides below are measured with these, and the lines they draw stand, some us on the launches' side.
 // Forward, a task takes the sum blocks among its products' children one after the other, each in 1.2 us and 0.12 us more per
 // chunk of 32 neighbour nodes in the row; a layer's own two launches take 10.8 us.  Measured on a sum layer and a root that reads
-// products of 5 / 6 / 7 / 8 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4 chunks 30.6 -> 18.3, 29.1 -> 20.2, 29.2 ->
-// 21.3, 29.2 -> 23.7, 28.9 -> 30.3 us; of 16 chunks 33.4 -> 30.9, 34.0 -> 33.8, 35.3 -> 36.0, 34.4 -> 39.5, 36.0 -> 53.2 us; of 32
-// chunks 40.7 -> 48.6 us and more.  Many tiles take 7 ns each, whatever their rows: HMMs of 16 layers of one block, B = 2048 / 4096 /
-// 8192 / 16384, launches -> dataflow: 32 nodes 127 -> 52, 132 -> 81, 144 -> 138, 157 -> 252 us (256 .. 2048 tiles a layer), 128 nodes
-// 173 -> 150, 207 -> 256 us (1024, 2048).
+// products of 5 / 6 / 7 / 8 / 10 / 12 sum blocks, B = 60, launches -> dataflow: rows of 4 chunks 22.2 -> 16.0, 21.8 -> 16.4, 22.2 -> 16.9, 23.4 ->
+// 17.6, 23.9 -> 21.2, 23.2 -> 24.6 us (taken up to 8); of 16 chunks 25.4 -> 23.7, 26.9 -> 25.3, 27.0 -> 27.5, 27.5 -> 31.0, 32.1 -> 38.8, 33.3 ->
+// 44.6 us; of 32 chunks 39.8 -> 44.1 us and more (none taken).  Many tiles take 7 ns each, whatever their rows: HMMs of 16 layers of one
+// block, launches -> dataflow: 64 nodes, B = 1024 / 2048 / 4096 / 8192 (256 .. 2048 tiles a layer) 128 -> 46, 140 -> 72, 143 -> 124, 158 -> 232
+// us (the last not taken), 128 nodes, B = 1024 / 2048 / 4096 (512 .. 2048 tiles) 154 -> 87, 162 -> 140, 193 -> 244 us (the last not taken).
+// A chain of blocks of 32 (k_chain) has no such tasks, yet is priced by the same formula: 16 layers, B = 2048 / 8192 / 16384 / 32768 123 -> 26,
+// 141 -> 38, 151 -> 56, 185 -> 96 us, of which the formula takes the first two.
 // Backward, it takes the product parents of its sum blocks one after the other, each in 0.5 us and 0.06 us more per chunk, and
 // what the workgroups do in all grows with tiles and waits; the launches take 11.5 us.  Measured on seven layers whose sum
-// blocks feed 4 / 8 / 12 / 16 / 24 products, launches -> dataflow: one block of 32 nodes per layer, B = 30, 79 -> 44, 80 -> 58, 85 ->
-// 74, 86 -> 89, 91 -> 118 us, B = 300 111 -> 78, 112 -> 99, 118 -> 125, 123 -> 149, 133 -> 209 us; four blocks of 32, B = 30, 86 ->
-// 52, 87 -> 76, 96 -> 104, 102 -> 123 us (16 products); one block of 128, B = 300, 209 -> 178, 224 -> 231, 233 -> 272 us (12 products).
+// blocks feed 4 / 8 / 12 / 16 / 24 products, launches -> dataflow: one block of 32 nodes per layer, B = 30, 77 -> 37, 77 -> 46, 82 ->
+// 59, 82 -> 69, 87 -> 91 us (taken up to 16), B = 300 108 -> 69, 109 -> 84, 117 -> 97, 125 -> 108, 131 -> 149 us (up to 8); four blocks of 32, B = 30, 77 ->
+// 43, 83 -> 58, 95 -> 74, 93 -> 87, 100 -> 114 us (up to 8); one block of 128, B = 300, 204 -> 163, 216 -> 194, 225 -> 223, 237 -> 274 us (4).
 static double flow_tiles(const pc_circuit *c, size_t li, int64_t Bs)
 {
     return (double)((int64_t)c->layers[li].blk_ids.size() * (c->K / 16) * (Bs / 16));
@@ -528,9 +531,10 @@ double flow_gain(const pc_circuit *c, size_t li, int64_t Bs)
     if (c->layers[li].kind == KIND_SUM) return 10.8 - std::max(std::max(waits, 1.0) * (1.2 + 0.12 * chunks), 0.007 * flow_tiles(c, li, Bs));
     return 11.5 - std::max(2 + waits * (0.5 + 0.06 * chunks) + 0.003 * load, 0.007 * load);
 }
-// The first layer of the launch finds neither weights nor values requested ahead.  Backward pass of a RAT-SPN's root over 256 product blocks
-// of 32 nodes, B = 16 (1024 tiles) 90 us in launches, 100 as dataflow; of a 3 x 32 HMM, B = 4096 (512 tiles a layer), 565 and 577 us,
-// where the layers' gain alone would be 20 us.  Forward passes of 3 x 32 and 3 x 128 HMMs, 1024 tiles a layer: 36 -> 40 and 47 -> 52 us.
+// The first layer of the launch finds neither weights nor values requested ahead.  Forward passes of 3 x 64 and 3 x 128 HMMs, 1024 tiles a
+// layer, launches -> dataflow 30.7 -> 35.8 and 42.0 -> 48.6 us, half the tiles 29.0 -> 23.7 and 39.8 -> 36.3 (taken); backward passes 771 -> 774 and
+// 886 -> 888, where the layers' gain alone would be 20 us.  With earlier kernels the backward pass of a RAT-SPN's root over 256 product blocks of
+// 32 nodes, B = 16 (1024 tiles): 90 us in launches, 100 as dataflow.
 double flow_start_up(const pc_circuit *c, size_t li, int64_t Bs)
 {
     return c->layers[li].kind == KIND_PRODUCT ? 0.04 * flow_load(c, li, Bs) : 0.012 * flow_tiles(c, li, Bs);

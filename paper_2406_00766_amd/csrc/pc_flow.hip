@@ -736,8 +736,8 @@ void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, con
                        n_cb, root_id, K, Bs, B, ent, n_ent, ticket);
 }
 
-// As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: 29 against 34 us for an HMM of
-// 16 x 32 states); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
+// As many waves as a row has chunks of 32 neighbour nodes, up to eight (a single one needs no merge: an HMM of 16 x 32
+// states, a chain of its own kernel since, 29 against 34 us); in longer rows a wave takes two or four chunks at once (HMM T = 60, H = 1024, B = 20, rows of 32 chunks: forward 421
 // us two at a time, 324 four; fewer waves with two chunks each lost everywhere but on a 3072-variable tree's forward pass, 2587 ->
 // 2502), but no more than two where the products' rounding errors are kept: four take 256 registers and spill (PD of 4 x 4 cells, rows of
 // 24 chunks, K = 64, B = 32 62 us four at a time, 44 two; K = 32, B = 64 86, 58).  Row tiles of 32 halve the number of tasks that read a neighbour, tiles of 16 leave a shorter chain and win where
