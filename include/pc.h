@@ -205,7 +205,8 @@ pc_status pc_forward(pc_circuit *c, const float *theta, const float *tables, con
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and same result as
  * pc_forward, but the workspace is a fixed array of PC_STATIC_SCRATCH_BYTES inside the library's device image (every
  * GPU the library runs on holds its copy until the process ends).  The call allocates nothing and records no timing
- * events; it only enqueues kernels on `stream`.  PC_ERR_WORKSPACE if pc_workspace_bytes(c, B) exceeds
+ * events; it only enqueues kernels on `stream` (a circuit that is a chain of single blocks of 32 or 64 nodes from its inputs to the
+ * root: one, with the arithmetic of pc_forward's).  PC_ERR_WORKSPACE if pc_workspace_bytes(c, B) exceeds
  * PC_STATIC_SCRATCH_BYTES.  All calls on one GPU share that array: calls that overlap in time on one GPU (two streams,
  * two threads, two circuits) race; the array keeps the last call's contents, and every call writes what it reads.  It
  * leaves no state for pc_backward (which returns PC_ERR_STATE after it). */
@@ -251,8 +252,8 @@ const char *pc_kernel_class_name(int32_t cls);
 
 /* Polls after which a wait inside a dataflow launch is given up (2^22 after pc_compile: some seconds).  The limit is the
  * handle's and applies from the next call on; 0 gives up on the first value that is not there yet, which is how the error
- * path is tested.  Any other limit than the first also sends chains of single blocks of 32 nodes, which are walked without waits
- * (k_chain), through a launch that waits; log-likelihoods and flows agree within the same tolerances. */
+ * path is tested.  Any other limit than the first also sends chains of single blocks of 32 or 64 nodes, which are walked without waits
+ * (k_chain, k_walk64), through a launch that waits; log-likelihoods and flows agree within the same tolerances. */
 pc_status pc_set_wait_limit(pc_circuit *c, int32_t polls);
 
 /* Achievable peaks of the device the calling thread has current, for quoting beside the published ones (measurement

@@ -284,11 +284,12 @@ static FlowDev flow_dev(const pc_circuit *c, const FlowTab &f, size_t li0, bool 
 }
 // The links from layer li0 up (words: forward a suffix, backward a prefix).  None where a limit of polls was set: that is for launches
 // that poll.
-static ChainDev chain_dev(const pc_circuit *c, const ChainTab &t, size_t li0, bool suffix)
+static ChainDev chain_dev(const pc_circuit *c, const ChainTab &t, size_t li0, bool suffix, int64_t Bs)
 {
     const int32_t n = t.from[li0];
-    if (n <= 0 || c->wait_limit != pc_circuit::kWaitLimit) return ChainDev{nullptr, 0};
-    return ChainDev{t.d_words + (suffix ? t.words.size() - (size_t)n * CHAIN_WORDS : 0), n};
+    const bool walks = chain_walks(t.few_weights, n, c->K, Bs);
+    if (n <= 0 || c->wait_limit != pc_circuit::kWaitLimit || (c->K != 32 && !walks)) return ChainDev{nullptr, 0, false};
+    return ChainDev{t.d_words + (suffix ? t.words.size() - (size_t)n * CHAIN_WORDS : 0), n, walks};
 }
 static int32_t max_width(const std::vector<GroupTab> &groups)
 {
@@ -459,8 +460,9 @@ pc_status pc_get_kernel(const pc_circuit *c, int32_t layer, int32_t dir, int32_t
                 print("k_prod_tile<%d, %d>", t.pairs, t.side);
             }
         } else if ((size_t)layer >= li0) {
-            if (chain_dev(c, bwd ? c->chain_bwd : c->chain_fwd, li0, !bwd).n_links > 0) {
-                print("k_chain<%s>", truth(bwd));
+            const ChainDev chain = chain_dev(c, bwd ? c->chain_bwd : c->chain_fwd, li0, !bwd, w.Bs);
+            if (chain.n_links > 0) {
+                print("%s<%s>", !chain.walks ? "k_chain_wide" : K == 32 ? "k_chain" : "k_walk64", truth(bwd));
             } else {
                 const FlowShape f = flow_shape(flow_dev(c, bwd ? c->flow_bwd : c->flow_fwd, li0, !bwd), bwd, K, w.Bs);
                 print("k_flow<%d, %d, %d, %s, %s>", f.waves, f.tiles, f.chunks, truth(bwd), truth(f.exact));
@@ -523,8 +525,13 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     const size_t L = c->layers.size(), li0 = flow_start(c, w, false);
     FlowDev flow{};
     ChainDev chain{};
-    if (li0 < L) chain = chain_dev(c, c->chain_fwd, li0, true);
+    if (li0 < L) chain = chain_dev(c, c->chain_fwd, li0, true, w.Bs);
     if (li0 < L && chain.n_links == 0) flow = flow_dev(c, c->flow_fwd, li0, true);
+    if (ll_only && li0 == 1 && chain.n_links > 0 && c->chain_fwd.whole && chain.walks) {
+        launch_walk_pass(theta, tables, x, mask, chain, K, B, c->n_vars, c->n_cats, ll, s);
+        PC_HIP(hipGetLastError());
+        return PC_OK;
+    }
     int32_t *ticket = (int32_t *)(base + w.tk_off);
     const bool null_mail = li0 < L || flow_start(c, w, true) < L;        // read by the dataflow launches of both directions
     launch_begin_forward(x, mask, B, c->n_vars, w.Bs, c->n_cats, xT, l, R, (float *)(base + w.n_off), null_mail, flow.ent, flow.n_ent, K, ticket,
@@ -550,7 +557,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
         }
     }
     if (li0 < L) {
-        if (chain.n_links > 0) launch_chain(theta, l, R, nullptr, false, chain, w.Bs, B, ll, s);
+        if (chain.n_links > 0) launch_chain(theta, l, R, nullptr, nullptr, nullptr, false, chain, K, w.Bs, B, ll, s);
         else launch_flow(theta, l, R, nullptr, (float *)(base + w.n_off), false, flow, K, w.Bs, B, ticket, ll, c->wait_limit, c->d_fault, s);
         if (!ll_only) launch_prod_fwd_rows(l, R, rows_dev(c->prod_fwd_rows, li0, true), K, w.Bs, s);
     }
@@ -623,13 +630,17 @@ pc_status pc_backward(pc_circuit *c, const float *theta, const float *tables, co
     const size_t li0 = flow_start(c, w, true);
     FlowDev flow{};
     ChainDev chain{};
-    if (li0 < c->layers.size()) chain = chain_dev(c, c->chain_bwd, li0, false);
+    if (li0 < c->layers.size()) chain = chain_dev(c, c->chain_bwd, li0, false, w.Bs);
     if (li0 < c->layers.size() && chain.n_links == 0) flow = flow_dev(c, c->flow_bwd, li0, false);
     int32_t *ticket = (int32_t *)(base + w.tk_off);
-    launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
-                          flow.n_ent, ticket, s);
+    // a chain that starts at the root in a circuit without other blocks for k_begin_backward does that launch's work
+    const bool chain_begins = chain.walks && c->init_ids.size() == 2 && c->chain_bwd.words[1] == (c->root_block + 1) * K;
+    if (!chain_begins)
+        launch_begin_backward(l, F, N, nfmax, c->d_init_ids, (int32_t)c->init_ids.size(), (c->root_block + 1) * K, K, w.Bs, B, flow.ent,
+                              flow.n_ent, ticket, s);
     if (li0 < c->layers.size()) {
-        if (chain.n_links > 0) launch_chain(theta, l, const_cast<float *>(R), F, true, chain, w.Bs, B, nullptr, s);
+        if (chain.n_links > 0)
+            launch_chain(theta, l, const_cast<float *>(R), F, chain_begins ? N : nullptr, nfmax, true, chain, K, w.Bs, B, nullptr, s);
         else launch_flow(theta, l, const_cast<float *>(R), F, N, true, flow, K, w.Bs, B, ticket, nullptr, c->wait_limit, c->d_fault, s);
         launch_prod_bwd_rows(l, F, N, nfmax, rows_dev(c->prod_bwd_rows, li0, false), K, w.Bs, w.bf16 ? base + w.ph_off : nullptr,
                              w.bf16 ? base + w.pl_off : nullptr, s);

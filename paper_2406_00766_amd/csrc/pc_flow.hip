@@ -575,21 +575,240 @@ __global__ __launch_bounds__(64 * W, W >= 8 ? 1 : 2) void k_flow(const float *__
 }
 
 
+struct ChainLink { int32_t id, nbr, src, in, par, root, next_par; };    // a link's words (ChainTab)
+
 // ------------------------------------------------------------------------------------------
-// Chains: the same layers where each is one block of 32 nodes that takes values of the layer before it only (ChainTab; an HMM of 32
-// states).  One wave walks the whole chain for 16 columns: in MFMA layout the results of one layer are the operands of the
-// next lane by lane, so they are handed on in registers.  Nothing is polled and nothing published.
-// Bound: the instructions of a layer, one wave's -- some 250, 0.6 us against 1.1 us for a task of k_flow with its hand-over.  For it to be
-// that and not the memory, nothing in a layer may wait: operands that do not depend on the chain are requested a layer ahead (two
-// and three made no difference), the words of a link come through the scalar cache a link before they are needed, and stores
-// that do not apply go to a descriptor of no bytes instead of round a branch (behind a branch the compiler does not know how many
-// stores are under way and waits for them all).  HMM 16 x 32: forward pass, one sample, 28.7 -> 21.9 us, backward
-// 41.1 -> 35.6; B = 128 30.8 -> 22.9, 55.9 -> 46.3.  The same for 64 nodes (four waves, results through LDS) took 1.4 us a layer forward and 3.5 backward, k_flow 1.6 and 3.1.
-struct ChainLink { int32_t id, nbr, src, in, par, root; };              // a link's words (ChainTab)
+// Chains: the same layers where each is one block of 32 or 64 nodes that takes values of the layer before it only (ChainTab; an HMM of
+// as many states).  A wave walks the whole chain for the columns its lanes hold a node each of (two of 32 nodes, one of 64), so the
+// values of a layer stay in registers; nothing is polled and nothing published.
+// Bound: the dependent instructions of a layer, one wave's.  A product of a K x K block and a column is K instructions on the vector ALU --
+// a lane has its node's row of the weights in registers, the operand comes from the lane's row of sixteen by DPP -- and every
+// column has a wave of its own for them, where the matrix cores take sixteen columns at the price of 512 cycles for 32 nodes (k_chain_wide)
+// and most of a small batch's are padding.  For it to be that and not the memory, nothing in a layer may wait: operands that do not
+// depend on the chain are requested four layers ahead (the stores between are counted with the loads, so one layer ahead is a wait
+// for the last layer's stores), weights are loaded where they change, those of the next change when this one's are taken over.
+// Layers of HMMs of 16 and 32 layers, k_chain_wide or k_flow -> here: 32 nodes 0.6 us -> 0.3 forward, 0.9 -> 0.4 backward (B = 128; launches of 16
+// layers 13.7 -> 8.2 and 19.9 -> 10.4 us); 64 nodes 1.6 -> 0.45, 1.8 -> 0.5.  pc_forward_static, 16 x 32, one sample, the whole pass 15.4 -> 7.2 us.
+// (DPP in assembly: the compiler turns these into a move and an operation each)
+template <int K> __device__ inline float chain_max(float v)             // over a column's lanes
+{
+#define PC_ROR(N) "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:" #N " row_mask:0xf bank_mask:0xf\n\t"
+    asm(PC_ROR(8) PC_ROR(4) PC_ROR(2) PC_ROR(1) : "+v"(v));
+#undef PC_ROR
+    float a = v, b = v;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    a = b = __builtin_amdgcn_fmed3f(a, b, __builtin_inff());            // (fmaxf would quiet both first)
+    if (K == 64) {
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+        a = __builtin_amdgcn_fmed3f(a, b, __builtin_inff());
+    }
+    return a;
+}
+// sum over n of w[n] p(node n of this lane's column)
+template <int K> __device__ inline float chain_dot(const float (&w)[K], float p)
+{
+    float q[K / 16];                                                    // nodes 16 i + j of the column in lane j of every row of sixteen
+    q[0] = q[1] = p;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(q[0]), "+v"(q[1]));
+    if constexpr (K == 64) {
+        q[2] = q[0]; q[3] = q[1];
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(q[0]), "+v"(q[2]));
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(q[1]), "+v"(q[3]));
+    }
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#define PC_FMA(A, W, J) "v_fmac_f32_dpp %" #A ", %4, %" #W " row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n\t"
+#pragma unroll
+    for (int i = 0; i < K / 16; ++i)
+        asm("s_nop 1\n\t" PC_FMA(0, 5, 0) PC_FMA(1, 6, 1) PC_FMA(2, 7, 2) PC_FMA(3, 8, 3) PC_FMA(0, 9, 4) PC_FMA(1, 10, 5) PC_FMA(2, 11, 6) PC_FMA(3, 12, 7)
+            PC_FMA(0, 13, 8) PC_FMA(1, 14, 9) PC_FMA(2, 15, 10) PC_FMA(3, 16, 11) PC_FMA(0, 17, 12) PC_FMA(1, 18, 13) PC_FMA(2, 19, 14) PC_FMA(3, 20, 15)
+            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+            : "v"(q[i]), "v"(w[16 * i]), "v"(w[16 * i + 1]), "v"(w[16 * i + 2]), "v"(w[16 * i + 3]), "v"(w[16 * i + 4]), "v"(w[16 * i + 5]), "v"(w[16 * i + 6]),
+              "v"(w[16 * i + 7]), "v"(w[16 * i + 8]), "v"(w[16 * i + 9]), "v"(w[16 * i + 10]), "v"(w[16 * i + 11]), "v"(w[16 * i + 12]), "v"(w[16 * i + 13]),
+              "v"(w[16 * i + 14]), "v"(w[16 * i + 15]));
+#undef PC_FMA
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+struct ChainIn { const float *tables; const int32_t *x; const uint8_t *mask; int32_t D, n_cats; };   // what DIRECT reads
+
+// DIRECT: the input blocks' values come from the tables, and nothing is kept but ll (pc_forward_static): the whole pass.
+// Backward, N not null: the root and the null block are the only blocks that no layer of the sweep writes, and this launch writes them
+// (as k_begin_backward).
+template <int K, bool BWD, bool DIRECT>
+__device__ inline void walk_chain(const float *__restrict__ theta, float *l, float *R, float *F, const int32_t *link_words, int32_t n_links, int64_t Bs,
+                                  float *__restrict__ ll, int32_t B, const ChainIn &in, float *N = nullptr, float *nfmax = nullptr)
+{
+    constexpr int D = 4;                                                // links whose operands are under way
+    const int lane = threadIdx.x & 63, node = lane % K;
+    const int64_t col = ((int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * (64 / K) + lane / K;
+    const TabPtr table = (TabPtr)(uintptr_t)link_words;
+    const int at = (int)((node * Bs + col) * 4), col_off = (int)(col * 4), first_off = node == 0 ? col_off : -1;   // -1: beyond every descriptor
+    auto buf = [](const void *p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, PC_BUF_FLAGS); };
+    auto load = [](__amdgpu_buffer_rsrc_t r, int voff) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0)); };
+    auto store = [](float v, __amdgpu_buffer_rsrc_t r, int voff) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, voff, 0, 0); };
+    auto words = [&](int k) -> ChainLink {
+        const TabPtr w = table + CHAIN_WORDS * (k < n_links ? k : n_links - 1);
+        return ChainLink{w[0], w[1], w[2], w[3], w[4], w[5], w[6]};
+    };
+
+    // DIRECT: rows of the tables (below 0: pc_category's), lane i those of link i of this run of 64, and of the columns of this wave
+    int32_t trow[64 / K] = {};
+    auto rows_of = [&](int k0) {
+        const int k = k0 + lane < n_links ? k0 + lane : n_links - 1;
+        const int32_t *w = link_words + CHAIN_WORDS * (int64_t)k;
+        const int32_t var = w[7], tab = w[8];
+#pragma unroll
+        for (int c = 0; c < 64 / K; ++c) {
+            const int32_t cat = pc_category(in.x, in.mask, col - lane / K + c, var, B, in.D, in.n_cats);
+            trow[c] = cat >= 0 ? tab * in.n_cats + cat : cat;
+        }
+    };
+
+    struct Operands { float a, b, Ra, Rb; int32_t row; };               // forward: the input's value (its reference is 0); backward: l of both blocks, their references
+    auto request = [&](int k, const ChainLink &w, Operands &o) {
+        if (DIRECT) {
+            int32_t r = __builtin_amdgcn_readlane(trow[0], k & 63);
+            if (K == 32) {
+                const int32_t r1 = __builtin_amdgcn_readlane(trow[K == 32 ? 1 : 0], k & 63);
+                r = lane < 32 ? r : r1;
+            }
+            o.row = r;
+            o.a = in.tables[(int64_t)max(r, 0) * K + node];
+        } else if (BWD) {
+            o.a = load(buf(l + (int64_t)w.nbr * Bs, PC_BUF_RANGE), at);
+            o.b = load(buf(l + (int64_t)w.id * Bs, PC_BUF_RANGE), at);
+            o.Ra = load(buf(R + (int64_t)(w.nbr / K) * Bs, PC_BUF_RANGE), col_off);
+            o.Rb = load(buf(R + (int64_t)(w.id / K) * Bs, PC_BUF_RANGE), col_off);
+        } else {
+            o.a = load(buf(l + (int64_t)w.in * Bs, PC_BUF_RANGE), at);   // (no input block: the null block's rows, 0)
+        }
+    };
+    float w[K], wn[K];                                                  // this lane's weights; those after the next change
+    auto weights = [&](int32_t par) {
+        if (BWD) {
+#pragma unroll
+            for (int n = 0; n < K; ++n) wn[n] = theta[(int64_t)par + n * K + node];
+        } else {
+            const floatx4 *src = reinterpret_cast<const floatx4 *>(theta + par + node * K);
+#pragma unroll
+            for (int n = 0; n < K / 4; ++n) {
+                const floatx4 t = src[n];
+                wn[4 * n] = t[0]; wn[4 * n + 1] = t[1]; wn[4 * n + 2] = t[2]; wn[4 * n + 3] = t[3];
+            }
+        }
+    };
+
+    ChainLink cur = words(0), next, far;
+    weights(cur.par);
+    // the values that the first link takes have been there before this launch (backward: the root's own flow, or 0 of an unused block)
+    float x = 0.0f, Rx = 0.0f;
+    if (BWD && N) {
+        const float lv = load(buf(l + (int64_t)cur.nbr * Bs, PC_BUF_RANGE), at);
+        const bool live = node == 0 && col < B && lv > PC_NEG_INF;
+        x = live ? 1.0f : 0.0f;
+        store(x, buf(F + (int64_t)cur.nbr * Bs, PC_BUF_RANGE), at);
+        store(live ? -lv : PC_NEG_INF, buf(N + (int64_t)cur.nbr * Bs, PC_BUF_RANGE), at);
+        store(live ? -lv : PC_NEG_INF, buf(nfmax + (int64_t)(cur.nbr / K) * Bs, PC_BUF_RANGE), first_off);
+        store(0.0f, buf(F, PC_BUF_RANGE), at);
+    } else if (BWD) x = load(buf(F + (int64_t)cur.nbr * Bs, PC_BUF_RANGE), at);
+    else if (!DIRECT) { x = load(buf(l + (int64_t)cur.src * Bs, PC_BUF_RANGE), at); Rx = R[(int64_t)(cur.src / K) * Bs + col]; }
+    // (the stores of a link go to a descriptor of no bytes here: the compiler waits for a count of accesses that holds on all paths into the loop)
+    Operands ops[D];
+    const __amdgpu_buffer_rsrc_t none = buf(theta, 0);
+    auto ahead = [&](int k0, int i) {
+        request(k0 + i, words(k0 + i), ops[i]);
+        asm volatile("" ::: "memory");
+        if (!DIRECT) store(0.0f, none, at);
+        if (!DIRECT && !BWD) store(0.0f, none, at);
+        if (!BWD) store(0.0f, none, at);
+        asm volatile("" ::: "memory");
+    };
+    int32_t par = 0;
+    auto link = [&](int k, Operands &o) {
+        if (cur.par != par) {                                           // uniform
+            par = cur.par;
+#pragma unroll
+            for (int n = 0; n < K; ++n) { w[n] = wn[n]; asm volatile("" : "+v"(w[n])); }   // (waits in here, not where the paths meet)
+            weights(cur.next_par);
+        }
+        const bool taken = cur.src != 0 || (BWD && k == 0);             // uniform
+        const float xt = taken ? x : 0.0f;
+        float y, base, val;
+        if (BWD) {
+            y = o.a > PC_NEG_INF ? __logf(xt) - o.a : PC_NEG_INF;       // flow 0: -inf
+            base = o.Rb - o.Ra;
+        } else if (DIRECT) {
+            const float e = o.row >= 0 ? __logf(o.a) : o.row == -1 ? 0.0f : PC_NEG_INF;
+            y = xt + (cur.in != 0 ? e : 0.0f);
+            base = taken ? Rx : 0.0f;
+        } else {
+            y = xt + o.a;
+            base = taken ? Rx : 0.0f;
+        }
+        const float lown = o.b;
+        request(k + D, far, o);
+        const ChainLink now = cur;
+        const int bytes = k < n_links ? PC_BUF_RANGE : 0;               // (the links are rounded up to whole turns of the loop)
+        cur = next; next = words(k + 2); far = words(k + D + 1);
+        float cm = chain_max<K>(y);
+        const bool live = cm > PC_NEG_INF;
+        cm = live ? rintf(cm) : 0.0f;
+        base = live ? base + cm : PC_NEG_INF;                           // the reference: there is but one chunk
+        // exp(y - cm + PC_UP); dead: y = -inf
+        const float p = __builtin_amdgcn_exp2f(fmaf(y - cm, PC_LOG2E, live ? PC_UP * PC_LOG2E : 0.0f));
+        const float sum = chain_dot<K>(w, p);
+        if (BWD) {                                                      // as in k_flow
+            const float add = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(sum) + (lown + (base - PC_UP)) * PC_LOG2E);
+            val = live ? add : 0.0f;
+            store(val, buf(F + (int64_t)now.id * Bs, bytes), at);
+        } else {
+            val = fmaf(__builtin_amdgcn_logf(sum * 0x1p-24f), 0.6931471805599453f, 16.635532333f - PC_UP);
+            Rx = live ? base : 0.0f;                                    // all children dead: any finite reference
+            if (!DIRECT) {
+                store(val, buf(l + (int64_t)now.id * Bs, bytes), at);
+                store(Rx, buf(R + (int64_t)(now.id / K) * Bs, bytes), first_off);
+            }
+            store(Rx + val, buf(ll, now.root && k < n_links ? 4 * B : 0), first_off);
+        }
+        x = val;
+        asm volatile("" :: "s"(cur.id), "s"(cur.nbr), "s"(cur.src), "s"(cur.in), "s"(cur.par), "s"(cur.root));   // the words are here by now
+    };
+    for (int k0 = 0; k0 < n_links; k0 += DIRECT ? 64 : n_links) {       // (DIRECT: a lane has the rows of one link in 64)
+        if (DIRECT) rows_of(k0);
+        const int k1 = DIRECT ? min(k0 + 64, n_links) : n_links;
+        next = words(k0 + 1); far = words(k0 + D);
+#pragma unroll
+        for (int i = 0; i < D; ++i) ahead(k0, i);
+        asm volatile("" : "+v"(x), "+v"(Rx));                           // (waited for here)
+        for (int k = k0; k < k1; k += D) { link(k, ops[0]); link(k + 1, ops[1]); link(k + 2, ops[2]); link(k + 3, ops[3]); }
+    }
+}
 
 template <bool BWD>
-__global__ __launch_bounds__(64) void k_chain(const float *__restrict__ theta, float *l, float *R, float *F, const int32_t *link_words,
-                                              int32_t n_links, int64_t Bs, float *__restrict__ ll, int32_t B)
+__global__ __launch_bounds__(256) void k_chain(const float *__restrict__ theta, float *l, float *R, float *F, float *N, float *nfmax, const int32_t *link_words, int32_t n_links,
+                                               int64_t Bs, float *__restrict__ ll, int32_t B)
+{
+    walk_chain<32, BWD, false>(theta, l, R, F, link_words, n_links, Bs, ll, B, ChainIn{}, N, nfmax);
+}
+template <bool BWD>
+__global__ __launch_bounds__(256) void k_walk64(const float *__restrict__ theta, float *l, float *R, float *F, float *N, float *nfmax, const int32_t *link_words, int32_t n_links,
+                                                int64_t Bs, float *__restrict__ ll, int32_t B)
+{
+    walk_chain<64, BWD, false>(theta, l, R, F, link_words, n_links, Bs, ll, B, ChainIn{}, N, nfmax);
+}
+template <int K>
+__global__ __launch_bounds__(256) void k_walk_pass(const float *__restrict__ theta, const int32_t *link_words, int32_t n_links, float *__restrict__ ll,
+                                                   int32_t B, const ChainIn in)
+{
+    walk_chain<K, false, true>(theta, nullptr, nullptr, nullptr, link_words, n_links, 0, ll, B, in);
+}
+
+// The same for large batches of 32 nodes: one wave per 16 columns, on the matrix cores; in MFMA layout the results of one layer are the
+// operands of the next lane by lane.  Bound: the instructions of a layer, some 250 of one wave, 0.6 us against 1.1 us for a task of
+// k_flow with its hand-over.
+template <bool BWD>
+__global__ __launch_bounds__(64) void k_chain_wide(const float *__restrict__ theta, float *l, float *R, float *F, const int32_t *link_words,
+                                                   int32_t n_links, int64_t Bs, float *__restrict__ ll, int32_t B)
 {
     constexpr int K = 32;
     const int lane = threadIdx.x, g = lane >> 4, j16 = lane & 15;
@@ -603,7 +822,7 @@ __global__ __launch_bounds__(64) void k_chain(const float *__restrict__ theta, f
 
     auto words = [&](int k) -> ChainLink {
         const TabPtr w = table + CHAIN_WORDS * (k < n_links ? k : n_links - 1);
-        return ChainLink{w[0], w[1], w[2], w[3], w[4], w[5]};
+        return ChainLink{w[0], w[1], w[2], w[3], w[4], w[5], 0};
     };
     auto rows = [&](const float *X, int32_t row, floatx4 (&x)[2]) {     // 32 rows in operand order: lane (j, g), rows 16 c2 + 4 g + e of column j
         const __amdgpu_buffer_rsrc_t r = buf(X + (int64_t)row * Bs, PC_BUF_RANGE);
@@ -784,12 +1003,42 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
 #undef PC_FLOW
 }
 
-void launch_chain(const float *theta, float *l, float *R, float *F, bool bwd, const ChainDev &c, int64_t Bs, int32_t B, float *ll, hipStream_t s)
+// Columns up to which a chain has a wave per column (two columns at K = 32): HMMs of 32 layers, K = 32 against k_chain_wide (forward +
+// backward) B = 128 26 + 39 -> 16 + 19 us, 2048 28 + 39 -> 22 + 26, 4096 28 + 40 -> 37 + 50; K = 64 against k_flow 51 + 58 -> 21 + 23, 2048 103 + 103 ->
+// 65 + 98, 4096 198 + 200 -> 122 + 195.  Where most links have weights of their own, loading them counts: K = 32 B = 128 26 + 39 -> 19 + 24, 1024 29 + 39 ->
+// 41 + 31; K = 64 51 + 58 -> 31 + 32, 58 + 66 -> 81 + 55. Short chains of 64 nodes gain little there: two layers, B = 512, 10 + 10 ->
+// 12 + 11, four 14 + 14 -> 12 + 12, six 17 + 18 -> 15 + 14.
+bool chain_walks(bool few_weights, int32_t n_links, int32_t K, int64_t Bs)
+{
+    return Bs <= (!few_weights || (K == 64 && n_links < 6) ? 256 : K == 32 ? 2048 : 4096);
+}
+
+void launch_chain(const float *theta, float *l, float *R, float *F, float *N, float *nfmax, bool bwd, const ChainDev &c, int32_t K, int64_t Bs, int32_t B,
+                  float *ll, hipStream_t s)
 {
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
+    if (c.walks) {
+        const int wgw = Bs >= 256 ? 4 : 1;                              // waves of a workgroup
+        const dim3 grid((unsigned)(Bs * K / 64 / wgw)), block(64 * wgw);
+        if (K == 32 && bwd) hipLaunchKernelGGL(k_chain<true>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
+        else if (K == 32) hipLaunchKernelGGL(k_chain<false>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
+        else if (bwd) hipLaunchKernelGGL(k_walk64<true>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
+        else hipLaunchKernelGGL(k_walk64<false>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
+        return;
+    }
     const dim3 grid((unsigned)(Bs / 16));
-    if (bwd) hipLaunchKernelGGL(k_chain<true>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
-    else hipLaunchKernelGGL(k_chain<false>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
+    if (bwd) hipLaunchKernelGGL(k_chain_wide<true>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
+    else hipLaunchKernelGGL(k_chain_wide<false>, grid, dim3(64), 0, s, theta, l, R, F, c.words, c.n_links, Bs, ll, B);
+}
+
+void launch_walk_pass(const float *theta, const float *tables, const int32_t *x, const uint8_t *mask, const ChainDev &c, int32_t K, int32_t B,
+                      int32_t n_vars, int32_t n_cats, float *ll, hipStream_t s)
+{
+    const ChainIn in{tables, x, mask, n_vars, n_cats};
+    const int wgw = B >= 256 ? 4 : 1, cols = 64 / K * wgw;
+    const dim3 grid((unsigned)((B + cols - 1) / cols)), block(64 * wgw);
+    if (K == 32) hipLaunchKernelGGL(k_walk_pass<32>, grid, block, 0, s, theta, c.words, c.n_links, ll, B, in);
+    else hipLaunchKernelGGL(k_walk_pass<64>, grid, block, 0, s, theta, c.words, c.n_links, ll, B, in);
 }
 
 }  // namespace pc

@@ -69,14 +69,18 @@ struct FlowTab {
     std::vector<int32_t> count_from, max_nbr_from;    // per layer index: entries in that layer and above; most neighbours of one
     int32_t *d_ent = nullptr, *d_rec = nullptr, *d_list = nullptr;
 };
-// The same launches where the circuit is a chain of single blocks of 32 nodes (k_chain): CHAIN_WORDS words per sum layer (forward,
+// The same launches where the circuit is a chain of single blocks of 32 or 64 nodes (k_chain): CHAIN_WORDS words per sum layer (forward,
 // ascending) or product layer (backward, descending), and per layer index how many of them from there up, -1: a layer there is no link
 // of a chain.
 //   0 node offset of the layer's block  1 its neighbour's (a product block; backward: a sum block)  2 the block whose published values
 //   the neighbour takes, 0: none  3 forward: the input block multiplied to them, 0: none  4 parameter offset  5 1 for the root
-constexpr int CHAIN_WORDS = 8;
+//   6 the next parameter offset that is another, or this  7, 8 forward: the input block's variable and table
+// few_weights: most links have the parameters of the one before.  whole: forward, the links and their input blocks are all there is, and
+// each link takes the one before
+constexpr int CHAIN_WORDS = 12;
 struct ChainTab {
     std::vector<int32_t> words, from;
+    bool few_weights = false, whole = false;
     int32_t *d_words = nullptr;
 };
 // The product layers that belong to them, as rows with neighbour lists (CSR): forward, product blocks by ascending layer with

@@ -43,6 +43,7 @@ struct FlowDev {             // a dataflow launch (pc_flow.hip): entries from la
 struct ChainDev {            // a dataflow launch over a chain (k_chain): its links in the order they are worked off
     const int32_t *words;
     int32_t n_links;         // 0: not a chain
+    bool walks;              // a wave per column (k_chain, k_walk64), else one per sixteen (k_chain_wide)
 };
 
 struct RowsDev {             // product-layer rows of a dataflow launch as neighbour lists
@@ -148,7 +149,13 @@ void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int3
                           int32_t *ticket, const float *tables, const GroupDev &in, hipStream_t s);
 void launch_begin_backward(const float *l, float *F, float *N, float *nfmax, const int32_t *blk_ids, int32_t n_blk, int32_t root_id,
                            int32_t K, int64_t Bs, int32_t B, const int32_t *ent, int32_t n_ent, int32_t *ticket, hipStream_t s);
-void launch_chain(const float *theta, float *l, float *R, float *F, bool bwd, const ChainDev &c, int64_t Bs, int32_t B, float *ll, hipStream_t s);
+bool chain_walks(bool few_weights, int32_t n_links, int32_t K, int64_t Bs);
+// N, nfmax not null (backward, where it walks): the launch does k_begin_backward's work for the root and the null block
+void launch_chain(const float *theta, float *l, float *R, float *F, float *N, float *nfmax, bool bwd, const ChainDev &c, int32_t K, int64_t Bs, int32_t B,
+                  float *ll, hipStream_t s);
+// the whole of a forward pass that keeps nothing but ll, over a circuit that is a chain from its inputs to the root (ChainTab::whole)
+void launch_walk_pass(const float *theta, const float *tables, const int32_t *x, const uint8_t *mask, const ChainDev &c, int32_t K, int32_t B,
+                      int32_t n_vars, int32_t n_cats, float *ll, hipStream_t s);
 void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, bool bwd, const FlowDev &f, int32_t K, int64_t Bs, int32_t B,
                  int32_t *ticket, float *ll, int32_t wait_limit, int32_t *fault, hipStream_t s);
 

@@ -1,0 +1,55 @@
+"""Chains of single blocks walked with a wave per column: both sides of the batch sizes where the kernel changes, more links than a
+lane holds rows of (64), weights that change with every link, and the pass of pc_forward_static in one launch; kernels asserted."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2406_00766_amd import binding as pcb
+from paper_2406_00766_amd import workloads as W
+from tests.refs import kernels
+from tests.test_gpu_dataflow import Dag
+from tests.test_gpu_parity import check_all, check_repeated
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,T,B,reps,names", [
+    (32, 3, 64, 32, ("k_chain<false>", "k_chain<true>")), (32, 3, 64, 33, ("k_chain_wide<false>", "k_chain_wide<true>")),
+    (64, 16, 16, 256, ("k_walk64<false>", "k_walk64<true>")), (64, 16, 16, 258, ("k_flow<", "k_flow<")),
+    (32, 70, 33, 1, ("k_chain<false>", "k_chain<true>")), (64, 67, 9, 1, ("k_walk64<false>", "k_walk64<true>")),
+])
+def test_walked_chains_match_oracle(K, T, B, reps, names):
+    w = W.hmm(T, K, 30, K, B, 96, alpha_trans=0.3)
+    print(f"case walk K={K} T={T} B={B} x {reps}", flush=True)
+    for direction in (0, 1):
+        assert any(k.startswith(names[direction]) for k in kernels(w, direction, B * reps))
+    check_repeated(w, reps, (np.random.default_rng(8).random(w.x.shape) < 0.2).astype(np.uint8))
+
+
+@pytest.mark.parametrize("K,B,name", [(32, 256, "k_chain<"), (32, 257, "k_chain_wide<"), (64, 256, "k_walk64<"), (64, 257, "k_flow<")])
+def test_chains_of_many_weights(K, B, name):
+    d = Dag(K)
+    s = d.sum([d.product([d.input()])])
+    for _ in range(9): s = d.sum([d.product([s, d.input()])])
+    w = d.workload(d.sum([d.product([s, d.input()])], n_real=1), B, 97)
+    print(f"case many weights K={K} B={B}", flush=True)
+    for direction in (0, 1): assert any(k.startswith(name) for k in kernels(w, direction))
+    check_all(w)
+
+
+@pytest.mark.parametrize("K,T,B", [(32, 16, 1), (32, 130, 3), (64, 64, 2), (64, 65, 300), (32, 5, 511)])
+def test_static_pass_in_one_launch(K, T, B):
+    """The same numbers as pc_forward, with masked variables, a category out of range and nothing read from the workspace."""
+    w = W.hmm(T, K, 30, K, B, 98, alpha_trans=0.3)
+    x, mask = w.x.copy(), (np.random.default_rng(9).random(w.x.shape) < 0.3).astype(np.uint8)
+    if B > 2: x[2, T - 1] = -7; mask[2, T - 1] = 0
+    c = pcb.Circuit(w)
+    c.set_batch(x, mask)
+    ref = c.forward().clone()
+    ll = torch.full_like(ref, float("nan"))
+    print(f"case static walk K={K} T={T} B={B}", flush=True)
+    pcb.pc_forward_static(c.handle, c.theta, c.tables, c.x, c.mask, B, ll)
+    torch.cuda.synchronize()
+    assert torch.equal(ll, ref) and (B <= 2 or ll[2] == -float("inf")) and torch.isfinite(ll).sum() >= B - 1
+    c.close()
