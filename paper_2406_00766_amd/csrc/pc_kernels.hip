@@ -1926,7 +1926,7 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma(const float *__restr
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
-    // n_split > 1 (a handful of parameter blocks with many tied pairs each, e.g. a small HMM): the pairs of a block
+    // n_split > 1 (a handful of parameter blocks with many tied pairs each, e.g. a small HMM): the chunks of a block's pairs
     // are dealt to n_split waves, which add their partial flows atomically
     const int64_t wtile = (int64_t)blockIdx.x * 4 + wave;
     const int64_t tile = wtile / n_split;
@@ -1948,14 +1948,14 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma(const float *__restr
             for (int e = 0; e < 16; ++e) acc[rt][ct][e] = 0.0f;
 
     const int chunks_per_inst = (int)(Bs / 32);
-    const int n_mine = i1 - i0 > spl ? (i1 - i0 - spl + n_split - 1) / n_split : 0;   // pairs spl, spl + n_split, ...
-    const int n_chunks = n_mine * chunks_per_inst;
+    const int all = (i1 - i0) * chunks_per_inst, share = n_split == 1 ? all : (all + n_split - 1) / n_split;
+    const int chunk0 = min(spl * share, all), n_chunks = min(share, all - chunk0);
     floatx4 nf_next[NA4], lc_next[NB4], mx_next, rs_next, rc_next;
 
 #define PC_ISSUE(C)                                                                                                   \
     do {                                                                                                              \
-        const int inst_ = i0 + spl + ((C) / chunks_per_inst) * n_split;                                               \
-        const int64_t b0_ = (int64_t)((C) % chunks_per_inst) * 32 + sc4;                                              \
+        const int inst_ = i0 + (chunk0 + (C)) / chunks_per_inst;                                                      \
+        const int64_t b0_ = (int64_t)((chunk0 + (C)) % chunks_per_inst) * 32 + sc4;                                   \
         const int32_t ms_ = pf_sum[inst_], ns_ = pf_child[inst_];                                                     \
         const float *np_ = N + (int64_t)(ms_ + r0 + srow) * Bs + b0_;                                                 \
         const float *lp_ = l + (int64_t)(ns_ + c0 + srow) * Bs + b0_;                                                 \
@@ -2094,7 +2094,7 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma_wg(const float *__re
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int r0 = (wave >> 1) * Q, c0 = (wave & 1) * Q;                // this wave's quarter of the block
-    // n_split > 1: the pairs of a block are dealt to n_split workgroups, which add their partial flows atomically
+    // n_split > 1: the chunks of a block's pairs are dealt to n_split workgroups, which add their partial flows atomically
     // (a handful of blocks with many tied pairs each would otherwise keep a handful of workgroups busy)
     const int pidx = blockIdx.x / n_split, spl = blockIdx.x % n_split;
     const int32_t pb = pf_pb[pidx];
@@ -2110,8 +2110,8 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma_wg(const float *__re
             for (int e = 0; e < 16; ++e) acc[rt][ct][e] = 0.0f;
 
     const int chunks_per_inst = (int)(Bs / 32);
-    const int n_mine = i1 - i0 > spl ? (i1 - i0 - spl + n_split - 1) / n_split : 0;   // pairs spl, spl + n_split, ...
-    const int n_chunks = n_mine * chunks_per_inst;
+    const int all = (i1 - i0) * chunks_per_inst, share = n_split == 1 ? all : (all + n_split - 1) / n_split;
+    const int chunk0 = min(spl * share, all), n_chunks = min(share, all - chunk0);
     // two register sets of fetched tiles (loads two chunks ahead)
     floatx4 nfA[NL], lcA[NL], mxA, rsA, rcA;
     floatx4 nfB[NL], lcB[NL], mxB, rsB, rcB;
@@ -2122,8 +2122,8 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma_wg(const float *__re
 
 #define PC_ISSUE(C, NF, LC, MX, RS, RC)                                                                               \
     do {                                                                                                              \
-        const int inst_ = i0 + spl + ((C) / chunks_per_inst) * n_split;                                               \
-        const int64_t b0_ = (int64_t)((C) % chunks_per_inst) * 32;                                                    \
+        const int inst_ = i0 + (chunk0 + (C)) / chunks_per_inst;                                                      \
+        const int64_t b0_ = (int64_t)((chunk0 + (C)) % chunks_per_inst) * 32;                                         \
         const int32_t ms_ = pf_sum[inst_], ns_ = pf_child[inst_];                                                     \
         const __amdgpu_buffer_rsrc_t rn_ = __builtin_amdgcn_make_buffer_rsrc((void *)(N + (int64_t)ms_ * Bs + b0_), 0, PC_BUF_RANGE, PC_BUF_FLAGS); \
         const __amdgpu_buffer_rsrc_t rl_ = __builtin_amdgcn_make_buffer_rsrc((void *)(l + (int64_t)ns_ * Bs + b0_), 0, PC_BUF_RANGE, PC_BUF_FLAGS); \
@@ -3069,9 +3069,11 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
         hipLaunchKernelGGL(k_param_flow_16, dim3((unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4)), dim3(256), 0, s, theta, l, R, N, nfmax, G,
                            pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
     } else if (K == 32) {
-        // few blocks with many tied pairs each: split the pairs over waves until the launch has some 256 of them
+        // few blocks with many tied pairs each: their chunks are dealt to waves, two or more to each, until the launch has some 512 of
+        // them.  Up to 64 per block, whose adds meet on the same addresses (HMM of 32 x 32, B = 512, launch of two blocks 41 us with whole
+        // pairs dealt to up to 256 waves, 27 with 256 waves a block, now 21; 16 x 32, B = 128 15 -> 12; 32 x 128, B = 300 40 -> 26).
         const int64_t avg_pairs = pf.n_pairs / pf.n_pb;
-        const int n_split = (int)std::max<int64_t>(1, std::min<int64_t>(avg_pairs, 256 / pf.n_pb));
+        const int n_split = avg_pairs < 2 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(avg_pairs * (Bs / 32) / 2, std::min(64, 512 / pf.n_pb)));
         const unsigned wgs = (unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4);
         if ((int64_t)pf.n_pairs * (Bs / 32) < 12 * (int64_t)pf.n_pb * n_split)   // fewer than 12 chunks per wave on average
             hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, true>), dim3(wgs), dim3(256), 0, s, theta, l,
@@ -3080,8 +3082,12 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
             hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, false>), dim3(wgs), dim3(256), 0, s, theta, l,
                                R, N, nfmax, G, pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
     } else {
-        // few blocks with many tied pairs each: split the pairs over workgroups until the launch has some 256 of them
-        const int n_split = (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));
+        // few blocks with many tied pairs each: the pairs are dealt to workgroups until the launch has some 256 of them; where that leaves
+        // short reductions (below), their chunks, two or more to each, until it has some 512 (HMM of 4 x 64, B = 512 38 -> 9 us, 32 x 64 39 ->
+        // 14; 32 x 512, B = 77 42 -> 31, with 1024 workgroups 34; K = 128, 32 x 128, B = 100 34 -> 25).
+        int n_split = (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));
+        const int64_t chunks = pf.n_pairs * (Bs / 32) / pf.n_pb;
+        if (n_split > 1 && chunks < 64 * n_split) n_split = (int)std::max<int64_t>(n_split, std::min<int64_t>(chunks / 2, std::min(128, 512 / pf.n_pb)));
         // short reductions (fewer than 64 chunks per workgroup on average): the single-tile form
         const bool one = (int64_t)pf.n_pairs * (Bs / 32) < 64 * (int64_t)pf.n_pb * n_split;
 #define PC_PF_WG(KK, ONE, BF)                                                                                       \
