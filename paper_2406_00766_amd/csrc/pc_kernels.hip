@@ -2305,20 +2305,19 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma_wg(const float *__re
 // SEG: much longer rows are cut into segments, and a wave takes one row of a segment: their sums come from k_em_row_sums (part),
 // every segment adds up those of its group.  Measured on one row of 10 000 blocks of 32 columns: 1519 us by one wave, so 40 us.
 template <int V, int NR, bool SEG>
-__global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, float *__restrict__ G, const int32_t *__restrict__ ptr,
-                                                  const int32_t *__restrict__ list, const int32_t *__restrict__ pb_rows,
-                                                  const int32_t *__restrict__ pb_cols, const int32_t *__restrict__ group_nch,
-                                                  int32_t n_groups, const int32_t *__restrict__ seg, const float *__restrict__ part,
-                                                  int32_t K, float step, float pc)
+__device__ inline void em_theta_rows(int g, int first_row, int row_step, float *__restrict__ theta, float *__restrict__ G, const int32_t *__restrict__ ptr,
+                                     const int32_t *__restrict__ list, const int32_t *__restrict__ pb_rows, const int32_t *__restrict__ pb_cols,
+                                     const int32_t *__restrict__ group_nch, int32_t n_groups, const int32_t *__restrict__ seg,
+                                     const float *__restrict__ part, int32_t K, float step, float pc)
 {
     typedef float vec __attribute__((ext_vector_type(V)));
-    const int g = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63;
     const int32_t *blk = list + ptr[g];
     const int n = ptr[g + 1] - ptr[g], kv = K / V, tot = n * kv;
     const int rows = g < n_groups ? pb_rows[blk[0]] : 0;
     const float share = g < n_groups ? pc / (float)(SEG ? seg[3 * g + 2] : group_nch[g]) : 0.0f;
     const vec zero = {};
-    for (int i = blockIdx.y * n_waves + wave; i < K; i += gridDim.y * n_waves) {
+    for (int i = first_row; i < K; i += row_step) {
         if (i >= rows) {                                                // wave-uniform: placeholders, unused blocks
             for (int q = lane; q < tot; q += 64)
                 *reinterpret_cast<vec *>(G + (int64_t)blk[q / kv] * K * K + (int64_t)i * K + (q % kv) * V) = zero;
@@ -2375,6 +2374,18 @@ __global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, flo
     }
 }
 
+template <int V, int NR, bool SEG>
+__global__ __launch_bounds__(256) void k_em_theta(float *__restrict__ theta, float *__restrict__ G, const int32_t *__restrict__ ptr,
+                                                  const int32_t *__restrict__ list, const int32_t *__restrict__ pb_rows,
+                                                  const int32_t *__restrict__ pb_cols, const int32_t *__restrict__ group_nch,
+                                                  int32_t n_groups, const int32_t *__restrict__ seg, const float *__restrict__ part,
+                                                  int32_t K, float step, float pc)
+{
+    const int wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    em_theta_rows<V, NR, SEG>(blockIdx.x, blockIdx.y * n_waves + wave, gridDim.y * n_waves, theta, G, ptr, list, pb_rows, pb_cols, group_nch, n_groups, seg,
+                              part, K, step, pc);
+}
+
 // Row sums of the segments of long rows: a wave per row of a segment.
 template <int V>
 __global__ __launch_bounds__(256) void k_em_row_sums(const float *__restrict__ G, const int32_t *__restrict__ ptr,
@@ -2402,11 +2413,21 @@ __global__ __launch_bounds__(256) void k_em_row_sums(const float *__restrict__ G
 // Tables whose flows one workgroup can hold in registers (16 float4 per thread): column sums and update in one pass, the flows
 // read once.  K a power of two >= 4; a thread owns nodes 4 kq .. 4 kq + 3 of every R-th category, the partial column sums of the
 // R rows of threads meet in LDS.  Measured on 12 288 tables of 256 x 64 (3.2 GB moved): 0.64 ms against 0.20 + 0.59 ms.
-template <int NT>
+// THETA: small models, where a launch costs as much as the work, have the parameters in the same launch: n_tables workgroups for the
+// tables, then those of k_em_theta, `shares` of a row group (16 x 32 HMM: 3.9 + 3.0 us, together 3.9).
+template <int NT, bool THETA>
 __global__ __launch_bounds__(NT) void k_em_tables_whole(float *__restrict__ tables, float *__restrict__ Gt, int32_t K, int32_t n_cats,
-                                                        float step, float pc)
+                                                        float step, float pc, int32_t n_tables, float *__restrict__ theta, float *__restrict__ G,
+                                                        const EmDev em, int32_t shares)
 {
     __shared__ float4 red[NT];
+    if constexpr (THETA)
+        if ((int)blockIdx.x >= n_tables) {
+            const int q = (int)blockIdx.x - n_tables;
+            em_theta_rows<4, 1, false>(q / shares, q % shares * 4 + (int)(threadIdx.x >> 6), shares * 4, theta, G, em.ptr, em.list, em.pb_rows, em.pb_cols,
+                                       em.group_nch, em.n_groups, nullptr, nullptr, K, step, pc);
+            return;
+        }
     const float share = pc / (float)n_cats;
     const int k4n = K / 4, kq = threadIdx.x % k4n, rs = threadIdx.x / k4n, R = NT / k4n;
     float4 *tb = reinterpret_cast<float4 *>(tables + (int64_t)blockIdx.x * n_cats * K) + kq;
@@ -3160,6 +3181,17 @@ void launch_sum_bf16(const void *Th, const void *Tl, const void *Ph, const void 
 void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow, const EmDev &em, int32_t K,
                int32_t n_tables, int32_t n_cats, float step, float pc, hipStream_t s)
 {
+    // one workgroup per table where it can hold the flows and there are enough tables, or too little data to share out
+    const int64_t per_table = (int64_t)n_cats * K;
+    const bool whole = K >= 4 && (K & (K - 1)) == 0 && per_table <= 65536 && (n_tables >= 64 || per_table <= 8192);
+    // up to the workgroups the chip holds at once with the tables' registers: beyond, the launch is little beside the work
+    const int32_t shares = (K + 3) / 4;
+    if (whole && per_table <= 16384 && em.n_seg == 0 && (K & 3) == 0 && em.avg_list * (K / 4) <= 64 && n_tables + (int64_t)em.n_all * shares <= 1024) {
+        Timed timed(KC_EM, s);
+        hipLaunchKernelGGL((k_em_tables_whole<256, true>), dim3((unsigned)(n_tables + em.n_all * shares)), dim3(256), 0, s, tables, table_flow, K, n_cats, step,
+                           pc, n_tables, theta, theta_flow, em, shares);
+        return;
+    }
     {
         Timed timed(KC_EM, s);
         // up to four rows per wave, fewer where that leaves less than eight waves per SIMD; registers for the average row
@@ -3192,14 +3224,15 @@ void launch_em(float *theta, float *tables, float *theta_flow, float *table_flow
 #undef PC_EM_SEG
         }
     }
-    // one workgroup per table where it can hold the flows and there are enough tables, or too little data to share out
-    const int64_t per_table = (int64_t)n_cats * K;
-    if (K >= 4 && (K & (K - 1)) == 0 && per_table <= 65536 && (n_tables >= 64 || per_table <= 8192)) {
+    if (whole) {
         Timed timed(KC_EM, s);
         const dim3 grid((unsigned)n_tables);
-        if (per_table <= 16384) hipLaunchKernelGGL(k_em_tables_whole<256>, grid, dim3(256), 0, s, tables, table_flow, K, n_cats, step, pc);
-        else if (per_table <= 32768) hipLaunchKernelGGL(k_em_tables_whole<512>, grid, dim3(512), 0, s, tables, table_flow, K, n_cats, step, pc);
-        else hipLaunchKernelGGL(k_em_tables_whole<1024>, grid, dim3(1024), 0, s, tables, table_flow, K, n_cats, step, pc);
+#define PC_EM_WHOLE(NN) \
+    hipLaunchKernelGGL((k_em_tables_whole<NN, false>), grid, dim3(NN), 0, s, tables, table_flow, K, n_cats, step, pc, n_tables, nullptr, nullptr, em, 0)
+        if (per_table <= 16384) PC_EM_WHOLE(256);
+        else if (per_table <= 32768) PC_EM_WHOLE(512);
+        else PC_EM_WHOLE(1024);
+#undef PC_EM_WHOLE
         return;
     }
     launch_fill(em.ztab, (int64_t)n_tables * K, 0.0f, s);
