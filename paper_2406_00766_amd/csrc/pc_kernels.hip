@@ -186,7 +186,8 @@ __global__ __launch_bounds__(256) void k_input_bwd_direct(const float *__restric
 // read-modify-write waits for its read (measured: 0.87 against 0.55 ms on 12 K blocks).  The order of the samples of
 // a category is whatever the sort's atomics gave, so sums may differ in the last bit between runs, as with the
 // other variants.
-__global__ __launch_bounds__(256) void k_input_bwd_sorted(const float *__restrict__ F, const int32_t *__restrict__ xT,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_input_bwd_sorted(const float *__restrict__ F, const int32_t *__restrict__ xT,
                                                           const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
                                                           const int32_t *__restrict__ tab, int32_t K, int32_t n_cats,
                                                           int64_t Bs, float *__restrict__ table_flow, int SB, int lpc)
@@ -197,32 +198,47 @@ __global__ __launch_bounds__(256) void k_input_bwd_sorted(const float *__restric
     int *cats = reinterpret_cast<int *>(tile + (size_t)K * LDT);        // [SB] category of a sample, < 0: no flow
     int *pos = cats + SB;                                               // [SB] column of a sample in the tile, -1: none
     int *start = pos + SB;                                              // [n_cats + 1] counts, then segment starts
-    int *wsum = start + n_cats + 1;                                     // [4] scan scratch
+    int *wsum = start + n_cats + 1;                                     // [NT / 64] scan scratch
+    constexpr int NV = 4;                                               // 16-byte loads in flight per thread
+    constexpr int PT = 1024 / NT;                                       // samples and categories of a thread, at most
     const int u = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t b0 = (int64_t)blockIdx.y * SB;
     const int nb = (int)((Bs - b0) < SB ? (Bs - b0) : SB);              // samples of this slab (a multiple of 32)
     const int32_t id = ids[u];
 
-    for (int c = tid; c <= n_cats; c += 256) start[c] = 0;
-    for (int i = tid; i < nb; i += 256) cats[i] = xT[(int64_t)var[u] * Bs + b0 + i];
+    // flows of the block: 16-byte loads along the batch, on their way while the samples are sorted
+    const int n4 = nb / 4, total = K * n4;
+    const uint32_t inv_n4 = 0xffffffffu / (uint32_t)n4 + 1;             // idx / n4 = umulhi(idx, inv_n4): idx < 2^16, 8 <= n4 <= 256
+    float4 v[NV];
+    auto load = [&](int base0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int idx = base0 + tid + NT * j;
+            const int row = (int)__umulhi((uint32_t)idx, inv_n4), c4 = (idx - row * n4) * 4;
+            v[j] = idx < total ? *reinterpret_cast<const float4 *>(F + (int64_t)(id + row) * Bs + b0 + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    load(0);
+    for (int c = tid; c <= n_cats; c += NT) start[c] = 0;
+    for (int i = tid; i < nb; i += NT) cats[i] = xT[(int64_t)var[u] * Bs + b0 + i];
     __syncthreads();
     // counting sort: rank inside the category, counts -> exclusive scan -> columns
-    int rank[4];                                                        // SB <= 1024: at most 4 samples per thread
+    int rank[PT];                                                       // SB <= 1024: at most PT samples per thread
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int i = tid + 256 * j;
+    for (int j = 0; j < PT; ++j) {
+        const int i = tid + NT * j;
         rank[j] = (i < nb && cats[i] >= 0) ? atomicAdd(start + cats[i], 1) : 0;
     }
     __syncthreads();
-    const int per = (n_cats + 255) / 256;                               // categories per thread (<= 4)
-    int loc[4], tot = 0;
+    const int per = (n_cats + NT - 1) / NT;                             // categories per thread (<= PT)
+    int loc[PT], tot = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < PT; ++j) {
         const int c = tid * per + j;
         loc[j] = (j < per && c < n_cats) ? start[c] : 0;
         tot += loc[j];
     }
-    int incl = tot;                                                     // inclusive scan over the wave, then over the 4 waves
+    int incl = tot;                                                     // inclusive scan over the wave, then over the waves
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int v = __shfl_up(incl, off);
@@ -233,35 +249,26 @@ __global__ __launch_bounds__(256) void k_input_bwd_sorted(const float *__restric
     int run = incl - tot;
     for (int w2 = 0; w2 < wave; ++w2) run += wsum[w2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < PT; ++j) {
         const int c = tid * per + j;
         if (j < per && c < n_cats) { start[c] = run; run += loc[j]; }
     }
-    if (tid == 255) start[n_cats] = run;
+    if (tid == NT - 1) start[n_cats] = run;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int i = tid + 256 * j;
+    for (int j = 0; j < PT; ++j) {
+        const int i = tid + NT * j;
         if (i < nb) pos[i] = cats[i] >= 0 ? start[cats[i]] + rank[j] : -1;
     }
     __syncthreads();
-    // flows of the block: 16-byte loads along the batch, columns scattered into category order
-    // (eight loads in flight per thread: a load waited for on its own costs a trip to HBM)
-    const int n4 = nb / 4, total = K * n4;
-    for (int base0 = tid; base0 < total; base0 += 256 * 8) {
-        float4 v[8];
+    // columns scattered into category order; rows of a tile of more than NT * NV quads come in further rounds
+    for (int base0 = 0; base0 < total; base0 += NT * NV) {
+        if (base0 > 0) load(base0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int idx = base0 + 256 * j;
-            const int row = idx / n4, c4 = (idx - row * n4) * 4;
-            v[j] = idx < total ? *reinterpret_cast<const float4 *>(F + (int64_t)(id + row) * Bs + b0 + c4)
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int idx = base0 + 256 * j;
+        for (int j = 0; j < NV; ++j) {
+            const int idx = base0 + tid + NT * j;
             if (idx >= total) break;
-            const int row = idx / n4, c4 = (idx - row * n4) * 4;
+            const int row = (int)__umulhi((uint32_t)idx, inv_n4), c4 = (idx - row * n4) * 4;
             float *dst = tile + row * LDT;
             const int p0 = pos[c4], p1 = pos[c4 + 1], p2 = pos[c4 + 2], p3 = pos[c4 + 3];
             if (p0 >= 0) dst[p0] = v[j].x;
@@ -272,7 +279,7 @@ __global__ __launch_bounds__(256) void k_input_bwd_sorted(const float *__restric
     }
     __syncthreads();
     // one group of lpc lanes per category at a time; a lane owns nodes k, k + lpc, ...
-    const int grp = tid / lpc, kl = tid % lpc, n_grp = 256 / lpc;
+    const int grp = tid / lpc, kl = tid % lpc, n_grp = NT / lpc;
     float *base = table_flow + (int64_t)tab[u] * n_cats * K;
     for (int c = grp; c < n_cats; c += n_grp) {
         const int s0 = start[c], s1 = start[c + 1];
@@ -2683,24 +2690,34 @@ void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int3
     if (!(attr_set.load(std::memory_order_relaxed) & bit)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_input_bwd_hist), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   96 * 1024);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_input_bwd_sorted), hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_input_bwd_sorted<256>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  96 * 1024);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_input_bwd_sorted<512>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  96 * 1024);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_input_bwd_sorted<1024>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   96 * 1024);
         attr_set.fetch_or(bit, std::memory_order_relaxed);
     }
-    // slab of samples for the sorted variant: a [K x SB] tile of at most 34 KB, four workgroups per CU (66 KB tiles
-    // combine more samples per category and were 5 % slower; 18 KB tiles 10 % slower)
+    // slab of samples for the sorted variant: a [K x SB] tile of at most 66 KB, two workgroups per CU.  Threads by the tile, four 16-byte
+    // loads each or less: 256 up to 16 KB (K = 32, B = 128, 25 088 blocks 157 us, with 512 194), 512 up to 48 KB (B = 352 345, with 256 468,
+    // with 1024 415), then 1024 (B = 512 486, with 512 542).  256 threads at every size had wanted tiles of 34 KB, four workgroups per CU,
+    // and more adds per category (B = 512 618; K = 64, 12 288 blocks, B = 256 507, now 322; 1568 blocks, B = 512 138, now 100).
     int SB = 1024;
-    while (SB > 32 && (size_t)K * (SB + 1) * 4 > 34 * 1024) SB >>= 1;
+    while (SB > 32 && (size_t)K * (SB + 1) * 4 > 66 * 1024) SB >>= 1;
     if (SB > Bs) SB = (int)Bs;
-    const size_t sorted_bytes = ((size_t)K * (SB + 1) + 2 * (size_t)SB + n_cats + 1 + 4) * 4;
+    const size_t sorted_bytes = ((size_t)K * (SB + 1) + 2 * (size_t)SB + n_cats + 1 + 16) * 4;
     if (hist_bytes <= 96 * 1024 && (int64_t)n_cats * 4 <= Bs) {           // many samples per category: privatise in LDS
         hipLaunchKernelGGL(k_input_bwd_hist, dim3((unsigned)g.n_rows), dim3(256), hist_bytes, s, F, xT, g.ids, g.nbr, g.par, K,
                            n_cats, Bs, table_flow, lps, g.tied ? 1 : 0);
     } else if (n_cats <= 1024 && SB >= 64) {                             // few samples per category: combine them first
         const int n_slabs = (int)((Bs + SB - 1) / SB);
         dim3 grid((unsigned)g.n_rows, (unsigned)n_slabs);
-        hipLaunchKernelGGL(k_input_bwd_sorted, grid, dim3(256), sorted_bytes, s, F, xT, g.ids, g.nbr, g.par, K, n_cats, Bs,
-                           table_flow, SB, lps);
+#define PC_SORTED(NT) hipLaunchKernelGGL(k_input_bwd_sorted<NT>, grid, dim3(NT), sorted_bytes, s, F, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, table_flow, SB, lps)
+        const int64_t tile = (int64_t)K * SB * 4;
+        if (tile <= 16 * 1024) PC_SORTED(256);
+        else if (tile <= 48 * 1024) PC_SORTED(512);
+        else PC_SORTED(1024);
+#undef PC_SORTED
     } else {
         dim3 grid((unsigned)g.n_rows, (unsigned)((Bs + 63) / 64));
         hipLaunchKernelGGL(k_input_bwd_direct, grid, dim3(256), tile_bytes, s, F, xT, g.ids, g.nbr, g.par, K, n_cats, Bs,
