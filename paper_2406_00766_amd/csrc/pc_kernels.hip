@@ -89,11 +89,13 @@ __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tab
 template <int KC, int COLS>
 __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                         const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
-                                                        const int32_t *__restrict__ tab, int32_t K, int32_t n_cats,
-                                                        int64_t Bs, float *__restrict__ l, float *__restrict__ R)
+                                                        const int32_t *__restrict__ tab, int32_t n_rows, int32_t n_ct, int32_t K,
+                                                        int32_t n_cats, int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
     extern __shared__ float smem[];
-    input_tile<KC, COLS, false>(smem, (int)blockIdx.x, (int64_t)blockIdx.y * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
+    const int u = input_tile_block((int)blockIdx.x, n_ct);
+    if (u >= n_rows) return;                                            // the whole workgroup
+    input_tile<KC, COLS, false>(smem, u, (int64_t)((int)(blockIdx.x >> 3) % n_ct) * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
 }
 
 // table_flow[t][x_b,v][k] += F[n,b] for observed variables.
@@ -2660,8 +2662,8 @@ void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g,
     if (g.n_rows == 0) return;
     if (input_tile_cols(g, K, Bs) > 0) {
 #define PC_INPUT_TILE(KK, CC) \
-        hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), dim3((unsigned)g.n_rows, (unsigned)((Bs + CC - 1) / CC)), dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, \
-                           tables, xT, g.ids, g.nbr, g.par, K, n_cats, Bs, l, R)
+        hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), dim3((unsigned)((g.n_rows + 7) / 8 * 8 * ((Bs + CC - 1) / CC))), dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, \
+                           tables, xT, g.ids, g.nbr, g.par, g.n_rows, (int32_t)((Bs + CC - 1) / CC), K, n_cats, Bs, l, R)
         if (input_tile_cols(g, K, Bs) == 128) PC_INPUT_TILE(32, 128);
         else if (K == 32) PC_INPUT_TILE(32, 64);
         else if (K == 64) PC_INPUT_TILE(64, 64);
