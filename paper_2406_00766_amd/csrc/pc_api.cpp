@@ -538,6 +538,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
                          tables, dev(c->layers[0].fwd[0]), s);
     const LaunchPlan &plan = *(const LaunchPlan *)c->plan;
     if (w.bf16) launch_split_theta(theta, (int64_t)c->n_param_blocks + 1, K, false, base + w.th_off, base + w.tl_off, s);
+    bool read_out = false;
     for (size_t li = 0; li < li0; ++li) {
         const LayerTab &L = c->layers[li];
         if (L.kind == KIND_INPUT) {
@@ -552,8 +553,8 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
                             plan.layers[li].fwd[0], K, w.Bs, s);
         } else {
             // product-scratch mode: the children are the product layer just before, in the window
-            launch_sum_fwd(theta, c->product_scratch ? window_base(c, c->layers[li - 1], l, w.Bs) : l, l, R, plan.layers[li].fwd, K,
-                           w.Bs, s);
+            read_out |= launch_sum_fwd(theta, c->product_scratch ? window_base(c, c->layers[li - 1], l, w.Bs) : l, l, R, (float *)(base + w.f_off),
+                                       plan.layers[li].fwd, K, w.Bs, (int32_t)li == c->root_layer ? ll : nullptr, B, s);
         }
     }
     if (li0 < L) {
@@ -563,7 +564,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     }
     // a root among the layers of the dataflow launch has written ll; blocks it does not reach may lie deeper, and then the
     // part that runs as dataflow can begin above the root
-    if ((size_t)c->root_layer < li0) {
+    if ((size_t)c->root_layer < li0 && !read_out) {
         launch_readout(l, R, (int64_t)(c->root_block + 1) * K, (int64_t)c->root_block + 1, w.Bs, B, ll, s);
     }
     PC_HIP(hipGetLastError());

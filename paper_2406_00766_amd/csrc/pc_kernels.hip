@@ -1387,7 +1387,8 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ct = wave / SPLIT, sp = wave % SPLIT;
-    const GroupRow gr = locate_row<MULTI ? PC_ROWS_MULTI : PC_ROWS_ONE>(gs, blockIdx.x / SUB);
+    constexpr bool PART = MODE == 3;                                    // one row, its chunks in gs.first[2] parts (sum_parts), results to F
+    const GroupRow gr = locate_row<MULTI ? PC_ROWS_MULTI : PC_ROWS_ONE>(gs, PART ? 0 : blockIdx.x / SUB);
     const int r = gr.r, sub = blockIdx.x % SUB;
     const int64_t col0 = ((int64_t)blockIdx.y * NCT + ct) * 32;
     const bool active = col0 < Bs;                                      // wave-uniform
@@ -1398,7 +1399,9 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     // backward: the first layer of the sweep that feeds this block stores its flow, later ones accumulate
     const bool first = (fl & 2) != 0;
     float *buf = lds + wave * WSZ;
-    const int n_chunks = (fl >> 8) * CPB;                               // real neighbours; padding sits at the end of a row
+    const int n_row = (fl >> 8) * CPB;                                  // real neighbours; padding sits at the end of a row
+    const int share = PART ? (n_row + gs.first[2] - 1) / gs.first[2] : n_row, chunk0 = PART ? (int)(blockIdx.x / SUB) * share : 0;
+    const int n_chunks = PART ? min(chunk0 + share, n_row) : n_row;
 
     // block reference of this row.  Backward: the row's own.  Forward: the maximum of the children's, found
     // on the fly -- Rrow is the maximum over the chunks seen so far and the running maximum m is relative to it
@@ -1544,7 +1547,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     };
     if (!PF) {
         Operands o;
-        for (int c = sp; c < n_chunks; c += SPLIT) {
+        for (int c = chunk0 + sp; c < n_chunks; c += SPLIT) {
             load_chunk(c, o);
             run_chunk(o);
         }
@@ -1600,6 +1603,16 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
         }
     }
     if (!active) return;
+    if (PART) {                                                         // K rows of sums, their maximum's shift and reference (k_sum_merge)
+        float *po = F + (int64_t)(blockIdx.x / SUB) * (K + 2) * Bs + col;
+#pragma unroll
+        for (int k = 0; k < ES; ++k) {
+            const int q = sp * ES + k;
+            po[(int64_t)(sub * TM + q / 16 * 32 + 8 * (q % 16 / 4) + 4 * half + q % 4) * Bs] = res[k];
+        }
+        if (sub == 0 && sp == 0) po[(int64_t)(K + half) * Bs] = half ? Rrow : m;
+        return;
+    }
     if (!BWD && sub == 0 && sp == 0 && half == 0) R[(int64_t)(id / K) * Bs + col] = Rrow;
     // Results out.  The rows are addressed through one buffer descriptor at the tile's first row with a scalar offset
     // per row.  Backward: log and exp are the hardware's base-2 instructions (the accumulator of a column with any
@@ -1632,6 +1645,57 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), ro, ooff, so, 0);
         }
     }
+}
+
+// The parts of a row (k_sum_mfma, MODE 3; 32 at most) merged as the waves of a workgroup merge theirs.  Workgroup = 8 rows x 32 columns,
+// thread = one of them; all its loads are requested at once.  ll not null: the row is the root's, node 0 of it is read out.
+__global__ __launch_bounds__(256) void k_sum_merge(const float *__restrict__ part, int32_t n_parts, float *__restrict__ l, float *__restrict__ R,
+                                                   const int32_t *__restrict__ ids, int32_t K, int64_t Bs, float *__restrict__ ll, int32_t B)
+{
+    __shared__ float scale[32][32], top[2][8][32];                      // a part's factor; the threads' largest references and shifts
+    const int c32 = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const int64_t col = (int64_t)blockIdx.y * 32 + c32, step = (int64_t)(K + 2) * Bs;
+    const int row = (int)blockIdx.x * 8 + g;
+    const float *p = part + col;
+    const int32_t id = ids[0];
+    float v[32];
+#pragma unroll
+    for (int s = 0; s < 32; ++s) v[s] = s < n_parts ? p[s * step + (int64_t)row * Bs] : 0.0f;
+    float ms[4], Ro[4], Rm = PC_NEG_INF, m = PC_NEG_INF;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int s = g + 8 * i;
+        ms[i] = s < n_parts ? p[s * step + (int64_t)K * Bs] : PC_NEG_INF;
+        Ro[i] = s < n_parts ? p[s * step + (int64_t)(K + 1) * Bs] : PC_NEG_INF;   // -inf: a part without chunks
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Rm = fmaxf(Rm, Ro[i]);
+    top[0][g][c32] = Rm;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) Rm = fmaxf(Rm, top[0][i][c32]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ms[i] = Ro[i] > PC_NEG_INF ? ms[i] + (Ro[i] - Rm) : PC_NEG_INF;
+        m = fmaxf(m, ms[i]);
+    }
+    top[1][g][c32] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = fmaxf(m, top[1][i][c32]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) scale[g + 8 * i][c32] = m > PC_NEG_INF ? pc_half_scale(ms[i] - m) : 0.0f;
+    __syncthreads();
+    float sum = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 32; ++s) {
+        const float h = scale[s][c32];
+        sum += v[s] * h * h;
+    }
+    const float out = fmaf(__builtin_amdgcn_logf(sum * 0x1p-24f), 0.6931471805599453f, m + (16.635532333f - PC_UP));
+    l[(int64_t)(id + row) * Bs + col] = out;
+    if (row == 0) R[(int64_t)(id / K) * Bs + col] = Rm;
+    if (row == 0 && ll && col < B) ll[col] = Rm + out;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2948,13 +3012,26 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
     while (split < (rt == 1 ? 16 : 4) && tiles * split < want && (int64_t)width * (K / 32) >= (split < 4 ? 2 : 4) * split) split <<= 1;
 }
 
+// Forward, a layer of one row block with a long row (a root): parts of the row to as many workgroups of four waves, two chunks to a wave and more,
+// and a launch that merges them.  One workgroup per tile reads through one CU's 64 bytes a clock, 8 KiB a chunk.  The parts lie in F, which
+// a forward pass does not use otherwise and which holds the row's children: parts * (K + 2) rows are fewer than theirs.
+// Root over 256 blocks of 32 nodes, sixteen waves and the readout / parts, merge and readout in one: B = 16 51 + 4 / 6 + 4 us, B = 512 49 + 5 / 9 + 5;
+// pass of the HMM of 4096 states in blocks of 128, B = 256 (32 tiles) 3921 / 3907.  Rows of fewer than 64 chunks are four to a wave of sixteen.
+static int sum_parts(int32_t K, int32_t n_groups, int32_t n_rows, int32_t width, int64_t Bs)
+{
+    const int64_t chunks = (int64_t)width * (K / 32), tiles = (K / 32) * ((Bs + 31) / 32);
+    if (n_groups != 1 || n_rows != 1 || chunks < 64 || tiles > 32) return 1;
+    return (int)std::min<int64_t>(std::min<int64_t>(32, chunks / 8), 512 / tiles);
+}
+
 void sum_kernel_name(char (&name)[64], const GroupSet &gs, bool bwd, int32_t K, int64_t Bs)
 {
     const char *dir = bwd ? "bwd" : "fwd";
     if (use_mfma(K)) {
         int rt, split;
         pick_sum_shape(K, set_rows(gs), set_width(gs), Bs, rt, split);
-        std::snprintf(name, sizeof(name), "k_sum_mfma<%d, %d, %d, %s>", (int)K, rt, split, bwd ? "true" : "false");
+        if (!bwd && sum_parts(K, gs.n, set_rows(gs), set_width(gs), Bs) > 1) std::snprintf(name, sizeof(name), "k_sum_mfma<%d, 1, 4, false, false, 3>", (int)K);
+        else std::snprintf(name, sizeof(name), "k_sum_mfma<%d, %d, %d, %s>", (int)K, rt, split, bwd ? "true" : "false");
     } else if (use_16(K)) {
         std::snprintf(name, sizeof(name), "k_sum_16<%s>", bwd ? "true" : "false");
     } else if (use_small(K)) {
@@ -2984,12 +3061,25 @@ static void launch_sum_16(const float *theta, const float *X, float *l, float *R
 #undef PC_SUM_16
 }
 
-void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, const std::vector<GroupSet> &sets, int32_t K,
-                    int64_t Bs, hipStream_t s)
+bool launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, float *part, const std::vector<GroupSet> &sets, int32_t K,
+                    int64_t Bs, float *ll, int32_t B, hipStream_t s)
 {
+    bool read_out = false;
     if (use_mfma(K)) {
         for (const GroupSet &gs : sets) {
             Timed timed(KC_SUM_FWD, s);
+            const int parts = sets.size() == 1 ? sum_parts(K, gs.n, set_rows(gs), set_width(gs), Bs) : 1;
+            if (parts > 1) {
+                GroupSet ps = gs;
+                ps.first[2] = parts;
+                const dim3 grid((unsigned)(parts * (K / 32)), (unsigned)(Bs / 32));
+#define PC_SUM_PART(KK) hipLaunchKernelGGL((k_sum_mfma<KK, 1, 4, false, false, 3>), grid, dim3(256), 0, s, theta, l, R, lch, (const float *)nullptr, part, ps, Bs)
+                if (K == 32) PC_SUM_PART(32); else if (K == 64) PC_SUM_PART(64); else PC_SUM_PART(128);
+#undef PC_SUM_PART
+                hipLaunchKernelGGL(k_sum_merge, dim3((unsigned)(K / 8), (unsigned)(Bs / 32)), dim3(256), 0, s, part, parts, l, R, gs.ids[0], K, Bs, ll, B);
+                read_out = ll != nullptr;
+                continue;
+            }
             int rt, split;
             pick_sum_shape(K, set_rows(gs), set_width(gs), Bs, rt, split);
             const int waves = std::max(split, 4);
@@ -3002,14 +3092,14 @@ void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, co
             PC_DISPATCH_SUM(false, grid, dim3(64 * waves), 0, s, theta, l, R, lch, (const float *)nullptr,
                             (float *)nullptr, gs, Bs);
         }
-        return;
+        return read_out;
     }
     if (use_16(K)) {
         for (const GroupSet &gs : sets) {
             Timed timed(KC_SUM_FWD, s);
             launch_sum_16(theta, lch, l, R, nullptr, nullptr, gs, Bs, s);
         }
-        return;
+        return read_out;
     }
     // other block sizes: one launch per group
     for (const GroupSet &gs : sets) for (int k = 0; k < gs.n; ++k) {
@@ -3024,6 +3114,7 @@ void launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, co
                                g.n_rows, g.width, K, Bs);
         }
     }
+    return read_out;
 }
 
 void launch_sum_bwd_child(const float *theta, const float *l, const float *R, const float *N, const float *nfmax, float *F,

@@ -4,6 +4,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from paper_2406_00766_amd import binding as pcb
 from tests.refs import kernels
 from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all
@@ -28,3 +29,23 @@ def test_split_reductions_match_oracle(K, widths, B, waves):
     for direction, n in enumerate(waves):
         assert kernels(w, direction)[2] == f"k_sum_mfma<{K}, 1, {n}, {'true' if direction else 'false'}>"
     check_all(w)
+
+
+@pytest.mark.parametrize("K,width,B,parts", [
+    (32, 63, 20, False), (32, 64, 20, True), (32, 81, 70, True),       # 81 chunks in ten parts of nine: the last is empty
+    (64, 40, 33, True), (128, 17, 100, True), (32, 300, 1, True),
+    (32, 64, 1024, True), (32, 64, 1025, False), (128, 16, 256, True), (128, 16, 257, False),   # 32 tiles and more
+])
+@pytest.mark.parametrize("scratch", [False, True])
+def test_root_in_parts_matches_oracle(K, width, B, parts, scratch):
+    """A root over many products of thirteen inputs, its row in parts of several workgroups; a sample of probability 0."""
+    d = Dag(K)
+    tables = [[d.input() for _ in range(13)] for _ in range(3)]
+    w = d.workload(d.sum([d.product(tables[i % 3][:13 - i % 2]) for i in range(width)], n_real=1), B, 92)
+    if scratch:
+        w = pcb.pc_order_for_scratch(w)
+    print(f"case root in parts K={K} width={width} B={B} scratch={scratch}", flush=True)
+    assert (kernels(w, 0)[2] == f"k_sum_mfma<{K}, 1, 4, false, false, 3>") == parts
+    x = w.x.copy()
+    x[0, 0] = w.n_cats + 2
+    check_all(w.with_batch(x))
