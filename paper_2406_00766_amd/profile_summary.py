@@ -30,7 +30,7 @@ def kernel_class(name: str) -> str:
     m = re.match(r"k_flow<\s*\d+,\s*\d+,\s*\d+,\s*(true|false)|k_(?:sum_16|chain|chain_wide|walk64)<\s*(true|false)", n)
     if m:
         return "sum_bwd_child" if "true" in m.groups() else "sum_fwd"
-    for prefix, cls in (("k_walk_pass", "sum_fwd"), ("k_split_", "split"), ("k_sum_fwd", "sum_fwd"), ("k_sum_bwd_child", "sum_bwd_child"), ("k_sum_bwd_small", "sum_bwd_child"),
+    for prefix, cls in (("k_walk_pass", "sum_fwd"), ("k_split_", "split"), ("k_sum_fwd", "sum_fwd"), ("k_sum_merge", "sum_fwd"), ("k_sum_bwd_child", "sum_bwd_child"), ("k_sum_bwd_small", "sum_bwd_child"),
                         ("k_sum_bwd_param", "sum_bwd_param"), ("k_param_flow", "sum_bwd_param"), ("k_prod_fwd", "prod_fwd"), ("k_prod_tile", "prod_fwd"), ("k_class_bwd", "prod_bwd"),
                         ("k_prod_bwd", "prod_bwd"), ("k_input_fwd", "input_fwd"), ("k_input_bwd", "input_bwd"), ("k_em_", "em"),
                         ("k_measure_copy", "measure_copy"), ("k_measure_mfma", "measure_mfma")):

@@ -10,6 +10,8 @@ from paper_2406_00766_amd.profile_summary import kernel_class
     ("pc::k_sum_16<false, 4>", "sum_fwd"),
     ("pc::k_sum_16<true, 1>", "sum_bwd_child"),
     ("pc::k_sum_mfma<64, 1, 4, true, false, 1>", "sum_bwd_child"),
+    ("pc::k_sum_mfma<32, 1, 4, false, false, 3>", "sum_fwd"),
+    ("pc::k_sum_merge", "sum_fwd"),
     ("pc::k_param_flow_16", "sum_bwd_param"),
     ("pc::k_prod_fwd<2, 4, 2, 8, double, false>", "prod_fwd"),
     ("pc::k_em_theta<4, 1, false>", "em"),
