@@ -1979,7 +1979,10 @@ __global__ __launch_bounds__(256, CT == 1 ? 2 : 1) void k_sum_bf16(const uint4 *
 // to reach the MFMA operand layouts (batch index on k: step q pairs lanes 0-31 with sample 8*(q/4) + q%4
 // and lanes 32-63 with sample 8*(q/4) + 4 + q%4); loads of the next chunk are issued before the
 // arithmetic of the current one.
-template <int K, int RT, int CT, bool ONE>
+//
+// ORDERED: the four waves of a workgroup take the chunks of one block and add up their parts in LDS, in a fixed order: no atomics, so the
+// flow repeats to the bit (launch_param_flow).
+template <int K, int RT, int CT, bool ONE, bool ORDERED>
 __global__ __launch_bounds__(256, 2) void k_param_flow_mfma(const float *__restrict__ theta, const float *__restrict__ l,
                                                             const float *__restrict__ R, const float *__restrict__ N,
                                                             const float *__restrict__ nfmax, float *__restrict__ G,
@@ -2002,10 +2005,11 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma(const float *__restr
     // n_split > 1 (a handful of parameter blocks with many tied pairs each, e.g. a small HMM): the chunks of a block's pairs
     // are dealt to n_split waves, which add their partial flows atomically
     const int64_t wtile = (int64_t)blockIdx.x * 4 + wave;
-    const int64_t tile = wtile / n_split;
-    const int spl = (int)(wtile % n_split);
+    const int64_t tile = ORDERED ? blockIdx.x : wtile / n_split;
+    const int spl = ORDERED ? wave : (int)(wtile % n_split);
     const int pidx = (int)(tile / TPB), tin = (int)(tile % TPB);
-    if (pidx >= n_pb) return;                                           // wave-uniform; no workgroup barrier below
+    static_assert(!ORDERED || TPB == 1, "a workgroup is one block's");
+    if (pidx >= n_pb) return;                                           // wave-uniform; ORDERED: there are n_pb workgroups
     const int r0 = (tin / (K / TNW)) * TMW, c0 = (tin % (K / TNW)) * TNW;
     const int32_t pb = pf_pb[pidx];
     const int i0 = pf_ptr[pidx], i1 = pf_ptr[pidx + 1];
@@ -2096,6 +2100,20 @@ __global__ __launch_bounds__(256, 2) void k_param_flow_mfma(const float *__restr
     }
 #undef PC_ISSUE
 
+    if constexpr (ORDERED) {
+        const int64_t at = (int64_t)pb + (int64_t)(threadIdx.x >> 3) * K + sc4;      // 16 bytes of the block per thread
+        const floatx4 th = *reinterpret_cast<const floatx4 *>(theta + at), old = *reinterpret_cast<const floatx4 *>(G + at);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) Qs[(8 * (e / 4) + 4 * half + (e % 4)) * LD + l32] = acc[0][0][e];
+        __syncthreads();
+        floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f}, out;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) sum += *reinterpret_cast<const floatx4 *>(lds + w * TLD * LD + (threadIdx.x >> 3) * LD + sc4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = th[e] > 0.0f ? pc_flow_out(th[e], sum[e]) : 0.0f;
+        *reinterpret_cast<floatx4 *>(G + at) = old + out;
+        return;
+    }
     // Results out, 32 x 32 at a time through the wave's LDS tile, so that theta and the flows come as 16-byte loads that are all
     // requested together.  (Element by element in the accumulator's layout, a load of theta, a test, a load of the flow and a store after
     // the other, a block of one chunk was 32 memory latencies: PD of 97 K parameter blocks, B = 20 443 -> 249 us, B = 256 831 -> 791; RAT-SPN of 28.6 K,
@@ -3203,20 +3221,26 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
         // few blocks with many tied pairs each: their chunks are dealt to waves, two or more to each, until the launch has some 512 of
         // them.  Up to 64 per block, whose adds meet on the same addresses (HMM of 32 x 32, B = 512, launch of two blocks 41 us with whole
         // pairs dealt to up to 256 waves, 27 with 256 waves a block, now 21; 16 x 32, B = 128 15 -> 12; 32 x 128, B = 300 40 -> 26).
-        const int64_t avg_pairs = pf.n_pairs / pf.n_pb;
-        const int n_split = avg_pairs < 2 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(avg_pairs * (Bs / 32) / 2, std::min(64, 512 / pf.n_pb)));
+        // From 128 blocks on the result has a fixed order: up to 255 blocks four waves of one workgroup to a block of four chunks and more
+        // (132 blocks, HMM of 64 x 352, B = 128, one wave 267 us, three that add atomically 95, now 71; B = 32 71, 30, 21; 240 blocks, 4 x 480,
+        // B = 128 18, 15, 7), then one.
+        const int64_t avg_pairs = pf.n_pairs / pf.n_pb, chunks = avg_pairs * (Bs / 32);
+        const bool ordered = avg_pairs >= 2 && chunks >= 4 && pf.n_pb >= 128 && pf.n_pb < 256;
+        const int n_split = ordered ? 4 : avg_pairs < 2 || pf.n_pb >= 128 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(chunks / 2, std::min(64, 512 / pf.n_pb)));
         const unsigned wgs = (unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4);
-        if ((int64_t)pf.n_pairs * (Bs / 32) < 12 * (int64_t)pf.n_pb * n_split)   // fewer than 12 chunks per wave on average
-            hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, true>), dim3(wgs), dim3(256), 0, s, theta, l,
-                               R, N, nfmax, G, pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
-        else
-            hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, false>), dim3(wgs), dim3(256), 0, s, theta, l,
-                               R, N, nfmax, G, pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
+        const bool one = (int64_t)pf.n_pairs * (Bs / 32) < 12 * (int64_t)pf.n_pb * n_split;   // fewer than 12 chunks per wave on average
+#define PC_PF_32(ONE, ORDERED) hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, ONE, ORDERED>), dim3(wgs), dim3(256), 0, s, theta, l, R, N, nfmax, G, \
+                                                  pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs)
+        if (ordered && one) PC_PF_32(true, true);
+        else if (ordered) PC_PF_32(false, true);
+        else if (one) PC_PF_32(true, false);
+        else PC_PF_32(false, false);
+#undef PC_PF_32
     } else {
         // few blocks with many tied pairs each: the pairs are dealt to workgroups until the launch has some 256 of them; where that leaves
         // short reductions (below), their chunks, two or more to each, until it has some 512 (HMM of 4 x 64, B = 512 38 -> 9 us, 32 x 64 39 ->
         // 14; 32 x 512, B = 77 42 -> 31, with 1024 workgroups 34; K = 128, 32 x 128, B = 100 34 -> 25).
-        int n_split = (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));
+        int n_split = pf.n_pb >= 128 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));   // 128 blocks: a fixed order
         const int64_t chunks = pf.n_pairs * (Bs / 32) / pf.n_pb;
         if (n_split > 1 && chunks < 64 * n_split) n_split = (int)std::max<int64_t>(n_split, std::min<int64_t>(chunks / 2, std::min(128, 512 / pf.n_pb)));
         // short reductions (fewer than 64 chunks per workgroup on average): the single-tile form

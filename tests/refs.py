@@ -78,3 +78,47 @@ def kernels(w, direction, B=None):
         return [pcb.pc_get_kernel(h, li, direction, B or w.B) for li in range(pcb.pc_get_sizes(h).n_layers)]
     finally:
         pcb.pc_destroy(h)
+
+
+def launches(call):
+    """What `call(stream)` enqueues, in order: (kernel, workgroups in x, y, z, threads of a workgroup).  The stream is being captured and the
+    graph is dropped, so nothing runs, and device addresses that the call hands on need not name memory."""
+    import ctypes as C
+    import torch
+    from paper_2406_00766_amd import binding as pcb
+
+    class Node(C.Structure):                           # hipKernelNodeParams
+        _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3), ("params", C.c_void_p),
+                    ("shared", C.c_uint32)]
+
+    hip, demangle = pcb.lib(), C.CDLL("libstdc++.so.6").__cxa_demangle
+    hip.hipKernelNameRefByPtr.restype = demangle.restype = C.c_char_p
+    demangle.argtypes = [C.c_char_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_int)]
+
+    def ok(status):
+        assert status == 0, f"HIP error {status}"
+
+    stream = torch.cuda.Stream()
+    handle, graph, n = C.c_void_p(stream.cuda_stream), C.c_void_p(), C.c_size_t()
+    torch.cuda.synchronize()
+    ok(hip.hipStreamBeginCapture(handle, 2))           # hipStreamCaptureModeRelaxed
+    try:
+        call(stream)
+    finally:
+        ok(hip.hipStreamEndCapture(handle, C.byref(graph)))
+    out = []
+    try:
+        ok(hip.hipGraphGetNodes(graph, None, C.byref(n)))
+        nodes = (C.c_void_p * n.value)()
+        ok(hip.hipGraphGetNodes(graph, nodes, C.byref(n)))
+        for node in nodes:
+            kind, k = C.c_int(), Node()
+            ok(hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)))
+            assert kind.value == 0, f"graph node of type {kind.value}, no kernel"
+            ok(hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(k)))
+            name = hip.hipKernelNameRefByPtr(C.c_void_p(k.func), handle)
+            full = demangle(name, None, None, C.byref(C.c_int())).decode()
+            out.append((full.split("(")[0].split("::")[-1], *k.grid, k.block[0] * k.block[1] * k.block[2]))
+    finally:
+        ok(hip.hipGraphDestroy(graph))
+    return out
