@@ -3218,15 +3218,21 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
         hipLaunchKernelGGL(k_param_flow_16, dim3((unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4)), dim3(256), 0, s, theta, l, R, N, nfmax, G,
                            pf.pb, pf.ptr, pf.sum, pf.child, pf.n_pb, n_split, Bs);
     } else if (K == 32) {
-        // few blocks with many tied pairs each: their chunks are dealt to waves, two or more to each, until the launch has some 512 of
-        // them.  Up to 64 per block, whose adds meet on the same addresses (HMM of 32 x 32, B = 512, launch of two blocks 41 us with whole
-        // pairs dealt to up to 256 waves, 27 with 256 waves a block, now 21; 16 x 32, B = 128 15 -> 12; 32 x 128, B = 300 40 -> 26).
+        // few blocks with many tied pairs each: their chunks are dealt to waves, which add their parts atomically.  Two chunks to a wave until the
+        // launch has 256 of them, one up to 24 waves a block, four until it has 512 (with two, 94 chunks of each of 12 blocks, HMM of 64 x 96, B = 64,
+        // took 18.2 us, now 15.1).  At most 64 waves a block: their adds meet on the same addresses.  Whole pairs dealt out / now: 16 x 32,
+        // B = 32 6.1 / 6.1 us (two chunks a wave 7.5), B = 128 12.5 / 9.4, B = 512 37.5 / 15.7; 64 x 64, B = 64 10.9 / 12.7, B = 512 40.6 / 30.7;
+        // 32 x 128, B = 32 8.8 / 9.4, B = 512 56 / 33; two blocks with 256 waves each 27, now 21.
         // From 128 blocks on the result has a fixed order: up to 255 blocks four waves of one workgroup to a block of four chunks and more
         // (132 blocks, HMM of 64 x 352, B = 128, one wave 267 us, three that add atomically 95, now 71; B = 32 71, 30, 21; 240 blocks, 4 x 480,
         // B = 128 18, 15, 7), then one.
         const int64_t avg_pairs = pf.n_pairs / pf.n_pb, chunks = avg_pairs * (Bs / 32);
         const bool ordered = avg_pairs >= 2 && chunks >= 4 && pf.n_pb >= 128 && pf.n_pb < 256;
-        const int n_split = ordered ? 4 : avg_pairs < 2 || pf.n_pb >= 128 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(chunks / 2, std::min(64, 512 / pf.n_pb)));
+        int n_split = ordered ? 4 : 1;
+        if (avg_pairs >= 2 && pf.n_pb < 128) {
+            const int64_t few = std::min(std::max(std::min<int64_t>(avg_pairs, 24), chunks / 2), (int64_t)256 / pf.n_pb);
+            n_split = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(few, std::min(chunks / 4, (int64_t)512 / pf.n_pb)), 64));
+        }
         const unsigned wgs = (unsigned)(((int64_t)pf.n_pb * n_split + 3) / 4);
         const bool one = (int64_t)pf.n_pairs * (Bs / 32) < 12 * (int64_t)pf.n_pb * n_split;   // fewer than 12 chunks per wave on average
 #define PC_PF_32(ONE, ORDERED) hipLaunchKernelGGL((k_param_flow_mfma<32, 1, 1, ONE, ORDERED>), dim3(wgs), dim3(256), 0, s, theta, l, R, N, nfmax, G, \

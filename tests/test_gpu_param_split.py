@@ -1,5 +1,5 @@
-"""How the parameter flows of tied models are dealt to waves and workgroups: where a block keeps one, and repeats bit for bit.  The launches are
-asserted."""
+"""How the parameter flows of tied models are dealt to waves and workgroups: as many as its chunks allow where a model is small, a
+fixed order where it has many blocks.  The launches are asserted."""
 import numpy as np
 import pytest
 
@@ -40,3 +40,15 @@ def test_many_tied_blocks_repeat_bit_for_bit(T, H, K, B, waves):
     runs = [gpu_run(w) for _ in range(3)]
     for r in runs[1:]: assert np.array_equal(r["theta_flow"], runs[0]["theta_flow"])
     for r in runs: r["circuit"].close()
+
+
+@pytest.mark.parametrize("T,H,B,workgroups", [
+    (8, 32, 20, 2), (16, 32, 1, 4), (8, 64, 32, 8),                      # one chunk a pair: as many waves as pairs,
+    (64, 32, 30, 12),                                                    # up to 24 a block
+    (16, 32, 128, 8), (16, 64, 100, 30), (64, 96, 60, 69), (16, 32, 512, 32),   # two chunks a wave; four; 64 waves a block
+])
+def test_chunks_dealt_to_waves_match_oracle(T, H, B, workgroups):
+    w = W.hmm(T, H, 20, 32, B, 100, alpha_trans=0.1)
+    print(f"case chunks dealt to waves T={T} H={H} B={B}", flush=True)
+    assert param_workgroups(w) == workgroups
+    check_all(w, (np.random.default_rng(6).random(w.x.shape) < 0.2).astype(np.uint8))
