@@ -89,13 +89,13 @@ __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tab
 template <int KC, int COLS>
 __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                         const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
-                                                        const int32_t *__restrict__ tab, int32_t n_rows, int32_t n_ct, int32_t K,
+                                                        const int32_t *__restrict__ tab, int32_t n_rows, int32_t n_ct, bool by_xcd, int32_t K,
                                                         int32_t n_cats, int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
     extern __shared__ float smem[];
-    const int u = input_tile_block((int)blockIdx.x, n_ct);
+    const int u = by_xcd ? input_tile_block((int)blockIdx.x, n_ct) : (int)blockIdx.x, ct = by_xcd ? (int)(blockIdx.x >> 3) % n_ct : (int)blockIdx.y;
     if (u >= n_rows) return;                                            // the whole workgroup
-    input_tile<KC, COLS, false>(smem, u, (int64_t)((int)(blockIdx.x >> 3) % n_ct) * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
+    input_tile<KC, COLS, false>(smem, u, (int64_t)ct * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
 }
 
 // table_flow[t][x_b,v][k] += F[n,b] for observed variables.
@@ -2742,11 +2742,15 @@ void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g,
 {
     Timed timed(KC_INPUT_FWD, s);
     if (g.n_rows == 0) return;
-    if (input_tile_cols(g, K, Bs) > 0) {
-#define PC_INPUT_TILE(KK, CC) \
-        hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), dim3((unsigned)((g.n_rows + 7) / 8 * 8 * ((Bs + CC - 1) / CC))), dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, \
-                           tables, xT, g.ids, g.nbr, g.par, g.n_rows, (int32_t)((Bs + CC - 1) / CC), K, n_cats, Bs, l, R)
-        if (input_tile_cols(g, K, Bs) == 128) PC_INPUT_TILE(32, 128);
+    const int cols = input_tile_cols(g, K, Bs);
+    if (cols > 0) {
+        // a dimension of a grid takes fewer than 2^32 threads (512 blocks of 4 nodes at 2^21 samples are as many): two dimensions then
+        const int64_t n_ct = (Bs + cols - 1) / cols, wgs = (g.n_rows + 7) / 8 * 8 * n_ct;
+        const bool by_xcd = wgs < (1 << 24);
+        const dim3 grid = by_xcd ? dim3((unsigned)wgs) : dim3((unsigned)g.n_rows, (unsigned)n_ct);
+#define PC_INPUT_TILE(KK, CC) hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), grid, dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, tables, xT, g.ids, g.nbr, g.par, \
+                                                 g.n_rows, (int32_t)n_ct, by_xcd, K, n_cats, Bs, l, R)
+        if (cols == 128) PC_INPUT_TILE(32, 128);
         else if (K == 32) PC_INPUT_TILE(32, 64);
         else if (K == 64) PC_INPUT_TILE(64, 64);
         else PC_INPUT_TILE(0, 64);

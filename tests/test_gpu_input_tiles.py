@@ -6,8 +6,10 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from paper_2406_00766_amd import binding as pcb
 from paper_2406_00766_amd import workloads as W
-from tests.refs import kernels
+from tests.refs import kernels, launches
+from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +32,17 @@ def test_input_tiles_match_oracle(D, S, K, B, kernel):
     x = w.x.copy()
     x[3, 0] = w.n_cats + 2; mask[3, 0] = 0                         # a sample of probability 0
     check_all(w.with_batch(x), mask)
+
+
+def test_largest_batch_is_within_the_limit_of_a_grid():
+    """512 blocks of 4 nodes and the most samples of a call: 2^24 workgroups of 256 threads, where HIP takes fewer than 2^32 threads in a dimension of a
+    grid.  The launches are captured and dropped; the addresses name no memory."""
+    d = Dag(4)
+    w = d.workload(d.sum([d.product([d.input() for _ in range(512)])], n_real=1), 1, 98)
+    h = pcb.pc_compile(w)
+    print("case largest batch of small blocks", flush=True)
+    somewhere, B = 1 << 40, 1 << 21
+    found = launches(lambda stream: pcb.pc_forward(h, somewhere, somewhere, somewhere, None, B, somewhere, pcb.pc_workspace_bytes(h, B), somewhere, stream))
+    pcb.pc_destroy(h)
+    assert [k[0] for k in found].count("k_input_fwd_tile<0, 64>") == 1
+    for k in found: assert all(n * t < 1 << 32 for n, t in zip(k[1:4], (k[4], 1, 1))), k
