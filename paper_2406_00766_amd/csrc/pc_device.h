@@ -37,9 +37,14 @@ __device__ inline int32_t pc_category(const int32_t *x, const uint8_t *mask, int
     return c < 0 || c >= n_cats ? -2 : c;
 }
 
-// Input tiles: those of a block run one after another on one XCD (workgroup h runs on XCD h mod 8): a table row that several of them need is in its L2
-// (12 288 blocks of 64, B = 256 280 -> 254 us, 1568 blocks, B = 512 67 -> 61; RAT-SPN of 784, B = 512 no change).
-__device__ inline int input_tile_block(int h, int n_ct) { return (h >> 3) / n_ct * 8 + (h & 7); }   // its column tile: (h >> 3) % n_ct
+// Which tile of the input layer a workgroup takes: of the first n_by_xcd blocks (a multiple of eight, input_by_xcd) those of a block one after
+// another on one XCD (workgroup h runs on XCD h mod 8), of the others the tiles of all XCDs in turn.
+struct InputTile { int block, col; };
+__device__ inline InputTile input_tile_at(int h, int n_rows, int n_by_xcd, int n_ct)
+{
+    const int q = h >> 3, rest = h - n_by_xcd * n_ct, others = n_rows - n_by_xcd;
+    return rest < 0 ? InputTile{q / n_ct * 8 + (h & 7), q % n_ct} : InputTile{n_by_xcd + rest % others, rest / others};
+}
 
 // Input layer through an LDS tile, for K a multiple of 4: one workgroup per (block u, COLS samples).  K / 4 lanes fetch one
 // sample's table row with 16-byte loads (every global read is a whole contiguous row), the logs go into a

@@ -126,20 +126,18 @@ __global__ __launch_bounds__(256) void k_begin_forward(const int32_t *__restrict
                                                        float *__restrict__ mail, bool null_mail, const int32_t *__restrict__ ent,
                                                        int32_t n_ent, int32_t K, int32_t *ticket, const float *__restrict__ tables,
                                                        const int32_t *__restrict__ in_ids, const int32_t *__restrict__ in_var,
-                                                       const int32_t *__restrict__ in_tab, int32_t n_in)
+                                                       const int32_t *__restrict__ in_tab, int32_t n_in, int32_t n_by_xcd)
 {
     if constexpr (KI != 0) {
         const int n_ct = (int)((Bs + 63) / 64);
-        if ((int)blockIdx.x < (n_in + 7) / 8 * 8 * n_ct) {
+        if ((int)blockIdx.x < n_in * n_ct) {
             __shared__ float smem[KI * 65 + 64];
-            const int u = input_tile_block((int)blockIdx.x, n_ct);
-            if (u >= n_in) return;                                      // the whole workgroup
-            input_tile<KI, 64, true>(smem, u, (int64_t)((int)(blockIdx.x >> 3) % n_ct) * 64, tables, x, mask, B, D, in_ids, in_var, in_tab, KI,
-                                     n_cats, Bs, l, R);
+            const InputTile t = input_tile_at((int)blockIdx.x, n_in, n_by_xcd, n_ct);
+            input_tile<KI, 64, true>(smem, t.block, (int64_t)t.col * 64, tables, x, mask, B, D, in_ids, in_var, in_tab, KI, n_cats, Bs, l, R);
             return;
         }
     }
-    const int block = KI ? (int)blockIdx.x - (n_in + 7) / 8 * 8 * (int)((Bs + 63) / 64) : (int)blockIdx.x;
+    const int block = KI ? (int)blockIdx.x - n_in * (int)((Bs + 63) / 64) : (int)blockIdx.x;
     __shared__ int32_t tile[32][33];
     if (block >= n_xtiles) {
         const int q = block - n_xtiles;
@@ -939,9 +937,9 @@ void launch_begin_forward(const int32_t *x, const uint8_t *mask, int32_t B, int3
     const bool with_input = input_in_begin(in, K, Bs);
     Timed timed(with_input ? KC_INPUT_FWD : KC_MISC, s);
     const int n_xb = (int)((Bs + 31) / 32), n_xt = n_xb * ((D + 31) / 32);
-    const unsigned wgs = (unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs) + (with_input ? (in.n_rows + 7) / 8 * 8 * ((Bs + 63) / 64) : 0));
+    const unsigned wgs = (unsigned)(n_xt + (n_ent + 1) * fill_shares(K, Bs) + (with_input ? in.n_rows * ((Bs + 63) / 64) : 0));
 #define PC_BEGIN(KI) hipLaunchKernelGGL(k_begin_forward<KI>, dim3(wgs), dim3(256), 0, s, x, mask, B, D, Bs, n_cats, xT, n_xb, n_xt, l, R, mail, null_mail, \
-                                        ent, n_ent, K, ticket, tables, in.ids, in.nbr, in.par, in.n_rows)
+                                        ent, n_ent, K, ticket, tables, in.ids, in.nbr, in.par, in.n_rows, input_by_xcd(in, K, Bs))
     if (with_input && K == 32) PC_BEGIN(32);
     else if (with_input) PC_BEGIN(64);
     else PC_BEGIN(0);

@@ -91,6 +91,7 @@ void launch_fill(float *p, int64_t n, float v, hipStream_t s);
 void launch_readout(const float *l, const float *R, int64_t root_row, int64_t root_blk, int64_t Bs, int32_t B, float *ll,
                     hipStream_t s);
 int input_tile_cols(const GroupDev &g, int32_t K, int64_t Bs);
+int input_by_xcd(const GroupDev &g, int32_t K, int64_t Bs);
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
                       float *l, float *R, hipStream_t s);
 void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,

@@ -89,13 +89,12 @@ __global__ __launch_bounds__(256) void k_input_fwd(const float *__restrict__ tab
 template <int KC, int COLS>
 __global__ __launch_bounds__(256) void k_input_fwd_tile(const float *__restrict__ tables, const int32_t *__restrict__ xT,
                                                         const int32_t *__restrict__ ids, const int32_t *__restrict__ var,
-                                                        const int32_t *__restrict__ tab, int32_t n_rows, int32_t n_ct, bool by_xcd, int32_t K,
+                                                        const int32_t *__restrict__ tab, int32_t n_rows, int32_t n_by_xcd, int32_t n_ct, int32_t K,
                                                         int32_t n_cats, int64_t Bs, float *__restrict__ l, float *__restrict__ R)
 {
     extern __shared__ float smem[];
-    const int u = by_xcd ? input_tile_block((int)blockIdx.x, n_ct) : (int)blockIdx.x, ct = by_xcd ? (int)(blockIdx.x >> 3) % n_ct : (int)blockIdx.y;
-    if (u >= n_rows) return;                                            // the whole workgroup
-    input_tile<KC, COLS, false>(smem, u, (int64_t)ct * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
+    const InputTile t = n_by_xcd ? input_tile_at((int)blockIdx.x, n_rows, n_by_xcd, n_ct) : InputTile{(int)blockIdx.x, (int)blockIdx.y};
+    input_tile<KC, COLS, false>(smem, t.block, (int64_t)t.col * COLS, tables, xT, nullptr, 0, 0, ids, var, tab, K, n_cats, Bs, l, R);
 }
 
 // table_flow[t][x_b,v][k] += F[n,b] for observed variables.
@@ -2737,6 +2736,17 @@ int input_tile_cols(const GroupDev &g, int32_t K, int64_t Bs)
     return K == 32 && g.n_rows * (Bs / 128) >= 2048 ? 128 : 64;
 }
 
+// Blocks of which the tiles run on one XCD (input_tile_at): a table row that several of them need is then in its L2.  That pays where the tables of
+// all blocks are more than an L2 holds, in whole eights (with a share of nine blocks one XCD has twice the others': B = 65536 45 us, all in turn 30).
+// In turn / by XCD, 256 categories: K = 64, 12 288 blocks, B = 256 280 / 254 us, 2000 blocks, B = 1000 194 / 161, 65 blocks, B = 30000
+// 125 / 121, 33 blocks 52 / 54; K = 32, 2000 blocks, B = 1000 86 / 80, 257 blocks, B = 1500 15.2 / 14.4, but B = 8000 68 / 73 and 600 blocks,
+// B = 3000 65 / 68; K = 20 600 blocks, B = 1000 17.7 / 19.5, B = 3000 53 / 61.
+int input_by_xcd(const GroupDev &g, int32_t K, int64_t Bs)
+{
+    const bool pays = K == 64 ? g.n_rows >= 64 : K == 32 && g.n_rows >= 256 && Bs <= 1536;
+    return pays ? g.n_rows & ~7 : 0;
+}
+
 void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g, int32_t K, int32_t n_cats, int64_t Bs,
                       float *l, float *R, hipStream_t s)
 {
@@ -2744,12 +2754,12 @@ void launch_input_fwd(const float *tables, const int32_t *xT, const GroupDev &g,
     if (g.n_rows == 0) return;
     const int cols = input_tile_cols(g, K, Bs);
     if (cols > 0) {
-        // a dimension of a grid takes fewer than 2^32 threads (512 blocks of 4 nodes at 2^21 samples are as many): two dimensions then
-        const int64_t n_ct = (Bs + cols - 1) / cols, wgs = (g.n_rows + 7) / 8 * 8 * n_ct;
-        const bool by_xcd = wgs < (1 << 24);
-        const dim3 grid = by_xcd ? dim3((unsigned)wgs) : dim3((unsigned)g.n_rows, (unsigned)n_ct);
+        // a dimension of a grid takes fewer than 2^32 threads (512 blocks of 4 nodes at 2^21 samples are as many)
+        const int64_t n_ct = (Bs + cols - 1) / cols;
+        const int by_xcd = g.n_rows * n_ct < (1 << 24) ? input_by_xcd(g, K, Bs) : 0;
+        const dim3 grid = by_xcd ? dim3((unsigned)(g.n_rows * n_ct)) : dim3((unsigned)g.n_rows, (unsigned)n_ct);
 #define PC_INPUT_TILE(KK, CC) hipLaunchKernelGGL((k_input_fwd_tile<KK, CC>), grid, dim3(256), ((size_t)K * (CC + 1) + CC) * 4, s, tables, xT, g.ids, g.nbr, g.par, \
-                                                 g.n_rows, (int32_t)n_ct, by_xcd, K, n_cats, Bs, l, R)
+                                                 g.n_rows, by_xcd, (int32_t)n_ct, K, n_cats, Bs, l, R)
         if (cols == 128) PC_INPUT_TILE(32, 128);
         else if (K == 32) PC_INPUT_TILE(32, 64);
         else if (K == 64) PC_INPUT_TILE(64, 64);
