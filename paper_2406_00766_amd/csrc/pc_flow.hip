@@ -1003,22 +1003,27 @@ void launch_flow(const float *theta, float *l, float *R, float *F, float *mail, 
 #undef PC_FLOW
 }
 
-// Columns up to which a chain has a wave per column (two columns at K = 32): HMMs of 32 layers, K = 32 against k_chain_wide (forward +
-// backward) B = 128 26 + 39 -> 16 + 19 us, 2048 28 + 39 -> 22 + 26, 4096 28 + 40 -> 37 + 50; K = 64 against k_flow 51 + 58 -> 21 + 23, 2048 103 + 103 ->
-// 65 + 98, 4096 198 + 200 -> 122 + 195.  Where most links have weights of their own, loading them counts: K = 32 B = 128 26 + 39 -> 19 + 24, 1024 29 + 39 ->
-// 41 + 31; K = 64 51 + 58 -> 31 + 32, 58 + 66 -> 81 + 55. Short chains of 64 nodes gain little there: two layers, B = 512, 10 + 10 ->
-// 12 + 11, four 14 + 14 -> 12 + 12, six 17 + 18 -> 15 + 14.
+// Columns up to which a chain has a wave per column (two columns at K = 32).  HMMs, forward + backward, another kernel (k_chain_wide at K = 32,
+// k_flow at 64; k_begin_backward's 4 us come on top) / here: K = 32, 32 layers, B = 128 61 / 31 us, 2048 62 / 43, 4096 63 / 84, four layers
+// 2048 11 / 14; K = 64, 32 layers, B = 128 103 / 40, 2048 201 / 157, 4096 393 / 315, eight layers 4096 forward 53 / 46, six 41 / 43, 2048 47 / 49.
+// Where most links have weights of their own, loading them counts: K = 32, 16 layers, B = 256 34 / 23, 1024 34 / 29, 2048 35 / 39; K = 64 58 / 35,
+// 512 62 / 44, 1024 65 / 71.  Chains of fewer than six layers of 64: two, B = 256 11.5 / 10.8, 512 15 / 14, 2048 11 / 18 forward, four
+// 19 / 12, 24 / 15, 35 / 40.  These two are walked to 256 columns, one workgroup on a CU; more would pay up to some 512.
 bool chain_walks(bool few_weights, int32_t n_links, int32_t K, int64_t Bs)
 {
-    return Bs <= (!few_weights || (K == 64 && n_links < 6) ? 256 : K == 32 ? 2048 : 4096);
+    return Bs <= (!few_weights || (K == 64 && n_links < 6) ? 256 : K == 32 || n_links < 8 ? 2048 : 4096);
 }
+// Waves of a workgroup of a walk: one while every workgroup has a CU for itself, where waves of one CU wait for each other's weights (K = 64,
+// 16 layers, B = 256 26 us, with two 28, four 36; weights of their own 35, 41, 65), then two (B = 512 32, 29, 38), then four, which share them
+// (B = 2048 100, 116, 87).
+static int walk_waves(int64_t waves) { return waves <= 256 ? 1 : waves <= 512 ? 2 : 4; }
 
 void launch_chain(const float *theta, float *l, float *R, float *F, float *N, float *nfmax, bool bwd, const ChainDev &c, int32_t K, int64_t Bs, int32_t B,
                   float *ll, hipStream_t s)
 {
     Timed timed(bwd ? KC_SUM_BWD_CHILD : KC_SUM_FWD, s);
     if (c.walks) {
-        const int wgw = Bs >= 256 ? 4 : 1;                              // waves of a workgroup
+        const int wgw = walk_waves(Bs * K / 64);
         const dim3 grid((unsigned)(Bs * K / 64 / wgw)), block(64 * wgw);
         if (K == 32 && bwd) hipLaunchKernelGGL(k_chain<true>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
         else if (K == 32) hipLaunchKernelGGL(k_chain<false>, grid, block, 0, s, theta, l, R, F, N, nfmax, c.words, c.n_links, Bs, ll, B);
@@ -1035,7 +1040,7 @@ void launch_walk_pass(const float *theta, const float *tables, const int32_t *x,
                       int32_t n_vars, int32_t n_cats, float *ll, hipStream_t s)
 {
     const ChainIn in{tables, x, mask, n_vars, n_cats};
-    const int wgw = B >= 256 ? 4 : 1, cols = 64 / K * wgw;
+    const int wgw = walk_waves(((int64_t)B * K + 63) / 64), cols = 64 / K * wgw;
     const dim3 grid((unsigned)((B + cols - 1) / cols)), block(64 * wgw);
     if (K == 32) hipLaunchKernelGGL(k_walk_pass<32>, grid, block, 0, s, theta, c.words, c.n_links, ll, B, in);
     else hipLaunchKernelGGL(k_walk_pass<64>, grid, block, 0, s, theta, c.words, c.n_links, ll, B, in);

@@ -7,7 +7,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2406_00766_amd import binding as pcb
 from paper_2406_00766_amd import workloads as W
-from tests.refs import kernels
+from tests.refs import kernels, launches
 from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all, check_repeated
 
@@ -53,3 +53,34 @@ def test_static_pass_in_one_launch(K, T, B):
     torch.cuda.synchronize()
     assert torch.equal(ll, ref) and (B <= 2 or ll[2] == -float("inf")) and torch.isfinite(ll).sum() >= B - 1
     c.close()
+
+
+@pytest.mark.parametrize("K,T,B,untied,names,workgroups,threads", [
+    (32, 5, 512, False, "k_chain", 256, 64), (32, 5, 513, False, "k_chain", 136, 128), (32, 5, 1025, False, "k_chain", 132, 256),
+    (64, 7, 256, False, "k_walk64", 256, 64), (64, 7, 257, False, "k_walk64", 144, 128), (64, 7, 513, False, "k_walk64", 136, 256),
+    (64, 5, 225, False, "k_walk64", 256, 64), (64, 7, 256, True, "k_walk64", 256, 64), (32, 7, 256, True, "k_chain", 128, 64),
+])
+def test_workgroups_of_walks(K, T, B, untied, names, workgroups, threads):
+    """A wave to a workgroup while there are no more of them than CUs, then two, then four."""
+    if untied:
+        d = Dag(K)
+        s = d.sum([d.product([d.input()])])
+        for _ in range(T - 2): s = d.sum([d.product([s, d.input()])])
+        w = d.workload(d.sum([d.product([s, d.input()])], n_real=1), B, 99)
+    else:
+        w = W.hmm(T, K, 30, K, B, 99, alpha_trans=0.3)
+    print(f"case workgroups of walks K={K} T={T} B={B} untied={untied}", flush=True)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    c.forward()
+    for bwd in (False, True):
+        def call(stream):
+            with torch.cuda.stream(stream): c.backward() if bwd else c.forward()
+        assert (f"{names}<{str(bwd).lower()}>", workgroups, 1, 1, threads) in launches(call)
+    c.close()
+    check_all(w)
+
+
+def test_short_chains_of_64_leave_the_walk_at_2048():
+    for T, B, name in ((7, 2048, "k_walk64<"), (7, 2049, "k_flow<"), (8, 2049, "k_walk64<")):
+        assert any(k.startswith(name) for k in kernels(W.hmm(T, 64, 30, 64, 2, 99), 0, B)), (T, B)
