@@ -289,7 +289,7 @@ static ChainDev chain_dev(const pc_circuit *c, const ChainTab &t, size_t li0, bo
     const int32_t n = t.from[li0];
     const bool walks = chain_walks(t.few_weights, n, c->K, Bs);
     if (n <= 0 || c->wait_limit != pc_circuit::kWaitLimit || (c->K != 32 && !walks)) return ChainDev{nullptr, 0, false};
-    return ChainDev{t.d_words + (suffix ? t.words.size() - (size_t)n * CHAIN_WORDS : 0), n, walks};
+    return ChainDev{t.d_words + (suffix ? (size_t)(t.n_links - n) * CHAIN_WORDS : 0), n, walks};
 }
 static int32_t max_width(const std::vector<GroupTab> &groups)
 {

@@ -141,13 +141,12 @@ void compile_chain(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &p
         if (u < 0 || d->child_ptr[u + 1] - d->child_ptr[u] != 1) return false;
         const int32_t p = d->child[d->child_ptr[u]];
         if (layer_of[p] != li - 1) return false;
-        w = {off(u), off(p), 0, 0, (d->param_blk[d->child_ptr[u]] + 1) * K * K, u == d->root_block ? 1 : 0, 0, 0, 0, 0, 0, 0};
+        w = {off(u), off(p), 0, 0, (d->param_blk[d->child_ptr[u]] + 1) * K * K, u == d->root_block ? 1 : 0, 0, 0};
         for (int64_t e = d->child_ptr[p]; e < d->child_ptr[p + 1]; ++e) {
             const int32_t k = d->child[e];
             int32_t &at = d->type[k] == KIND_INPUT ? w[3] : w[2];
             if (at != 0 || (d->type[k] == KIND_SUM && k != only(li - 2))) return false;
             at = off(k);
-            if (d->type[k] == KIND_INPUT) { w[7] = d->in_var[k]; w[8] = d->in_table[k]; }
         }
         return true;
     };
@@ -156,7 +155,7 @@ void compile_chain(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &p
         if (u < 0 || par_ptr[u + 1] - par_ptr[u] != 1) return false;
         const int32_t s = par_of[par_ptr[u]], ns = par_ptr[s + 1] - par_ptr[s];
         if (layer_of[s] != li + 1 || ns > 1) return false;
-        w = {off(u), off(s), 0, 0, (d->param_blk[par_edge[par_ptr[u]]] + 1) * K * K, 0, 0, 0, 0, 0, 0, 0};
+        w = {off(u), off(s), 0, 0, (d->param_blk[par_edge[par_ptr[u]]] + 1) * K * K, 0, 0, 0};
         // a flow that is there already (the root's, or 0 of an unused block) is read by the first link only
         if (ns == 0) return s != d->root_block || c->chain_bwd.words.empty();
         const int32_t p = par_of[par_ptr[s]];
@@ -178,6 +177,7 @@ void compile_chain(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &p
     for (size_t k = fwd.size(); k-- > 0;) c->chain_fwd.words.insert(c->chain_fwd.words.end(), fwd[k].begin(), fwd[k].end());
     for (ChainTab *t : {&c->chain_fwd, &c->chain_bwd}) {
         const size_t n = t->words.size() / CHAIN_WORDS;
+        t->n_links = (int32_t)n;
         size_t changes = 0;
         for (size_t k = n; k-- > 0;) {
             int32_t *w = t->words.data() + k * CHAIN_WORDS;
@@ -186,13 +186,17 @@ void compile_chain(const pc_dag *d, pc_circuit *c, const std::vector<int32_t> &p
         }
         t->few_weights = changes <= 1 + n / 8;
     }
-    const std::vector<int32_t> &fw = c->chain_fwd.words;
+    std::vector<int32_t> &fw = c->chain_fwd.words;
     bool whole = from == 1 && c->chain_fwd.from[1] > 0 && d->n_blocks == 3 * c->chain_fwd.from[1];
     for (int32_t k = 0; whole && k < c->chain_fwd.from[1]; ++k) {
         const int32_t *w = fw.data() + k * CHAIN_WORDS;
         whole = w[3] != 0 && par_ptr[w[3] / K] - par_ptr[w[3] / K - 1] == 1 && w[2] == (k ? w[-CHAIN_WORDS] : 0);
     }
     c->chain_fwd.whole = whole;
+    for (int32_t k = 0; whole && k < c->chain_fwd.from[1]; ++k) {
+        const int32_t in = fw[k * CHAIN_WORDS + 3] / K - 1;
+        fw.insert(fw.end(), {d->in_var[in], d->in_table[in]});
+    }
 }
 
 // Tables of the dataflow launches (pc_internal.h, pc_flow.hip), for the layers such a launch may cover at some batch size.

@@ -655,8 +655,8 @@ __device__ inline void walk_chain(const float *__restrict__ theta, float *l, flo
     int32_t trow[64 / K] = {};
     auto rows_of = [&](int k0) {
         const int k = k0 + lane < n_links ? k0 + lane : n_links - 1;
-        const int32_t *w = link_words + CHAIN_WORDS * (int64_t)k;
-        const int32_t var = w[7], tab = w[8];
+        const int32_t *w = link_words + CHAIN_WORDS * (int64_t)n_links + 2 * (int64_t)k;
+        const int32_t var = w[0], tab = w[1];
 #pragma unroll
         for (int c = 0; c < 64 / K; ++c) {
             const int32_t cat = pc_category(in.x, in.mask, col - lane / K + c, var, B, in.D, in.n_cats);

@@ -74,12 +74,13 @@ struct FlowTab {
 // of a chain.
 //   0 node offset of the layer's block  1 its neighbour's (a product block; backward: a sum block)  2 the block whose published values
 //   the neighbour takes, 0: none  3 forward: the input block multiplied to them, 0: none  4 parameter offset  5 1 for the root
-//   6 the next parameter offset that is another, or this  7, 8 forward: the input block's variable and table
+//   6 the next parameter offset that is another, or this
 // few_weights: most links have the parameters of the one before.  whole: forward, the links and their input blocks are all there is, and
-// each link takes the one before
-constexpr int CHAIN_WORDS = 12;
+// each link takes the one before; every link's variable and table then follow the words of the last
+constexpr int CHAIN_WORDS = 8;    // two links to a line of the scalar cache: with 12 words the backward pass of k_chain_wide took 8 % longer
 struct ChainTab {
     std::vector<int32_t> words, from;
+    int32_t n_links = 0;
     bool few_weights = false, whole = false;
     int32_t *d_words = nullptr;
 };
