@@ -517,7 +517,7 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
     if (check_fault(c) != PC_OK) return PC_ERR_HIP;
     ProfScope prof(ll_only ? nullptr : c);
     char *base = (char *)workspace;
-    float *l = (float *)(base + w.l_off), *R = (float *)(base + w.r_off);
+    float *l = (float *)(base + w.l_off), *F = (float *)(base + w.f_off), *R = (float *)(base + w.r_off);
     int32_t *xT = (int32_t *)(base + w.xt_off);
     const int32_t K = c->K;
     c->fw_B = -1;
@@ -553,7 +553,8 @@ static pc_status forward_on(pc_circuit *c, const float *theta, const float *tabl
                             plan.layers[li].fwd[0], K, w.Bs, s);
         } else {
             // product-scratch mode: the children are the product layer just before, in the window
-            read_out |= launch_sum_fwd(theta, c->product_scratch ? window_base(c, c->layers[li - 1], l, w.Bs) : l, l, R, (float *)(base + w.f_off),
+            read_out |= launch_sum_fwd(theta, c->product_scratch ? window_base(c, c->layers[li - 1], l, w.Bs) : l, l, R,
+                                       c->product_scratch ? window_base(c, c->layers[li - 1], F, w.Bs) : (float *)(base + w.n_off),
                                        plan.layers[li].fwd, K, w.Bs, (int32_t)li == c->root_layer ? ll : nullptr, B, s);
         }
     }

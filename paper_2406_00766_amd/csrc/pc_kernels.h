@@ -117,7 +117,8 @@ void launch_prod_bwd_classes(float *F, const ClassesDev &c, int32_t K, int64_t B
 void launch_prod_fwd_rows(float *l, float *R, const RowsDev &rows, int32_t K, int64_t Bs, hipStream_t s);
 void launch_prod_bwd_rows(const float *l, float *F, float *N, float *nfmax, const RowsDev &rows, int32_t K, int64_t Bs, void *Ph,
                           void *Pl, hipStream_t s);
-// lch: base the product children are read from; l: base of the sum rows written; part: scratch of as many rows as l has (F).  ll not null:
+// lch: base the product children are read from; l: base of the sum rows written; part: base of scratch
+// rows for the product children.  ll not null:
 // the layer is the root alone; true if it has been read out into ll[0 .. B)
 void sum_kernel_name(char (&name)[64], const GroupSet &gs, bool bwd, int32_t K, int64_t Bs);
 bool launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, float *part, const std::vector<GroupSet> &sets, int32_t K,

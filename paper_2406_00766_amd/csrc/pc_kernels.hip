@@ -1386,7 +1386,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ct = wave / SPLIT, sp = wave % SPLIT;
-    constexpr bool PART = MODE == 3;                                    // one row, its chunks in gs.first[2] parts (sum_parts), results to F
+    constexpr bool PART = MODE == 3;                                    // one row, its chunks in gs.first[2] parts, results to F (sum_parts)
     const GroupRow gr = locate_row<MULTI ? PC_ROWS_MULTI : PC_ROWS_ONE>(gs, PART ? 0 : blockIdx.x / SUB);
     const int r = gr.r, sub = blockIdx.x % SUB;
     const int64_t col0 = ((int64_t)blockIdx.y * NCT + ct) * 32;
@@ -1401,6 +1401,8 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     const int n_row = (fl >> 8) * CPB;                                  // real neighbours; padding sits at the end of a row
     const int share = PART ? (n_row + gs.first[2] - 1) / gs.first[2] : n_row, chunk0 = PART ? (int)(blockIdx.x / SUB) * share : 0;
     const int n_chunks = PART ? min(chunk0 + share, n_row) : n_row;
+    const int part = PART ? (int)blockIdx.x / SUB : 0;
+    const int32_t part_row = PART ? row_nbr[part] : 0, part_top = PART ? row_nbr[gs.first[2] + part / (K / 2)] + part % (K / 2) * 2 : 0;
 
     // block reference of this row.  Backward: the row's own.  Forward: the maximum of the children's, found
     // on the fly -- Rrow is the maximum over the chunks seen so far and the running maximum m is relative to it
@@ -1603,13 +1605,13 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
     }
     if (!active) return;
     if (PART) {                                                         // K rows of sums, their maximum's shift and reference (k_sum_merge)
-        float *po = F + (int64_t)(blockIdx.x / SUB) * (K + 2) * Bs + col;
+        float *po = F + (int64_t)part_row * Bs + col;
 #pragma unroll
         for (int k = 0; k < ES; ++k) {
             const int q = sp * ES + k;
             po[(int64_t)(sub * TM + q / 16 * 32 + 8 * (q % 16 / 4) + 4 * half + q % 4) * Bs] = res[k];
         }
-        if (sub == 0 && sp == 0) po[(int64_t)(K + half) * Bs] = half ? Rrow : m;
+        if (sub == 0 && sp == 0) F[(int64_t)(part_top + half) * Bs + col] = half ? Rrow : m;
         return;
     }
     if (!BWD && sub == 0 && sp == 0 && half == 0) R[(int64_t)(id / K) * Bs + col] = Rrow;
@@ -1647,25 +1649,28 @@ __global__ __launch_bounds__(SPLIT > 4 ? 64 * SPLIT : 256, SPLIT > 4 ? 1 : 2) vo
 }
 
 // The parts of a row (k_sum_mfma, MODE 3; 32 at most) merged as the waves of a workgroup merge theirs.  Workgroup = 8 rows x 32 columns,
-// thread = one of them; all its loads are requested at once.  ll not null: the row is the root's, node 0 of it is read out.
-__global__ __launch_bounds__(256) void k_sum_merge(const float *__restrict__ part, int32_t n_parts, float *__restrict__ l, float *__restrict__ R,
+// thread = one of them; all its loads are requested at once.  at: the children, in whose rows of `part` the parts lie (sum_parts).  ll not null:
+// the row is the root's, node 0 of it is read out.
+__global__ __launch_bounds__(256) void k_sum_merge(const float *__restrict__ part, const int32_t *__restrict__ at, int32_t n_parts, float *__restrict__ l, float *__restrict__ R,
                                                    const int32_t *__restrict__ ids, int32_t K, int64_t Bs, float *__restrict__ ll, int32_t B)
 {
     __shared__ float scale[32][32], top[2][8][32];                      // a part's factor; the threads' largest references and shifts
     const int c32 = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int64_t col = (int64_t)blockIdx.y * 32 + c32, step = (int64_t)(K + 2) * Bs;
+    const int64_t col = (int64_t)blockIdx.y * 32 + c32;
     const int row = (int)blockIdx.x * 8 + g;
     const float *p = part + col;
     const int32_t id = ids[0];
     float v[32];
 #pragma unroll
-    for (int s = 0; s < 32; ++s) v[s] = s < n_parts ? p[s * step + (int64_t)row * Bs] : 0.0f;
+    for (int s = 0; s < 32; ++s) v[s] = s < n_parts ? p[(int64_t)(at[min(s, n_parts - 1)] + row) * Bs] : 0.0f;
+    const int32_t top0 = at[n_parts], top1 = at[n_parts + 1];           // 16 parts to a block of 32
     float ms[4], Ro[4], Rm = PC_NEG_INF, m = PC_NEG_INF;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int s = g + 8 * i;
-        ms[i] = s < n_parts ? p[s * step + (int64_t)K * Bs] : PC_NEG_INF;
-        Ro[i] = s < n_parts ? p[s * step + (int64_t)(K + 1) * Bs] : PC_NEG_INF;   // -inf: a part without chunks
+        const float *top_rows = p + (int64_t)(K == 32 && i >= 2 ? top1 + 2 * (s - 16) : top0 + 2 * s) * Bs;
+        ms[i] = s < n_parts ? top_rows[0] : PC_NEG_INF;
+        Ro[i] = s < n_parts ? top_rows[Bs] : PC_NEG_INF;                // -inf: a part without chunks
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) Rm = fmaxf(Rm, Ro[i]);
@@ -3045,8 +3050,10 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
 }
 
 // Forward, a layer of one row block with a long row (a root): parts of the row to as many workgroups of four waves, two chunks to a wave and more,
-// and a launch that merges them.  One workgroup per tile reads through one CU's 64 bytes a clock, 8 KiB a chunk.  The parts lie in F, which
-// a forward pass does not use otherwise and which holds the row's children: parts * (K + 2) rows are fewer than theirs.
+// and a launch that merges them.  One workgroup per tile reads through one CU's 64 bytes a clock, 8 KiB a chunk.  The parts lie in
+// rows that belong to the row's children in an array that nobody reads them from (N; with recomputed products the window of F): the rows of the
+// first child are the first part's sums, and so on; two rows a part, its shift and reference, follow in those of the next child or, at K = 32, two
+// (they are there: parts <= width * K / 256, and 64 chunks).
 // Root over 256 blocks of 32 nodes, sixteen waves and the readout / parts, merge and readout in one: B = 16 51 + 4 / 6 + 4 us, B = 512 49 + 5 / 9 + 5;
 // pass of the HMM of 4096 states in blocks of 128, B = 256 (32 tiles) 3921 / 3907.  Rows of fewer than 64 chunks are four to a wave of sixteen.
 static int sum_parts(int32_t K, int32_t n_groups, int32_t n_rows, int32_t width, int64_t Bs)
@@ -3108,7 +3115,7 @@ bool launch_sum_fwd(const float *theta, const float *lch, float *l, float *R, fl
 #define PC_SUM_PART(KK) hipLaunchKernelGGL((k_sum_mfma<KK, 1, 4, false, false, 3>), grid, dim3(256), 0, s, theta, l, R, lch, (const float *)nullptr, part, ps, Bs)
                 if (K == 32) PC_SUM_PART(32); else if (K == 64) PC_SUM_PART(64); else PC_SUM_PART(128);
 #undef PC_SUM_PART
-                hipLaunchKernelGGL(k_sum_merge, dim3((unsigned)(K / 8), (unsigned)(Bs / 32)), dim3(256), 0, s, part, parts, l, R, gs.ids[0], K, Bs, ll, B);
+                hipLaunchKernelGGL(k_sum_merge, dim3((unsigned)(K / 8), (unsigned)(Bs / 32)), dim3(256), 0, s, part, gs.nbr[0], parts, l, R, gs.ids[0], K, Bs, ll, B);
                 read_out = ll != nullptr;
                 continue;
             }

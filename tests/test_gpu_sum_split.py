@@ -5,6 +5,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from paper_2406_00766_amd import binding as pcb
+from paper_2406_00766_amd import workloads as W
 from tests.refs import kernels
 from tests.test_gpu_dataflow import Dag
 from tests.test_gpu_parity import check_all
@@ -49,3 +50,26 @@ def test_root_in_parts_matches_oracle(K, width, B, parts, scratch):
     x = w.x.copy()
     x[0, 0] = w.n_cats + 2
     check_all(w.with_batch(x))
+
+
+@pytest.mark.parametrize("K,width,B", [(32, 81, 70), (64, 40, 33), (128, 17, 100)])
+@pytest.mark.parametrize("scratch", [False, True])
+def test_flows_outlive_the_next_forward_pass(K, width, B, scratch):
+    """The parts of a root's row lie where no node buffer is: a forward pass leaves the flows of the batch before."""
+    d = Dag(K)
+    tables = [[d.input() for _ in range(13)] for _ in range(3)]
+    w = d.workload(d.sum([d.product(tables[i % 3][:13 - i % 2]) for i in range(width)], n_real=1), B, 93)
+    if scratch:
+        w = pcb.pc_order_for_scratch(w)
+    print(f"case flows outlive K={K} width={width} B={B} scratch={scratch}", flush=True)
+    assert kernels(w, 0)[2] == f"k_sum_mfma<{K}, 1, 4, false, false, 3>"
+    c = pcb.Circuit(w)
+    c.set_batch(w.x)
+    c.forward(); c.backward()
+    F = c.node_buffers()[1]
+    if scratch: F = F[:(1 + (w.type != W.PRODUCT).sum()) * K]          # product rows are not kept
+    before = F.clone()
+    assert before.abs().sum() > 0
+    c.forward()
+    assert torch.equal(F, before)
+    c.close()
