@@ -1,15 +1,17 @@
 """Chains of single blocks walked with a wave per column: both sides of the batch sizes where the kernel changes, more links than a
-lane holds rows of (64), weights that change with every link, and the pass of pc_forward_static in one launch; kernels asserted."""
+lane holds rows of (64), weights that change with every link, and the pass of pc_forward_static in one launch, where the circuit is nothing but
+a chain; kernels asserted, those of a static pass from a capture of it."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import pc_oracle as orc
 from paper_2406_00766_amd import binding as pcb
 from paper_2406_00766_amd import workloads as W
 from tests.refs import kernels, launches
 from tests.test_gpu_dataflow import Dag
-from tests.test_gpu_parity import check_all, check_repeated
+from tests.test_gpu_parity import assert_logprob_close, check_all, check_repeated
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +40,11 @@ def test_chains_of_many_weights(K, B, name):
     check_all(w)
 
 
+def static_kernels(c):
+    ll = torch.empty(c.B, device="cuda")
+    return [k[0] for k in launches(lambda stream: pcb.pc_forward_static(c.handle, c.theta, c.tables, c.x, c.mask, c.B, ll, stream))]
+
+
 @pytest.mark.parametrize("K,T,B", [(32, 16, 1), (32, 130, 3), (64, 64, 2), (64, 65, 300), (32, 5, 511)])
 def test_static_pass_in_one_launch(K, T, B):
     """The same numbers as pc_forward, with masked variables, a category out of range and nothing read from the workspace."""
@@ -52,6 +59,33 @@ def test_static_pass_in_one_launch(K, T, B):
     pcb.pc_forward_static(c.handle, c.theta, c.tables, c.x, c.mask, B, ll)
     torch.cuda.synchronize()
     assert torch.equal(ll, ref) and (B <= 2 or ll[2] == -float("inf")) and torch.isfinite(ll).sum() >= B - 1
+    assert static_kernels(c) == [f"k_walk_pass<{K}>"]
+    c.close()
+
+
+@pytest.mark.parametrize("kind,one", [("untied", True), ("shared_input", False), ("bare_sum", False), ("unused_input", False), ("wait_limit", False)])
+@pytest.mark.parametrize("K,T,B", [(32, 70, 5), (64, 67, 33), (32, 9, 256)])
+def test_static_pass_of_chains_and_others_matches_oracle(K, T, B, kind, one):
+    """Weights that change with every link, also where a lane's rows run out; circuits that a chain's walk from the tables does not cover."""
+    d = Dag(K)
+    first = d.input()
+    s = d.sum([d.product([first])])
+    for i in range(T - 2):
+        if kind == "bare_sum" and i == 2: s = d.sum([d.product([s])])
+        else: s = d.sum([d.product([s, first if kind == "shared_input" and i == 2 else d.input()])])
+    if kind == "unused_input": d.input()
+    w = d.workload(d.sum([d.product([s, d.input()])], n_real=1), B, 101)
+    mask = (np.random.default_rng(10).random(w.x.shape) < 0.2).astype(np.uint8)
+    w.x[1, 0] = w.n_cats; mask[1, 0] = 0
+    print(f"case static pass {kind} K={K} T={T} B={B}", flush=True)
+    c = pcb.Circuit(w)
+    c.set_batch(w.x, mask)
+    if kind == "wait_limit": pcb.pc_set_wait_limit(c.handle, 1 << 21)
+    ll = torch.full((B,), float("nan"), device="cuda")
+    pcb.pc_forward_static(c.handle, c.theta, c.tables, c.x, c.mask, B, ll)
+    assert_logprob_close(ll.double().cpu().numpy(), orc.forward(w, w.theta, w.tables, w.x, mask)[1], "ll")
+    found = static_kernels(c)
+    assert (found == [f"k_walk_pass<{K}>"]) == one and (one or len(found) > 1)
     c.close()
 
 
