@@ -2801,10 +2801,12 @@ void launch_input_bwd(const float *F, const int32_t *xT, const GroupDev &g, int3
                                   96 * 1024);
         attr_set.fetch_or(bit, std::memory_order_relaxed);
     }
-    // slab of samples for the sorted variant: a [K x SB] tile of at most 66 KB, two workgroups per CU.  Threads by the tile, four 16-byte
-    // loads each or less: 256 up to 16 KB (K = 32, B = 128, 25 088 blocks 157 us, with 512 194), 512 up to 48 KB (B = 352 345, with 256 468,
-    // with 1024 415), then 1024 (B = 512 486, with 512 542).  256 threads at every size had wanted tiles of 34 KB, four workgroups per CU,
-    // and more adds per category (B = 512 618; K = 64, 12 288 blocks, B = 256 507, now 322; 1568 blocks, B = 512 138, now 100).
+    // slab of samples for the sorted variant: a [K x SB] tile of at most 66 KB, two workgroups per CU.  Threads by the tile: 256 up to 16 KB (K = 32,
+    // B = 128, 25 088 blocks 157 us, with 512 194), 512 up to 48 KB (B = 352 345, with 256 468, with 1024 415), then 1024 (B = 512 486, with 512
+    // 542).  Four 16-byte loads of a thread are on their way during the sort, the whole tile up to 16 KB, 32 KB and 64 KB; what is left of a tile
+    // of 32 to 48 KB or of the largest follows behind it.  256 threads at every size had wanted tiles of 34 KB, four workgroups per CU, and more
+    // adds per category (B = 512 618; K = 64, 12 288 blocks, B = 256 507, now 322; 1568 blocks, B = 512 138, now 100).  Half as many workgroups
+    // pay for few blocks, too: 4 blocks of 64, B = 512 16 -> 10, 64 blocks 17 -> 11, 16 blocks of 128 17 -> 11, 64 of 32 15 -> 9.
     int SB = 1024;
     while (SB > 32 && (size_t)K * (SB + 1) * 4 > 66 * 1024) SB >>= 1;
     if (SB > Bs) SB = (int)Bs;

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (32, 384, 100), (32, 385, 200),                              # 48 and 52 KB: 512 and 1024
     (32, 512, 256), (32, 520, 140), (64, 300, 128),              # the largest slab, two slabs of which the last has 32 or 64 columns
     (65, 256, 128),                                              # 4160 quads, 4096 a round
+    (16, 900, 256), (128, 128, 256), (128, 150, 100),            # 1024 threads: the longest slab, the widest; a second slab of 32 columns
     (16, 100, 1023), (32, 330, 1024), (64, 70, 513),
 ])
 def test_flows_per_category_match_oracle(K, B, n_cats):
