@@ -230,7 +230,7 @@ def check_repeated(w, reps, mask=None):
     # The parameter-flow kernels have a two-tile form for long reductions -- at K = 32 from 12 chunks of 32 samples per
     # wave, at K = 64 and 128 from 64 chunks per workgroup (the forms the full-size configurations run).
     (lambda: W.reduced(2, B=400), 1),                              # K = 32, untied: 13 chunks per block
-    (lambda: W.hmm(41, 64, 30, 32, 100, 47), 10),                   # K = 32, tied, pairs dealt to 27 waves: 32 chunks each
+    (lambda: W.hmm(41, 64, 30, 32, 100, 47), 10),                   # K = 32, tied, chunks dealt to 64 waves a block: 20 each
     (lambda: W.hclt(12, 128, 64, 256, 48, n_cats=16), 8),           # K = 64, untied: 64 chunks per block
     (lambda: W.hclt(6, 256, 128, 128, 49, n_cats=16), 16),          # K = 128, untied: 64 chunks per block
     (lambda: W.hmm(40, 256, 60, 128, 128, 50), 16),                 # K = 128, tied, pairs dealt to 26 workgroups: 64 chunks each
