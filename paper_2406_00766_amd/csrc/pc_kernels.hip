@@ -3267,11 +3267,18 @@ void launch_param_flow(const float *theta, const float *l, const float *R, const
 #undef PC_PF_32
     } else {
         // few blocks with many tied pairs each: the pairs are dealt to workgroups until the launch has some 256 of them; where that leaves
-        // short reductions (below), their chunks, two or more to each, until it has some 512 (HMM of 4 x 64, B = 512 38 -> 9 us, 32 x 64 39 ->
-        // 14; 32 x 512, B = 77 42 -> 31, with 1024 workgroups 34; K = 128, 32 x 128, B = 100 34 -> 25).
-        int n_split = pf.n_pb >= 128 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));   // 128 blocks: a fixed order
+        // short reductions (below), their chunks, two or more to each.  Up to 512 workgroups with eight chunks each, or up to 32 a block with five
+        // (K = 64: two): a workgroup's adds meet those of the block's others.  256 workgroups and pairs / now: HMM of 4 x 64, B = 512 36 / 7 us, 32 x 64
+        // 39 / 14, 32 x 512, B = 77 42 / 31 (1024 workgroups 34), 64 x 128, B = 128 14.3 / 12.6 (84 of two chunks a block 17.4); K = 128 4 x 128, B = 128
+        // 29 / 18, 16 x 512, B = 300 65 / 57, B = 128 33.5 / 29 (24 of two chunks 38), 64 x 256, B = 128 37 / 41 (84 of two chunks 57), 64 x 512, B = 1
+        // 30 / 30 (25 of two 38).  128 blocks and more keep one each: a fixed order.
+        int n_split = pf.n_pb >= 128 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(pf.n_pairs / pf.n_pb, 256 / pf.n_pb));
         const int64_t chunks = pf.n_pairs * (Bs / 32) / pf.n_pb;
-        if (n_split > 1 && chunks < 64 * n_split) n_split = (int)std::max<int64_t>(n_split, std::min<int64_t>(chunks / 2, std::min(128, 512 / pf.n_pb)));
+        if (n_split > 1 && chunks < 64 * n_split) {
+            const int64_t half = std::min(chunks / 2, (int64_t)256 / pf.n_pb), few = std::min(chunks / (K == 64 ? 2 : 5), (int64_t)32);
+            const int64_t most = std::min(128, 512 / pf.n_pb);
+            n_split = (int)std::max<int64_t>(n_split, std::min(std::max({half, few, chunks / 8}), most));
+        }
         // short reductions (fewer than 64 chunks per workgroup on average): the single-tile form
         const bool one = (int64_t)pf.n_pairs * (Bs / 32) < 64 * (int64_t)pf.n_pb * n_split;
 #define PC_PF_WG(KK, ONE, BF)                                                                                       \

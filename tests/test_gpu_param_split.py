@@ -52,3 +52,16 @@ def test_chunks_dealt_to_waves_match_oracle(T, H, B, workgroups):
     print(f"case chunks dealt to waves T={T} H={H} B={B}", flush=True)
     assert param_workgroups(w) == workgroups
     check_all(w, (np.random.default_rng(6).random(w.x.shape) < 0.2).astype(np.uint8))
+
+
+@pytest.mark.parametrize("T,H,K,B,workgroups", [
+    (4, 64, 64, 128, 2 * 4), (4, 128, 128, 100, 2 * 4),                  # two chunks each while there are few workgroups
+    (64, 128, 64, 100, 6 * 42), (64, 256, 128, 70, 6 * 42),              # 42 pairs and 168 or 126 chunks a block: a workgroup a pair
+    (16, 256, 64, 300, 20 * 25), (16, 512, 128, 100, 20 * 12), (16, 512, 128, 300, 20 * 24),   # few a block: two chunks at K = 64, five at 128
+    (40, 128, 64, 512, 6 * 52),                                          # more than 32: eight (421 a block)
+])
+def test_chunks_dealt_to_workgroups_match_oracle(T, H, K, B, workgroups):
+    w = W.hmm(T, H, 20, K, B, 102, alpha_trans=0.1)
+    print(f"case chunks dealt to workgroups T={T} H={H} K={K} B={B}", flush=True)
+    assert param_workgroups(w) == workgroups
+    check_all(w, (np.random.default_rng(7).random(w.x.shape) < 0.2).astype(np.uint8))
