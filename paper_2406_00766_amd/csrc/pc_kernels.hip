@@ -3057,7 +3057,8 @@ static void pick_sum_shape(int32_t K, int32_t n_rows, int32_t width, int64_t Bs,
 // first child are the first part's sums, and so on; two rows a part, its shift and reference, follow in those of the next child or, at K = 32, two
 // (they are there: parts <= width * K / 256, and 64 chunks).
 // Root over 256 blocks of 32 nodes, sixteen waves and the readout / parts, merge and readout in one: B = 16 51 + 4 / 6 + 4 us, B = 512 49 + 5 / 9 + 5;
-// pass of the HMM of 4096 states in blocks of 128, B = 256 (32 tiles) 3921 / 3907.  Rows of fewer than 64 chunks are four to a wave of sixteen.
+// at 32 tiles, RAT-SPN of 64 variables, all sum launches of a forward pass: K = 32, B = 1000 166 / 133, K = 128, S = 512, B = 256 81 / 45.  Both lines
+// lie inside what pays: 64 tiles of 128 (B = 500) 108 / 78, rows of 48 chunks of 32 (R = 3, S = 128, B = 500) 29 / 21.
 static int sum_parts(int32_t K, int32_t n_groups, int32_t n_rows, int32_t width, int64_t Bs)
 {
     const int64_t chunks = (int64_t)width * (K / 32), tiles = (K / 32) * ((Bs + 31) / 32);
