@@ -205,11 +205,11 @@ pc_status pc_forward(pc_circuit *c, const float *theta, const float *tables, con
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and same result as
  * pc_forward, but the workspace is a fixed array of PC_STATIC_SCRATCH_BYTES inside the library's device image (every
  * GPU the library runs on holds its copy until the process ends).  The call allocates nothing and records no timing
- * events; it only enqueues kernels on `stream`, pc_forward's but for one case: a circuit that is nothing but a chain of single
- * blocks of 32 or 64 nodes, with an input block of its own at each layer (an HMM of as many states), takes one kernel with the same
- * arithmetic while the batch is one at which pc_get_kernel names k_chain or k_walk64 for its sum layers.  PC_ERR_WORKSPACE if pc_workspace_bytes(c, B) exceeds
- * PC_STATIC_SCRATCH_BYTES.  All calls on one GPU share that array: calls that overlap in time on one GPU (two streams,
- * two threads, two circuits) race; the array keeps the last call's contents, and every call writes what it reads.  It
+ * events; it only enqueues kernels on `stream`, pc_forward's but for one case: a circuit that is nothing but a chain of
+ * single blocks of 32 or 64 nodes, with an input block of its own at each layer (an HMM of as many states), takes one
+ * kernel with the same arithmetic while the batch is one at which pc_get_kernel names k_chain or k_walk64 for its sum
+ * layers.  PC_ERR_WORKSPACE if pc_workspace_bytes(c, B) exceeds PC_STATIC_SCRATCH_BYTES.  All calls on one GPU share that
+ * array: calls that overlap in time on one GPU (two streams, two threads, two circuits) race; every call writes what it reads.  It
  * leaves no state for pc_backward (which returns PC_ERR_STATE after it). */
 #define PC_STATIC_SCRATCH_BYTES (64u << 20)
 pc_status pc_forward_static(pc_circuit *c, const float *theta, const float *tables, const int32_t *x,
